@@ -25,6 +25,22 @@
 //     writes its non-zero counters out once, at its end (a global atomic on a shared cache line costs about as much as a
 //     thousand instructions of a wave).
 // Models that flush subnormal inputs come last in a launch (the staged values are flushed in place once).
+//
+// T-FDPA on tiles of up to 16 k (FAST) goes further.  The kernel is bound by vector-ALU issue, and of the 10.7 (FP8) to 11.5
+// (BF16) instructions per term that the loop above took, the products (formed again for every model from LDS: 1 of 4 in pass
+// 2, and in binary64 for BF16, where the LDS reads were as long as the arithmetic), the group ends and the statistics were
+// what many models can share or a shorter form can do:
+//   * a thread's four outputs keep all their products in registers (64 for 16 k), formed once per pass (and once more where
+//     models flush their inputs); BF16 products are held in binary32 relative to their quarter's maximum exponent;
+//   * groups are unrolled, exponents stay biased, the scale's inverse takes the place of a second scaling: 13 instead of 24
+//     instructions per group end; the kept maxima, the accumulators and the reference outputs wait in LDS as 128-bit words;
+//   * special values follow from one IEEE sum per group, taken only by wavefronts that hold any (bit patterns full of NaNs
+//     ran at half the speed of ordinary data through the routes of the general loop);
+//   * the reference's ordered keys are formed once per pass, a histogram entry is counted by leading zeros, and the two
+//     reductions over the wavefront run only where they can change something.
+// Measured, one launch of the sixteen sets of the closed-loop scan on 2^16 tiles of 16x16x16, before and after: FP8 1194 ->
+// 770 us (6.9 instructions per term), BF16 bit patterns 1495 -> 1110 us (8.6), all FP16 bit patterns (a quarter of the tiles)
+// 584 -> 259 us; three sets on 2^18 tiles of 32x32x8 2028 -> 1430 us.  What is left is still issue: VALU busy 86 to 99 %.
 #include "emulate_tiled.hpp"
 
 namespace mmaemu {
@@ -63,7 +79,8 @@ __device__ __forceinline__ ScanArgs::Hot scan_hot(uint32_t mi)
 // held in binary64 when any element lies outside [2^-31, 2^32).
 // (Four waves per SIMD are asked for outright where the LDS allows four workgroups per CU: left alone the compiler settles
 // at about 150 vector registers and three waves; the handful of registers that go to scratch instead cost less than the
-// fourth wave brings: +6 % on both workloads.  Five waves were slower.  The 16 x 16 x 32 instantiations hold two or three
+// fourth wave brings: +6 %.  Five waves were slower.  The BF16 kernels that keep 64 products take three: at four, 300 to 600
+// registers went to scratch memory, 3785 against 1307 us a launch.  The 16 x 16 x 32 instantiations hold two or three
 // workgroups per CU and are compiled for that many waves.)
 // Algorithm "TR-FDPA", steps 3 and 4, and the variations of it that the model switches name, in binary64 (every quantity
 // is an integer of fewer than 53 bits times a power of two, hence exact): T counts units of 2^(em - F) (have_T: a product
@@ -100,6 +117,45 @@ __device__ __forceinline__ double scan_rd_value(double T, bool have_T, int em, i
     return sm == 0.0 ? 0.0 : ldexp(q, unit);
 }
 
+// A kept quarter maximum (FAM 0: biased exponent) at or above this one holds a NaN or an infinity.
+constexpr uint32_t TAGGED = 0x2000u;
+
+__device__ __forceinline__ uint32_t opaque_thread_index()
+{
+    uint32_t t = threadIdx.x;
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("" : "+v"(t));
+#endif
+    return t;
+}
+
+// Ordered key of a binary32 pattern that is no NaN (sign-magnitude patterns read as integers: -|x| for a negative x, x
+// for a positive one), plus 2^31; |key(x) - key(y)| is then one v_sad_u32 (the compiler makes none of these by itself).
+__device__ __forceinline__ uint32_t ordered_key(uint32_t x)
+{
+    const uint32_t s = (uint32_t)((int32_t)x >> 31);                       // 0 or all ones
+#if defined(__HIP_DEVICE_COMPILE__)
+    uint32_t c, k;
+    asm("v_bfi_b32 %0, %1, 1, %2" : "=v"(c) : "v"(s), "s"(0x80000000u));   // s ? 1 : 2^31
+    asm("v_xad_u32 %0, %1, %2, %3" : "=v"(k) : "v"(x), "v"(s), "v"(c));    // (x ^ s) + c
+    return k;
+#else
+    return (x ^ s) + (s ? 1u : 0x80000000u);
+#endif
+}
+__device__ __forceinline__ uint32_t key_distance(uint32_t kx, uint32_t ky)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    uint32_t d;
+    asm("v_sad_u32 %0, %1, %2, 0" : "=v"(d) : "v"(kx), "v"(ky));
+    return d;
+#else
+    return kx > ky ? kx - ky : ky - kx;
+#endif
+}
+// A value that every lane of the wavefront holds alike, in a scalar register.
+__device__ __forceinline__ uint32_t scalar(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
+
 // LDS of one workgroup: staged values and exponents, the kept quarter maxima, the statistics
 template <int TM, int KC, bool ADAPT, int FAM>
 constexpr int scan_lds_bytes()
@@ -107,14 +163,16 @@ constexpr int scan_lds_bytes()
     constexpr int SLOTS = 256 / ((TM / 2) * (TM / 2));
     constexpr int VS = KC + 4, VSD = KC + 2, ES = KC / 2 + (KC == 8 ? 4 : 2);
     constexpr int KEPT = FAM == 3 ? KC / 4 : (KC / 4 + 1) / 2;            // dwords of kept maxima per output
-    return 2 * SLOTS * TM * (ADAPT ? VSD * 8 : VS * 4) + 2 * SLOTS * TM * ES * 4 + KEPT * 4 * 256 * 4 + (int)sizeof(MultiLds);
+    return 2 * SLOTS * TM * (ADAPT ? VSD * 8 : VS * 4) + 2 * SLOTS * TM * ES * 4 + KEPT * 4 * 256 * 4 + (FAM == 0 && KC <= 16 ? 3 : 1) * 4 * 256 * 4 +
+           (int)sizeof(MultiLds) + 16;
 }
 // workgroups (of four waves, one per SIMD) that a CU's 160 KB of LDS hold, four at most: the waves per SIMD to compile for
 template <int TM, int KC, bool ADAPT, int FAM>
 constexpr int scan_waves()
 {
     constexpr int by_lds = (160 * 1024) / scan_lds_bytes<TM, KC, ADAPT, FAM>();
-    return by_lds >= 4 ? 4 : by_lds;
+    constexpr int most = FAM == 0 && KC == 16 && ADAPT ? 3 : 4;
+    return by_lds >= most ? most : by_lds;
 }
 
 // FAM 0: T-FDPA, the accumulator a term of the sum; FAM 1: TR-FDPA (unsplit groups), the accumulator added after the
@@ -131,18 +189,31 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
     constexpr int R = 2, C = 2, TN = TM;
     constexpr int TI = TM / R, TJ = TN / C, TPS = TI * TJ, SLOTS = 256 / TPS;
     static_assert(TPS * SLOTS == 256, "thread layout");
+    constexpr bool FAST = FAM == 0 && KC <= 16;                   // the products of a thread's outputs fit its registers
     constexpr int VS = KC + 4, VSD = KC + 2, ES = KC / 2 + (KC == 8 ? 4 : 2);
     constexpr int NQ4 = KC / 4;                                   // quarter groups per row
     constexpr int NK2 = (NQ4 + 1) / 2;                            // dwords of kept maxima per output
     constexpr int VBYTES = SLOTS * TM * (ADAPT ? VSD * 8 : VS * 4);
     constexpr int EBYTES = SLOTS * TM * ES * 4;
     __shared__ __attribute__((aligned(16))) unsigned char smem[2 * VBYTES + 2 * EBYTES];
-    __shared__ uint32_t m2k[FAM == 3 ? NQ4 : NK2][R * C][256];            // (FAM 3: a quarter's even and odd maximum, one dword)
+    // (one 128-bit LDS word holds a kept dword of all four outputs of a thread; FAM 3: a quarter's even and odd maximum, one dword)
+    __shared__ __attribute__((aligned(16))) uint32_t m2k[FAM == 3 ? NQ4 : NK2][256][R * C];
+    __shared__ __attribute__((aligned(16))) uint32_t ref_key[256][R * C];
+    // (FAST: the accumulators and reference outputs of a pass wait in LDS, not in registers that the products need)
+    __shared__ __attribute__((aligned(16))) uint32_t c0_kept[FAST ? 256 : 1][R * C], ref_kept[FAST ? 256 : 1][R * C];
     __shared__ MultiLds ml;
     constexpr int HC = HIST_COPIES;
     const uint32_t tid = threadIdx.x;
     for (uint32_t i = tid; i < MULTI_MAX * 34 * HC; i += 256) (&ml.hist[0][0][0])[i] = 0;
     if (tid < MULTI_MAX) { ml.naneq[tid] = 0; ml.maxd[tid] = 0; ml.first[tid] = ~0ull; }
+    // (FAST, ADAPT) some element of the pass needs binary64 products: a flag by the pass's parity, set before a barrier, read
+    // after it and cleared after the next pass's: one barrier instead of a reduction's three
+    __shared__ volatile uint32_t flag_wild[2];
+    uint32_t parity = 0;
+    if constexpr (FAST && ADAPT) {
+        if (tid < 2) flag_wild[tid] = 0u;
+        __syncthreads();
+    }
     // (the first staging's barriers come before any thread counts anything)
 
     unsigned char *Av_raw = smem, *Bv_raw = smem + VBYTES;
@@ -161,55 +232,99 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
     const uint32_t *ae = Ae + (slot * TM + ti) * ES;
     const uint32_t *be = Be + (slot * TN + tj) * ES;
     const uint32_t count = sa_.count, ref_first = sa_.ref_is_first;
+    uint32_t found = 0;                        // models for which this wavefront has put a first differing index into LDS
     const bool dumping = sa_.dout != nullptr;
     const uint32_t *dref = sa->dref;
 
-    constexpr int NQ = (SLOTS * TM * (KC / 4) + 255) / 256;
+    // Staging: the tiles of a pass lie one after the other and are staged whole, so quad q of a panel (four consecutive k of
+    // one row) starts 4 q elements behind the pass's first element: one scalar base and a 32-bit offset per thread.  Where
+    // both panels together have at most 256 quads (32 x 32 tiles) a wavefront stages one of A's or one of B's, not both.
+    constexpr int QUADS = SLOTS * TM * (KC / 4);
+    constexpr bool SHARED_PASS = 2 * QUADS <= 256;
+    constexpr int NQ = SHARED_PASS ? 1 : (QUADS + 255) / 256;
+    constexpr int NM = SHARED_PASS ? 1 : 2;                      // panels a thread has a hand in
+    static_assert(SHARED_PASS ? (QUADS % 64 == 0 && 256 % QUADS == 0) : QUADS % 256 == 0, "quads per thread");
+    const bool stages_b = SHARED_PASS && (__builtin_amdgcn_readfirstlane((int)tid) / QUADS) % 2 != 0;      // (uniform over a wavefront)
+    auto quad_of = [&](int i) -> uint32_t { return SHARED_PASS ? tid % QUADS : tid + 256u * i; };
+    auto load_quads = [&](const void *base, uint32_t es, uint64_t first_item, uint2 (&raw)[NQ]) {
+        const uint64_t left = nitems - first_item;               // (surplus slots of the last pass re-read its last tile)
+        const uint8_t *p0 = static_cast<const uint8_t *>(base) + first_item * (uint64_t)(TM * KC) * es;
+#pragma unroll
+        for (int i = 0; i < NQ; ++i) {
+            const uint32_t q = quad_of(i), sl = q / (TM * KC / 4);
+            uint32_t e = 4u * q;
+            if (left < SLOTS && sl >= (uint32_t)left) e -= (sl - ((uint32_t)left - 1u)) * (uint32_t)(TM * KC);
+            if (es == 1) { raw[i].x = *reinterpret_cast<const uint32_t *>(p0 + e); raw[i].y = 0; }
+            else raw[i] = *reinterpret_cast<const uint2 *>(p0 + 2u * e);
+        }
+    };
+    auto load_pass = [&](uint64_t first_item, uint2 (&raw)[NM][NQ]) {
+        if constexpr (SHARED_PASS) load_quads(stages_b ? B : A, stages_b ? esb : esa, first_item, raw[0]);
+        else {
+            load_quads(A, esa, first_item, raw[0]);
+            load_quads(B, esb, first_item, raw[NM - 1]);
+        }
+    };
+    auto store_quads = [&](bool is_b, const float (&f)[NQ][4], const uint2 (&x)[NQ], bool as_double) {
+        unsigned char *const lv = is_b ? Bv_raw : Av_raw;
+        uint32_t *const le = is_b ? Be : Ae;
+#pragma unroll
+        for (int i = 0; i < NQ; ++i) {
+            const uint32_t q = quad_of(i), row = q / (KC / 4), kq = q % (KC / 4);
+            *reinterpret_cast<uint2 *>(le + row * ES + 2 * kq) = x[i];
+            if (as_double) {
+                double *dst = reinterpret_cast<double *>(lv) + row * VSD + 4 * kq;
+                *reinterpret_cast<double2 *>(dst) = make_double2((double)f[i][0], (double)f[i][1]);
+                *reinterpret_cast<double2 *>(dst + 2) = make_double2((double)f[i][2], (double)f[i][3]);
+            } else {
+                *reinterpret_cast<float4 *>(reinterpret_cast<float *>(lv) + row * VS + 4 * kq) = make_float4(f[i][0], f[i][1], f[i][2], f[i][3]);
+            }
+        }
+    };
+    // first output of the thread, counted from the pass's first (surplus slots: the last tile's)
+    auto out_offset = [&](uint64_t first_item) -> uint32_t {
+        const uint64_t left = nitems - first_item;
+        const uint32_t sl = (left < SLOTS && slot >= (uint32_t)left) ? (uint32_t)left - 1u : slot;
+        return (sl * TM + ti) * TN + tj;                         // + TI * r * TN + TJ * c
+    };
     // AHEAD (the 32 x 32 tiles of FP8 / FP16 operands, whose kernels have registers to spare under the four-wave budget):
     // a pass's global loads (operand quads, accumulator inputs, reference) are issued one pass ahead, right after the
     // previous pass has been staged, so that they arrive while its models run.
     constexpr bool AHEAD = TM == 32 && !ADAPT && FAM == 0;
     constexpr int NA = AHEAD ? NQ : 1, RA = AHEAD ? R : 1, CA = AHEAD ? C : 1;
-    uint2 nraw_a[NA], nraw_b[NA];
+    uint2 nraw[NM][NA];
     uint32_t nc0[RA][CA], nref[RA][CA];
     auto fetch_pass = [&](uint32_t wg) {
         if constexpr (AHEAD) {
             const uint64_t it0 = (uint64_t)wg * SLOTS;
-            StagePlan<NQ> pa, pb;
-            make_plan<TM, KC, SLOTS, VS, ES, true, NQ>(pa, A, esa, it0, nitems, 1u, 1u, TM, KC);
-            make_plan<TN, KC, SLOTS, VS, ES, false, NQ>(pb, B, esb, it0, nitems, 1u, 1u, TN, KC);
-            load_panel<NQ>(esa, pa, 0, nraw_a);
-            load_panel<NQ>(esb, pb, 0, nraw_b);
-            const uint64_t tile = it0 + slot < nitems ? it0 + slot : nitems - 1;
-            const uint64_t off = (tile * TM + ti) * (uint64_t)TN + tj;
+            load_pass(it0, nraw);
+            const uint32_t off = out_offset(it0);
+            const uint32_t *cp = Cm + it0 * (uint64_t)(TM * TN), *rp = dref + it0 * (uint64_t)(TM * TN);
 #pragma unroll
             for (int r = 0; r < R; ++r)
 #pragma unroll
                 for (int c = 0; c < C; ++c) {
-                    const uint64_t o = off + (uint64_t)(TI * r) * TN + TJ * c;
-                    nc0[r][c] = Cm[o];
-                    nref[r][c] = ref_first ? 0u : dref[o];
+                    nc0[r][c] = cp[off + (TI * r) * TN + TJ * c];
+                    nref[r][c] = ref_first ? 0u : rp[off + (TI * r) * TN + TJ * c];
                 }
         }
     };
     if (AHEAD && blockIdx.x < nblocks) fetch_pass(blockIdx.x);
     for (uint32_t pass_wg = blockIdx.x; pass_wg < nblocks; pass_wg += gridDim.x) {
-        // ---- this pass's tiles: staging plans, outputs, operands in flight ----
+        // ---- this pass's tiles: outputs, operands in flight ----
         const uint64_t item0 = (uint64_t)pass_wg * SLOTS;
-        StagePlan<NQ> plan_a, plan_b;
-        make_plan<TM, KC, SLOTS, VS, ES, true, NQ>(plan_a, A, esa, item0, nitems, 1u, 1u, TM, KC);
-        make_plan<TN, KC, SLOTS, VS, ES, false, NQ>(plan_b, B, esb, item0, nitems, 1u, 1u, TN, KC);
-        uint2 raw_a[NQ], raw_b[NQ];
+        const uint64_t out0 = item0 * (uint64_t)(TM * TN);
+        uint2 raw[NM][NQ];
         if constexpr (AHEAD) {
 #pragma unroll
-            for (int q = 0; q < NQ; ++q) { raw_a[q] = nraw_a[q]; raw_b[q] = nraw_b[q]; }
+            for (int w = 0; w < NM; ++w)
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) raw[w][q] = nraw[w][q];
         } else {
-            load_panel<NQ>(esa, plan_a, 0, raw_a);
-            load_panel<NQ>(esb, plan_b, 0, raw_b);
+            load_pass(item0, raw);
         }
-        const bool live = item0 + slot < nitems;
-        const uint64_t my_tile = live ? item0 + slot : nitems - 1;
-        const uint64_t d_off = (my_tile * TM + ti) * (uint64_t)TN + tj;             // + TI * r * TN + TJ * c
+        const bool live = scalar(item0 + slot < nitems ? 1u : 0u) != 0;      // (a wavefront works on one tile)
+        const uint32_t d_off = out_offset(item0);                // (behind out0)
         uint32_t c0[R][C], ref[R][C];
 #pragma unroll
         for (int r = 0; r < R; ++r)
@@ -219,9 +334,9 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
                     c0[r][c] = nc0[r][c];
                     ref[r][c] = nref[r][c];
                 } else {
-                    const uint64_t o = d_off + (uint64_t)(TI * r) * TN + TJ * c;
-                    c0[r][c] = Cm[o];
-                    ref[r][c] = ref_first ? 0u : dref[o];
+                    const uint32_t o = d_off + (TI * r) * TN + TJ * c;
+                    c0[r][c] = (Cm + out0)[o];
+                    ref[r][c] = ref_first ? 0u : (dref + out0)[o];
                 }
             }
         // ---- decode and stage (as the first model wants them) ----
@@ -230,19 +345,27 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
         {
             const uint32_t ftz0 = scan_hot(0).flags & FL_FTZ_IN;
             staged = ftz0 ? 1 : 0;
-            float fa[NQ][4], fb[NQ][4];
-            uint2 xa[NQ], xb[NQ];
+            float f[NM][NQ][4];
+            uint2 x[NM][NQ];
             const uint32_t zbias = FAM != 0 ? sa_.zbias : 0u;
-            bool wild = decode_any<NQ>(ta, raw_a, ftz0, zbias, fa, xa);
-            wild |= decode_any<NQ>(tb, raw_b, ftz0, zbias, fb, xb);
-            if (ADAPT) chunk_is_double = __syncthreads_or(wild) != 0;         // (also protects the previous pass's readers)
+            bool wild = decode_any<NQ>(stages_b ? tb : ta, raw[0], ftz0, zbias, f[0], x[0]);
+            if constexpr (NM == 2) wild |= decode_any<NQ>(tb, raw[1], ftz0, zbias, f[1], x[1]);
+            // (the barrier also protects the previous pass's readers)
+            if constexpr (ADAPT && FAST) {
+                if (wild) flag_wild[parity] = 1u;
+                __syncthreads();
+                chunk_is_double = __builtin_amdgcn_readfirstlane((int)flag_wild[parity]) != 0;
+                if (tid == 0) flag_wild[parity ^ 1u] = 0u;
+                parity ^= 1u;
+            } else if (ADAPT) chunk_is_double = __syncthreads_or(wild) != 0;
             else __syncthreads();
-            store_panel<NQ, VS, VSD>(plan_a, fa, xa, Av_raw, Ae, chunk_is_double, 3);
-            store_panel<NQ, VS, VSD>(plan_b, fb, xb, Bv_raw, Be, chunk_is_double, 3);
+            store_quads(stages_b, f[0], x[0], chunk_is_double);
+            if constexpr (NM == 2) store_quads(true, f[1], x[1], chunk_is_double);
             __syncthreads();
         }
         if (AHEAD && pass_wg + gridDim.x < nblocks) fetch_pass(pass_wg + gridDim.x);
         // ---- pass 1, once: the maximum of e'_a + e'_b over each quarter group, two quarters per kept dword ----
+        uint32_t top = 0;                                         // (FAST) the largest kept maximum of the thread's outputs
 #pragma unroll
         for (int q = 0; q < NQ4; ++q) {
             uint2 ea[R], eb[C];
@@ -256,15 +379,463 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
                 for (int c = 0; c < C; ++c) {
                     const uint32_t x = pk_max_u16(pk_add_u16(ea[r].x, eb[c].x), pk_add_u16(ea[r].y, eb[c].y));
                     const uint32_t lo = x & 0xFFFFu, hi = x >> 16;
-                    const uint32_t mx = lo > hi ? lo : hi;
+                    uint32_t mx = lo > hi ? lo : hi;
+                    if constexpr (FAM == 0) {
+                        // kept as a biased binary32 exponent, 1 at least (the accumulator's own is never below 1, so what lies
+                        // under it cannot be the group's maximum); a tagged one stays far above every other
+                        const int mb = (int)mx + ebase + 127;
+                        mx = mb < 1 ? 1u : (uint32_t)mb;
+                        if constexpr (FAST) top = mx > top ? mx : top;
+                    }
                     // (each thread its own words: no barrier needed)
-                    if constexpr (FAM == 3) m2k[q][r * C + c][tid] = x;           // low half: the even k, high half: the odd k
-                    else if (q % 2 == 0) m2k[q / 2][r * C + c][tid] = mx;
-                    else m2k[q / 2][r * C + c][tid] |= mx << 16;
+                    if constexpr (FAM == 3) m2k[q][tid][r * C + c] = x;           // low half: the even k, high half: the odd k
+                    else if (q % 2 == 0) m2k[q / 2][tid][r * C + c] = mx;
+                    else m2k[q / 2][tid][r * C + c] |= mx << 16;
                 }
         }
 
+        // ---- a model's outputs against the reference ----
+        // Per output that differs: one LDS atomic on its histogram bucket (bucket 0 of the LDS copy counts pairs that
+        // differ at distance 0: zeros of both signs, NaNs of two patterns), so the number of mismatches is the
+        // histogram's sum.  The largest distance is reduced over the wavefront only where it passes the one in LDS, and
+        // the first index once per wavefront and model: a workgroup's passes go through ascending tiles, so no later
+        // pass can lower it.
+        // (An LDS histogram is kept by leading zeros of the distance: place 32 - bucket, and 33 for bucket 33.  The keys of the
+        // reference outputs sit in LDS, formed once per pass.)
+        uint32_t ref_nan = 1u;                                    // some reference output of the wavefront may be a NaN
+        auto take_reference = [&](const uint32_t (&ref)[R][C]) {
+            bool any = false;
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+#pragma unroll
+                for (int c = 0; c < C; ++c) {
+                    any |= (ref[r][c] & 0x7FFFFFFFu) > 0x7F800000u;
+                    ref_key[tid][r * C + c] = ordered_key(ref[r][c]);
+                    if (FAST) ref_kept[tid][r * C + c] = ref[r][c];
+                }
+            ref_nan = scalar(__any(any) ? 1u : 0u);
+        };
+        if (!ref_first) take_reference(ref);
+        auto write_nan = [&](uint32_t (&x)[R][C], uint32_t nan_pattern) {
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+#pragma unroll
+                for (int c = 0; c < C; ++c) if ((x[r][c] & 0x7FFFFFFFu) > 0x7F800000u) x[r][c] = nan_pattern;
+        };
+        // (x: the model's outputs, every NaN already the model's pattern; nan_seen: there may be one)
+        auto account = [&](uint32_t mi, const uint32_t (&x)[R][C], bool nan_seen) {
+            if (!live) return;
+            const uint32_t tid = opaque_thread_index();           // (addresses formed here, not kept across the models' loop)
+            uint32_t *dout = nullptr;
+            uint64_t dump_off = 0;
+            if (dumping) { dout = sa->dout; dump_off = (uint64_t)sa->slot[mi] * sa->out_stride + out0; }       // (uniform)
+            uint32_t maxd = 0;
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+#pragma unroll
+                for (int c = 0; c < C; ++c) {
+                    if (dumping) (dout + dump_off)[d_off + (TI * r) * TN + TJ * c] = x[r][c];
+                }
+            if (__builtin_expect(ref_first && mi == 0, 0)) {
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+#pragma unroll
+                    for (int c = 0; c < C; ++c) ref[r][c] = x[r][c];
+                take_reference(x);
+                return;                                           // (its own row reports no mismatch)
+            }
+            uint32_t y[R][C];
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+#pragma unroll
+                for (int c = 0; c < C; ++c) y[r][c] = FAST ? ref_kept[tid][r * C + c] : ref[r][c];
+            uint32_t *const hist = &ml.hist[mi][0][tid & (HC - 1)];
+            if (__builtin_expect(nan_seen || ref_nan != 0u, 0)) {
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+#pragma unroll
+                    for (int c = 0; c < C; ++c) {
+                        if (x[r][c] != y[r][c]) {
+                            const uint32_t dist = key_distance(ordered_key(x[r][c]), ref_key[tid][r * C + c]);
+                            const bool nx = (x[r][c] & 0x7FFFFFFFu) > 0x7F800000u, ny = (y[r][c] & 0x7FFFFFFFu) > 0x7F800000u;
+                            uint32_t place = (uint32_t)__clz((int)dist);                                  // (__clz(0) = 32)
+                            if (nx || ny) {
+                                place = (nx && ny) ? 32u : 33u;
+                                if (nx && ny) atomicAdd(&ml.naneq[mi], 1u);                               // (rare)
+                            } else {
+                                maxd = dist > maxd ? dist : maxd;
+                            }
+                            atomicAdd(hist + place * HC, 1u);
+                        }
+                    }
+            } else {
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+#pragma unroll
+                    for (int c = 0; c < C; ++c)
+                        if (x[r][c] != y[r][c]) {
+                            const uint32_t dist = key_distance(ordered_key(x[r][c]), ref_key[tid][r * C + c]);
+                            maxd = dist > maxd ? dist : maxd;
+                            atomicAdd(hist + (uint32_t)__clz((int)dist) * HC, 1u);
+                        }
+            }
+            if (scalar(__any(maxd > ml.maxd[mi]) ? 1u : 0u)) {
+                const uint32_t wmax = wave_reduce_to_lane63<true>(maxd);
+                if ((tid & 63u) == 63u) atomicMax(&ml.maxd[mi], wmax);
+            }
+            if (!((found >> mi) & 1u)) {
+                uint32_t rel = 0xFFFFFFFFu;
+#pragma unroll
+                for (int r = R - 1; r >= 0; --r)
+#pragma unroll
+                    for (int c = C - 1; c >= 0; --c)
+                        if (x[r][c] != y[r][c]) rel = d_off + (uint32_t)((TI * r) * TN + TJ * c);
+                const uint32_t wmin = wave_reduce_to_lane63<false>(rel);
+                if ((tid & 63u) == 63u && wmin != 0xFFFFFFFFu)
+                    atomicMin(&ml.first[mi], (unsigned long long)(sa->index_base + out0 + wmin));
+                if (scalar(__any(rel != 0xFFFFFFFFu) ? 1u : 0u)) found |= 1u << mi;
+                found = scalar(found);
+            }
+        };
+
+        if constexpr (FAST) {
+            // ---- the products of the thread's outputs in registers, shared by all the models ----
+            // special: an operand of the wavefront's is a NaN or an infinity, or an accumulator is one or may become one.  The
+            // groups' results then follow Sec. 4.2 through an IEEE sum of the group's products and its accumulator (special_sum).
+            // (An infinity that a BF16 chain reaches by overflow is no such case: it stays by itself, see rho32.)
+            bool odd = top >= TAGGED;
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+#pragma unroll
+                for (int c = 0; c < C; ++c) {
+                    c0_kept[tid][r * C + c] = c0[r][c];
+                    odd |= ((c0[r][c] >> 23) & 0xFFu) >= 254u;      // (FP8 / FP16 sums stay below 2^40: from 253 no chain overflows)
+                }
+            const bool special = scalar(__any(odd) ? 1u : 0u) != 0u;
+            {
+                // (the scheduler would interleave the outputs' sums and the quarters' products, for registers that go to scratch memory)
+                auto one_at_a_time = [] {
+#if defined(__HIP_DEVICE_COMPILE__)
+                    __builtin_amdgcn_sched_barrier(0);
+#endif
+                };
+                float p[R][C][KC];
+                auto kept = [&](int q, int r, int c) -> uint32_t { return (m2k[q / 2][tid][r * C + c] >> (16 * (q & 1))) & 0xFFFFu; };
+                // p = a b, exact; BF16: a b 2^-(quarter's maximum exponent), exact wherever the term can reach the sum's unit
+                // (a product 2^-126 below its quarter's largest is cut to zero at any width).  In a quarter with a NaN or an
+                // infinity the finite products are scaled away.
+                auto form_products = [&](bool flush) {
+                    const float min_a = flush ? min_normal_of(ta) : 0.0f, min_b = flush ? min_normal_of(tb) : 0.0f;
+#pragma unroll
+                    for (int q = 0; q < NQ4; ++q) {
+                        int down[ADAPT ? R : 1][ADAPT ? C : 1];          // the power of two that a quarter's products are scaled by
+                        if constexpr (ADAPT) {
+#pragma unroll
+                            for (int r = 0; r < R; ++r)
+#pragma unroll
+                                for (int c = 0; c < C; ++c) down[r][c] = 127 - (int)kept(q, r, c);
+                            if (__builtin_expect(special, 0)) {
+#pragma unroll
+                                for (int r = 0; r < R; ++r)
+#pragma unroll
+                                    for (int c = 0; c < C; ++c) down[r][c] = down[r][c] < -400 ? -400 : down[r][c];
+                            }
+                        }
+                        if (ADAPT && chunk_is_double) {
+                            double sc[ADAPT ? R : 1][ADAPT ? C : 1];
+#pragma unroll
+                            for (int r = 0; r < R; ++r)
+#pragma unroll
+                                for (int c = 0; c < C; ++c) if constexpr (ADAPT) sc[r][c] = __hiloint2double((1023 + down[r][c]) << 20, 0);
+#pragma unroll
+                            for (int h = 0; h < 4; h += 2) {
+                                double a[R][2], b[C][2];
+#pragma unroll
+                                for (int r = 0; r < R; ++r) {
+                                    const double2 v = *reinterpret_cast<const double2 *>(avd + TI * r * VSD + 4 * q + h);
+                                    a[r][0] = __builtin_fabs(v.x) < (double)min_a ? 0.0 : v.x;
+                                    a[r][1] = __builtin_fabs(v.y) < (double)min_a ? 0.0 : v.y;
+                                }
+#pragma unroll
+                                for (int c = 0; c < C; ++c) {
+                                    const double2 v = *reinterpret_cast<const double2 *>(bvd + TJ * c * VSD + 4 * q + h);
+                                    b[c][0] = __builtin_fabs(v.x) < (double)min_b ? 0.0 : v.x;
+                                    b[c][1] = __builtin_fabs(v.y) < (double)min_b ? 0.0 : v.y;
+                                }
+#pragma unroll
+                                for (int r = 0; r < R; ++r)
+#pragma unroll
+                                    for (int c = 0; c < C; ++c) {
+                                        p[r][c][4 * q + h] = (float)((a[r][0] * b[c][0]) * sc[ADAPT ? r : 0][ADAPT ? c : 0]);
+                                        p[r][c][4 * q + h + 1] = (float)((a[r][1] * b[c][1]) * sc[ADAPT ? r : 0][ADAPT ? c : 0]);
+                                    }
+                            }
+                            one_at_a_time();
+                        } else {
+                            float a[R][4], b[C][4];
+#pragma unroll
+                            for (int r = 0; r < R; ++r) {
+                                const float4 v = *reinterpret_cast<const float4 *>(av + TI * r * VS + 4 * q);
+                                a[r][0] = v.x; a[r][1] = v.y; a[r][2] = v.z; a[r][3] = v.w;
+                            }
+#pragma unroll
+                            for (int c = 0; c < C; ++c) {
+                                const float4 v = *reinterpret_cast<const float4 *>(bv + TJ * c * VS + 4 * q);
+                                b[c][0] = v.x; b[c][1] = v.y; b[c][2] = v.z; b[c][3] = v.w;
+                            }
+                            if (flush) {
+#pragma unroll
+                                for (int w = 0; w < 4; ++w) {
+#pragma unroll
+                                    for (int r = 0; r < R; ++r) a[r][w] = __builtin_fabsf(a[r][w]) < min_a ? 0.0f : a[r][w];
+#pragma unroll
+                                    for (int c = 0; c < C; ++c) b[c][w] = __builtin_fabsf(b[c][w]) < min_b ? 0.0f : b[c][w];
+                                }
+                            }
+#pragma unroll
+                            for (int w = 0; w < 4; ++w)
+#pragma unroll
+                                for (int r = 0; r < R; ++r)
+#pragma unroll
+                                    for (int c = 0; c < C; ++c) {
+                                        const float x = a[r][w] * b[c][w];
+                                        p[r][c][4 * q + w] = ADAPT ? ldexpf(x, down[ADAPT ? r : 0][ADAPT ? c : 0]) : x;
+                                    }
+                            one_at_a_time();
+                        }
+                    }
+                };
+                form_products(false);
+                bool flushed = staged != 0;
+#pragma unroll 1
+                for (uint32_t mi = 0; mi < count; ++mi) {
+                    const ScanArgs::Hot hot = scan_hot(mi);
+                    const int F = hot.F;
+                    const uint32_t fl = hot.flags;
+                    const bool twin = TWIN && hot.twin != 0;
+                    if ((fl & FL_FTZ_IN) && !flushed) { form_products(true); flushed = true; }
+                    set_f32_round_toward_zero((fl & FL_RZ) != 0);
+                    // (the kept maxima are read again for every model: hoisted out of this loop they would take up to 28 registers)
+                    const uint32_t tid = opaque_thread_index();
+                    auto kept = [&](int q, int r, int c) -> uint32_t { return (m2k[q / 2][tid][r * C + c] >> (16 * (q & 1))) & 0xFFFFu; };
+                    uint32_t d[R][C], d2[R][C] = {};
+#pragma unroll
+                    for (int r = 0; r < R; ++r)
+#pragma unroll
+                        for (int c = 0; c < C; ++c) d[r][c] = c0_kept[tid][r * C + c];
+                    // rho of a 32-bit sum S in units of 2^(emb - 127 - F): one int -> float conversion under the wavefront's
+                    // rounding mode, then an exact scaling; the result is zero or normal
+                    auto rho32 = [&](int32_t S, float back, uint32_t emb, uint32_t dp, uint32_t fe, uint32_t om) -> uint32_t {
+                        const float f = (float)S;
+                        uint32_t o;
+                        if constexpr (ADAPT) {
+                            o = __float_as_uint(ldexpf(f, (int)emb - (F + 127)));
+                            if (fe & FL_RZ) {
+                                if ((o & 0x7FFFFFFFu) == 0x7F800000u) o -= 1u;             // overflow: the largest finite number
+                                o &= om;
+                            }
+                            if ((dp & 0x7F800000u) == 0x7F800000u) o = dp;                 // an infinity that the chain has reached stays
+                        } else {
+                            o = __float_as_uint(f * back);
+                            if (fe & FL_RZ) o &= om;
+                        }
+                        return o;
+                    };
+                    auto rho64 = [&](double v, uint32_t fe, uint32_t om) -> uint32_t {
+                        uint32_t o = __float_as_uint((float)v);
+                        if (fe & FL_RZ) {
+                            const double b = (double)__uint_as_float(o);
+                            if (__builtin_fabs(b) > __builtin_fabs(v)) o -= 1u;            // rounded away from zero: step back
+                            o &= om;
+                        }
+                        if (ADAPT && (fe & FL_FTZ_OUT) && (o & 0x7F800000u) == 0) o &= 0x80000000u;
+                        return o;
+                    };
+                    // Sec. 4.2 for group g of GL products: their IEEE sum with the accumulator is a NaN or an infinity exactly where
+                    // the group's result is (finite products are far too small to make one), and is then that result; the
+                    // infinities that BF16 chains reach by overflow stay through it too.
+                    auto special_sum = [&](auto gl_c, int g, int r, int c, uint32_t dp) -> uint32_t {
+                        constexpr int GL = decltype(gl_c)::value;
+                        float t = p[r][c][g * GL];
+#pragma unroll
+                        for (int w = 1; w < GL; ++w) t += p[r][c][g * GL + w];
+                        return __float_as_uint(t + __uint_as_float(dp));
+                    };
+                    auto run_fast = [&](auto gl_c, auto wide_c) -> bool {
+                        constexpr int GL = decltype(gl_c)::value;
+                        constexpr bool WIDE = decltype(wide_c)::value != 0, PAIRS = decltype(wide_c)::value == 1;
+                        if constexpr (GL <= KC) {
+#pragma unroll
+                        for (int g = 0; g < KC / GL; ++g) {
+                            uint32_t emb[R][C], before[R][C];      // the group's maximum exponent, biased; its accumulator
+                            bool low = false;
+#pragma unroll
+                            for (int r = 0; r < R; ++r)
+#pragma unroll
+                                for (int c = 0; c < C; ++c) {
+                                    uint32_t e;
+                                    if constexpr (GL == 4) e = kept(g, r, c);
+                                    else {
+                                        uint32_t x = m2k[g * (GL / 8)][tid][r * C + c];
+#pragma unroll
+                                        for (int i = 1; i < GL / 8; ++i) x = pk_max_u16(x, m2k[g * (GL / 8) + i][tid][r * C + c]);
+                                        const uint32_t lo = x & 0xFFFFu, hi = x >> 16;
+                                        e = lo > hi ? lo : hi;
+                                    }
+                                    const uint32_t Ec = (d[r][c] >> 23) & 0xFFu;
+                                    emb[r][c] = e > Ec ? e : Ec;
+                                    if constexpr (ADAPT && !WIDE) low |= emb[r][c] < (uint32_t)(F + 1);
+                                }
+                            if constexpr (ADAPT && !WIDE) { if (__any(low)) return false; }
+                            if constexpr (!WIDE) {
+                                int32_t S[R][C];
+                                float back[R][C];
+#pragma unroll
+                                for (int r = 0; r < R; ++r)
+#pragma unroll
+                                    for (int c = 0; c < C; ++c) {
+                                        float scale;
+                                        if constexpr (ADAPT) {
+                                            // (the accumulator's exponent may lie anywhere below the group's maximum)
+                                            S[r][c] = (int32_t)ldexpf(__uint_as_float(d[r][c]), (F + 127) - (int)emb[r][c]);
+                                            back[r][c] = 0.0f;
+                                        } else {
+                                            const uint32_t sb = (uint32_t)(F + 254 - (int)emb[r][c]) << 23;         // 2^(F - e_max), normal
+                                            scale = __uint_as_float(sb);
+                                            back[r][c] = __uint_as_float(0x7F000000u - sb);                        // its inverse
+                                            S[r][c] = (int32_t)(__uint_as_float(d[r][c]) * scale);
+                                        }
+#pragma unroll
+                                        for (int q = 0; q < GL / 4; ++q) {
+                                            if constexpr (ADAPT) {
+                                                const int se = (F + 127) + (int)kept(g * (GL / 4) + q, r, c) - (int)emb[r][c];
+                                                scale = __uint_as_float((uint32_t)(se < 1 ? 1 : se) << 23);
+                                            }
+#pragma unroll
+                                            for (int w = 0; w < 4; ++w) S[r][c] += (int32_t)(p[r][c][g * GL + 4 * q + w] * scale);
+                                        }
+                                        one_at_a_time();
+                                    }
+                                if constexpr (TWIN && GL == KC) {
+                                    if (twin) {
+                                        const ScanArgs::Hot h2 = scan_hot(mi + 1);
+                                        set_f32_round_toward_zero((h2.flags & FL_RZ) != 0);
+#pragma unroll
+                                        for (int r = 0; r < R; ++r)
+#pragma unroll
+                                            for (int c = 0; c < C; ++c) {
+                                                // (a copy the optimiser cannot see through: to it the conversions under the two rounding modes are one)
+                                                int32_t S2 = S[r][c];
+#if defined(__HIP_DEVICE_COMPILE__)
+                                                asm volatile("" : "+v"(S2));
+#endif
+                                                d2[r][c] = rho32(S2, back[r][c], emb[r][c], d[r][c], h2.flags, h2.out_mask);
+                                            }
+                                        set_f32_round_toward_zero((fl & FL_RZ) != 0);
+                                    }
+                                }
+#pragma unroll
+                                for (int r = 0; r < R; ++r)
+#pragma unroll
+                                    for (int c = 0; c < C; ++c) {
+                                        before[r][c] = d[r][c];
+                                        d[r][c] = rho32(S[r][c], back[r][c], emb[r][c], d[r][c], fl, hot.out_mask);
+                                    }
+                            } else {
+                                double v[R][C];
+#pragma unroll
+                                for (int r = 0; r < R; ++r)
+#pragma unroll
+                                    for (int c = 0; c < C; ++c) {
+                                        // (FlushSubnormal on the accumulator, and on the result below: FP8 / FP16 products keep
+                                        // every group's unit far above the subnormals, whose aligned image is zero)
+                                        if (ADAPT && (fl & FL_FTZ_IN) && (d[r][c] & 0x7F800000u) == 0) d[r][c] = 0;
+                                        const int unit = (int)emb[r][c] - 127 - F;
+                                        double T = 0.0 + __builtin_trunc(ldexp((double)__uint_as_float(d[r][c]), -unit));      // (+0.0 whatever the signs)
+                                        float scale = __uint_as_float((uint32_t)(F + 254 - (int)emb[r][c]) << 23);
+#pragma unroll
+                                        for (int q = 0; q < GL / 4; ++q) {
+                                            if constexpr (ADAPT) {
+                                                const int se = (F + 127) + (int)kept(g * (GL / 4) + q, r, c) - (int)emb[r][c];
+                                                scale = __uint_as_float((uint32_t)(se < 1 ? 1 : se) << 23);
+                                            }
+                                            // aligned and truncated in binary32, exactly; F of 28 and 29: two terms fit 32 bits
+#pragma unroll
+                                            for (int w = 0; w < 4; w += 2) {
+                                                const float t0 = p[r][c][g * GL + 4 * q + w] * scale, t1 = p[r][c][g * GL + 4 * q + w + 1] * scale;
+                                                if constexpr (PAIRS) T += (double)((int32_t)t0 + (int32_t)t1);
+                                                else {
+                                                    T += (double)__builtin_truncf(t0);
+                                                    T += (double)__builtin_truncf(t1);
+                                                }
+                                            }
+                                        }
+                                        v[r][c] = ldexp(T, unit);                                                  // exact: integers below 2^53
+                                        one_at_a_time();
+                                    }
+                                if constexpr (TWIN && GL == KC) {
+                                    if (twin) {
+                                        const ScanArgs::Hot h2 = scan_hot(mi + 1);
+#pragma unroll
+                                        for (int r = 0; r < R; ++r)
+#pragma unroll
+                                            for (int c = 0; c < C; ++c) {
+                                                d2[r][c] = rho64(v[r][c], h2.flags, h2.out_mask);
+                                            }
+                                    }
+                                }
+#pragma unroll
+                                for (int r = 0; r < R; ++r)
+#pragma unroll
+                                    for (int c = 0; c < C; ++c) {
+                                        before[r][c] = d[r][c];
+                                        d[r][c] = rho64(v[r][c], fl, hot.out_mask);
+                                    }
+                            }
+                            if (__builtin_expect(special, 0)) {
+#pragma unroll
+                                for (int r = 0; r < R; ++r)
+#pragma unroll
+                                    for (int c = 0; c < C; ++c) {
+                                        const uint32_t t = special_sum(gl_c, g, r, c, before[r][c]);
+                                        const bool sp = (t & 0x7F800000u) == 0x7F800000u;
+                                        d[r][c] = sp ? t : d[r][c];
+                                        if (TWIN && GL == KC) d2[r][c] = sp ? t : d2[r][c];
+                                        one_at_a_time();
+                                    }
+                            }
+                        }
+                        }
+                        return true;
+                    };
+                    auto by_width = [&](auto gl_c) {
+                        constexpr int GL = decltype(gl_c)::value;
+                        const bool fits = F >= 1 && F <= 28 && ((uint64_t)(GL + 1) << (F + 2)) <= (1ull << 31);
+                        if (fits) {
+                            if (run_fast(gl_c, std::integral_constant<int, 0>{})) return;
+#pragma unroll
+                            for (int r = 0; r < R; ++r)
+#pragma unroll
+                                for (int c = 0; c < C; ++c) d[r][c] = c0_kept[tid][r * C + c];      // a group whose result may be subnormal: the chain again, in binary64
+                        }
+                        if (F <= 29) run_fast(gl_c, std::integral_constant<int, 1>{}); else run_fast(gl_c, std::integral_constant<int, 2>{});
+                    };
+                    if (hot.L == 4) by_width(std::integral_constant<int, 4>{});
+                    else if (hot.L == 8) by_width(std::integral_constant<int, 8>{});
+                    else by_width(std::integral_constant<int, 16>{});
+                    if (__builtin_expect(special, 0)) write_nan(d, hot.nan_bits);
+                    account(mi, d, special);
+                    if (twin) {
+                        ++mi;
+                        if (__builtin_expect(special, 0)) write_nan(d2, scan_hot(mi).nan_bits);
+                        account(mi, d2, special);
+                    }
+                }
+                set_f32_round_toward_zero(false);
+            }
+        } else {
         // ---- the models ----
+        {
 #pragma unroll 1
         for (uint32_t mi = 0; mi < count; ++mi) {
             const ScanArgs::Hot hot = scan_hot(mi);
@@ -273,12 +844,8 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
             typename std::conditional<TWIN, uint32_t, const uint32_t>::type out_mask = hot.out_mask, nan_bits = hot.nan_bits;
             typename std::conditional<TWIN, uint32_t, const uint32_t>::type fe = fl;   // the switches the end of a group reads (a twin brings its own)
             const bool twin = TWIN && hot.twin != 0;
-            uint32_t dfirst[TWIN ? R : 1][TWIN ? C : 1];      // the first model's outputs of a pair of twins
+            uint32_t dfirst[R][C];                            // the first model's outputs of a pair of twins
             const uint32_t nan_first = hot.nan_bits;
-            // rho = RZ-FP32: the short route's int -> float conversion truncates under the binary32 rounding mode "toward
-            // zero" (every other binary32 operation of the loop is exact in either mode, and the binary64 route checks the
-            // direction of its own conversion)
-            if constexpr (FAM == 0) set_f32_round_toward_zero((fl & FL_RZ) != 0);
             (void)kind;
             if ((fl & FL_FTZ_IN) && !staged) {
                 // FlushSubnormal on the staged values, in place (exponents do not change: a subnormal keeps Exp = 1 - bias)
@@ -296,6 +863,10 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
                 __syncthreads();
                 staged = 1;
             }
+            // rho = RZ-FP32: the short route's int -> float conversion truncates under the binary32 rounding mode "toward
+            // zero" (every other binary32 operation of the loop is exact in either mode, and the binary64 route checks the
+            // direction of its own conversion)
+            if constexpr (FAM == 0) set_f32_round_toward_zero((fl & FL_RZ) != 0);
             uint32_t d[R][C];
 #pragma unroll
             for (int r = 0; r < R; ++r)
@@ -318,11 +889,11 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
                     bool have[R][C];                          // (FAM 1) a product took part
                     auto group_max = [&](int r, int c) -> uint32_t {
                         if constexpr (GL == 4) {
-                            return (m2k[g / 2][r * C + c][tid] >> (16 * (g & 1))) & 0xFFFFu;
+                            return (m2k[g / 2][tid][r * C + c] >> (16 * (g & 1))) & 0xFFFFu;
                         } else {
-                            uint32_t x = m2k[g * (GL / 8)][r * C + c][tid];
+                            uint32_t x = m2k[g * (GL / 8)][tid][r * C + c];
 #pragma unroll
-                            for (int i = 1; i < GL / 8; ++i) x = pk_max_u16(x, m2k[g * (GL / 8) + i][r * C + c][tid]);
+                            for (int i = 1; i < GL / 8; ++i) x = pk_max_u16(x, m2k[g * (GL / 8) + i][tid][r * C + c]);
                             const uint32_t lo = x & 0xFFFFu, hi = x >> 16;
                             return lo > hi ? lo : hi;
                         }
@@ -332,7 +903,7 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
 #pragma unroll
                         for (int c = 0; c < C; ++c) {
                             uint32_t e = group_max(r, c);
-                            const int em = (int)e + ebase;
+                            const int em = FAM == 0 ? (int)e - 127 : (int)e + ebase;
                             have[r][c] = true;
                             if constexpr (FAM == 1) {
                                 // (zero terms kept out of the maxima: a product with a zero factor has an exponent sum below 2 ZBIAS)
@@ -345,8 +916,8 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
                                 emax[r][c] = em;
                                 continue;
                             }
-                            tg[r][c] = e & 0xC000u;
-                            tagged |= e;
+                            tg[r][c] = e >= TAGGED ? 0xC000u : 0u;
+                            tagged |= tg[r][c];
                             uint32_t dd = d[r][c];
                             if ((fl & FL_FTZ_IN) && (dd & 0x7F800000u) == 0) { dd = 0; d[r][c] = 0; }     // FlushSubnormal on the accumulator
                             const uint32_t Ec = (dd >> 23) & 0xFFu;                                        // (a flushed subnormal keeps Exp = -126)
@@ -626,11 +1197,11 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
                     // the packed maximum of sub-group sg of the staged tile (SL terms), from the kept quarter maxima
                     auto sub_max = [&](int sg, int r, int c) -> uint32_t {
                         if constexpr (SL == 4) {
-                            return (m2k[sg / 2][r * C + c][tid] >> (16 * (sg & 1))) & 0xFFFFu;
+                            return (m2k[sg / 2][tid][r * C + c] >> (16 * (sg & 1))) & 0xFFFFu;
                         } else {
-                            uint32_t x = m2k[sg * (SL / 8)][r * C + c][tid];
+                            uint32_t x = m2k[sg * (SL / 8)][tid][r * C + c];
 #pragma unroll
-                            for (int i = 1; i < SL / 8; ++i) x = pk_max_u16(x, m2k[sg * (SL / 8) + i][r * C + c][tid]);
+                            for (int i = 1; i < SL / 8; ++i) x = pk_max_u16(x, m2k[sg * (SL / 8) + i][tid][r * C + c]);
                             const uint32_t lo = x & 0xFFFFu, hi = x >> 16;
                             return lo > hi ? lo : hi;
                         }
@@ -733,9 +1304,9 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
                     for (int r = 0; r < R; ++r)
 #pragma unroll
                         for (int c = 0; c < C; ++c) {
-                            uint32_t x = m2k[g * (GL / 4)][r * C + c][tid];
+                            uint32_t x = m2k[g * (GL / 4)][tid][r * C + c];
 #pragma unroll
-                            for (int i = 1; i < GL / 4; ++i) x = pk_max_u16(x, m2k[g * (GL / 4) + i][r * C + c][tid]);
+                            for (int i = 1; i < GL / 4; ++i) x = pk_max_u16(x, m2k[g * (GL / 4) + i][tid][r * C + c]);
                             const uint32_t lo = x & 0xFFFFu, hi = x >> 16;
                             tg[r][c] = x & SENTINEL_MASK;
                             tagged |= x;
@@ -816,63 +1387,20 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
             }
 
             // ---- this model's outputs against the reference ----
-            // Per output that differs: one LDS atomic on its histogram bucket (bucket 0 of the LDS copy counts pairs that
-            // differ at distance 0: zeros of both signs, NaNs of two patterns), so the number of mismatches is the
-            // histogram's sum; the largest distance and the first index are reduced over the wavefront with row shifts,
-            // and lane 63 puts them into LDS.
             // (a pair of twins: the first model's outputs were set aside; then the twin's, in the next place of the arrays)
-            constexpr int ACCOUNTS = TWIN ? 2 : 1;
-#pragma unroll 1
-            for (int acc = 0; acc < ACCOUNTS && (acc == 0 || twin); ++acc) {
-            const bool set_aside = TWIN && twin && acc == 0;
-            if (TWIN && acc == 1) ++mi;
-            uint32_t maxd = 0;
-            uint32_t first_off = 0xFFFFFFFFu;
-            if (live) {
-                uint32_t *dout = nullptr;
-                uint64_t dump_off = 0;
-                if (dumping) { dout = sa->dout; dump_off = (uint64_t)sa->slot[mi] * sa->out_stride; }       // (uniform)
-#pragma unroll
-                for (int r = 0; r < R; ++r)
-#pragma unroll
-                    for (int c = 0; c < C; ++c) {
-                        uint32_t x = set_aside ? dfirst[TWIN ? r : 0][TWIN ? c : 0] : d[r][c];
-                        if (slow_seen && (x & 0x7FFFFFFFu) > 0x7F800000u) x = set_aside ? nan_first : nan_bits;          // (the short route produces no NaN)
-                        const uint64_t o = d_off + (uint64_t)(TI * r) * TN + TJ * c;
-                        if (dumping) dout[dump_off + o] = x;
-                        if (ref_first && mi == 0) ref[r][c] = x;
-                        const uint32_t y = ref[r][c];
-                        if (x != y) {
-                            const uint32_t off = (uint32_t)((TI * r) * TN + TJ * c);
-                            first_off = off < first_off ? off : first_off;
-                            const uint32_t ax = x & 0x7FFFFFFFu, ay = y & 0x7FFFFFFFu;
-                            const bool nx = ax > 0x7F800000u, ny = ay > 0x7F800000u;
-                            uint32_t bucket;
-                            if (nx || ny) {
-                                bucket = (nx && ny) ? 0u : 33u;
-                                if (nx && ny) atomicAdd(&ml.naneq[mi], 1u);                      // (rare)
-                            } else {
-                                // distance of the ordered keys (sign-magnitude patterns read as signed integers): below 2^32
-                                const int32_t sx = (int32_t)x >> 31, sy = (int32_t)y >> 31;                    // 0 or -1
-                                const int32_t kx = ((int32_t)ax ^ sx) - sx, ky = ((int32_t)ay ^ sy) - sy;       // -|x| for a negative x
-                                const uint32_t dist = kx >= ky ? (uint32_t)kx - (uint32_t)ky : (uint32_t)ky - (uint32_t)kx;
-                                maxd = dist > maxd ? dist : maxd;
-                                bucket = 32u - (uint32_t)__clz((int)dist);                                      // (__clz(0) = 32)
-                            }
-                            atomicAdd(&ml.hist[mi][bucket][tid & (HC - 1)], 1u);
-                        }
-                    }
+            if constexpr (TWIN) {
+                if (twin) {
+                    write_nan(dfirst, nan_first);
+                    account(mi, dfirst, true);
+                    ++mi;
+                }
             }
-            // (offsets relative to the first output of this pass of the workgroup: 32 bits do for the reduction)
-            const uint32_t rel = first_off == 0xFFFFFFFFu ? 0xFFFFFFFFu : (uint32_t)(d_off - item0 * (uint64_t)(TM * TN)) + first_off;
-            const uint32_t wmin = wave_reduce_to_lane63<false>(rel), wmax = wave_reduce_to_lane63<true>(maxd);
-            if ((tid & 63u) == 63u && wmin != 0xFFFFFFFFu) {
-                atomicMin(&ml.first[mi], (unsigned long long)(sa->index_base + item0 * (uint64_t)(TM * TN) + wmin));
-                if (wmax) atomicMax(&ml.maxd[mi], wmax);
-            }
-            }
+            if (slow_seen) write_nan(d, nan_bits);                 // (the short route produces no NaN)
+            account(mi, d, slow_seen);
+        }
         }
         set_f32_round_toward_zero(false);
+        }
     }
     __syncthreads();
     // one global atomic per non-zero counter per workgroup; n_compared and bucket 0 are known up front: workgroup 0 adds
@@ -884,8 +1412,8 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
         if (b == 0) {
             uint32_t nonzero = 0, mism = 0;
             for (int bb = 1; bb < 34; ++bb)
-                for (int cpy = 0; cpy < HC; ++cpy) nonzero += ml.hist[mi][bb][cpy];
-            for (int cpy = 0; cpy < HC; ++cpy) mism += ml.hist[mi][0][cpy];         // differing patterns at distance 0
+                for (int cpy = 0; cpy < HC; ++cpy) nonzero += ml.hist[mi][bb == 33 ? 33 : 32 - bb][cpy];
+            for (int cpy = 0; cpy < HC; ++cpy) mism += ml.hist[mi][32][cpy];        // differing patterns at distance 0
             mism += nonzero;
             const unsigned long long total = (unsigned long long)nitems * (TM * TN);
             if (blockIdx.x == 0) { atomicAdd(&g[0], total); atomicAdd(&g[5], total); }
@@ -898,7 +1426,7 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
             if (ml.maxd[mi]) atomicMax(&g[4], (unsigned long long)ml.maxd[mi]);
         } else {
             uint32_t t = 0;
-            for (int cpy = 0; cpy < HC; ++cpy) t += ml.hist[mi][b][cpy];
+            for (int cpy = 0; cpy < HC; ++cpy) t += ml.hist[mi][b == 33 ? 33 : 32 - b][cpy];
             if (t) atomicAdd(&g[5 + b], (unsigned long long)t);
         }
     }

@@ -185,6 +185,50 @@ def test_special_values_and_wide_bf16_inside_the_fused_kernels(mm):
         assert_same(D[i], o1_emulate(p, A, B, C, fm.BF16, fm.BF16), "rational oracle, set %d" % i)
 
 
+@pytest.mark.parametrize("ta,tb,m,k,nb", [(fm.BF16, fm.BF16, 16, 16, 70001), (fm.E5M2, fm.FP16, 16, 16, 66001), (fm.FP16, fm.FP16, 32, 8, 17003),
+                                          (fm.BF16, fm.FP16, 32, 16, 16390)])
+@pytest.mark.parametrize("ref_first", [False, True])
+def test_many_passes_per_workgroup_with_special_and_tiny_tiles(mm, ta, tb, m, k, nb, ref_first):
+    """More tiles than one pass of the persistent workgroups (8 to 9 passes each, a ragged last one), wavefronts with and
+    without NaNs, infinities, overflowing and subnormal results side by side: statistics (the first differing index among
+    them) equal to one emulation and one comparison launch per model."""
+    import torch
+    rng = np.random.default_rng(77 + k + m)
+    A, B, C = make_case(rng, ta, tb, 64, m, m, k)
+    A2, B2, _ = make_case(rng, ta, tb, 16, m, m, k, special_frac=0.02)
+    pick = rng.integers(0, 64, size=nb)
+    A, B, C = A[pick], B[pick], C[pick].copy()
+    odd = rng.choice(nb, size=nb // 50, replace=False)
+    A[odd], B[odd] = A2[rng.integers(0, 16, size=odd.size)], B2[rng.integers(0, 16, size=odd.size)]
+    if ta == fm.BF16:                                            # products around the bottom of binary32, zero or subnormal accumulators
+        tiny = rng.choice(nb, size=nb // 60, replace=False)
+        A[tiny] = synth.narrow_exponent_bits(rng, (tiny.size, m, k), ta, 40, 60)
+        B[tiny] = synth.narrow_exponent_bits(rng, (tiny.size, m, k), tb, 5 if tb == fm.FP16 else 40, 12 if tb == fm.FP16 else 60)
+        C[tiny] &= 0x807FFFFF
+    huge = rng.choice(nb, size=nb // 70, replace=False)          # accumulators next to and at infinity
+    C[huge] = (C[huge] & 0x807FFFFF) | (rng.integers(252, 256, size=C[huge].shape).astype(np.uint32) << 23)
+    plist = [ModelParams(group_len=min(L, k), frac_bits=F, out_round=rho, ftz_in=bool(z), ftz_out=bool(z), nan_bits=0x7FC00000 + i)
+             for i, (F, L, rho, z) in enumerate(SETS16)]
+    hs = _handles(mm, plist)
+    dA, dB, dC = to_dev(A.astype(NP[ta])), to_dev(B.astype(NP[tb])), to_dev(C.astype(np.uint32))
+    D = dev_empty((2, nb, m, m), np.uint32)
+    st = torch.empty(2 * 16 * mm.STATS_BYTES, dtype=torch.uint8, device="cuda")
+    for i in range(32):
+        mm.stats_reset(st[i * mm.STATS_BYTES:])
+    dt = (ta, tb, fm.FP32, fm.FP32)
+    mm.emulate_mma(hs[0 if ref_first else 9], dA, dB, dC, D[0], m, m, k, nb, dt)
+    mm.emulate_compare_many(hs, dA, dB, dC, None if ref_first else D[0], None, m, m, k, nb, dt, st, index_base=5)
+    assert mm.last_kernel().startswith("multi x16")
+    for i, h in enumerate(hs):
+        mm.emulate_mma(h, dA, dB, dC, D[1], m, m, k, nb, dt)
+        mm.compare(D[1], D[0], nb * m * m, st[(16 + i) * mm.STATS_BYTES:], index_base=5)
+    got = mm.read_stats_array(st, 32)
+    for i in range(16):
+        assert got[i] == got[16 + i], (i, plist[i])
+        mm.model_destroy(hs[i])
+    assert sum(s["n_mismatch_bits"] > 0 for s in got[:16]) >= 12 and any(s["n_mismatch_nan_equiv"] for s in got[:16])
+
+
 def rd_sets(rng, k, count):
     """TR-FDPA sets (unsplit groups) with the variation switches drawn at random, group lengths the fused kernel takes."""
     from test_gpu_tiled_rd import random_rd_params
