@@ -103,118 +103,233 @@ __device__ __noinline__ void delta_wide(DynFmt fa, DynFmt fb, const uint8_t *a, 
     ad = ldexp((double)mag, lsb);
 }
 
+// Eight elements of one row as binary32 values (NaN and infinities as themselves), one branch on the type for all
+__device__ __forceinline__ void elem_floats8(uint32_t t, const uint32_t (&bits)[8], float (&v)[8])
+{
+    auto all = [&](auto type_tag) {
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            uint32_t ex;
+            bool wild = false;
+            decode_elem<decltype(type_tag)::value>(bits[q], 0u, 0u, v[q], ex, wild);
+        }
+    };
+    switch (t) {   // uniform
+    case MMAEMU_FP8_E4M3: all(std::integral_constant<int, MMAEMU_FP8_E4M3>{}); break;
+    case MMAEMU_FP8_E5M2: all(std::integral_constant<int, MMAEMU_FP8_E5M2>{}); break;
+    case MMAEMU_FP6_E2M3: all(std::integral_constant<int, MMAEMU_FP6_E2M3>{}); break;
+    case MMAEMU_FP6_E3M2: all(std::integral_constant<int, MMAEMU_FP6_E3M2>{}); break;
+    case MMAEMU_FP4_E2M1: all(std::integral_constant<int, MMAEMU_FP4_E2M1>{}); break;
+    case MMAEMU_FP16: all(std::integral_constant<int, MMAEMU_FP16>{}); break;
+    default: all(std::integral_constant<int, MMAEMU_BF16>{}); break;
+    }
+}
+
+// The products' sum of FP16, FP8, FP6 and FP4 operands in two binary64 numbers: every product is a multiple of 2^-48 below
+// 2^32 in magnitude, so adding and taking away a constant whose last place is 2^-8 splits it there; the upper parts are
+// multiples of 2^-8 that stay below 2^45 and the lower ones multiples of 2^-48 below 2^4 for k up to SPLIT_MAX_K: both
+// sums are exact.  An infinite or NaN operand leaves a NaN in the lower sum.
+constexpr uint32_t SPLIT_MAX_K = 8192;
+struct SplitSum {
+    double upper = 0.0, lower = 0.0;
+    __device__ __forceinline__ void add(float x, float y)
+    {
+        constexpr double M = 0x1.8p+44;
+        const double p = (double)(x * y);                            // exact: 22 significant bits
+        const double u = (p + M) - M;
+        upper += u;
+        lower += p - u;
+    }
+};
+__host__ __device__ constexpr bool splits(uint32_t t)
+{
+    return t == MMAEMU_FP16 || t == MMAEMU_FP8_E4M3 || t == MMAEMU_FP8_E5M2 || t == MMAEMU_FP6_E2M3 || t == MMAEMU_FP6_E3M2 || t == MMAEMU_FP4_E2M1;
+}
+
+// One thread per W consecutive outputs of a row (W = 4: every output sampled, n a multiple of 4; else one sample each).
+// SPLIT: products summed as SplitSum does (7 vector instructions per term), only D, the accumulator and the two sums go
+// through the pair of binary64 numbers; else (BF16: hundreds of binary places, or k beyond SPLIT_MAX_K) every product does
+// (15 per term).  With one output per thread, all through the pair, checks per element, 64-bit divisions per sample and three
+// LDS atomics per sample on few addresses, 2^24 outputs of 32x32x8 FP16 tiles took 229 us; now 119 us (5.6e11 -> 1.1e12 terms/s; bound by binary64 issue).
+template <int W, bool SPLIT>
 __global__ void __launch_bounds__(256)
 deviation_kernel(const void *__restrict__ A, const void *__restrict__ B, const uint32_t *__restrict__ C,
                  const uint32_t *__restrict__ D, uint32_t m, uint32_t n, uint32_t k, uint32_t ta, uint32_t tb, uint64_t stride,
-                 uint64_t nsamples, int bin_exp, mmaemu_deviation_hist *hist)
+                 uint64_t nitems, int bin_exp, mmaemu_deviation_hist *hist)
 {
-    constexpr int NB = MMAEMU_DEVIATION_BINS;
-    __shared__ uint32_t counts[5 + NB];
-    if (threadIdx.x < 5 + NB) counts[threadIdx.x] = 0u;
+    constexpr int NB = MMAEMU_DEVIATION_BINS, COPIES = 8;
+    __shared__ uint32_t counts[5], bins[NB][COPIES];                 // (lanes of a wavefront spread over copies: most samples share few bins)
+    if (threadIdx.x < 5) counts[threadIdx.x] = 0u;
+    for (uint32_t i = threadIdx.x; i < NB * COPIES; i += 256) (&bins[0][0])[i] = 0u;
     __syncthreads();
     const DynFmt fa = dyn_fmt(ta), fb = dyn_fmt(tb);
     const uint32_t esa = (uint32_t)fa.width_ / 8u, esb = (uint32_t)fb.width_ / 8u;
     const uint64_t per_tile = (uint64_t)m * n;
     const int unit_bit = bin_exp - XBASE;                            // index of the bit that weighs one bin width
     const bool vec_a = (reinterpret_cast<uintptr_t>(A) & 15u) == 0 && k % 8u == 0, vec_b = (reinterpret_cast<uintptr_t>(B) & 15u) == 0 && k % 8u == 0;
+    const double finite_max = 0x1.fffffffffffffp+1023;
     double sum = 0.0, sum_abs = 0.0, sum_sq = 0.0;
-    // (a workgroup handles at most 2^32 / 256 samples: the 32-bit LDS counters cannot overflow, see the launch)
-    for (uint64_t sidx = (uint64_t)blockIdx.x * 256u + threadIdx.x; sidx < nsamples; sidx += (uint64_t)gridDim.x * 256u) {
-        const uint64_t o = sidx * stride;
-        const uint64_t tile = o / per_tile;
-        const uint32_t rem = (uint32_t)(o - tile * per_tile), i = rem / n, j = rem - i * n;
+    uint32_t n_seen = 0, n_bad = 0, n_neg = 0, n_zero = 0;
+    // (a workgroup handles at most 2^32 / 256 samples: the 32-bit counters cannot overflow, see the launch)
+    for (uint64_t item = (uint64_t)blockIdx.x * 256u + threadIdx.x; item < nitems; item += (uint64_t)gridDim.x * 256u) {
+        const uint64_t o = W == 1 ? item * stride : item * (uint64_t)W;
+        uint64_t tile;
+        uint32_t rem;
+        if ((o >> 32) == 0 && (per_tile >> 32) == 0) {               // (a 64-bit division costs a hundred instructions)
+            const uint32_t q = (uint32_t)o / (uint32_t)per_tile;
+            tile = q;
+            rem = (uint32_t)o - q * (uint32_t)per_tile;
+        } else {
+            tile = o / per_tile;
+            rem = (uint32_t)(o - tile * per_tile);
+        }
+        const uint32_t i = rem / n, j = rem - i * n;
         const uint8_t *a = static_cast<const uint8_t *>(A) + (tile * m + i) * (uint64_t)k * esa;
         const uint8_t *b = static_cast<const uint8_t *>(B) + (tile * n + j) * (uint64_t)k * esb;
-        // delta first as an unevaluated pair of binary64 numbers (efdpa_pair.hpp): D, then every product and the accumulator
-        // taken away; while the pair holds the sum exactly (always for FP16 / FP8 operands; BF16 or FP32 operands spread
-        // over hundreds of binary places may leave it) sign, bin and binary64 image follow from the normalised pair
-        const uint32_t cb = C ? C[o] : 0u, db = D[o];
-        bool bad = (cb & 0x7F800000u) == 0x7F800000u || (db & 0x7F800000u) == 0x7F800000u;
-        ExactPair pr;
-        pr.start(db);
-        const double finite_max = 0x1.fffffffffffffp+1023;
-        uint32_t kk = 0;
-        for (; kk + 8 <= k; kk += 8) {
-            // (eight elements of each row fetched before the first is used: one wait per eight terms)
-            uint32_t ra[8], rb[8];
-            load8(ta, esa, a, kk, vec_a, ra);
-            load8(tb, esb, b, kk, vec_b, rb);
-            double xa[8], xb[8];
-            elem_values(ta, ra, 0u, xa);                             // (one branch on the type per eight elements)
-            elem_values(tb, rb, 0u, xb);
+        uint32_t cb[W], db[W];
+        if constexpr (W == 4) {
+            const uint4 d4 = *reinterpret_cast<const uint4 *>(D + o), c4 = C ? *reinterpret_cast<const uint4 *>(C + o) : make_uint4(0u, 0u, 0u, 0u);
+            db[0] = d4.x; db[1] = d4.y; db[2] = d4.z; db[3] = d4.w;
+            cb[0] = c4.x; cb[1] = c4.y; cb[2] = c4.z; cb[3] = c4.w;
+        } else {
+            cb[0] = C ? C[o] : 0u;
+            db[0] = D[o];
+        }
+        // delta as an unevaluated pair of binary64 numbers (efdpa_pair.hpp): D, then the products and the accumulator taken
+        // away; while the pair holds the sum exactly (always for FP16 / FP8 operands; BF16 operands spread over hundreds of
+        // binary places may leave it) sign, bin and binary64 image follow from the normalised pair
+        ExactPair pr[W];
+        bool bad[W];
 #pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                bad |= !(__builtin_fabs(xa[q]) <= finite_max) || !(__builtin_fabs(xb[q]) <= finite_max);
-                pr.add(-xa[q], xb[q]);
+        for (int w = 0; w < W; ++w) {
+            bad[w] = (cb[w] & 0x7F800000u) == 0x7F800000u || (db[w] & 0x7F800000u) == 0x7F800000u;
+            pr[w].start(db[w]);
+        }
+        if constexpr (SPLIT) {
+            SplitSum sp[W];
+            uint32_t kk = 0;
+            for (; kk + 8 <= k; kk += 8) {
+                uint32_t raw[8];
+                float xa[8], xb[8];
+                load8(ta, esa, a, kk, vec_a, raw);
+                elem_floats8(ta, raw, xa);
+#pragma unroll
+                for (int w = 0; w < W; ++w) {
+                    load8(tb, esb, b + (uint64_t)w * k * esb, kk, vec_b, raw);
+                    elem_floats8(tb, raw, xb);
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) sp[w].add(xa[q], xb[q]);
+                }
             }
-        }
-        for (; kk < k; ++kk) {
-            const double x = elem_value(ta, elem_bits(ta, esa, a, kk), 0u), y = elem_value(tb, elem_bits(tb, esb, b, kk), 0u);
-            bad |= !(__builtin_fabs(x) <= finite_max) || !(__builtin_fabs(y) <= finite_max);
-            pr.add(-x, y);
-        }
-        if (bad) { atomicAdd(&counts[1], 1u); continue; }
-        pr.add(-(double)__uint_as_float(cb), 1.0);
-        uint32_t neg;
-        bool zero;
-        int fi;
-        double ad;
-        if (pr.lost == 0.0) {
-            double h, l;
-            two_sum(pr.hi, pr.lo, h, l);                                 // h = RN(delta), l = delta - h
-            neg = h < 0.0;
-            zero = h == 0.0;
-            ad = __builtin_fabs(h);
-            // floor(delta / 2^bin_exp): of h, and one less where h is a whole number of bins and l lies below it (a
-            // fractional h / w keeps at least one of its own last places to either side, more than |l / w|)
-            const double qh = ldexp(h, -bin_exp);
-            if (qh >= (double)NB) fi = NB;
-            else if (qh <= -(double)NB) fi = -NB;
-            else if (qh == 0.0) fi = neg ? -1 : 0;                       // (h / w below the binary64 range)
-            else {
-                const double fl = __builtin_floor(qh);
-                fi = (int)fl - ((fl == qh && l < 0.0) ? 1 : 0);
+            for (; kk < k; ++kk) {
+                const float x = (float)elem_value(ta, elem_bits(ta, esa, a, kk), 0u);
+#pragma unroll
+                for (int w = 0; w < W; ++w) sp[w].add(x, (float)elem_value(tb, elem_bits(tb, esb, b + (uint64_t)w * k * esb, kk), 0u));
+            }
+#pragma unroll
+            for (int w = 0; w < W; ++w) {
+                bad[w] |= !(__builtin_fabs(sp[w].lower) <= finite_max);
+                // (hi + lo = D - upper exactly; the lower sum joins lo, and what lo cannot hold shows in `lost`)
+                two_sum(pr[w].hi, -sp[w].upper, pr[w].hi, pr[w].lo);
+                two_sum(pr[w].lo, -sp[w].lower, pr[w].lo, pr[w].lost);
             }
         } else {
-            delta_wide(fa, fb, a, b, k, cb, db, unit_bit, neg, zero, fi, ad);
+            uint32_t kk = 0;
+            for (; kk + 8 <= k; kk += 8) {
+                // (eight elements of each row fetched before the first is used: one wait per eight terms)
+                uint32_t ra[8], rb[8];
+                load8(ta, esa, a, kk, vec_a, ra);
+                load8(tb, esb, b, kk, vec_b, rb);
+                double xa[8], xb[8];
+                elem_values(ta, ra, 0u, xa);                             // (one branch on the type per eight elements)
+                elem_values(tb, rb, 0u, xb);
+#pragma unroll
+                for (int q = 0; q < 8; ++q) {
+                    bad[0] |= !(__builtin_fabs(xa[q]) <= finite_max) || !(__builtin_fabs(xb[q]) <= finite_max);
+                    pr[0].add(-xa[q], xb[q]);
+                }
+            }
+            for (; kk < k; ++kk) {
+                const double x = elem_value(ta, elem_bits(ta, esa, a, kk), 0u), y = elem_value(tb, elem_bits(tb, esb, b, kk), 0u);
+                bad[0] |= !(__builtin_fabs(x) <= finite_max) || !(__builtin_fabs(y) <= finite_max);
+                pr[0].add(-x, y);
+            }
         }
-        atomicAdd(&counts[0], 1u);
-        if (zero) {
-            atomicAdd(&counts[3], 1u);
-            atomicAdd(&counts[5 + NB / 2], 1u);
-            continue;
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            if (bad[w]) { ++n_bad; continue; }
+            pr[w].add(-(double)__uint_as_float(cb[w]), 1.0);
+            uint32_t neg;
+            bool zero;
+            int fi;
+            double ad;
+            if (pr[w].lost == 0.0) {
+                double h, l;
+                two_sum(pr[w].hi, pr[w].lo, h, l);                       // h = RN(delta), l = delta - h
+                neg = h < 0.0;
+                zero = h == 0.0;
+                ad = __builtin_fabs(h);
+                // floor(delta / 2^bin_exp): of h, and one less where h is a whole number of bins and l lies below it (a
+                // fractional h / w keeps at least one of its own last places to either side, more than |l / w|)
+                const double qh = ldexp(h, -bin_exp);
+                if (qh >= (double)NB) fi = NB;
+                else if (qh <= -(double)NB) fi = -NB;
+                else if (qh == 0.0) fi = neg ? -1 : 0;                   // (h / w below the binary64 range)
+                else {
+                    const double fl = __builtin_floor(qh);
+                    fi = (int)fl - ((fl == qh && l < 0.0) ? 1 : 0);
+                }
+            } else {
+                delta_wide(fa, fb, a, b + (uint64_t)w * k * esb, k, cb[w], db[w], unit_bit, neg, zero, fi, ad);
+            }
+            ++n_seen;
+            n_zero += zero ? 1u : 0u;
+            n_neg += (!zero && neg) ? 1u : 0u;
+            int bin = zero ? NB / 2 : fi + NB / 2;
+            bin = bin < 0 ? 0 : (bin > NB - 1 ? NB - 1 : bin);
+            atomicAdd(&bins[bin][threadIdx.x % COPIES], 1u);
+            ad = zero ? 0.0 : ad;
+            sum += neg ? -ad : ad;
+            sum_abs += ad;
+            sum_sq += ad * ad;
         }
-        atomicAdd(&counts[neg ? 2 : 4], 1u);
-        int bin = fi + NB / 2;
-        bin = bin < 0 ? 0 : (bin > NB - 1 ? NB - 1 : bin);
-        atomicAdd(&counts[5 + bin], 1u);
-        sum += neg ? -ad : ad;
-        sum_abs += ad;
-        sum_sq += ad * ad;
     }
-    // the three sums: over the wavefront by lane exchanges, over the workgroup through LDS, then one atomic per workgroup
-    // and sum (thousands of wavefronts adding to the same three words took longer than everything else in the kernel)
+    // the counts and the three sums: over the wavefront by lane exchanges, over the workgroup through LDS, then one atomic per
+    // workgroup and word (thousands of wavefronts adding to the same few words took longer than everything else in the kernel)
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) {
         sum += __shfl_xor(sum, off, 64);
         sum_abs += __shfl_xor(sum_abs, off, 64);
         sum_sq += __shfl_xor(sum_sq, off, 64);
+        n_seen += __shfl_xor(n_seen, off, 64);
+        n_bad += __shfl_xor(n_bad, off, 64);
+        n_neg += __shfl_xor(n_neg, off, 64);
+        n_zero += __shfl_xor(n_zero, off, 64);
     }
     __shared__ double wave_sums[4][3];
     if ((threadIdx.x & 63u) == 0u) {
         wave_sums[threadIdx.x >> 6][0] = sum;
         wave_sums[threadIdx.x >> 6][1] = sum_abs;
         wave_sums[threadIdx.x >> 6][2] = sum_sq;
+        const uint32_t c5[5] = {n_seen, n_bad, n_neg, n_zero, n_seen - n_neg - n_zero};
+#pragma unroll
+        for (int q = 0; q < 5; ++q) if (c5[q]) atomicAdd(&counts[q], c5[q]);
     }
     __syncthreads();
     double *gd = reinterpret_cast<double *>(reinterpret_cast<uint64_t *>(hist) + 5 + NB);
+    unsigned long long *gc = reinterpret_cast<unsigned long long *>(hist);
     if (threadIdx.x < 3) {
         const double t = (wave_sums[0][threadIdx.x] + wave_sums[1][threadIdx.x]) + (wave_sums[2][threadIdx.x] + wave_sums[3][threadIdx.x]);
         if (t != 0.0) atomicAdd(&gd[threadIdx.x], t);
+    } else if (threadIdx.x >= 64u && threadIdx.x < 64u + 5u) {
+        if (counts[threadIdx.x - 64u]) atomicAdd(gc + (threadIdx.x - 64u), (unsigned long long)counts[threadIdx.x - 64u]);
+    } else if (threadIdx.x >= 128u && threadIdx.x < 128u + NB) {
+        const uint32_t bin = threadIdx.x - 128u;
+        uint32_t t = 0;
+#pragma unroll
+        for (int q = 0; q < COPIES; ++q) t += bins[bin][q];
+        if (t) atomicAdd(gc + 5 + bin, (unsigned long long)t);
     }
-    __syncthreads();
-    if (threadIdx.x < 5 + NB && counts[threadIdx.x])
-        atomicAdd(reinterpret_cast<unsigned long long *>(hist) + threadIdx.x, (unsigned long long)counts[threadIdx.x]);
 }
 
 mmaemu_status launch_deviation_reset(mmaemu_deviation_hist *h, hipStream_t s)
@@ -231,11 +346,20 @@ mmaemu_status launch_deviation_sample(const void *A, const void *B, const uint32
     const uint64_t total = batch * m * n;
     const uint64_t nsamples = (total + stride - 1) / stride;
     if (nsamples == 0) return MMAEMU_OK;
-    uint64_t blocks = (nsamples + 255) / 256;
+    // Four outputs of a row per thread where every output is sampled and rows hold whole fours at 16-byte steps; the split sum
+    // for every type but BF16 (whose products span more than the split holds) up to the k for which it is exact.
+    const bool split = splits(ta) && splits(tb) && k <= SPLIT_MAX_K;
+    const bool wide = split && stride == 1 && n % 4 == 0 && ((reinterpret_cast<uintptr_t>(C) | reinterpret_cast<uintptr_t>(D)) & 15u) == 0;
+    const uint64_t nitems = wide ? nsamples / 4 : nsamples;
+    uint64_t blocks = (nitems + 255) / 256;
     if (blocks > 2048) blocks = 2048;                                // grid-stride beyond that: two rounds of what the chip holds
     if ((nsamples + blocks - 1) / blocks > 0xFFFFFFFFull) { set_error("deviation_sample: more than 2^43 samples in one call"); return MMAEMU_ERR_SHAPE; }
-    hipLaunchKernelGGL(deviation_kernel, dim3((uint32_t)blocks), dim3(256), 0, s, A, B, C, D, m, n, k, ta, tb, stride, nsamples,
-                       bin_exp, h);
+#define DEVIATION_LAUNCH(W_, S_)                                                                                              \
+    hipLaunchKernelGGL((deviation_kernel<W_, S_>), dim3((uint32_t)blocks), dim3(256), 0, s, A, B, C, D, m, n, k, ta, tb, stride, nitems, bin_exp, h)
+    if (wide) DEVIATION_LAUNCH(4, true);
+    else if (split) DEVIATION_LAUNCH(1, true);
+    else DEVIATION_LAUNCH(1, false);
+#undef DEVIATION_LAUNCH
     MMAEMU_HIP(hipGetLastError());
     return MMAEMU_OK;
 }

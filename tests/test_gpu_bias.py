@@ -134,6 +134,30 @@ def test_deviation_sample_matches_oracle(mm):
             assert got["n_skipped"] > 0 and len([b for b in got["bins"] if b]) > 8
 
 
+@pytest.mark.parametrize("ta,tb,shape,stride,c_offset", [
+    (fm.FP16, fm.FP16, (3, 5, 4, 8), 1, 0), (fm.FP16, fm.E5M2, (1, 3, 4, 8192), 1, 0), (fm.FP16, fm.FP16, (1, 2, 4, 8200), 1, 0),
+    (fm.E5M2, fm.E5M2, (2, 3, 8, 17), 1, 0), (fm.FP16, fm.FP16, (4, 7, 6, 8), 1, 0), (fm.FP16, fm.FP16, (3, 5, 8, 12), 1, 1),
+    (fm.E4M3, fm.E4M3, (3, 4, 8, 16), 3, 0)])
+def test_deviation_sample_split_sum(mm, ta, tb, shape, stride, c_offset):
+    """Products at both ends of the narrow types' ranges (the split sum's two halves full), the k at which the split ends, rows
+    of four outputs per thread and rows that are not, an accumulator that is not 16-byte aligned."""
+    import torch
+    rng = np.random.default_rng(5 + shape[3])
+    nb, m, n, k = shape
+    A, B = synth.random_bits(rng, (nb, m, k), ta), synth.random_bits(rng, (nb, n, k), tb)
+    big = {fm.FP16: 0x7BFF, fm.E5M2: 0x7B, fm.E4M3: 0x7E}
+    A = np.where(rng.random(A.shape) < 0.4, np.where(rng.random(A.shape) < 0.5, big[ta], 1), A).astype(A.dtype)
+    B = np.where(rng.random(B.shape) < 0.4, np.where(rng.random(B.shape) < 0.5, big[tb], 1), B).astype(B.dtype)
+    C = synth.narrow_exponent_bits(rng, (nb, m, n), fm.FP32, 90, 160)
+    D = o2lib.emulate_mma(ModelParams(group_len=k, frac_bits=24), A, B, C, ta, tb)[0]
+    D[0, 0, 0] = 0x7F800000
+    h = torch.empty(mm.DEVIATION_HIST_BYTES, dtype=torch.uint8, device="cuda")
+    mm.deviation_hist_reset(h)
+    dC = to_dev(np.concatenate([np.zeros(c_offset, np.uint32), C.ravel()]))[c_offset:]
+    mm.deviation_sample(to_dev(A), to_dev(B), dC, to_dev(D), m, n, k, nb, (ta, tb, fm.FP32, fm.FP32), stride, -3, h)
+    same_hist(mm.read_deviation_hist(h), deviation_hist(A, B, C, D, ta, tb, stride, -3), shape)
+
+
 def test_deviation_sample_extremes_and_errors(mm):
     import torch
     # the widest reach of the exact sum: BF16 products at both ends of the range next to binary32's smallest subnormal
