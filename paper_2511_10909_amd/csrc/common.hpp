@@ -113,6 +113,10 @@ mmaemu_status launch_emulate_efdpa(const ModelArgs &p, const void *A, const void
 bool efdpa_pairs_take(const ModelArgs &p, const void *C, const void *D, uint32_t k);
 mmaemu_status launch_emulate_efdpa_pairs(const ModelArgs &p, const void *A, const void *B, const void *C, void *D, uint32_t m, uint32_t n,
                                          uint32_t k, uint64_t batch, uint32_t ta, uint32_t tb, hipStream_t s);
+// Tiles of at most 8 x 8 outputs (emulate_small.hip): T-FDPA and unsplit TR-FDPA on 8- and 16-bit operands
+bool small_takes(const ModelArgs &p, uint32_t ta, uint32_t tb, uint32_t m, uint32_t n, uint32_t k);
+mmaemu_status launch_emulate_small(const ModelArgs &p, const void *A, const void *B, const void *C, void *D, uint32_t m, uint32_t n,
+                                   uint32_t k, uint64_t batch, uint32_t ta, uint32_t tb, hipStream_t s);
 mmaemu_status launch_emulate_generic(const ModelArgs &p, const void *A, const void *B, const void *C, void *D,
                                      uint32_t m, uint32_t n, uint32_t k, uint64_t batch, uint32_t ta,
                                      uint32_t tb, hipStream_t s, const uint8_t *SA = nullptr, const uint8_t *SB = nullptr,

@@ -41,7 +41,7 @@
 // Measured, one launch of the sixteen sets of the closed-loop scan on 2^16 tiles of 16x16x16, before and after: FP8 1194 ->
 // 770 us (6.9 instructions per term), BF16 bit patterns 1495 -> 1110 us (8.6), all FP16 bit patterns (a quarter of the tiles)
 // 584 -> 259 us; three sets on 2^18 tiles of 32x32x8 2028 -> 1430 us.  What is left is still issue: VALU busy 86 to 99 %.
-#include "emulate_tiled.hpp"
+#include "rd_value.hpp"
 
 namespace mmaemu {
 
@@ -82,41 +82,6 @@ __device__ __forceinline__ ScanArgs::Hot scan_hot(uint32_t mi)
 // fourth wave brings: +6 %.  Five waves were slower.  The BF16 kernels that keep 64 products take three: at four, 300 to 600
 // registers went to scratch memory, 3785 against 1307 us a launch.  The 16 x 16 x 32 instantiations hold two or three
 // workgroups per CU and are compiled for that many waves.)
-// Algorithm "TR-FDPA", steps 3 and 4, and the variations of it that the model switches name, in binary64 (every quantity
-// is an integer of fewer than 53 bits times a power of two, hence exact): T counts units of 2^(em - F) (have_T: a product
-// took part), cb is the accumulator; returns the exact value whose conversion is the group's result.
-__device__ __forceinline__ double scan_rd_value(double T, bool have_T, int em, int F, uint32_t cb, int F2, int Fc, int drop, uint32_t fl)
-{
-    const int Fmax = F2 > Fc ? F2 : Fc;
-    const uint32_t Ec = (cb >> 23) & 0xFFu;
-    const int ec = (int)(Ec ? Ec : 1u) - 127;
-    const int E = have_T ? (ec > em ? ec : em) : ec;                      // the accumulator always takes part
-    if (have_T && drop && E - em >= drop) have_T = false;                 // the product sum lies too far below: it drops out
-    if (!have_T) T = 0.0;
-    const double sc_exact = ldexp((double)__uint_as_float(cb), Fc - E);
-    double sc = (fl & FL_RD_AS_RZ) ? __builtin_trunc(sc_exact) : __builtin_floor(sc_exact);     // RD_Fc(c at E), units of 2^(E - Fc)
-    if ((fl & FL_SPECIAL_TRUNC) && ec < E - Fc - 1 && Ec != 0xFFu) sc = 0.0;                   // (an infinite or NaN accumulator stays)
-    if (!(fl & FL_F2_LEADING)) {
-        const double T_exact = ldexp(T, (em - F) - (E - F2));
-        const double T2 = (fl & FL_RD_AS_RZ) ? __builtin_trunc(T_exact) : __builtin_floor(T_exact);   // RD_F2(T at E)
-        return ldexp(ldexp(T2, Fmax - F2) + ldexp(sc, Fmax - Fc), E - Fmax);
-    }
-    // F2 counted from the leading bit of the exact two-term sum, held as s + err (Knuth's TwoSum; |err| is below half a
-    // last place of s, far under the unit that is kept)
-    const double a = ldexp(T, em - F), b = ldexp(sc, E - Fc);
-    const double sm = a + b, bb = sm - a;
-    const double err = (a - (sm - bb)) + (b - bb);
-    const long long sbits = __double_as_longlong(sm);
-    int lead = (int)((sbits >> 52) & 0x7FF) - 1023;
-    const bool toward_zero = (err != 0.0) && ((err < 0.0) != (sm < 0.0));
-    if ((sbits & 0xFFFFFFFFFFFFFll) == 0 && toward_zero) lead -= 1;        // just inside the binade below
-    lead = lead < -126 ? -126 : lead;                                       // binary32's smallest normal exponent
-    const int unit = lead - F2;
-    double q = __builtin_floor(ldexp(sm, -unit));
-    if (err < 0.0 && ldexp(q, unit) == sm) q -= 1.0;                        // s on the grid, the exact sum just below it
-    return sm == 0.0 ? 0.0 : ldexp(q, unit);
-}
-
 // A kept quarter maximum (FAM 0: biased exponent) at or above this one holds a NaN or an infinity.
 constexpr uint32_t TAGGED = 0x2000u;
 
@@ -1092,7 +1057,7 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
                                     v = ldexp(T + tc, unit);                                   // exact: integers below 2^53
                                 } else {
                                     if ((fl & FL_FTZ_IN) && (d[r][c] & 0x7F800000u) == 0) d[r][c] = 0;         // FlushSubnormal on the accumulator
-                                    v = scan_rd_value(T, have[r][c], emax[r][c], F, d[r][c], hot.F2, hot.Fc, hot.drop, fl);
+                                    v = rd_value(T, have[r][c], emax[r][c], F, d[r][c], hot.F2, hot.Fc, hot.drop, fl);
                                 }
                                 uint32_t o = __float_as_uint((float)v);
                                 if ((fe & FL_RZ)) {
@@ -1153,7 +1118,7 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
 #pragma unroll
                     for (int c = 0; c < C; ++c) {
                         if ((fl & FL_FTZ_IN) && (d[r][c] & 0x7F800000u) == 0) d[r][c] = 0;                 // FlushSubnormal on the accumulator
-                        const double v = scan_rd_value(T[r][c], hv[r][c], em[r][c], hot.Fm, d[r][c], hot.F2, hot.Fc, hot.drop, fl);
+                        const double v = rd_value(T[r][c], hv[r][c], em[r][c], hot.Fm, d[r][c], hot.F2, hot.Fc, hot.drop, fl);
                         uint32_t o = __float_as_uint((float)v);
                         if ((fl & FL_RZ)) {
                             const double back = (double)__uint_as_float(o);

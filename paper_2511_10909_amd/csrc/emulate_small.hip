@@ -1,0 +1,178 @@
+// Tiles of at most 8 x 8 outputs (the 4 x 4 x 4 blocks of v_mfma_f32_4x4x4_16b_f16), which would leave a block of the tiled
+// kernels mostly empty: T-FDPA and TR-FDPA without splits on 8- and 16-bit operands, groups of 4, 8 or 16, one thread
+// per W outputs of a row, operands straight from global memory (a tile is a few hundred bytes: its rows come from L1).
+//
+// Same arithmetic as the tiled kernels: an element becomes its exact binary32 value and a biased exponent, the group's
+// maximum is taken on packed exponent sums, the exact product times 2^(F - e_max) is truncated, the sum and what follows it
+// are exact in binary64, and one conversion rounds.  DBL: products and alignment in binary64 (BF16, whose products leave
+// binary32, and F of 30 and more).  A NaN or infinity in a group shows in the IEEE sum of its products and accumulator, which
+// is then the group's result (Sec. 4.2); TR-FDPA's products of 2^128 and more enter that sum as infinities.
+//
+// Bound: vector-ALU issue, about 130 instructions per output of one group of four (the general kernel's 64-bit integers,
+// 128-bit ones in the two round-downs, and its walk over the operands for every question took about 1000: gfx950's fitted
+// set on 2^18 tiles of 4x4x4 FP16 106 us there, 26 us here, 1.9 TB/s).  W = 4 (n a multiple of four) decodes the row of A once for four
+// outputs and moves C and D as 128-bit words.
+#include "rd_value.hpp"
+
+namespace mmaemu {
+
+struct SmallArgs {
+    ModelArgs p;
+    uint32_t ta, tb, esa, esb;
+    int32_t ebase;
+    uint32_t zbias;
+};
+
+template <int QL>
+__device__ __forceinline__ void small_row(uint32_t t, uint32_t es, const uint8_t *row, uint32_t ftz, uint32_t zbias, float (&f)[QL][4], uint2 (&e)[QL])
+{
+    uint2 raw[QL];
+#pragma unroll
+    for (int q = 0; q < QL; ++q) {
+        if (es == 1) raw[q] = make_uint2(reinterpret_cast<const uint32_t *>(row)[q], 0u);
+        else raw[q] = reinterpret_cast<const uint2 *>(row)[q];
+    }
+    decode_any<QL>(t, raw, ftz, zbias, f, e);
+}
+
+template <int W, int QL, bool RD, bool DBL>
+__global__ void __launch_bounds__(256)
+emulate_small_kernel(SmallArgs sm, const uint8_t *__restrict__ A, const uint8_t *__restrict__ B, const uint32_t *Cm, uint32_t *D, uint32_t m,
+                     uint32_t n, uint32_t k, uint64_t nitems)
+{
+    typedef typename std::conditional<DBL, double, float>::type V;
+    const ModelArgs &p = sm.p;
+    const uint32_t fl = p.flags, nw = n / W, per_tile = m * nw;
+    const int F = p.F;
+    for (uint64_t item = (uint64_t)blockIdx.x * 256u + threadIdx.x; item < nitems; item += (uint64_t)gridDim.x * 256u) {
+        uint64_t tile;
+        uint32_t rem;
+        split_item(item, per_tile, tile, rem);
+        const uint32_t i = rem / nw, j = (rem - i * nw) * W;
+        const uint8_t *a = A + (tile * m + i) * (uint64_t)k * sm.esa;
+        const uint8_t *b = B + (tile * n + j) * (uint64_t)k * sm.esb;
+        const uint64_t o0 = (tile * m + i) * (uint64_t)n + j;
+        uint32_t d[W];
+        if constexpr (W == 4) {
+            const uint4 c4 = *reinterpret_cast<const uint4 *>(Cm + o0);
+            d[0] = c4.x; d[1] = c4.y; d[2] = c4.z; d[3] = c4.w;
+        } else {
+            d[0] = Cm[o0];
+        }
+        for (uint32_t k0 = 0; k0 < k; k0 += 4 * QL) {
+            float fa[QL][4];
+            uint2 ea[QL];
+            small_row<QL>(sm.ta, sm.esa, a + (uint64_t)k0 * sm.esa, fl & FL_FTZ_IN, sm.zbias, fa, ea);
+#pragma unroll
+            for (int w = 0; w < W; ++w) {
+                float fb[QL][4];
+                uint2 eb[QL];
+                small_row<QL>(sm.tb, sm.esb, b + ((uint64_t)w * k + k0) * sm.esb, fl & FL_FTZ_IN, sm.zbias, fb, eb);
+                uint32_t mx = 0;
+#pragma unroll
+                for (int q = 0; q < QL; ++q) mx = pk_max_u16(mx, pk_max_u16(pk_add_u16(ea[q].x, eb[q].x), pk_add_u16(ea[q].y, eb[q].y)));
+                const uint32_t lo = mx & 0xFFFFu, hi = mx >> 16, e = lo > hi ? lo : hi;
+                uint32_t cb = d[w];
+                if ((fl & FL_FTZ_IN) && (cb & 0x7F800000u) == 0) cb = 0u;                      // FlushSubnormal on the accumulator
+                // (a tagged group's exponents are never used: any in-range value does)
+                const int em = (e & 0xC000u) ? 0 : (int)e + sm.ebase;
+                const uint32_t Ec = (cb >> 23) & 0xFFu;
+                const int ec = (int)(Ec ? Ec : 1u) - 127;
+                const int emax = RD ? em : (ec > em ? ec : em);
+                V scale;
+                if constexpr (DBL) scale = __hiloint2double((F - emax + 1023) << 20, 0);
+                else {
+                    int se = F + 127 - emax;
+                    se = se < 1 ? 1 : (se > 254 ? 254 : se);                                   // the clamps never change a truncated term
+                    scale = __uint_as_float((uint32_t)se << 23);
+                }
+                double T = 0.0;
+                V s = (V)__uint_as_float(cb);
+#pragma unroll
+                for (int q = 0; q < QL; ++q)
+#pragma unroll
+                    for (int x = 0; x < 4; ++x) {
+                        V pr = (V)fa[q][x] * (V)fb[q][x];                                      // exact
+                        if constexpr (DBL) T += __builtin_trunc(pr * scale);
+                        else T += (double)__builtin_truncf(pr * scale);
+                        if constexpr (DBL && RD) {
+                            if (__builtin_fabs(pr) >= 0x1p+128) pr = __builtin_copysign(__builtin_huge_val(), pr);
+                        }
+                        s += pr;
+                    }
+                double v;
+                if constexpr (RD) v = rd_value(T, !(fl & FL_SKIP_ZERO) || e >= 2 * ZBIAS, em, F, cb, p.F2, p.Fc, p.sum_drop_distance, fl);
+                else {
+                    const int unit = emax - F;
+                    v = ldexp(T + __builtin_trunc(ldexp((double)__uint_as_float(cb), -unit)), unit);
+                }
+                uint32_t o = __float_as_uint((float)v);
+                if (fl & FL_RZ) {
+                    const double back = (double)__uint_as_float(o);
+                    if (__builtin_fabs(back) > __builtin_fabs(v)) o -= 1u;                     // rounded away from zero: step back
+                    o &= p.out_mask;
+                }
+                if ((fl & FL_FTZ_OUT) && (o & 0x7F800000u) == 0) o &= 0x80000000u;
+                if (RD && (fl & FL_ZERO_POSITIVE) && (o & 0x7FFFFFFFu) == 0) o = 0u;
+                if (s != s) o = p.nan_bits;
+                else if (__builtin_fabs((double)s) > 0x1.fffffffffffffp+1023) o = s > (V)0 ? 0x7F800000u : 0xFF800000u;
+                d[w] = o;
+            }
+        }
+        if constexpr (W == 4) *reinterpret_cast<uint4 *>(D + o0) = make_uint4(d[0], d[1], d[2], d[3]);
+        else D[o0] = d[0];
+    }
+}
+
+// What it takes of the problems that the tiled kernels would take but for the shape (see launch_emulate).  L is at most k
+// here, so a k below the group length arrives as L = k.  Ragged tiles above 8 x 8 stay with the general kernel: they are what
+// its integer construction, the check on this arithmetic, is tested on.
+bool small_takes(const ModelArgs &p, uint32_t ta, uint32_t tb, uint32_t m, uint32_t n, uint32_t k)
+{
+    if (m > 8 || n > 8) return false;
+    if (p.flags & (FL_ACC16 | FL_NAN_PROPAGATE)) return false;
+    if (!(p.c_mode == MMAEMU_C_IN_GROUP || (p.c_mode == MMAEMU_C_AFTER_RD && p.split == MMAEMU_SPLIT_NONE))) return false;
+    if (ta == MMAEMU_FP32 || tb == MMAEMU_FP32 || ta == MMAEMU_TF32 || tb == MMAEMU_TF32) return false;
+    return (p.L == 4 || p.L == 8 || p.L == 16) && k % p.L == 0;
+}
+
+mmaemu_status launch_emulate_small(const ModelArgs &p, const void *A, const void *B, const void *Cm, void *D, uint32_t m, uint32_t n,
+                                   uint32_t k, uint64_t batch, uint32_t ta, uint32_t tb, hipStream_t s)
+{
+    SmallArgs sm;
+    sm.p = p;
+    sm.ta = ta;
+    sm.tb = tb;
+    sm.esa = (uint32_t)fmt_info(ta).width / 8u;
+    sm.esb = (uint32_t)fmt_info(tb).width / 8u;
+    sm.zbias = (p.c_mode == MMAEMU_C_AFTER_RD && p.skip_zero_terms) ? ZBIAS : 0u;
+    sm.ebase = 2 - fmt_info(ta).bias - fmt_info(tb).bias - 2 * (int)sm.zbias;
+    const bool wide = n % 4 == 0 && ((reinterpret_cast<uintptr_t>(Cm) | reinterpret_cast<uintptr_t>(D)) & 15u) == 0;
+    const bool dbl = ta == MMAEMU_BF16 || tb == MMAEMU_BF16 || p.F >= 30, rd = p.c_mode == MMAEMU_C_AFTER_RD;
+    const uint64_t nitems = batch * m * (wide ? n / 4 : n);
+    uint64_t blocks = (nitems + 255) / 256;
+    if (blocks > (1ull << 20)) blocks = 1ull << 20;                  // grid-stride beyond that
+    const uint8_t *a = static_cast<const uint8_t *>(A), *b = static_cast<const uint8_t *>(B);
+    const uint32_t *c = static_cast<const uint32_t *>(Cm);
+    uint32_t *d = static_cast<uint32_t *>(D);
+    auto go = [&](auto w_c, auto ql_c, auto rd_c, auto dbl_c) {
+        hipLaunchKernelGGL((emulate_small_kernel<decltype(w_c)::value, decltype(ql_c)::value, decltype(rd_c)::value, decltype(dbl_c)::value>),
+                           dim3((uint32_t)blocks), dim3(256), 0, s, sm, a, b, c, d, m, n, k, nitems);
+    };
+    auto by_mode = [&](auto w_c, auto ql_c) {
+        if (rd) { if (dbl) go(w_c, ql_c, std::true_type{}, std::true_type{}); else go(w_c, ql_c, std::true_type{}, std::false_type{}); }
+        else { if (dbl) go(w_c, ql_c, std::false_type{}, std::true_type{}); else go(w_c, ql_c, std::false_type{}, std::false_type{}); }
+    };
+    auto by_len = [&](auto w_c) {
+        if (p.L == 4) by_mode(w_c, std::integral_constant<int, 1>{});
+        else if (p.L == 8) by_mode(w_c, std::integral_constant<int, 2>{});
+        else by_mode(w_c, std::integral_constant<int, 4>{});
+    };
+    if (wide) by_len(std::integral_constant<int, 4>{});
+    else by_len(std::integral_constant<int, 1>{});
+    MMAEMU_HIP(hipGetLastError());
+    set_last_kernel("small tiles, %d output%s per thread, L=%u%s%s", wide ? 4 : 1, wide ? "s" : "", p.L, rd ? " rd" : "", dbl ? " binary64" : "");
+    return MMAEMU_OK;
+}
+
+} // namespace mmaemu
