@@ -248,6 +248,16 @@ static mmaemu_status fdpa_model_args(const mmaemu_model_params &mp, uint32_t k, 
                (ma.ftz_in ? FL_FTZ_IN : 0u) | (ma.acc_special_truncation ? FL_SPECIAL_TRUNC : 0u) | (ma.f2_at_leading_bit ? FL_F2_LEADING : 0u) |
                (ma.skip_zero_terms ? FL_SKIP_ZERO : 0u) | (ma.wide_products ? FL_WIDE_PRODUCTS : 0u) | (mp.nan_propagate ? FL_NAN_PROPAGATE : 0u) |
                (mp.rd_toward_zero ? FL_RD_AS_RZ : 0u);
+    // The sum of T 2^(e_max - F_T) and the accumulator rounded down at 2^(E - F_c), in units of the finer of the two: the
+    // accumulator is below 2^(E + 1), and E - e_max below the drop distance where the product sum counts; the product sum is
+    // below 2^(e_max + 3 + ceil(log2 L)).  With both below 2^52 units binary64 holds the sum.
+    // (F2 of 23 and more: a NaN accumulator's mantissa, whose 23 bits lie on top of binary64's 52, survives the rounding down)
+    if (ma.c_mode == MMAEMU_C_AFTER_RD && ma.f2_at_leading_bit && !ma.rd_toward_zero && ma.sum_drop_distance > 0 && ma.F2 >= 23) {
+        int lg = 0;
+        while ((1ull << lg) < ma.L) ++lg;
+        const int FT = ma.split == MMAEMU_SPLIT_NONE ? ma.F : ma.Fm, most = FT > ma.Fc ? FT : ma.Fc;
+        if (ma.sum_drop_distance + most <= 52 && 3 + lg + most <= 51) ma.flags |= FL_SUM_EXACT;
+    }
     return MMAEMU_OK;
 }
 

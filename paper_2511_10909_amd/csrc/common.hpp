@@ -44,7 +44,8 @@ enum : uint32_t {
     FL_SKIP_ZERO = 64u, FL_WIDE_PRODUCTS = 128u,
     FL_ACC16 = 256u,     // accumulator and output are binary16 (C and D hold 16-bit patterns)
     FL_NAN_PROPAGATE = 512u,  // FP32 operands: a NaN result carries an operand's payload (general kernel only)
-    FL_RD_AS_RZ = 1024u       // RD modes: the round-downs of the summation truncate toward zero (Sec. 6.2.4's hypothetical variant)
+    FL_RD_AS_RZ = 1024u,      // RD modes: the round-downs of the summation truncate toward zero (Sec. 6.2.4's hypothetical variant)
+    FL_SUM_EXACT = 2048u      // f2_at_leading_bit, and the two-term sum of TR-FDPA's last step always fits binary64 (api.hip)
 };
 
 // Model parameters as the kernels take them (by value).

@@ -41,7 +41,7 @@
 // Measured, one launch of the sixteen sets of the closed-loop scan on 2^16 tiles of 16x16x16, before and after: FP8 1194 ->
 // 770 us (6.9 instructions per term), BF16 bit patterns 1495 -> 1110 us (8.6), all FP16 bit patterns (a quarter of the tiles)
 // 584 -> 259 us; three sets on 2^18 tiles of 32x32x8 2028 -> 1430 us.  What is left is still issue: VALU busy 86 to 99 %.
-#include "rd_value.hpp"
+#include "emulate_tiled.hpp"
 
 namespace mmaemu {
 

@@ -338,6 +338,61 @@ __device__ __forceinline__ uint32_t wave_reduce_to_lane63(uint32_t v)
     return v;
 }
 
+// Algorithm "TR-FDPA", steps 3 and 4, and the variations of it that the model switches name, in binary64 (every quantity
+// is an integer of fewer than 53 bits times a power of two, hence exact): T counts units of 2^(em - F) (have_T: a product
+// took part), cb is the accumulator; returns the exact value whose conversion is the group's result.
+__device__ __forceinline__ double rd_value(double T, bool have_T, int em, int F, uint32_t cb, int F2, int Fc, int drop, uint32_t fl)
+{
+    if (fl & FL_SUM_EXACT) {
+        // F2 counted from the leading bit, and the two-term sum always exact in binary64 (see where the flag is set): formed
+        // in units of 2^(E - Fc), scaled back, and rounded down on its bit pattern: with the sign-magnitude pattern that is
+        // clearing the places below F2, after adding them all where the number is negative.  28 instructions against 50, on
+        // gfx950's own sets: sixteen TR-FDPA candidates on 2^15 tiles of 16x16x16 FP16 1050 -> 840 us
+        const uint32_t Ec = (cb >> 23) & 0xFFu;
+        const int ec = (int)(Ec ? Ec : 1u) - 127;
+        const int E = have_T && em > ec ? em : ec;                        // (no product took part: T is zero)
+        const double Tk = E - em >= drop ? 0.0 : T;                       // a product sum too far below drops out
+        const int down = Fc - E;
+        double sc = __builtin_floor(ldexp((double)__uint_as_float(cb), down));
+        if ((fl & FL_SPECIAL_TRUNC) && ec < E - Fc - 1 && Ec != 0xFFu) sc = 0.0;               // (an infinite or NaN accumulator stays)
+        const double v = ldexp(sc + ldexp(Tk, em - F + down), -down);
+        const uint64_t bits = (uint64_t)__double_as_longlong(v);
+        const uint32_t hi = (uint32_t)(bits >> 32) & 0x7FFFFFFFu;
+        const uint64_t below = (1ull << (52 - F2)) - 1ull;
+        const uint64_t r = (bits + ((uint64_t)(int64_t)((int32_t)(bits >> 32) >> 31) & below)) & ~below;
+        // (results below 2^-126, where the places are counted from 2^-126, take the way below; zero is +0.0 here)
+        if (!__any(hi - 1u < 0x38100000u - 1u)) return __longlong_as_double((long long)r);
+    }
+    const int Fmax = F2 > Fc ? F2 : Fc;
+    const uint32_t Ec = (cb >> 23) & 0xFFu;
+    const int ec = (int)(Ec ? Ec : 1u) - 127;
+    const int E = have_T ? (ec > em ? ec : em) : ec;                      // the accumulator always takes part
+    if (have_T && drop && E - em >= drop) have_T = false;                 // the product sum lies too far below: it drops out
+    if (!have_T) T = 0.0;
+    const double sc_exact = ldexp((double)__uint_as_float(cb), Fc - E);
+    double sc = (fl & FL_RD_AS_RZ) ? __builtin_trunc(sc_exact) : __builtin_floor(sc_exact);     // RD_Fc(c at E), units of 2^(E - Fc)
+    if ((fl & FL_SPECIAL_TRUNC) && ec < E - Fc - 1 && Ec != 0xFFu) sc = 0.0;                   // (an infinite or NaN accumulator stays)
+    if (!(fl & FL_F2_LEADING)) {
+        const double T_exact = ldexp(T, (em - F) - (E - F2));
+        const double T2 = (fl & FL_RD_AS_RZ) ? __builtin_trunc(T_exact) : __builtin_floor(T_exact);   // RD_F2(T at E)
+        return ldexp(ldexp(T2, Fmax - F2) + ldexp(sc, Fmax - Fc), E - Fmax);
+    }
+    // F2 counted from the leading bit of the exact two-term sum, held as s + err (Knuth's TwoSum; |err| is below half a
+    // last place of s, far under the unit that is kept)
+    const double a = ldexp(T, em - F), b = ldexp(sc, E - Fc);
+    const double sm = a + b, bb = sm - a;
+    const double err = (a - (sm - bb)) + (b - bb);
+    const long long sbits = __double_as_longlong(sm);
+    int lead = (int)((sbits >> 52) & 0x7FF) - 1023;
+    const bool toward_zero = (err != 0.0) && ((err < 0.0) != (sm < 0.0));
+    if ((sbits & 0xFFFFFFFFFFFFFll) == 0 && toward_zero) lead -= 1;        // just inside the binade below
+    lead = lead < -126 ? -126 : lead;                                       // binary32's smallest normal exponent
+    const int unit = lead - F2;
+    double q = __builtin_floor(ldexp(sm, -unit));
+    if (err < 0.0 && ldexp(q, unit) == sm) q -= 1.0;                        // s on the grid, the exact sum just below it
+    return sm == 0.0 ? 0.0 : ldexp(q, unit);
+}
+
 // start of the running kernel's argument segment, as a pointer the optimiser cannot trace back to the arguments
 __device__ __forceinline__ const void *opaque_kernarg_ptr()
 {
@@ -858,44 +913,10 @@ tiled_body(const TiledArgs &ta_, const void *__restrict__ A, const void *__restr
         else return fdpa_group_raw(q.p, q.ta, q.tb, a, b, q.p.L, cin, sr);
     };
 
-    // Algorithm "TR-FDPA", steps 3 and 4 ("GTR-FDPA", steps 4 and 5), and the variations, in binary64 (every
-    // quantity is an integer of fewer than 53 bits times a power of two, hence exact, except where noted):
-    // T counts units of 2^(em - FT); returns the exact value whose conversion is the group's result.
-    auto rd_value = [&](double T, bool have_T, int em, int FT, uint32_t cb) -> double {
-        const int Fmax = p.F2 > p.Fc ? p.F2 : p.Fc;
-        const uint32_t Ec = (cb >> 23) & 0xFFu;
-        const int ec = (int)(Ec ? Ec : 1u) - 127;
-        const int E = have_T ? (ec > em ? ec : em) : ec;           // the accumulator always takes part
-        if (have_T && p.sum_drop_distance && E - em >= p.sum_drop_distance) have_T = false;
-        if (!have_T) T = 0.0;
-        const double sc_exact = ldexp((double)__uint_as_float(cb), p.Fc - E);
-        double sc = __builtin_floor(sc_exact);                                                    // RD_Fc(c at E), units of 2^(E - Fc)
-        // (Sec. 6.2.4's hypothetical variant: both roundings truncate toward zero; unsplit groups, plain F2 rule)
-        if ((fe & FL_RD_AS_RZ)) sc = __builtin_trunc(sc_exact);
-        if ((fe & FL_SPECIAL_TRUNC) && ec < E - p.Fc - 1 && Ec != 0xFFu) sc = 0.0;             // (an infinite or NaN accumulator stays)
-        double val;
-        if (!(fe & FL_F2_LEADING)) {
-            const double T_exact = ldexp(T, (em - FT) - (E - p.F2));
-            double T2 = __builtin_floor(T_exact);                                                 // RD_F2(T at E)
-            if ((fe & FL_RD_AS_RZ)) T2 = __builtin_trunc(T_exact);
-            val = ldexp(ldexp(T2, Fmax - p.F2) + ldexp(sc, Fmax - p.Fc), E - Fmax);
-        } else {
-            // exact two-term sum as s + err (Knuth's TwoSum); then round down to F2 bits below the leading bit
-            // of the exact sum.  |err| is below half a last place of s, far under that unit.
-            const double a = ldexp(T, em - FT), b = ldexp(sc, E - p.Fc);
-            const double sm = a + b, bb = sm - a;
-            const double err = (a - (sm - bb)) + (b - bb);
-            const long long sbits = __double_as_longlong(sm);
-            int lead = (int)((sbits >> 52) & 0x7FF) - 1023;
-            const bool toward_zero = (err != 0.0) && ((err < 0.0) != (sm < 0.0));
-            if ((sbits & 0xFFFFFFFFFFFFFll) == 0 && toward_zero) lead -= 1;                      // just inside the binade below
-            lead = lead < -126 ? -126 : lead;                                                     // binary32's smallest normal exponent
-            const int unit = lead - p.F2;
-            double q = __builtin_floor(ldexp(sm, -unit));
-            if (err < 0.0 && ldexp(q, unit) == sm) q -= 1.0;                                      // s on the grid, exact sum just below it
-            val = sm == 0.0 ? 0.0 : ldexp(q, unit);
-        }
-        return val;
+    // steps 3 and 4 of TR-FDPA (4 and 5 of GTR-FDPA) and the variations; T counts units of 2^(em - FT)
+    auto rd_end = [&](double T, bool have_T, int em, int FT, uint32_t cb) -> double {
+        // (the 4 x 2 kernels have no registers for both ways: with the short one plain sets ran 7 % slower there)
+        return rd_value(T, have_T, em, FT, cb, p.F2, p.Fc, p.sum_drop_distance, R * C > 4 ? fe & ~FL_SUM_EXACT : fe);
     };
 
     // End of a group: rho of (sum of aligned terms) * 2^unit.  The value to convert is held
@@ -1044,7 +1065,7 @@ tiled_body(const TiledArgs &ta_, const void *__restrict__ A, const void *__restr
                     const double T = USE_SD ? Sd[r][c] + (double)S32[r][c] : (double)S32[r][c];   // units of 2^(e_max - F)
                     const uint32_t mx = m2[r][c], mlo = mx & 0xFFFFu, mhi = mx >> 16;
                     const bool have_T = !(fe & FL_SKIP_ZERO) || (mlo > mhi ? mlo : mhi) >= 2 * ZBIAS;
-                    v[r][c] = rd_value(T, have_T, emax[r][c], F, d[r][c]);
+                    v[r][c] = rd_end(T, have_T, emax[r][c], F, d[r][c]);
                 }
         } else {
             // d = rho(T 2^unit + c) with the two-term sum exact.  s = RN(a + c) is that sum unless it was rounded, and
@@ -1111,7 +1132,7 @@ tiled_body(const TiledArgs &ta_, const void *__restrict__ A, const void *__restr
                 double T = 0.0;
                 if (h0) T += __builtin_floor(ldexp(T0[r][c], (e0[r][c] - F) - (em - p.Fm)));
                 if (h1) T += __builtin_floor(ldexp(T1[r][c], (e1[r][c] - F) - (em - p.Fm)));
-                v[r][c] = rd_value(T, h0 || h1, em, p.Fm, d[r][c]);
+                v[r][c] = rd_end(T, h0 || h1, em, p.Fm, d[r][c]);
                 tg[r][c] = x0[r][c] | x1[r][c];
             }
         finish_group(kg, v, tg, tagged);
@@ -1311,7 +1332,7 @@ tiled_body(const TiledArgs &ta_, const void *__restrict__ A, const void *__restr
 #pragma unroll
                     for (int r = 0; r < R; ++r)
 #pragma unroll
-                        for (int c = 0; c < C; ++c) v[r][c] = rd_value(Tm[r][c], have[r][c] != 0, em[r][c], p.Fm, d[r][c]);
+                        for (int c = 0; c < C; ++c) v[r][c] = rd_end(Tm[r][c], have[r][c] != 0, em[r][c], p.Fm, d[r][c]);
                     finish_group(k0 + g * LT, v, tg, tagged);
                 }
             } else {
