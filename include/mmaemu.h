@@ -536,7 +536,7 @@ mmaemu_status mmaemu_issue_probe(uint32_t op, uint32_t iterations, uint32_t work
 const char *mmaemu_status_string(mmaemu_status s);
 const char *mmaemu_last_error(void); /* thread-local, never NULL */
 /* Name of the kernel family the calling thread's last successful mmaemu_emulate_mma
- * enqueued ("general", or "tiled TMxTN kc=.. L=.. c_mode=.."); for tests and reports. */
+ * enqueued ("general", "small tiles, ..", or "tiled TMxTN kc=.. L=.. c_mode=.."); for tests and reports. */
 const char *mmaemu_last_kernel(void);
 /* Library version as major*10000 + minor*100 + patch. */
 uint32_t mmaemu_version(void);
