@@ -38,9 +38,10 @@
 //     ran at half the speed of ordinary data through the routes of the general loop);
 //   * the reference's ordered keys are formed once per pass, a histogram entry is counted by leading zeros, and the two
 //     reductions over the wavefront run only where they can change something.
-// Measured, one launch of the sixteen sets of the closed-loop scan on 2^16 tiles of 16x16x16, before and after: FP8 1194 ->
-// 770 us (6.9 instructions per term), BF16 bit patterns 1495 -> 1110 us (8.6), all FP16 bit patterns (a quarter of the tiles)
-// 584 -> 259 us; three sets on 2^18 tiles of 32x32x8 2028 -> 1430 us.  What is left is still issue: VALU busy 86 to 99 %.
+// Measured, one launch of the sixteen sets of the closed-loop scan on 2^16 tiles of 16x16x16, before and after: FP8 1108 ->
+// 688 us (6.06 instructions per term), BF16 bit patterns 1433 -> 1149 us (8.66), all FP16 bit patterns (a quarter of the
+// tiles) 584 -> 259 us; three sets on 2^18 tiles of 32x32x8 1953 -> 1431 us (7.38).  What is left is still issue: 0.82 to
+// 0.96 of the nominal rate.
 #include "emulate_tiled.hpp"
 
 namespace mmaemu {
