@@ -72,7 +72,6 @@ struct WgStats {
     uint32_t hist[34 * 32];
     uint32_t mism, nan_equiv;
     unsigned long long first, maxd;
-    uint32_t tot[34];
 };
 
 __device__ __forceinline__ void wg_init(WgStats &ws)
@@ -85,49 +84,55 @@ __device__ __forceinline__ void wg_init(WgStats &ws)
 // lanes -> wavefront -> workgroup -> the caller's struct
 __device__ __forceinline__ void wg_flush(WgStats &ws, Local lc, uint64_t count, mmaemu_stats *st)
 {
-    // one set of LDS atomics per wavefront, not per lane: 64 lanes on one address take 64 turns
+    unsigned long long *g = reinterpret_cast<unsigned long long *>(st);
+    // one set of LDS atomics per wavefront, not per lane: 64 lanes on one address take 64 turns.  Every counter and every
+    // bucket but bucket 0 needs a differing pair, so a wavefront without one has nothing to reduce
+    if (__ballot(lc.mism != 0u)) {
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        lc.mism += __shfl_xor(lc.mism, o);
-        lc.nan_equiv += __shfl_xor(lc.nan_equiv, o);
-        const unsigned long long f = __shfl_xor((unsigned long long)lc.first, o), d = __shfl_xor((unsigned long long)lc.maxd, o);
-        lc.first = f < lc.first ? f : lc.first;
-        lc.maxd = d > lc.maxd ? d : lc.maxd;
-    }
-    if ((threadIdx.x & 63u) == 0) {
-        if (lc.mism) {
+        for (int o = 32; o > 0; o >>= 1) {
+            lc.mism += __shfl_xor(lc.mism, o);
+            lc.nan_equiv += __shfl_xor(lc.nan_equiv, o);
+            const unsigned long long f = __shfl_xor((unsigned long long)lc.first, o), d = __shfl_xor((unsigned long long)lc.maxd, o);
+            lc.first = f < lc.first ? f : lc.first;
+            lc.maxd = d > lc.maxd ? d : lc.maxd;
+        }
+        if ((threadIdx.x & 63u) == 0) {
             atomicAdd(&ws.mism, lc.mism);
             atomicMin(&ws.first, (unsigned long long)lc.first);
+            if (lc.nan_equiv) atomicAdd(&ws.nan_equiv, lc.nan_equiv);
+            if (lc.maxd) atomicMax(&ws.maxd, (unsigned long long)lc.maxd);
         }
-        if (lc.nan_equiv) atomicAdd(&ws.nan_equiv, lc.nan_equiv);
-        if (lc.maxd) atomicMax(&ws.maxd, (unsigned long long)lc.maxd);
     }
     __syncthreads();
+    if (threadIdx.x >= 64) return;
 
-    unsigned long long *g = reinterpret_cast<unsigned long long *>(st);
-    if (threadIdx.x < 34) {
-        uint32_t t = 0;
-        for (int cpy = 0; cpy < 32; ++cpy) t += ws.hist[threadIdx.x * 32 + cpy];
-        ws.tot[threadIdx.x] = t;
-        if (threadIdx.x >= 1 && t) atomicAdd(&g[5 + threadIdx.x], (unsigned long long)t);
+    // n_compared and bucket 0 are known up front: workgroup 0 adds the whole count once, every workgroup takes its
+    // non-zero buckets back out of bucket 0 (sums are modular, so the order does not matter); equal inputs then cost no
+    // further atomics at all
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        atomicAdd(&g[0], (unsigned long long)count);
+        atomicAdd(&g[5 + 0], (unsigned long long)count);
     }
-    __syncthreads();
+    if (!ws.mism) return;
+    // The first wavefront folds the histogram, lane = bucket.  The copies are read in rotated order: in plain order all
+    // lanes are on one bank in every step.
+    uint32_t t = 0;
+    if (threadIdx.x >= 1 && threadIdx.x < 34) {
+#pragma unroll
+        for (uint32_t cpy = 0; cpy < 32; ++cpy) t += ws.hist[threadIdx.x * 32u + ((cpy + threadIdx.x) & 31u)];
+    }
+    uint32_t nonzero = t;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) nonzero += __shfl_xor(nonzero, o);
+    // all additions in one instruction, a lane for each word of the struct (the workgroups' atomics meet on its lines)
+    unsigned long long add = t;
+    uint32_t word = 5u + threadIdx.x;
+    if (threadIdx.x == 0) add = 0ull - (unsigned long long)nonzero;
+    if (threadIdx.x == 34) { add = ws.mism; word = 1; }
+    if (threadIdx.x == 35) { add = ws.nan_equiv; word = 2; }
+    if (add) atomicAdd(&g[word], add);
     if (threadIdx.x == 0) {
-        uint32_t nonzero = 0;
-        for (int b = 1; b < 34; ++b) nonzero += ws.tot[b];
-        // n_compared and bucket 0 are known up front: workgroup 0 adds the whole count once,
-        // every workgroup takes its non-zero buckets back out of bucket 0 (sums are modular,
-        // so the order does not matter); equal inputs then cost no further atomics at all
-        if (blockIdx.x == 0) {
-            atomicAdd(&g[0], (unsigned long long)count);
-            atomicAdd(&g[5 + 0], (unsigned long long)count);
-        }
-        if (nonzero) atomicAdd(&g[5 + 0], 0ull - (unsigned long long)nonzero);
-        if (ws.mism) {
-            atomicAdd(&g[1], (unsigned long long)ws.mism);
-            atomicMin(&g[3], ws.first);
-        }
-        if (ws.nan_equiv) atomicAdd(&g[2], (unsigned long long)ws.nan_equiv);
+        atomicMin(&g[3], ws.first);
         if (ws.maxd) atomicMax(&g[4], ws.maxd);
     }
 }

@@ -1,0 +1,35 @@
+"""The comparison where few pairs differ or none: workgroups with nothing to fold beside one with a single pair."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+from oracle import formats as fm, stats as ostats
+from test_gpu_parity import dev_empty, mm, to_dev  # noqa: F401
+
+# width: type, word, quiet NaN, another NaN, -0
+WIDTHS = {16: (fm.FP16, np.uint16, 0x7E00, 0xFE01, 0x8000), 32: (fm.FP32, np.uint32, 0x7FC00000, 0xFFC00001, 0x80000000),
+          64: (fm.FP64, np.uint64, 0x7FF8000000000000, 0xFFF8000000000001, 1 << 63)}
+
+
+@pytest.mark.parametrize("width", sorted(WIDTHS))
+@pytest.mark.parametrize("count,misalign", [(5, 0), (16384 * 3 + 7, 0), (16384 * 2 + 3, 1)])
+def test_single_differing_pairs(mm, width, count, misalign):
+    dtype, word, nan, nan2, minus_zero = WIDTHS[width]
+    rng = np.random.default_rng(width + count)
+    x = rng.integers(0, 1 << width, size=count + misalign, dtype=word)
+    x[::97] = nan                                                    # equal NaNs: bucket 0, no mismatch
+    st = dev_empty(mm.STATS_BYTES)
+    mm.stats_reset(st)
+    want = ostats.empty_stats()
+    places = {0, 3, count // 2, count - 4, count - 1} | ({16383, 16384} if count > 16384 else set())
+    base = 0
+    for at in [None] + sorted(places):
+        for a, b in ((1, 2), (0, minus_zero), (nan, nan2), (nan, 1)) if at is not None else ((0, 0),):
+            x1, y1 = x.copy(), x.copy()
+            if at is not None:
+                x1[misalign + at], y1[misalign + at] = a, b
+            mm.compare(to_dev(x1)[misalign:], to_dev(y1)[misalign:], count, st, index_base=base, d=dtype)
+            want = ostats.compare(x1[misalign:], y1[misalign:], stats=want, index_base=base, width=width)
+            assert mm.read_stats(st) == want, (at, hex(int(a)), hex(int(b)))
+            base += count
