@@ -741,13 +741,20 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
                                     }
                                 if constexpr (TWIN && GL == KC) {
                                     if (twin) {
+                                        // (the binary64 -> binary32 conversion follows the binary32 rounding mode too)
                                         const ScanArgs::Hot h2 = scan_hot(mi + 1);
+                                        set_f32_round_toward_zero((h2.flags & FL_RZ) != 0);
 #pragma unroll
                                         for (int r = 0; r < R; ++r)
 #pragma unroll
                                             for (int c = 0; c < C; ++c) {
-                                                d2[r][c] = rho64(v[r][c], h2.flags, h2.out_mask);
+                                                double v2 = v[r][c];
+#if defined(__HIP_DEVICE_COMPILE__)
+                                                asm volatile("" : "+v"(v2));                   // (as for S2 above)
+#endif
+                                                d2[r][c] = rho64(v2, h2.flags, h2.out_mask);
                                             }
+                                        set_f32_round_toward_zero((fl & FL_RZ) != 0);
                                     }
                                 }
 #pragma unroll

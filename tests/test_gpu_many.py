@@ -229,6 +229,26 @@ def test_many_passes_per_workgroup_with_special_and_tiny_tiles(mm, ta, tb, m, k,
     assert sum(s["n_mismatch_bits"] > 0 for s in got[:16]) >= 12 and any(s["n_mismatch_nan_equiv"] for s in got[:16])
 
 
+@pytest.mark.parametrize("m,k", [(16, 16), (32, 8), (32, 16), (16, 32)])
+@pytest.mark.parametrize("ta,tb", [(fm.FP16, fm.FP16), (fm.BF16, fm.BF16), (fm.E4M3, fm.E5M2)])
+@pytest.mark.parametrize("first", [RNE, RZ])
+def test_twins_of_either_order_of_rounding(mm, ta, tb, m, k, first):
+    """Two sets on whole tiles that differ in the output conversion alone and share their sums, at widths of every kind of
+    sum (32 bits, pairs, binary64): each keeps its own rounding, whichever comes first."""
+    rng = np.random.default_rng(900 + 10 * ta + m + k)
+    nb = 9
+    A, B, C = make_case(rng, ta, tb, nb, m, m, k, c_exp=(110, 140), special_frac=0.001)
+    A[:6] = synth.narrow_exponent_bits(rng, (6, m, k), ta, *((10, 20) if ta == fm.FP16 else (5, 9) if ta == fm.E4M3 else (120, 134)))
+    for F in (16, 24, 26, 27, 28, 30, 32, 40):
+        plist = [ModelParams(group_len=k, frac_bits=F, out_round=rho, ftz_out=rho == RZ, nan_bits=0x7FC00001 + rho) for rho in (first, RNE + RZ - first)]
+        want = oracle_outputs(plist, A, B, C, ta, tb)
+        st, D, kern, _ = run_many(mm, plist, A, B, C, ta, tb, ref=want[0])
+        assert kern.startswith("multi x2 tiled"), kern
+        for i in range(2):
+            assert_same(D[i], want[i], str(plist[i]))
+            assert st[i] == ostats.compare(want[i], want[0]), plist[i]
+
+
 def rd_sets(rng, k, count):
     """TR-FDPA sets (unsplit groups) with the variation switches drawn at random, group lengths the fused kernel takes."""
     from test_gpu_tiled_rd import random_rd_params
