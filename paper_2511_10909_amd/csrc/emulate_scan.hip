@@ -725,7 +725,7 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
                                                 const int se = (F + 127) + (int)kept(g * (GL / 4) + q, r, c) - (int)emb[r][c];
                                                 scale = __uint_as_float((uint32_t)(se < 1 ? 1 : se) << 23);
                                             }
-                                            // aligned and truncated in binary32, exactly; F of 28 and 29: two terms fit 32 bits
+                                            // aligned and truncated in binary32, exactly; PAIRS: two terms to a 32-bit sum
 #pragma unroll
                                             for (int w = 0; w < 4; w += 2) {
                                                 const float t0 = p[r][c][g * GL + 4 * q + w] * scale, t1 = p[r][c][g * GL + 4 * q + w + 1] * scale;
@@ -791,7 +791,9 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
 #pragma unroll
                                 for (int c = 0; c < C; ++c) d[r][c] = c0_kept[tid][r * C + c];      // a group whose result may be subnormal: the chain again, in binary64
                         }
-                        if (F <= 29) run_fast(gl_c, std::integral_constant<int, 1>{}); else run_fast(gl_c, std::integral_constant<int, 2>{});
+                        // (an aligned term is below 2^(F+2): two of them stay inside 32 bits up to F = 28)
+                        const bool pairs = (2ull << (F + 2)) <= (1ull << 31);
+                        if (pairs) run_fast(gl_c, std::integral_constant<int, 1>{}); else run_fast(gl_c, std::integral_constant<int, 2>{});
                     };
                     if (hot.L == 4) by_width(std::integral_constant<int, 4>{});
                     else if (hot.L == 8) by_width(std::integral_constant<int, 8>{});

@@ -239,7 +239,7 @@ def test_twins_of_either_order_of_rounding(mm, ta, tb, m, k, first):
     nb = 9
     A, B, C = make_case(rng, ta, tb, nb, m, m, k, c_exp=(110, 140), special_frac=0.001)
     A[:6] = synth.narrow_exponent_bits(rng, (6, m, k), ta, *((10, 20) if ta == fm.FP16 else (5, 9) if ta == fm.E4M3 else (120, 134)))
-    for F in (16, 24, 26, 27, 28, 30, 32, 40):
+    for F in (16, 24, 26, 27, 28, 29, 30, 32, 40):
         plist = [ModelParams(group_len=k, frac_bits=F, out_round=rho, ftz_out=rho == RZ, nan_bits=0x7FC00001 + rho) for rho in (first, RNE + RZ - first)]
         want = oracle_outputs(plist, A, B, C, ta, tb)
         st, D, kern, _ = run_many(mm, plist, A, B, C, ta, tb, ref=want[0])
@@ -247,6 +247,51 @@ def test_twins_of_either_order_of_rounding(mm, ta, tb, m, k, first):
         for i in range(2):
             assert_same(D[i], want[i], str(plist[i]))
             assert st[i] == ostats.compare(want[i], want[0]), plist[i]
+
+
+def top_of_binade(rng, shape, dtype):
+    """Elements with all or nearly all mantissa bits set, one exponent per row, mostly of one sign: products just below
+    four times the power of two of their exponent, so that aligned terms and their partial sums reach their bounds."""
+    f = fm.FORMATS[dtype]
+    e = rng.integers(max(1, f.bias - 6), f.bias + 7, size=shape[:-1] + (1,))
+    mant = (1 << f.mbits) - 1 - (rng.random(shape) < 0.1)
+    sign = rng.random(shape) < rng.choice([0.0, 0.0, 0.1, 1.0], size=shape[:-1] + (1,))
+    return (sign.astype(np.uint32) << (f.ebits + f.mbits)) | (e.astype(np.uint32) << f.mbits) | mant.astype(np.uint32)
+
+
+def width_sets(rng, k):
+    """T-FDPA sets of every width 0 .. 40 and group length, the switches at random (25 .. 31, where the arithmetic changes
+    with the width, under both roundings)."""
+    sets = []
+    for F in range(41):
+        for L in (4, 8, 16, 32):
+            if L <= k:
+                for rho in ((RNE, RZ) if 25 <= F <= 31 else (RZ if rng.random() < 0.5 else RNE,)):
+                    zi, zo, cut = rng.random(3) < 0.3
+                    sets.append(ModelParams(group_len=L, frac_bits=F, out_round=rho, ftz_in=bool(zi), ftz_out=bool(zo),
+                                            out_mant_bits=13 if rho == RZ and cut else 23, nan_bits=0x7FC00000 + len(sets)))
+    return sets
+
+
+@pytest.mark.parametrize("m,k", [(16, 16), (32, 8), (32, 16), (16, 32)])
+@pytest.mark.parametrize("ta,tb", [(fm.FP16, fm.FP16), (fm.BF16, fm.BF16), (fm.E4M3, fm.E5M2), (fm.BF16, fm.FP16)])
+def test_every_width_and_group_length(mm, ta, tb, m, k):
+    rng = np.random.default_rng(4000 + 100 * ta + 10 * tb + m + k)
+    nb = 13 if m == 16 else 5
+    A, B, C = make_case(rng, ta, tb, nb, m, m, k, c_exp=(100, 150), special_frac=0.001)
+    top = 3 * nb // 5
+    A[:top], B[:top] = top_of_binade(rng, (top, m, k), ta), top_of_binade(rng, (top, m, k), tb)
+    C[:top] = synth.narrow_exponent_bits(rng, (top, m, m), fm.FP32, 120, 136)
+    C[:, 0] = 0
+    sets = width_sets(rng, k)
+    rng.shuffle(sets)
+    for plist in (sets[i:i + 16] for i in range(0, len(sets), 16)):
+        want = oracle_outputs(plist, A, B, C, ta, tb)
+        st, D, kern, _ = run_many(mm, plist, A, B, C, ta, tb, ref=want[0])
+        assert kern.startswith("multi x%d tiled" % len(plist)), kern
+        for p, d, w, s in zip(plist, D, want, st):
+            assert_same(d, w, str(p))
+            assert s == ostats.compare(w, want[0]), p
 
 
 def rd_sets(rng, k, count):
