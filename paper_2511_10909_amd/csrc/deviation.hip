@@ -229,9 +229,12 @@ deviation_kernel(const void *__restrict__ A, const void *__restrict__ B, const u
 #pragma unroll
             for (int w = 0; w < W; ++w) {
                 bad[w] |= !(__builtin_fabs(sp[w].lower) <= finite_max);
-                // (hi + lo = D - upper exactly; the lower sum joins lo, and what lo cannot hold shows in `lost`)
+                // (hi + lo = D - upper exactly; the lower sum joins lo, and what lo cannot hold shows in `lost`, a sum of
+                // magnitudes: the accumulator below cannot cancel it)
+                double residue;
                 two_sum(pr[w].hi, -sp[w].upper, pr[w].hi, pr[w].lo);
-                two_sum(pr[w].lo, -sp[w].lower, pr[w].lo, pr[w].lost);
+                two_sum(pr[w].lo, -sp[w].lower, pr[w].lo, residue);
+                pr[w].lost = __builtin_fabs(residue);
             }
         } else {
             uint32_t kk = 0;

@@ -158,6 +158,22 @@ def test_deviation_sample_split_sum(mm, ta, tb, shape, stride, c_offset):
     same_hist(mm.read_deviation_hist(h), deviation_hist(A, B, C, D, ta, tb, stride, -3), shape)
 
 
+@pytest.mark.parametrize("sign", [1, -1])
+def test_deviation_sample_residue_of_the_lower_sum(mm, sign):
+    """D so large that the low half of the pair cannot hold both sums, and an accumulator of the size of what is left over, of
+    either sign: products 2^39 in all and one of 2^-40, c = +-2^-40, D from 2^44 to +-2^98."""
+    k = 1032
+    A, B = np.zeros((1, 4, k), dtype=np.uint16), np.zeros((1, 4, k), dtype=np.uint16)
+    A[..., :1024], B[..., :1024] = 29 << 10, 30 << 10                   # 2^14 times 2^15
+    A[..., 1024], B[..., 1024] = 0x0010, 0x0010                         # 2^-20 each
+    C = np.full((1, 4, 4), (87 << 23) | (0x80000000 if sign < 0 else 0), dtype=np.uint32)         # +-2^-40
+    D = np.full((1, 4, 4), (127 + 98) << 23, dtype=np.uint32)
+    D[0, 1], D[0, 2], D[0, 3] = (127 + 93) << 23, ((127 + 98) << 23) | 0x80000000, (127 + 44) << 23
+    for bin_exp in (98, 60, 44, -40):
+        h = dev_hist(mm, A, B, C, D, fm.FP16, fm.FP16, 1, bin_exp)
+        same_hist(h, deviation_hist(A, B, C, D, fm.FP16, fm.FP16, 1, bin_exp), (sign, bin_exp))
+
+
 def test_deviation_sample_extremes_and_errors(mm):
     import torch
     # the widest reach of the exact sum: BF16 products at both ends of the range next to binary32's smallest subnormal
