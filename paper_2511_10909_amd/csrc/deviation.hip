@@ -170,7 +170,7 @@ deviation_kernel(const void *__restrict__ A, const void *__restrict__ B, const u
     const double finite_max = 0x1.fffffffffffffp+1023;
     double sum = 0.0, sum_abs = 0.0, sum_sq = 0.0;
     uint32_t n_seen = 0, n_bad = 0, n_neg = 0, n_zero = 0;
-    // (a workgroup handles at most 2^32 / 256 samples: the 32-bit counters cannot overflow, see the launch)
+    // (a workgroup handles at most 2^31 samples: the 32-bit counters cannot overflow, see the launch)
     for (uint64_t item = (uint64_t)blockIdx.x * 256u + threadIdx.x; item < nitems; item += (uint64_t)gridDim.x * 256u) {
         const uint64_t o = W == 1 ? item * stride : item * (uint64_t)W;
         uint64_t tile;
@@ -355,8 +355,12 @@ mmaemu_status launch_deviation_sample(const void *A, const void *B, const uint32
     const bool wide = split && stride == 1 && n % 4 == 0 && ((reinterpret_cast<uintptr_t>(C) | reinterpret_cast<uintptr_t>(D)) & 15u) == 0;
     const uint64_t nitems = wide ? nsamples / 4 : nsamples;
     uint64_t blocks = (nitems + 255) / 256;
-    if (blocks > 2048) blocks = 2048;                                // grid-stride beyond that: two rounds of what the chip holds
-    if ((nsamples + blocks - 1) / blocks > 0xFFFFFFFFull) { set_error("deviation_sample: more than 2^43 samples in one call"); return MMAEMU_ERR_SHAPE; }
+    // Grid-stride beyond 2048 workgroups (two rounds of what the chip holds); beyond 2^42 samples 4096, so that no workgroup
+    // counts more than 2^31: its rounds of 256 items come to nitems / 2^19 (2^20) rounded up, at most 2^23 rounds of 256 samples
+    // or 2^21 of 1024.
+    const uint64_t most = nsamples > (1ull << 42) ? 4096 : 2048;
+    if (blocks > most) blocks = most;
+    if (nsamples > (1ull << 43)) { set_error("deviation_sample: more than 2^43 samples in one call"); return MMAEMU_ERR_SHAPE; }
 #define DEVIATION_LAUNCH(W_, S_)                                                                                              \
     hipLaunchKernelGGL((deviation_kernel<W_, S_>), dim3((uint32_t)blocks), dim3(256), 0, s, A, B, C, D, m, n, k, ta, tb, stride, nitems, bin_exp, h)
     if (wide) DEVIATION_LAUNCH(4, true);

@@ -148,3 +148,17 @@ def test_compare_many_classes_is_a_host_side_query():
         mm.model_destroy(h)
     for h in hs + [wide]:
         mm.model_destroy(h)
+
+
+def test_deviation_sample_takes_up_to_2_43_samples():
+    """The limit of the 32-bit counters of a workgroup, decided before anything is launched; without a GPU the largest
+    accepted call ends in a HIP error, not in a refusal of its shape."""
+    import torch
+    from paper_2511_10909_amd import binding as mm
+    if torch.cuda.is_available():
+        pytest.skip("the accepted call must not reach a device")
+    call = lambda batch: mm.deviation_sample(4096, 4096, 4096, 4096, 1, 1, 8, batch, (mm.FP16, mm.FP16, mm.FP32, mm.FP32), 1, 0, 4096, stream=0)
+    for batch, status in (((1 << 43) + 1, 3), (1 << 43, 4), (1 << 42, 4)):
+        with pytest.raises(mm.MmaemuError) as ei:
+            call(batch)
+        assert ei.value.status == status, (batch, str(ei.value))
