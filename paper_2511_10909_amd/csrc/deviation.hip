@@ -146,7 +146,7 @@ __host__ __device__ constexpr bool splits(uint32_t t)
     return t == MMAEMU_FP16 || t == MMAEMU_FP8_E4M3 || t == MMAEMU_FP8_E5M2 || t == MMAEMU_FP6_E2M3 || t == MMAEMU_FP6_E3M2 || t == MMAEMU_FP4_E2M1;
 }
 
-// One thread per W consecutive outputs of a row (W = 4: every output sampled, n a multiple of 4; else one sample each).
+// One thread per W consecutive outputs of a row (W = 4: every output sampled, n a multiple of 4, many outputs; else one sample each).
 // SPLIT: products summed as SplitSum does (7 vector instructions per term), only D, the accumulator and the two sums go
 // through the pair of binary64 numbers; else (BF16: hundreds of binary places, or k beyond SPLIT_MAX_K) every product does
 // (15 per term).  With one output per thread, all through the pair, checks per element, 64-bit divisions per sample and three
@@ -237,21 +237,30 @@ deviation_kernel(const void *__restrict__ A, const void *__restrict__ B, const u
                 pr[w].lost = __builtin_fabs(residue);
             }
         } else {
+            // (T: the type of both operands where it is known when the loop is compiled, else -1.  With the branches on the type
+            // inside the loop few wavefronts wait for them: 64x64x4096 in BF16 476 us with, 306 us without)
             uint32_t kk = 0;
-            for (; kk + 8 <= k; kk += 8) {
-                // (eight elements of each row fetched before the first is used: one wait per eight terms)
-                uint32_t ra[8], rb[8];
-                load8(ta, esa, a, kk, vec_a, ra);
-                load8(tb, esb, b, kk, vec_b, rb);
-                double xa[8], xb[8];
-                elem_values(ta, ra, 0u, xa);                             // (one branch on the type per eight elements)
-                elem_values(tb, rb, 0u, xb);
+            auto eights = [&](auto type_c) {
+                constexpr int T = decltype(type_c)::value;
+                const uint32_t t_a = T < 0 ? ta : (uint32_t)T, t_b = T < 0 ? tb : (uint32_t)T, es_a = T < 0 ? esa : 2u, es_b = T < 0 ? esb : 2u;
+                for (; kk + 8 <= k; kk += 8) {
+                    // (eight elements of each row fetched before the first is used: one wait per eight terms)
+                    uint32_t ra[8], rb[8];
+                    load8(t_a, es_a, a, kk, vec_a, ra);
+                    load8(t_b, es_b, b, kk, vec_b, rb);
+                    double xa[8], xb[8];
+                    elem_values(t_a, ra, 0u, xa);                        // (one branch on the type per eight elements)
+                    elem_values(t_b, rb, 0u, xb);
 #pragma unroll
-                for (int q = 0; q < 8; ++q) {
-                    bad[0] |= !(__builtin_fabs(xa[q]) <= finite_max) || !(__builtin_fabs(xb[q]) <= finite_max);
-                    pr[0].add(-xa[q], xb[q]);
+                    for (int q = 0; q < 8; ++q) {
+                        bad[0] |= !(__builtin_fabs(xa[q]) <= finite_max) || !(__builtin_fabs(xb[q]) <= finite_max);
+                        pr[0].add(-xa[q], xb[q]);
+                    }
                 }
-            }
+            };
+            if (ta == MMAEMU_BF16 && tb == MMAEMU_BF16) eights(std::integral_constant<int, MMAEMU_BF16>{});
+            else if (ta == MMAEMU_FP16 && tb == MMAEMU_FP16) eights(std::integral_constant<int, MMAEMU_FP16>{});
+            else eights(std::integral_constant<int, -1>{});
             for (; kk < k; ++kk) {
                 const double x = elem_value(ta, elem_bits(ta, esa, a, kk), 0u), y = elem_value(tb, elem_bits(tb, esb, b, kk), 0u);
                 bad[0] |= !(__builtin_fabs(x) <= finite_max) || !(__builtin_fabs(y) <= finite_max);
@@ -349,10 +358,15 @@ mmaemu_status launch_deviation_sample(const void *A, const void *B, const uint32
     const uint64_t total = batch * m * n;
     const uint64_t nsamples = (total + stride - 1) / stride;
     if (nsamples == 0) return MMAEMU_OK;
-    // Four outputs of a row per thread where every output is sampled and rows hold whole fours at 16-byte steps; the split sum
-    // for every type but BF16 (whose products span more than the split holds) up to the k for which it is exact.
+    // The split sum for every type but BF16 (whose products span more than the split holds) up to the k for which it is exact.
+    // Four outputs of a row per thread where every output is sampled, rows hold whole fours at 16-byte steps, and there are
+    // enough of them: a thread then runs four chains, so with few outputs the chip idles behind them, while with many the row of
+    // A is decoded once and a quarter of the workgroups end in atomics.  FP16, one / four per thread: 2^12 outputs, k = 1024
+    // 91 / 238 us; 2^18, k = 512 81 / 139; 2^19, k = 512 162 / 164; 2^20, k = 512 304 / 264; 2^17, k = 32 14.3 / 14.7;
+    // 2^18, k = 32 19.4 / 16.3; 2^19, k = 8 30 / 13.
     const bool split = splits(ta) && splits(tb) && k <= SPLIT_MAX_K;
-    const bool wide = split && stride == 1 && n % 4 == 0 && ((reinterpret_cast<uintptr_t>(C) | reinterpret_cast<uintptr_t>(D)) & 15u) == 0;
+    const bool fours = split && stride == 1 && n % 4 == 0 && ((reinterpret_cast<uintptr_t>(C) | reinterpret_cast<uintptr_t>(D)) & 15u) == 0;
+    const bool wide = fours && (nsamples >= (1ull << 19) || (k <= 32 && nsamples >= (1ull << 18)));
     const uint64_t nitems = wide ? nsamples / 4 : nsamples;
     uint64_t blocks = (nitems + 255) / 256;
     // Grid-stride beyond 2048 workgroups (two rounds of what the chip holds); beyond 2^42 samples 4096, so that no workgroup

@@ -139,8 +139,8 @@ def test_deviation_sample_matches_oracle(mm):
     (fm.E5M2, fm.E5M2, (2, 3, 8, 17), 1, 0), (fm.FP16, fm.FP16, (4, 7, 6, 8), 1, 0), (fm.FP16, fm.FP16, (3, 5, 8, 12), 1, 1),
     (fm.E4M3, fm.E4M3, (3, 4, 8, 16), 3, 0)])
 def test_deviation_sample_split_sum(mm, ta, tb, shape, stride, c_offset):
-    """Products at both ends of the narrow types' ranges (the split sum's two halves full), the k at which the split ends, rows
-    of four outputs per thread and rows that are not, an accumulator that is not 16-byte aligned."""
+    """Products at both ends of the narrow types' ranges (the split sum's two halves full), the k at which the split ends,
+    rows of whole fours and rows that are not, an accumulator that is not 16-byte aligned (one output per thread: few outputs)."""
     import torch
     rng = np.random.default_rng(5 + shape[3])
     nb, m, n, k = shape
@@ -156,6 +156,55 @@ def test_deviation_sample_split_sum(mm, ta, tb, shape, stride, c_offset):
     dC = to_dev(np.concatenate([np.zeros(c_offset, np.uint32), C.ravel()]))[c_offset:]
     mm.deviation_sample(to_dev(A), to_dev(B), dC, to_dev(D), m, n, k, nb, (ta, tb, fm.FP32, fm.FP32), stride, -3, h)
     same_hist(mm.read_deviation_hist(h), deviation_hist(A, B, C, D, ta, tb, stride, -3), shape)
+
+
+@pytest.mark.parametrize("ta,tb,n,k", [(fm.FP16, fm.FP16, 8, 8), (fm.E4M3, fm.E5M2, 4, 40), (fm.E5M2, fm.FP16, 12, 17), (fm.FP16, fm.FP16, 4, 8192)])
+def test_deviation_sample_four_outputs_per_thread(mm, ta, tb, n, k):
+    """Enough outputs for four per thread: the oracle's histogram of one problem, many times over; one output per thread (an
+    accumulator that is not 16-byte aligned) counts the same."""
+    import torch
+    rng = np.random.default_rng(60 + k)
+    nb, m = 3, 5
+    A, B = synth.random_bits(rng, (nb, m, k), ta), synth.random_bits(rng, (nb, n, k), tb)
+    A[0, 0, 1] = synth.SPECIAL_CODES[ta][0]
+    C = synth.narrow_exponent_bits(rng, (nb, m, n), fm.FP32, 100, 140)
+    D = o2lib.emulate_mma(ModelParams(group_len=k, frac_bits=14), A, B, C, ta, tb)[0]
+    # many problems; of long rows, one many times as high and wide
+    reps = (1, 120, 240) if k == 8192 else ((1 << 19) // (nb * m * n) + 1, 1, 1)
+    copies = reps[0] * reps[1] * reps[2]
+    want = deviation_hist(A, B, C, D, ta, tb, 1, -6)
+    want = {key: [v * copies for v in x] if key == "bins" else x * copies for key, x in want.items()}
+    A, B, C, D = np.tile(A, (reps[0], reps[1], 1)), np.tile(B, (reps[0], reps[2], 1)), np.tile(C, reps), np.tile(D, reps)
+    nb, m, n = D.shape
+    for offset in (0, 1):
+        dC = to_dev(np.concatenate([np.zeros(offset, np.uint32), C.ravel()]))[offset:]
+        h = torch.empty(mm.DEVIATION_HIST_BYTES, dtype=torch.uint8, device="cuda")
+        mm.deviation_hist_reset(h)
+        mm.deviation_sample(to_dev(A), to_dev(B), dC, to_dev(D), m, n, k, nb, (ta, tb, fm.FP32, fm.FP32), 1, -6, h)
+        same_hist(mm.read_deviation_hist(h), want, (offset, k))
+
+
+def test_few_outputs_with_long_rows_keep_one_per_thread(mm):
+    """4096 outputs of 4096 terms: as fast as the call whose accumulator is not 16-byte aligned, which always runs one output
+    per thread (four per thread took 2.6 times as long)."""
+    import torch
+    m, k = 64, 4096
+    z = torch.zeros(m * k, dtype=torch.int16, device="cuda")
+    C = torch.zeros(m * m + 4, dtype=torch.int32, device="cuda")
+    h = torch.empty(mm.DEVIATION_HIST_BYTES, dtype=torch.uint8, device="cuda")
+    mm.deviation_hist_reset(h)
+    best = []
+    for offset in (1, 0):
+        times = []
+        for _ in range(8):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            mm.deviation_sample(z, z, C[offset:], C, m, m, k, 1, (fm.FP16, fm.FP16, fm.FP32, fm.FP32), 1, 0, h)
+            end.record()
+            torch.cuda.synchronize()
+            times.append(start.elapsed_time(end))
+        best.append(min(times))
+    assert best[1] < 1.6 * best[0], best
 
 
 @pytest.mark.parametrize("sign", [1, -1])
