@@ -617,6 +617,11 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
                         if (ADAPT && (fe & FL_FTZ_OUT) && (o & 0x7F800000u) == 0) o &= 0x80000000u;
                         return o;
                     };
+                    // rho of a 32-bit sum whose result may be subnormal
+                    auto rho_low = [&](int32_t S, uint32_t emb, uint32_t dp, uint32_t fe, uint32_t om) -> uint32_t {
+                        const uint32_t o = rho64(ldexp((double)S, (int)emb - (F + 127)), fe, om);
+                        return (dp & 0x7F800000u) == 0x7F800000u ? dp : o;                     // (as in rho32)
+                    };
                     // Sec. 4.2 for group g of GL products: their IEEE sum with the accumulator is a NaN or an infinity exactly where
                     // the group's result is (finite products are far too small to make one), and is then that result; the
                     // infinities that BF16 chains reach by overflow stay through it too.
@@ -627,7 +632,7 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
                         for (int w = 1; w < GL; ++w) t += p[r][c][g * GL + w];
                         return __float_as_uint(t + __uint_as_float(dp));
                     };
-                    auto run_fast = [&](auto gl_c, auto wide_c) -> bool {
+                    auto run_fast = [&](auto gl_c, auto wide_c) {
                         constexpr int GL = decltype(gl_c)::value;
                         constexpr bool WIDE = decltype(wide_c)::value != 0, PAIRS = decltype(wide_c)::value == 1;
                         if constexpr (GL <= KC) {
@@ -652,8 +657,15 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
                                     emb[r][c] = e > Ec ? e : Ec;
                                     if constexpr (ADAPT && !WIDE) low |= emb[r][c] < (uint32_t)(F + 1);
                                 }
-                            if constexpr (ADAPT && !WIDE) { if (__any(low)) return false; }
+                            // (a group of the wavefront's whose result may be subnormal: its 32-bit sums are converted from binary64)
+                            const bool some_low = ADAPT && !WIDE && __any(low);
                             if constexpr (!WIDE) {
+                                if (ADAPT && some_low && (fl & FL_FTZ_IN)) {
+#pragma unroll
+                                    for (int r = 0; r < R; ++r)
+#pragma unroll
+                                        for (int c = 0; c < C; ++c) if ((d[r][c] & 0x7F800000u) == 0) d[r][c] = 0;      // FlushSubnormal on the accumulator
+                                }
                                 int32_t S[R][C];
                                 float back[R][C];
 #pragma unroll
@@ -695,7 +707,7 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
 #if defined(__HIP_DEVICE_COMPILE__)
                                                 asm volatile("" : "+v"(S2));
 #endif
-                                                d2[r][c] = rho32(S2, back[r][c], emb[r][c], d[r][c], h2.flags, h2.out_mask);
+                                                d2[r][c] = some_low ? rho_low(S2, emb[r][c], d[r][c], h2.flags, h2.out_mask) : rho32(S2, back[r][c], emb[r][c], d[r][c], h2.flags, h2.out_mask);
                                             }
                                         set_f32_round_toward_zero((fl & FL_RZ) != 0);
                                     }
@@ -705,7 +717,7 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
 #pragma unroll
                                     for (int c = 0; c < C; ++c) {
                                         before[r][c] = d[r][c];
-                                        d[r][c] = rho32(S[r][c], back[r][c], emb[r][c], d[r][c], fl, hot.out_mask);
+                                        d[r][c] = some_low ? rho_low(S[r][c], emb[r][c], d[r][c], fl, hot.out_mask) : rho32(S[r][c], back[r][c], emb[r][c], d[r][c], fl, hot.out_mask);
                                     }
                             } else {
                                 double v[R][C];
@@ -779,18 +791,11 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
                             }
                         }
                         }
-                        return true;
                     };
                     auto by_width = [&](auto gl_c) {
                         constexpr int GL = decltype(gl_c)::value;
                         const bool fits = F >= 1 && F <= 28 && ((uint64_t)(GL + 1) << (F + 2)) <= (1ull << 31);
-                        if (fits) {
-                            if (run_fast(gl_c, std::integral_constant<int, 0>{})) return;
-#pragma unroll
-                            for (int r = 0; r < R; ++r)
-#pragma unroll
-                                for (int c = 0; c < C; ++c) d[r][c] = c0_kept[tid][r * C + c];      // a group whose result may be subnormal: the chain again, in binary64
-                        }
+                        if (fits) { run_fast(gl_c, std::integral_constant<int, 0>{}); return; }
                         // (an aligned term is below 2^(F+2): two of them stay inside 32 bits up to F = 28)
                         const bool pairs = (2ull << (F + 2)) <= (1ull << 31);
                         if (pairs) run_fast(gl_c, std::integral_constant<int, 1>{}); else run_fast(gl_c, std::integral_constant<int, 2>{});

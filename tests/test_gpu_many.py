@@ -294,6 +294,40 @@ def test_every_width_and_group_length(mm, ta, tb, m, k):
             assert s == ostats.compare(w, want[0]), p
 
 
+@pytest.mark.parametrize("ta,tb", [(fm.BF16, fm.BF16), (fm.BF16, fm.E5M2)])
+@pytest.mark.parametrize("m,k", [(16, 16), (32, 8), (32, 16)])
+def test_results_below_the_normal_range_from_32_bit_sums(mm, ta, tb, m, k):
+    """Chains whose results are subnormal, or become so and leave that range again, among ordinary ones, infinities and overflow
+    in the same wavefront; accumulators flushed or not, every rounding, and twins."""
+    rng = np.random.default_rng(52 + m + k + tb)
+    nb = 24
+    A, B, C = make_case(rng, ta, tb, nb, m, m, k, special_frac=0.0)
+    for t in range(18):                                          # products around 2^-125 .. 2^-145
+        mid_a, mid_b = (52, 66) if tb == fm.BF16 else (5, 4)
+        A[t] = synth.narrow_exponent_bits(rng, (m, k), ta, mid_a - 4, mid_a + 2 * (t % 3))
+        B[t] = synth.narrow_exponent_bits(rng, (m, k), tb, mid_b - 3, mid_b + 2)
+        C[t] = synth.narrow_exponent_bits(rng, (m, m), fm.FP32, 0, 3 + t)
+        if t % 4 == 0:
+            C[t] &= 0x807FFFFF
+        if t % 6 == 1:                                           # one ordinary row and column, one accumulator in nine next to infinity
+            A[t, 0] = synth.narrow_exponent_bits(rng, (k,), ta, 120, 134)
+            C[t, 1, ::3] = 0x7F7FFFFF
+            C[t, 2, ::3] = 0xFF800000
+    sets = [ModelParams(group_len=L, frac_bits=F, out_round=rho, out_mant_bits=cut, ftz_in=zi, ftz_out=zo, nan_bits=0x7FC00000 + F)
+            for L in (4, 8, 16) if L <= k for F, rho, cut in ((0, RNE, 23), (7, RZ, 23), (16, RNE, 23), (16, RZ, 13), (23, RZ, 23), (24, RNE, 23))
+            for zi, zo in ((False, False), (True, False), (False, True), (True, True))]
+    rng.shuffle(sets)
+    for plist in (sets[i:i + 16] for i in range(0, len(sets), 16)):
+        want = oracle_outputs(plist, A, B, C, ta, tb)
+        st, D, kern, _ = run_many(mm, plist, A, B, C, ta, tb, ref=want[0])
+        assert kern.startswith("multi x%d tiled" % len(plist)), kern
+        for p, d, w, s in zip(plist, D, want, st):
+            assert_same(d, w, str(p))
+            assert s == ostats.compare(w, want[0]), p
+        low = [((w & 0x7F800000) == 0) & ((w & 0x7FFFFF) != 0) for w in want]
+        assert max(x.sum() for x in low) > 1000
+
+
 def rd_sets(rng, k, count):
     """TR-FDPA sets (unsplit groups) with the variation switches drawn at random, group lengths the fused kernel takes."""
     from test_gpu_tiled_rd import random_rd_params
