@@ -359,9 +359,14 @@ __device__ __forceinline__ double rd_value(double T, bool have_T, int em, int F,
         const uint64_t bits = (uint64_t)__double_as_longlong(v);
         const uint32_t hi = (uint32_t)(bits >> 32) & 0x7FFFFFFFu;
         const uint64_t below = (1ull << (52 - F2)) - 1ull;
-        const uint64_t r = (bits + ((uint64_t)(int64_t)((int32_t)(bits >> 32) >> 31) & below)) & ~below;
-        // (results below 2^-126, where the places are counted from 2^-126, take the way below; zero is +0.0 here)
-        if (!__any(hi - 1u < 0x38100000u - 1u)) return __longlong_as_double((long long)r);
+        double r = __longlong_as_double((long long)((bits + ((uint64_t)(int64_t)((int32_t)(bits >> 32) >> 31) & below)) & ~below));
+        // results below 2^-126, where the places are counted from 2^-126 (zero is +0.0 here)
+        const bool low = hi - 1u < 0x38100000u - 1u;
+        if (__any(low)) {
+            const double q = ldexp(__builtin_floor(ldexp(v, 126 + F2)), -(126 + F2));
+            r = low ? q : r;
+        }
+        return r;
     }
     const int Fmax = F2 > Fc ? F2 : Fc;
     const uint32_t Ec = (cb >> 23) & 0xFFu;

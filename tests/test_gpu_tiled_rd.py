@@ -247,3 +247,25 @@ def test_four_product_shapes(mm, ta, tb):
                     one = o1_emulate(p, A[t:t + 1, i:i + 1, :], B[t:t + 1, j:j + 1, :], C[t:t + 1, i:i + 1, j:j + 1], ta, tb)[0, 0, 0]
                     assert got[t, i, j] == one, "%s: output %s: got %08x, the rational form gives %08x" % (what, (t, i, j), got[t, i, j], one)
     assert tiled >= 0.7 * cases, (tiled, cases)          # (some of the random round-down variations run in the general kernel)
+
+
+@pytest.mark.parametrize("m,k,tb", [(16, 16, fm.BF16), (32, 8, fm.BF16), (4, 8, fm.BF16), (16, 16, fm.E5M2), (5, 24, fm.BF16)])
+def test_leading_bit_rule_at_the_bottom_of_the_normal_range(mm, m, k, tb):
+    """Results on both sides of 2^-126, where the places stop following the leading bit, of either sign, beside ordinary ones."""
+    rng = np.random.default_rng(126 + m + k + tb)
+    nb, ta = 20, fm.BF16
+    mid_a, mid_b = (52, 71) if tb == fm.BF16 else (5, 4)          # products around 2^-125 .. 2^-139
+    A = synth.narrow_exponent_bits(rng, (nb, m, k), ta, mid_a - 3, mid_a + 3)
+    B = synth.narrow_exponent_bits(rng, (nb, m, k), tb, mid_b - 3, mid_b + 3)
+    C = synth.narrow_exponent_bits(rng, (nb, m, m), fm.FP32, 0, 8)
+    C[::4] &= 0x807FFFFF
+    C[1, 0, 0], C[2, 0, 0], C[3, 0, 0] = 0x00800000, 0x80800000, 0x80000000
+    A[5, 0] = synth.narrow_exponent_bits(rng, (k,), ta, 120, 134)
+    base = ModelParams(group_len=8, frac_bits=24, frac_bits2=31, c_mode=C_AFTER_RD, f2_at_leading_bit=True, sum_drop_distance=28, nan_bits=0xFFC00000)
+    seen = 0
+    for p in (base, base.with_(skip_zero_terms=True, zero_result_positive=True), base.with_(frac_bits2=23, out_round=1), base.with_(frac_bits2=24, group_len=4),
+              base.with_(frac_bits2=25, frac_bits=20, ftz_out=True), base.with_(frac_bits2=36, ftz_in=True), base.with_(frac_bits2=27, acc_special_truncation=True, sum_drop_distance=20)):
+        want, _ = o2lib.emulate_mma(p, A, B, C, ta, tb)
+        assert_same(gpu_emulate(mm, p, A, B, C, ta, tb), want, "%s" % p)
+        seen = max(seen, int((((want & 0x7F800000) == 0) & ((want & 0x7FFFFF) != 0)).sum()))
+    assert seen > want.size // 10
