@@ -129,7 +129,7 @@ constexpr int scan_lds_bytes()
     constexpr int SLOTS = 256 / ((TM / 2) * (TM / 2));
     constexpr int VS = KC + 4, VSD = KC + 2, ES = KC / 2 + (KC == 8 ? 4 : 2);
     constexpr int KEPT = FAM == 3 ? KC / 4 : (KC / 4 + 1) / 2;            // dwords of kept maxima per output
-    return 2 * SLOTS * TM * (ADAPT ? VSD * 8 : VS * 4) + 2 * SLOTS * TM * ES * 4 + KEPT * 4 * 256 * 4 + (FAM == 0 && KC <= 16 ? 3 : 1) * 4 * 256 * 4 +
+    return 2 * SLOTS * TM * (ADAPT ? VSD * 8 : VS * 4) + 2 * SLOTS * TM * ES * 4 + KEPT * 4 * 256 * 4 + (FAM == 0 && KC <= 16 ? 3 : 0) * 4 * 256 * 4 +
            (int)sizeof(MultiLds) + 16;
 }
 // workgroups (of four waves, one per SIMD) that a CU's 160 KB of LDS hold, four at most: the waves per SIMD to compile for
@@ -164,9 +164,8 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
     __shared__ __attribute__((aligned(16))) unsigned char smem[2 * VBYTES + 2 * EBYTES];
     // (one 128-bit LDS word holds a kept dword of all four outputs of a thread; FAM 3: a quarter's even and odd maximum, one dword)
     __shared__ __attribute__((aligned(16))) uint32_t m2k[FAM == 3 ? NQ4 : NK2][256][R * C];
-    __shared__ __attribute__((aligned(16))) uint32_t ref_key[256][R * C];
-    // (FAST: the accumulators and reference outputs of a pass wait in LDS, not in registers that the products need)
-    __shared__ __attribute__((aligned(16))) uint32_t c0_kept[FAST ? 256 : 1][R * C], ref_kept[FAST ? 256 : 1][R * C];
+    // (FAST: the accumulators, the reference outputs and their keys wait in LDS, not in registers that the products need)
+    __shared__ __attribute__((aligned(16))) uint32_t c0_kept[FAST ? 256 : 1][R * C], ref_kept[FAST ? 256 : 1][R * C], ref_key[FAST ? 256 : 1][R * C];
     __shared__ MultiLds ml;
     constexpr int HC = HIST_COPIES;
     const uint32_t tid = threadIdx.x;
@@ -366,8 +365,9 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
         // histogram's sum.  The largest distance is reduced over the wavefront only where it passes the one in LDS, and
         // the first index once per wavefront and model: a workgroup's passes go through ascending tiles, so no later
         // pass can lower it.
-        // (An LDS histogram is kept by leading zeros of the distance: place 32 - bucket, and 33 for bucket 33.  The keys of the
-        // reference outputs sit in LDS, formed once per pass.)
+        // (An LDS histogram is kept by leading zeros of the distance: place 32 - bucket, and 33 for bucket 33.  FAST: the keys of
+        // the reference outputs sit in LDS, formed once per pass; the other families, with fewer models to share them, form a key
+        // where it is needed.)
         uint32_t ref_nan = 1u;                                    // some reference output of the wavefront may be a NaN
         auto take_reference = [&](const uint32_t (&ref)[R][C]) {
             bool any = false;
@@ -376,17 +376,26 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
 #pragma unroll
                 for (int c = 0; c < C; ++c) {
                     any |= (ref[r][c] & 0x7FFFFFFFu) > 0x7F800000u;
-                    ref_key[tid][r * C + c] = ordered_key(ref[r][c]);
-                    if (FAST) ref_kept[tid][r * C + c] = ref[r][c];
+                    if (FAST) {
+                        ref_key[tid][r * C + c] = ordered_key(ref[r][c]);
+                        ref_kept[tid][r * C + c] = ref[r][c];
+                    }
                 }
             ref_nan = scalar(__any(any) ? 1u : 0u);
         };
         if (!ref_first) take_reference(ref);
-        auto write_nan = [&](uint32_t (&x)[R][C], uint32_t nan_pattern) {
+        // every NaN becomes the model's pattern; returns whether the wavefront holds one
+        auto write_nan = [&](uint32_t (&x)[R][C], uint32_t nan_pattern) -> bool {
+            bool any = false;
 #pragma unroll
             for (int r = 0; r < R; ++r)
 #pragma unroll
-                for (int c = 0; c < C; ++c) if ((x[r][c] & 0x7FFFFFFFu) > 0x7F800000u) x[r][c] = nan_pattern;
+                for (int c = 0; c < C; ++c)
+                    if ((x[r][c] & 0x7FFFFFFFu) > 0x7F800000u) {
+                        x[r][c] = nan_pattern;
+                        any = true;
+                    }
+            return scalar(__any(any) ? 1u : 0u) != 0u;
         };
         // (x: the model's outputs, every NaN already the model's pattern; nan_seen: there may be one)
         auto account = [&](uint32_t mi, const uint32_t (&x)[R][C], bool nan_seen) {
@@ -422,7 +431,7 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
 #pragma unroll
                     for (int c = 0; c < C; ++c) {
                         if (x[r][c] != y[r][c]) {
-                            const uint32_t dist = key_distance(ordered_key(x[r][c]), ref_key[tid][r * C + c]);
+                            const uint32_t dist = key_distance(ordered_key(x[r][c]), FAST ? ref_key[tid][r * C + c] : ordered_key(y[r][c]));
                             const bool nx = (x[r][c] & 0x7FFFFFFFu) > 0x7F800000u, ny = (y[r][c] & 0x7FFFFFFFu) > 0x7F800000u;
                             uint32_t place = (uint32_t)__clz((int)dist);                                  // (__clz(0) = 32)
                             if (nx || ny) {
@@ -440,7 +449,7 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
 #pragma unroll
                     for (int c = 0; c < C; ++c)
                         if (x[r][c] != y[r][c]) {
-                            const uint32_t dist = key_distance(ordered_key(x[r][c]), ref_key[tid][r * C + c]);
+                            const uint32_t dist = key_distance(ordered_key(x[r][c]), FAST ? ref_key[tid][r * C + c] : ordered_key(y[r][c]));
                             maxd = dist > maxd ? dist : maxd;
                             atomicAdd(hist + (uint32_t)__clz((int)dist) * HC, 1u);
                         }
@@ -456,10 +465,11 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
 #pragma unroll
                     for (int c = C - 1; c >= 0; --c)
                         if (x[r][c] != y[r][c]) rel = d_off + (uint32_t)((TI * r) * TN + TJ * c);
-                const uint32_t wmin = wave_reduce_to_lane63<false>(rel);
-                if ((tid & 63u) == 63u && wmin != 0xFFFFFFFFu)
-                    atomicMin(&ml.first[mi], (unsigned long long)(sa->index_base + out0 + wmin));
-                if (scalar(__any(rel != 0xFFFFFFFFu) ? 1u : 0u)) found |= 1u << mi;
+                if (scalar(__any(rel != 0xFFFFFFFFu) ? 1u : 0u)) {
+                    const uint32_t wmin = wave_reduce_to_lane63<false>(rel);
+                    if ((tid & 63u) == 63u) atomicMin(&ml.first[mi], (unsigned long long)(sa->index_base + out0 + wmin));
+                    found |= 1u << mi;
+                }
                 found = scalar(found);
             }
         };
@@ -803,12 +813,10 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
                     if (hot.L == 4) by_width(std::integral_constant<int, 4>{});
                     else if (hot.L == 8) by_width(std::integral_constant<int, 8>{});
                     else by_width(std::integral_constant<int, 16>{});
-                    if (__builtin_expect(special, 0)) write_nan(d, hot.nan_bits);
-                    account(mi, d, special);
+                    account(mi, d, __builtin_expect(special, 0) && write_nan(d, hot.nan_bits));
                     if (twin) {
                         ++mi;
-                        if (__builtin_expect(special, 0)) write_nan(d2, scan_hot(mi).nan_bits);
-                        account(mi, d2, special);
+                        account(mi, d2, __builtin_expect(special, 0) && write_nan(d2, scan_hot(mi).nan_bits));
                     }
                 }
                 set_f32_round_toward_zero(false);
@@ -1059,6 +1067,21 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
                     if (!done) {
                         slow_seen = true;
                         uint32_t dn[R][C];
+                        double vrd[R][C];                         // (FAM 1) the value to convert; one branch on the way for all four outputs
+                        if constexpr (FAM == 1) {
+                            auto all = [&](auto exact_c) {
+#pragma unroll
+                                for (int r = 0; r < R; ++r)
+#pragma unroll
+                                    for (int c = 0; c < C; ++c) {
+                                        if ((fl & FL_FTZ_IN) && (d[r][c] & 0x7F800000u) == 0) d[r][c] = 0;         // FlushSubnormal on the accumulator
+                                        const double T = Sd[r][c] + (double)S32[r][c];
+                                        if constexpr (decltype(exact_c)::value) vrd[r][c] = rd_exact(T, have[r][c], emax[r][c], F, d[r][c], hot.F2, hot.Fc, hot.drop, fl);
+                                        else vrd[r][c] = rd_general(T, have[r][c], emax[r][c], F, d[r][c], hot.F2, hot.Fc, hot.drop, fl);
+                                    }
+                            };
+                            if (fl & FL_SUM_EXACT) all(std::true_type{}); else all(std::false_type{});
+                        }
 #pragma unroll
                         for (int r = 0; r < R; ++r)
 #pragma unroll
@@ -1071,8 +1094,7 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
                                     const double tc = __builtin_trunc(ldexp((double)__uint_as_float(d[r][c]), -unit));
                                     v = ldexp(T + tc, unit);                                   // exact: integers below 2^53
                                 } else {
-                                    if ((fl & FL_FTZ_IN) && (d[r][c] & 0x7F800000u) == 0) d[r][c] = 0;         // FlushSubnormal on the accumulator
-                                    v = rd_value(T, have[r][c], emax[r][c], F, d[r][c], hot.F2, hot.Fc, hot.drop, fl);
+                                    v = vrd[r][c];
                                 }
                                 uint32_t o = __float_as_uint((float)v);
                                 if ((fe & FL_RZ)) {
@@ -1370,13 +1392,11 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
             // (a pair of twins: the first model's outputs were set aside; then the twin's, in the next place of the arrays)
             if constexpr (TWIN) {
                 if (twin) {
-                    write_nan(dfirst, nan_first);
-                    account(mi, dfirst, true);
+                    account(mi, dfirst, write_nan(dfirst, nan_first));
                     ++mi;
                 }
             }
-            if (slow_seen) write_nan(d, nan_bits);                 // (the short route produces no NaN)
-            account(mi, d, slow_seen);
+            account(mi, d, slow_seen && write_nan(d, nan_bits));   // (the short route produces no NaN)
         }
         }
         set_f32_round_toward_zero(false);
