@@ -168,7 +168,7 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
     __shared__ __attribute__((aligned(16))) uint32_t c0_kept[FAST ? 256 : 1][R * C], ref_kept[FAST ? 256 : 1][R * C], ref_key[FAST ? 256 : 1][R * C];
     __shared__ MultiLds ml;
     constexpr int HC = HIST_COPIES;
-    const uint32_t tid = threadIdx.x;
+    uint32_t tid = threadIdx.x;
     for (uint32_t i = tid; i < MULTI_MAX * 34 * HC; i += 256) (&ml.hist[0][0][0])[i] = 0;
     if (tid < MULTI_MAX) { ml.naneq[tid] = 0; ml.maxd[tid] = 0; ml.first[tid] = ~0ull; }
     // (FAST, ADAPT) some element of the pass needs binary64 products: a flag by the pass's parity, set before a barrier, read
@@ -185,17 +185,35 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
     uint32_t *Ae = reinterpret_cast<uint32_t *>(smem + 2 * VBYTES);
     uint32_t *Be = reinterpret_cast<uint32_t *>(smem + 2 * VBYTES + EBYTES);
     const ScanArgs *sa = reinterpret_cast<const ScanArgs *>(opaque_kernarg_ptr());
-    const uint32_t slot = tid / TPS, ti = (tid % TPS) / TJ, tj = tid % TJ;
+    uint32_t slot = tid / TPS, ti = (tid % TPS) / TJ, tj = tid % TJ;
     const uint32_t ta = sa_.ta, tb = sa_.tb;
     const int ebase = sa_.ebase;
     const uint32_t esa = (ta <= MMAEMU_FP8_E5M2 || ta >= MMAEMU_FP6_E2M3) ? 1u : 2u;
     const uint32_t esb = (tb <= MMAEMU_FP8_E5M2 || tb >= MMAEMU_FP6_E2M3) ? 1u : 2u;
-    const float *av = reinterpret_cast<const float *>(Av_raw) + (slot * TM + ti) * VS;
-    const float *bv = reinterpret_cast<const float *>(Bv_raw) + (slot * TN + tj) * VS;
-    const double *avd = reinterpret_cast<const double *>(Av_raw) + (slot * TM + ti) * VSD;
-    const double *bvd = reinterpret_cast<const double *>(Bv_raw) + (slot * TN + tj) * VSD;
-    const uint32_t *ae = Ae + (slot * TM + ti) * ES;
-    const uint32_t *be = Be + (slot * TN + tj) * ES;
+    const float *av, *bv;
+    const double *avd, *bvd;
+    const uint32_t *ae, *be;
+    auto find_rows = [&] {
+        av = reinterpret_cast<const float *>(Av_raw) + (slot * TM + ti) * VS;
+        bv = reinterpret_cast<const float *>(Bv_raw) + (slot * TN + tj) * VS;
+        avd = reinterpret_cast<const double *>(Av_raw) + (slot * TM + ti) * VSD;
+        bvd = reinterpret_cast<const double *>(Bv_raw) + (slot * TN + tj) * VSD;
+        ae = Ae + (slot * TM + ti) * ES;
+        be = Be + (slot * TN + tj) * ES;
+    };
+    find_rows();
+    // AGAIN (64 products in four waves' registers): a thread's places are worked out again for every pass and every forming of the
+    // products; kept across the models they sent 8 to 12 registers to scratch memory, 2 to 4 % of a launch of one set
+    constexpr bool AGAIN = FAST && KC == 16 && !ADAPT;
+    auto places_again = [&] {
+        if constexpr (AGAIN) {
+            tid = opaque_thread_index();
+            slot = TPS == 256 ? 0u : tid / TPS;
+            ti = (tid % TPS) / TJ;
+            tj = tid % TJ;
+            find_rows();
+        }
+    };
     const uint32_t count = sa_.count, ref_first = sa_.ref_is_first;
     uint32_t found = 0;                        // models for which this wavefront has put a first differing index into LDS
     const bool dumping = sa_.dout != nullptr;
@@ -276,6 +294,7 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
     };
     if (AHEAD && blockIdx.x < nblocks) fetch_pass(blockIdx.x);
     for (uint32_t pass_wg = blockIdx.x; pass_wg < nblocks; pass_wg += gridDim.x) {
+        places_again();
         // ---- this pass's tiles: outputs, operands in flight ----
         const uint64_t item0 = (uint64_t)pass_wg * SLOTS;
         const uint64_t out0 = item0 * (uint64_t)(TM * TN);
@@ -501,6 +520,7 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
                 // (a product 2^-126 below its quarter's largest is cut to zero at any width).  In a quarter with a NaN or an
                 // infinity the finite products are scaled away.
                 auto form_products = [&](bool flush) {
+                    places_again();
                     const float min_a = flush ? min_normal_of(ta) : 0.0f, min_b = flush ? min_normal_of(tb) : 0.0f;
 #pragma unroll
                     for (int q = 0; q < NQ4; ++q) {
