@@ -147,7 +147,13 @@ mmaemu_status launch_emulate_small(const ModelArgs &p, const void *A, const void
     sm.esb = (uint32_t)fmt_info(tb).width / 8u;
     sm.zbias = (p.c_mode == MMAEMU_C_AFTER_RD && p.skip_zero_terms) ? ZBIAS : 0u;
     sm.ebase = 2 - fmt_info(ta).bias - fmt_info(tb).bias - 2 * (int)sm.zbias;
-    const bool wide = n % 4 == 0 && ((reinterpret_cast<uintptr_t>(Cm) | reinterpret_cast<uintptr_t>(D)) & 15u) == 0;
+    // Four outputs per thread: the row of A decoded once for them, C and D as 128-bit words; one where long rows meet few outputs
+    // (a thread is a serial chain of k terms per output, and the chip waits for it).  8x8 tiles of FP16, T-FDPA, one / four per
+    // thread: 2^12 outputs, k = 64 12.4 / 28.5 us; k = 1024 142 / 389; 2^18, k = 64 21.7 / 30.1; 2^20, k = 64 63 / 57, k = 8 14 / 11.
+    // Rows of up to 48 stay with four at any count, so that one rule serves the small calls: 2^12 outputs, k = 16 8.7 / 9.6 us, k = 48
+    // 10.1 / 21.4 (the general kernel 48).
+    const bool few = k > 48 && batch * m * n < (1ull << 19);
+    const bool wide = !few && n % 4 == 0 && ((reinterpret_cast<uintptr_t>(Cm) | reinterpret_cast<uintptr_t>(D)) & 15u) == 0;
     const bool dbl = ta == MMAEMU_BF16 || tb == MMAEMU_BF16 || p.F >= 30, rd = p.c_mode == MMAEMU_C_AFTER_RD;
     const uint64_t nitems = batch * m * (wide ? n / 4 : n);
     uint64_t blocks = (nitems + 255) / 256;

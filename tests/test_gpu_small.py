@@ -35,3 +35,46 @@ def test_small_tiles(mm, ta, tb, m, n, k):
         got = gpu_emulate(mm, p, A, B, C, ta, tb)
         assert gpu_emulate.last_kernel.startswith("small tiles, %d output" % (4 if n % 4 == 0 else 1)), gpu_emulate.last_kernel
         assert_same(got, want, "set %d, %s" % (i, (ta, tb, m, n, k)))
+
+
+@pytest.mark.parametrize("ta,tb", [(fm.FP16, fm.FP16), (fm.BF16, fm.BF16), (fm.E4M3, fm.E5M2)])
+@pytest.mark.parametrize("m,n,k,nb,outputs", [(8, 8, 64, 20, 1), (4, 4, 56, 3, 1), (8, 4, 64, (1 << 19) // 32, 4), (8, 4, 64, (1 << 19) // 32 - 1, 1), (4, 8, 48, 7, 4)])
+def test_outputs_per_thread(mm, ta, tb, m, n, k, nb, outputs):
+    """Both sides of the line between one and four outputs per thread (long rows: from 2^19 outputs); the larger batches hold one
+    small problem many times."""
+    rng = np.random.default_rng(nb + k + ta)
+    some = min(nb, 20)
+    A, B, C = make_case(rng, ta, tb, some, m, n, k, special_frac=0.001, c_exp=(100, 150))
+    pick = np.arange(nb) % some
+    for p in (ModelParams(group_len=8, frac_bits=24), FITTED):
+        want, _ = o2lib.emulate_mma(p, A, B, C, ta, tb)
+        got = gpu_emulate(mm, p, A[pick], B[pick], C[pick], ta, tb)
+        assert gpu_emulate.last_kernel.startswith("small tiles, %d output" % outputs), gpu_emulate.last_kernel
+        assert_same(got, want[pick], str(p))
+
+
+def test_few_outputs_with_long_rows_run_one_per_thread(mm):
+    """64 tiles of 8x8x4096, all bit patterns: as fast as the call whose arrays are not 16-byte aligned, which always runs one
+    output per thread (four per thread took 2.6 times as long, longer than the general kernel)."""
+    import torch
+    m, k, nb = 8, 4096, 64
+    A = torch.empty(nb * m * k, dtype=torch.int16, device="cuda")
+    B = torch.empty_like(A)
+    mm.generate(A, mm.FP16, m * k, 0, nb, mm.GEN_RANDOM_BITS, seed=1, operand=0)
+    mm.generate(B, mm.FP16, m * k, 0, nb, mm.GEN_RANDOM_BITS, seed=1, operand=1)
+    C = torch.zeros(nb * m * m + 4, dtype=torch.int32, device="cuda")
+    D = torch.empty_like(C)
+    h = mm.model_create(group_len=8, frac_bits=24)
+    best = []
+    for offset in (1, 0):
+        times = []
+        for _ in range(8):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            mm.emulate_mma(h, A, B, C[offset:], D[offset:], m, m, k, nb, (mm.FP16, mm.FP16, mm.FP32, mm.FP32))
+            end.record()
+            torch.cuda.synchronize()
+            times.append(start.elapsed_time(end))
+        best.append(min(times))
+    mm.model_destroy(h)
+    assert best[1] < 1.6 * best[0], best
