@@ -1100,7 +1100,7 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
                                         else vrd[r][c] = rd_general(T, have[r][c], emax[r][c], F, d[r][c], hot.F2, hot.Fc, hot.drop, fl);
                                     }
                             };
-                            if (fl & FL_SUM_EXACT) all(std::true_type{}); else all(std::false_type{});
+                            if (__builtin_expect((fl & FL_SUM_EXACT) != 0u, 0)) all(std::true_type{}); else all(std::false_type{});
                         }
 #pragma unroll
                         for (int r = 0; r < R; ++r)
@@ -1170,12 +1170,23 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
                 constexpr int GLT = decltype(glt_c)::value;
                 slow_seen = true;
                 uint32_t dn[R][C];
+                double vrd[R][C];
+                auto all = [&](auto exact_c) {
+#pragma unroll
+                    for (int r = 0; r < R; ++r)
+#pragma unroll
+                        for (int c = 0; c < C; ++c) {
+                            if ((fl & FL_FTZ_IN) && (d[r][c] & 0x7F800000u) == 0) d[r][c] = 0;             // FlushSubnormal on the accumulator
+                            if constexpr (decltype(exact_c)::value) vrd[r][c] = rd_exact(T[r][c], hv[r][c], em[r][c], hot.Fm, d[r][c], hot.F2, hot.Fc, hot.drop, fl);
+                            else vrd[r][c] = rd_general(T[r][c], hv[r][c], em[r][c], hot.Fm, d[r][c], hot.F2, hot.Fc, hot.drop, fl);
+                        }
+                };
+                if (__builtin_expect((fl & FL_SUM_EXACT) != 0u, 0)) all(std::true_type{}); else all(std::false_type{});
 #pragma unroll
                 for (int r = 0; r < R; ++r)
 #pragma unroll
                     for (int c = 0; c < C; ++c) {
-                        if ((fl & FL_FTZ_IN) && (d[r][c] & 0x7F800000u) == 0) d[r][c] = 0;                 // FlushSubnormal on the accumulator
-                        const double v = rd_value(T[r][c], hv[r][c], em[r][c], hot.Fm, d[r][c], hot.F2, hot.Fc, hot.drop, fl);
+                        const double v = vrd[r][c];
                         uint32_t o = __float_as_uint((float)v);
                         if ((fl & FL_RZ)) {
                             const double back = (double)__uint_as_float(o);

@@ -924,10 +924,25 @@ tiled_body(const TiledArgs &ta_, const void *__restrict__ A, const void *__restr
         else return fdpa_group_raw(q.p, q.ta, q.tb, a, b, q.p.L, cin, sr);
     };
 
-    // steps 3 and 4 of TR-FDPA (4 and 5 of GTR-FDPA) and the variations; T counts units of 2^(em - FT)
-    auto rd_end = [&](double T, bool have_T, int em, int FT, uint32_t cb) -> double {
-        // (the 4 x 2 kernels have no registers for both ways: with the short one plain sets ran 7 % slower there)
-        return rd_value(T, have_T, em, FT, cb, p.F2, p.Fc, p.sum_drop_distance, R * C > 4 ? fe & ~FL_SUM_EXACT : fe);
+    // Steps 3 and 4 of TR-FDPA (4 and 5 of GTR-FDPA) and the variations, for every output of the thread: one(r, c, end) finishes
+    // one of them through end(T, have_T, em, FT, cb), T counting units of 2^(em - FT).  One branch on the way for all of them,
+    // the short way out of line: a branch per output made sets without it 3 to 15 % slower (the CDNA3 set on 512^3 FP16 86 us
+    // before there were two ways, 98 with that, 88 now; 16x16x16 tiles 16.7, 17.4, 16.4).  The 4 x 2 kernels have no registers for both.
+    auto rd_each = [&](auto one) {
+        auto through = [&](auto exact_c) {
+            auto end = [&](double T, bool have_T, int em, int FT, uint32_t cb) -> double {
+                if constexpr (decltype(exact_c)::value) return rd_exact(T, have_T, em, FT, cb, p.F2, p.Fc, p.sum_drop_distance, fe);
+                else return rd_general(T, have_T, em, FT, cb, p.F2, p.Fc, p.sum_drop_distance, fe);
+            };
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+#pragma unroll
+                for (int c = 0; c < C; ++c) one(r, c, end);
+        };
+        if constexpr (R * C <= 4) {
+            if (__builtin_expect((fe & FL_SUM_EXACT) != 0u, 0)) { through(std::true_type{}); return; }
+        }
+        through(std::false_type{});
     };
 
     // End of a group: rho of (sum of aligned terms) * 2^unit.  The value to convert is held
@@ -1069,15 +1084,12 @@ tiled_body(const TiledArgs &ta_, const void *__restrict__ A, const void *__restr
                     v[r][c] = ldexp(T + tc, unit);                      // exact: integers below 2^53
                 }
         } else if (CMODE == MMAEMU_C_AFTER_RD) {
-#pragma unroll
-            for (int r = 0; r < R; ++r)
-#pragma unroll
-                for (int c = 0; c < C; ++c) {
-                    const double T = USE_SD ? Sd[r][c] + (double)S32[r][c] : (double)S32[r][c];   // units of 2^(e_max - F)
-                    const uint32_t mx = m2[r][c], mlo = mx & 0xFFFFu, mhi = mx >> 16;
-                    const bool have_T = !(fe & FL_SKIP_ZERO) || (mlo > mhi ? mlo : mhi) >= 2 * ZBIAS;
-                    v[r][c] = rd_end(T, have_T, emax[r][c], F, d[r][c]);
-                }
+            rd_each([&](int r, int c, auto end) {
+                const double T = USE_SD ? Sd[r][c] + (double)S32[r][c] : (double)S32[r][c];   // units of 2^(e_max - F)
+                const uint32_t mx = m2[r][c], mlo = mx & 0xFFFFu, mhi = mx >> 16;
+                const bool have_T = !(fe & FL_SKIP_ZERO) || (mlo > mhi ? mlo : mhi) >= 2 * ZBIAS;
+                v[r][c] = end(T, have_T, emax[r][c], F, d[r][c]);
+            });
         } else {
             // d = rho(T 2^unit + c) with the two-term sum exact.  s = RN(a + c) is that sum unless it was rounded, and
             // it was not exactly when bb = RN(s - a) equals c and RN(s - bb) equals a: the difference of s and the
@@ -1130,22 +1142,19 @@ tiled_body(const TiledArgs &ta_, const void *__restrict__ A, const void *__restr
         flush_accumulators();
         double v[R][C];
         uint32_t tg[R][C];
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-#pragma unroll
-            for (int c = 0; c < C; ++c) {
-                // x0 / x1: the packed exponent maxima the sub-sums came from (both halves of the word for a half
-                // group, the low / high half for the even / odd split)
-                const uint32_t m0 = halves ? ((x0[r][c] & 0xFFFFu) > (x0[r][c] >> 16) ? (x0[r][c] & 0xFFFFu) : (x0[r][c] >> 16)) : (x0[r][c] & 0xFFFFu);
-                const uint32_t m1 = halves ? ((x1[r][c] & 0xFFFFu) > (x1[r][c] >> 16) ? (x1[r][c] & 0xFFFFu) : (x1[r][c] >> 16)) : (x1[r][c] >> 16);
-                const bool h0 = !(fe & FL_SKIP_ZERO) || m0 >= 2 * ZBIAS, h1 = !(fe & FL_SKIP_ZERO) || m1 >= 2 * ZBIAS;
-                const int em = (h0 && h1) ? (e0[r][c] > e1[r][c] ? e0[r][c] : e1[r][c]) : (h0 ? e0[r][c] : e1[r][c]);
-                double T = 0.0;
-                if (h0) T += __builtin_floor(ldexp(T0[r][c], (e0[r][c] - F) - (em - p.Fm)));
-                if (h1) T += __builtin_floor(ldexp(T1[r][c], (e1[r][c] - F) - (em - p.Fm)));
-                v[r][c] = rd_end(T, h0 || h1, em, p.Fm, d[r][c]);
-                tg[r][c] = x0[r][c] | x1[r][c];
-            }
+        rd_each([&](int r, int c, auto end) {
+            // x0 / x1: the packed exponent maxima the sub-sums came from (both halves of the word for a half
+            // group, the low / high half for the even / odd split)
+            const uint32_t m0 = halves ? ((x0[r][c] & 0xFFFFu) > (x0[r][c] >> 16) ? (x0[r][c] & 0xFFFFu) : (x0[r][c] >> 16)) : (x0[r][c] & 0xFFFFu);
+            const uint32_t m1 = halves ? ((x1[r][c] & 0xFFFFu) > (x1[r][c] >> 16) ? (x1[r][c] & 0xFFFFu) : (x1[r][c] >> 16)) : (x1[r][c] >> 16);
+            const bool h0 = !(fe & FL_SKIP_ZERO) || m0 >= 2 * ZBIAS, h1 = !(fe & FL_SKIP_ZERO) || m1 >= 2 * ZBIAS;
+            const int em = (h0 && h1) ? (e0[r][c] > e1[r][c] ? e0[r][c] : e1[r][c]) : (h0 ? e0[r][c] : e1[r][c]);
+            double T = 0.0;
+            if (h0) T += __builtin_floor(ldexp(T0[r][c], (e0[r][c] - F) - (em - p.Fm)));
+            if (h1) T += __builtin_floor(ldexp(T1[r][c], (e1[r][c] - F) - (em - p.Fm)));
+            v[r][c] = end(T, h0 || h1, em, p.Fm, d[r][c]);
+            tg[r][c] = x0[r][c] | x1[r][c];
+        });
         finish_group(kg, v, tg, tagged);
     };
 
@@ -1340,10 +1349,7 @@ tiled_body(const TiledArgs &ta_, const void *__restrict__ A, const void *__restr
                     }
                     flush_accumulators();
                     double v[R][C];
-#pragma unroll
-                    for (int r = 0; r < R; ++r)
-#pragma unroll
-                        for (int c = 0; c < C; ++c) v[r][c] = rd_end(Tm[r][c], have[r][c] != 0, em[r][c], p.Fm, d[r][c]);
+                    rd_each([&](int r, int c, auto end) { v[r][c] = end(Tm[r][c], have[r][c] != 0, em[r][c], p.Fm, d[r][c]); });
                     finish_group(k0 + g * LT, v, tg, tagged);
                 }
             } else {
