@@ -728,27 +728,35 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
                                     if (twin) {
                                         const ScanArgs::Hot h2 = scan_hot(mi + 1);
                                         set_f32_round_toward_zero((h2.flags & FL_RZ) != 0);
+                                        auto second = [&](auto low_c) {
 #pragma unroll
-                                        for (int r = 0; r < R; ++r)
+                                            for (int r = 0; r < R; ++r)
 #pragma unroll
-                                            for (int c = 0; c < C; ++c) {
-                                                // (a copy the optimiser cannot see through: to it the conversions under the two rounding modes are one)
-                                                int32_t S2 = S[r][c];
+                                                for (int c = 0; c < C; ++c) {
+                                                    // (a copy the optimiser cannot see through: to it the conversions under the two rounding modes are one)
+                                                    int32_t S2 = S[r][c];
 #if defined(__HIP_DEVICE_COMPILE__)
-                                                asm volatile("" : "+v"(S2));
+                                                    asm volatile("" : "+v"(S2));
 #endif
-                                                d2[r][c] = some_low ? rho_low(S2, emb[r][c], d[r][c], h2.flags, h2.out_mask) : rho32(S2, back[r][c], emb[r][c], d[r][c], h2.flags, h2.out_mask);
-                                            }
+                                                    if constexpr (decltype(low_c)::value) d2[r][c] = rho_low(S2, emb[r][c], d[r][c], h2.flags, h2.out_mask);
+                                                    else d2[r][c] = rho32(S2, back[r][c], emb[r][c], d[r][c], h2.flags, h2.out_mask);
+                                                }
+                                        };
+                                        if (ADAPT && __builtin_expect(some_low, 0)) second(std::true_type{}); else second(std::false_type{});
                                         set_f32_round_toward_zero((fl & FL_RZ) != 0);
                                     }
                                 }
+                                auto first = [&](auto low_c) {
 #pragma unroll
-                                for (int r = 0; r < R; ++r)
+                                    for (int r = 0; r < R; ++r)
 #pragma unroll
-                                    for (int c = 0; c < C; ++c) {
-                                        before[r][c] = d[r][c];
-                                        d[r][c] = some_low ? rho_low(S[r][c], emb[r][c], d[r][c], fl, hot.out_mask) : rho32(S[r][c], back[r][c], emb[r][c], d[r][c], fl, hot.out_mask);
-                                    }
+                                        for (int c = 0; c < C; ++c) {
+                                            before[r][c] = d[r][c];
+                                            if constexpr (decltype(low_c)::value) d[r][c] = rho_low(S[r][c], emb[r][c], d[r][c], fl, hot.out_mask);
+                                            else d[r][c] = rho32(S[r][c], back[r][c], emb[r][c], d[r][c], fl, hot.out_mask);
+                                        }
+                                };
+                                if (ADAPT && __builtin_expect(some_low, 0)) first(std::true_type{}); else first(std::false_type{});
                             } else {
                                 double v[R][C];
 #pragma unroll

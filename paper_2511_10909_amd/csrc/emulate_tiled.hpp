@@ -362,7 +362,7 @@ __device__ __forceinline__ double rd_exact(double T, bool have_T, int em, int F,
     double r = __longlong_as_double((long long)((bits + ((uint64_t)(int64_t)((int32_t)(bits >> 32) >> 31) & below)) & ~below));
     // results below 2^-126, where the places are counted from 2^-126 (zero is +0.0 here)
     const bool low = hi - 1u < 0x38100000u - 1u;
-    if (__any(low)) {
+    if (__builtin_expect(__any(low), 0)) {
         const double q = ldexp(__builtin_floor(ldexp(v, 126 + F2)), -(126 + F2));
         r = low ? q : r;
     }
