@@ -39,9 +39,9 @@
 //   * the reference's ordered keys are formed once per pass, a histogram entry is counted by leading zeros, and the two
 //     reductions over the wavefront run only where they can change something.
 // Measured, one launch of the sixteen sets of the closed-loop scan on 2^16 tiles of 16x16x16, before and after: FP8 1108 ->
-// 688 us (6.06 instructions per term), BF16 bit patterns 1433 -> 1149 us (8.66), all FP16 bit patterns (a quarter of the
-// tiles) 584 -> 259 us; three sets on 2^18 tiles of 32x32x8 1953 -> 1431 us (7.38).  What is left is still issue: 0.82 to
-// 0.96 of the nominal rate.
+// 682 us (6.16 instructions per term), BF16 bit patterns 1433 -> 1145 us (8.62), all FP16 bit patterns (a quarter of the
+// tiles) 584 -> 259 us; three sets on 2^18 tiles of 32x32x8 1953 -> 1403 us (7.27).  What is left is still issue: 0.82 to
+// 0.99 of the nominal rate.
 #include "emulate_tiled.hpp"
 
 namespace mmaemu {
@@ -80,8 +80,8 @@ __device__ __forceinline__ ScanArgs::Hot scan_hot(uint32_t mi)
 // held in binary64 when any element lies outside [2^-31, 2^32).
 // (Four waves per SIMD are asked for outright where the LDS allows four workgroups per CU: left alone the compiler settles
 // at about 150 vector registers and three waves; the handful of registers that go to scratch instead cost less than the
-// fourth wave brings: +6 %.  Five waves were slower.  The BF16 kernels that keep 64 products take three: at four, 300 to 600
-// registers went to scratch memory, 3785 against 1307 us a launch.  The 16 x 16 x 32 instantiations hold two or three
+// fourth wave brings: +6 %.  Five waves were slower.  The BF16 kernels that keep 64 products take three: they hold about 140
+// registers, and 16 x 16 x 16's LDS holds three workgroups.  The 16 x 16 x 32 instantiations hold two or three
 // workgroups per CU and are compiled for that many waves.)
 // A kept quarter maximum (FAM 0: biased exponent) at or above this one holds a NaN or an infinity.
 constexpr uint32_t TAGGED = 0x2000u;
@@ -841,10 +841,12 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
                     if (hot.L == 4) by_width(std::integral_constant<int, 4>{});
                     else if (hot.L == 8) by_width(std::integral_constant<int, 8>{});
                     else by_width(std::integral_constant<int, 16>{});
-                    account(mi, d, __builtin_expect(special, 0) && write_nan(d, hot.nan_bits));
+                    if (__builtin_expect(special, 0)) write_nan(d, hot.nan_bits);
+                    account(mi, d, special);
                     if (twin) {
                         ++mi;
-                        account(mi, d2, __builtin_expect(special, 0) && write_nan(d2, scan_hot(mi).nan_bits));
+                        if (__builtin_expect(special, 0)) write_nan(d2, scan_hot(mi).nan_bits);
+                        account(mi, d2, special);
                     }
                 }
                 set_f32_round_toward_zero(false);
