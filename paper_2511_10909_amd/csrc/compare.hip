@@ -81,7 +81,10 @@ __device__ __forceinline__ void wg_init(WgStats &ws)
     __syncthreads();
 }
 
-// lanes -> wavefront -> workgroup -> the caller's struct
+// lanes -> wavefront -> workgroup -> the caller's struct.  What bounds a comparison beside its bytes is this end: the
+// workgroups' atomics meet on the struct's lines.  Nothing is reduced where nothing differs, and all additions of a workgroup
+// go out in one instruction (34 lanes folding the histogram, then an atomic per counter one after the other, before): 2^20 pairs,
+// equal / 1 % / 80 % differing 8.2 / 12.2 / 12.7 -> 6.9 / 10.6 / 10.7 us; 2^24, 80 % 42.3 -> 33.2 us.
 __device__ __forceinline__ void wg_flush(WgStats &ws, Local lc, uint64_t count, mmaemu_stats *st)
 {
     unsigned long long *g = reinterpret_cast<unsigned long long *>(st);
@@ -234,12 +237,12 @@ mmaemu_status launch_compare64(const void *d0, const void *d1, uint64_t count, u
 mmaemu_status launch_compare(const void *d0, const void *d1, uint64_t count, uint64_t base, bool half,
                              mmaemu_stats *st, hipStream_t s)
 {
-    // Few, fat workgroups: every workgroup ends with up to ~40 global atomics on the same
-    // few addresses, and those serialise across the chip (measured: ~40-80 ns per workgroup), so a
-    // workgroup covers at least 16K pairs before it pays for them; 1024 threads each, so that a
-    // workgroup has 16 waves' worth of loads in flight (a small comparison is latency-bound).  One workgroup per CU at
-    // most: with two, equal inputs stream 4 % faster, but inputs that differ pay twice the atomics (2^24 pairs: 40 us
-    // against 46 us), and the closed-loop workloads compare mostly differing outputs.
+    // Few, fat workgroups: a workgroup with differing pairs ends with atomics on up to 38 words of the same few lines, and
+    // those serialise across the chip (about 30 ns per workgroup: 2^24 pairs, 256 workgroups, 24.6 us equal and 33.2 differing),
+    // so a workgroup covers at least 16K pairs before it pays for them; 1024 threads each, so that a workgroup has 16 waves' worth
+    // of loads in flight (a small comparison is latency-bound).  One workgroup per CU at most: with two, equal inputs streamed
+    // 4 % faster, but inputs that differ paid twice the atomics (15 % more at 2^24 pairs, measured when each counter was an
+    // atomic of its own), and the closed-loop workloads compare mostly differing outputs.
     uint64_t blocks = (count + 16383) / 16384;
     if (blocks < 1) blocks = 1;
     if (blocks > 256) blocks = 256;

@@ -39,8 +39,8 @@
 //   * the reference's ordered keys are formed once per pass, a histogram entry is counted by leading zeros, and the two
 //     reductions over the wavefront run only where they can change something.
 // Measured, one launch of the sixteen sets of the closed-loop scan on 2^16 tiles of 16x16x16, before and after: FP8 1108 ->
-// 682 us (6.16 instructions per term), BF16 bit patterns 1433 -> 1145 us (8.62), all FP16 bit patterns (a quarter of the
-// tiles) 584 -> 259 us; three sets on 2^18 tiles of 32x32x8 1953 -> 1403 us (7.27).  What is left is still issue: 0.82 to
+// 675 us (6.10 instructions per term), BF16 bit patterns 1433 -> 1152 us (8.64), all FP16 bit patterns (a quarter of the
+// tiles) 571 -> 253 us; three sets on 2^18 tiles of 32x32x8 1953 -> 1441 us (7.27).  What is left is still issue: 0.82 to
 // 0.99 of the nominal rate.
 #include "emulate_tiled.hpp"
 

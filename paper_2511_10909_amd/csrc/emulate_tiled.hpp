@@ -347,7 +347,7 @@ __device__ __forceinline__ double rd_exact(double T, bool have_T, int em, int F,
     // F2 counted from the leading bit, and the two-term sum always exact in binary64 (see where the flag is set): formed
     // in units of 2^(E - Fc), scaled back, and rounded down on its bit pattern: with the sign-magnitude pattern that is
     // clearing the places below F2, after adding them all where the number is negative.  28 instructions against 50, on
-    // gfx950's own sets: sixteen TR-FDPA candidates on 2^15 tiles of 16x16x16 FP16 1050 -> 840 us
+    // gfx950's own sets: sixteen TR-FDPA candidates on 2^15 tiles of 16x16x16 FP16 1081 -> 819 us
     const uint32_t Ec = (cb >> 23) & 0xFFu;
     const int ec = (int)(Ec ? Ec : 1u) - 127;
     const int E = have_T && em > ec ? em : ec;                        // (no product took part: T is zero)
