@@ -377,13 +377,20 @@ __device__ __forceinline__ double rd_general(double T, bool have_T, int em, int 
     if (have_T && drop && E - em >= drop) have_T = false;                 // the product sum lies too far below: it drops out
     if (!have_T) T = 0.0;
     const double sc_exact = ldexp((double)__uint_as_float(cb), Fc - E);
-    double sc = (fl & FL_RD_AS_RZ) ? __builtin_trunc(sc_exact) : __builtin_floor(sc_exact);     // RD_Fc(c at E), units of 2^(E - Fc)
-    if ((fl & FL_SPECIAL_TRUNC) && ec < E - Fc - 1 && Ec != 0xFFu) sc = 0.0;                   // (an infinite or NaN accumulator stays)
+    double sc = __builtin_floor(sc_exact);                                // RD_Fc(c at E), units of 2^(E - Fc)
+    const bool far_below = (fl & FL_SPECIAL_TRUNC) && ec < E - Fc - 1 && Ec != 0xFFu;          // (an infinite or NaN accumulator stays)
     if (!(fl & FL_F2_LEADING)) {
         const double T_exact = ldexp(T, (em - F) - (E - F2));
-        const double T2 = (fl & FL_RD_AS_RZ) ? __builtin_trunc(T_exact) : __builtin_floor(T_exact);   // RD_F2(T at E)
+        double T2 = __builtin_floor(T_exact);                                                    // RD_F2(T at E)
+        if (__builtin_expect((fl & FL_RD_AS_RZ) != 0u, 0)) {
+            // (+ 0.0: two negative numbers cut to -0.0 would make a sum of -0.0, and an exact zero is +0.0)
+            sc = __builtin_trunc(sc_exact) + 0.0;
+            T2 = __builtin_trunc(T_exact);
+        }
+        if (far_below) sc = 0.0;
         return ldexp(ldexp(T2, Fmax - F2) + ldexp(sc, Fmax - Fc), E - Fmax);
     }
+    if (far_below) sc = 0.0;
     // F2 counted from the leading bit of the exact two-term sum, held as s + err (Knuth's TwoSum; |err| is below half a
     // last place of s, far under the unit that is kept)
     const double a = ldexp(T, em - F), b = ldexp(sc, E - Fc);

@@ -14,7 +14,7 @@ from oracle.fdpa import ModelParams, C_AFTER_RD, C_AFTER_RD_EVEN_ODD, SPLIT_HALV
 from paper_2511_10909_amd import synth
 from gpu_utils import to_dev, to_host
 from o1_jobs import run_pool
-from test_gpu_parity import mm, gpu_emulate  # noqa: F401
+from test_gpu_parity import mm, gpu_emulate, assert_same  # noqa: F401
 
 TRZ = ModelParams(group_len=8, frac_bits=24, frac_bits2=31, c_mode=C_AFTER_RD, rd_toward_zero=True)
 
@@ -156,6 +156,28 @@ def test_deviation_sample_split_sum(mm, ta, tb, shape, stride, c_offset):
     dC = to_dev(np.concatenate([np.zeros(c_offset, np.uint32), C.ravel()]))[c_offset:]
     mm.deviation_sample(to_dev(A), to_dev(B), dC, to_dev(D), m, n, k, nb, (ta, tb, fm.FP32, fm.FP32), stride, -3, h)
     same_hist(mm.read_deviation_hist(h), deviation_hist(A, B, C, D, ta, tb, stride, -3), shape)
+
+
+@pytest.mark.parametrize("m,n", [(1, 4), (3, 5), (16, 16), (32, 32)])
+@pytest.mark.parametrize("many", [False, True])
+def test_truncating_variant_makes_zeros_positive(mm, m, n, many):
+    """Both terms of the last sum negative and cut to zero: an exact zero, +0.0 (small tiles, tiled kernels, the scan kernel)."""
+    half = lambda x: int(np.float16(x).view(np.uint16))
+    nb, k = 3, 16 if m == 16 else 8
+    A, B = np.zeros((nb, m, k), dtype=np.uint16), np.zeros((nb, n, k), dtype=np.uint16)
+    A[..., -3], A[..., -2], A[..., -1] = half(1), half(-1 - 2.0 ** -10), half(2.0 ** -10)        # 1 - (1 + 2^-10) + (2^-10 - 2^-21)
+    B[..., -3], B[..., -2], B[..., -1] = half(1), half(1), half(1 - 2.0 ** -11)
+    C = np.resize(np.array([0x80000000, 0xB0000000, 0x80000001, 0, 0x30000000, 0xBF800000], dtype=np.uint32), (nb, m, n))
+    p = TRZ.with_(group_len=8, frac_bits=23, frac_bits2=11)
+    want = o2lib.emulate_mma(p, A, B, C, fm.FP16, fm.FP16)[0]
+    assert (want == 0).any() and not (want == 0x80000000).any()
+    if many and m == n:
+        from test_gpu_many import run_many
+        _, D, kern, _ = run_many(mm, [p, p.with_(frac_bits2=12)], A, B, C, fm.FP16, fm.FP16, ref=want)
+        assert kern.startswith("multi x2"), kern
+        assert_same(D[0], want, (m, n))
+    else:
+        assert_same(gpu_emulate(mm, p, A, B, C, fm.FP16, fm.FP16), want, (m, n))
 
 
 @pytest.mark.parametrize("ta,tb,n,k", [(fm.FP16, fm.FP16, 8, 8), (fm.E4M3, fm.E5M2, 4, 40), (fm.E5M2, fm.FP16, 12, 17), (fm.FP16, fm.FP16, 4, 8192)])
