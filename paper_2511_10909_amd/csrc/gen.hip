@@ -15,10 +15,10 @@
 
 namespace mmaemu {
 
-__device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
-                                              uint32_t k0, uint32_t k1, uint32_t out[4])
+// (keys: the round keys, k + r W, worked out by the host: twenty scalar additions per wavefront less)
+__device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, const uint32_t (&keys)[20], uint32_t out[4])
 {
-    constexpr uint32_t M0 = 0xD2511F53u, M1 = 0xCD9E8D57u, W0 = 0x9E3779B9u, W1 = 0xBB67AE85u;
+    constexpr uint32_t M0 = 0xD2511F53u, M1 = 0xCD9E8D57u;
 #pragma unroll
     for (int r = 0; r < 10; ++r) {
         // (one 32 x 32 -> 64-bit multiply per product: both halves from one instruction)
@@ -26,18 +26,17 @@ __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t
         const uint32_t hi0 = (uint32_t)(p0 >> 32), lo0 = (uint32_t)p0;
         const uint32_t hi1 = (uint32_t)(p1 >> 32), lo1 = (uint32_t)p1;
         // (a ^ b ^ c in one instruction: v_bitop3_b32 with the truth table of the three-input exclusive or)
-        c0 = __builtin_amdgcn_bitop3_b32(hi1, c1, k0, 0x96);
+        c0 = __builtin_amdgcn_bitop3_b32(hi1, c1, keys[2 * r], 0x96);
         c1 = lo1;
-        c2 = __builtin_amdgcn_bitop3_b32(hi0, c3, k1, 0x96);
+        c2 = __builtin_amdgcn_bitop3_b32(hi0, c3, keys[2 * r + 1], 0x96);
         c3 = lo0;
-        k0 += W0;
-        k1 += W1;
     }
     out[0] = c0; out[1] = c1; out[2] = c2; out[3] = c3;
 }
 
 struct GenArgs {
-    uint32_t family, operand, k0, k1;
+    uint32_t family, operand;
+    uint32_t keys[20];                    // Philox's round keys
     uint32_t width, mbits, nmag;          // output format (width: bits of a code, sign on top); nmag = number of finite magnitudes
     uint32_t exp_lo, nchoices, exp_zero;  // UNIFORM_EXP
     uint32_t fp32_two_words;              // UNIFORM_EXP with FP32 output
@@ -49,39 +48,46 @@ struct GenArgs {
 
 __device__ __forceinline__ void block_words(const GenArgs &g, uint64_t blk, uint32_t w[4])
 {
-    philox4x32_10((uint32_t)blk, (uint32_t)(blk >> 32), g.operand, 0u, g.k0, g.k1, w);
+    philox4x32_10((uint32_t)blk, (uint32_t)(blk >> 32), g.operand, 0u, g.keys, w);
 }
 
 // ---- bit-pattern families ------------------------------------------------------------
 
-__device__ __forceinline__ uint32_t bits_from_word(const GenArgs &g, uint32_t r, uint32_t r1)
+// One element of every word (two words per element where the output is FP32 UNIFORM_EXP), one branch on the family for all of them.
+template <int N> __device__ __forceinline__ void bits_from_words(const GenArgs &g, const uint32_t (&r)[N], const uint32_t (&r1)[N], uint32_t (&v)[N])
 {
-    // (CANCELLING draws like UNIFORM_EXP; the pairing of even and odd elements is applied by the caller)
-    if (g.family == MMAEMU_GEN_RANDOM_BITS) return g.width == 32 ? r : (r & ((1u << g.width) - 1u));
-    if (g.family == MMAEMU_GEN_FINITE_BITS) {
-        const uint32_t v = __umulhi(r, 2u * g.nmag);
-        const uint32_t sign = v >= g.nmag;
-        return (sign << (g.width - 1)) | (v - sign * g.nmag);
-    }
-    if (g.family == MMAEMU_GEN_SIGNED_ZEROS) {
-        const uint32_t kind = r >> 30, sign = (r >> 29) & 1u;
-        const uint32_t mag = kind == 2u ? (g.bias << g.mbits) : (kind == 3u ? 1u : 0u);
-        return (sign << (g.width - 1)) | mag;
-    }
-    // UNIFORM_EXP (scale codes have no sign bit)
-    const uint32_t sign = g.dtype == MMAEMU_E8M0 ? 0u : (r >> 31);
-    uint32_t idx, mant;
-    if (g.fp32_two_words) {
-        idx = (uint32_t)(((uint64_t)(r & 0x7FFFFFFFu) * g.nchoices) >> 31);
-        mant = r1 & 0x7FFFFFu;
+    const uint32_t sign_place = g.width - 1u;
+    if (g.family == MMAEMU_GEN_RANDOM_BITS) {
+        const uint32_t mask = 0xFFFFFFFFu >> (32u - g.width);
+#pragma unroll
+        for (int j = 0; j < N; ++j) v[j] = r[j] & mask;
+    } else if (g.family == MMAEMU_GEN_FINITE_BITS) {
+        const uint32_t up = (1u << sign_place) - g.nmag;             // (what a negative number's code lies above its place)
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            const uint32_t x = __umulhi(r[j], 2u * g.nmag);
+            v[j] = x + (x >= g.nmag ? up : 0u);
+        }
+    } else if (g.family == MMAEMU_GEN_SIGNED_ZEROS) {
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            const uint32_t kind = r[j] >> 30, mag = kind == 2u ? (g.bias << g.mbits) : (kind == 3u ? 1u : 0u);
+            v[j] = (((r[j] >> 29) & 1u) << sign_place) | mag;
+        }
     } else {
-        const uint32_t nsel = 31u - g.mbits;
-        const uint32_t sel = (r >> g.mbits) & ((1u << nsel) - 1u);
-        idx = (uint32_t)(((uint64_t)sel * g.nchoices) >> nsel);
-        mant = r & ((1u << g.mbits) - 1u);
+        // UNIFORM_EXP, and CANCELLING, which draws like it (the pairing of even and odd elements is applied by the caller).  The
+        // exponent's index is floor(sel nchoices / 2^nsel), sel the nsel = 31 - mbits bits below the sign (31 of them with two words):
+        // the high half of one product.  Scale codes have no sign bit.
+        const uint32_t sel_mask = g.fp32_two_words ? 0xFFFFFFFEu : ~((2u << g.mbits) - 1u), mant_mask = (1u << g.mbits) - 1u;
+        const uint32_t sign_mask = g.dtype == MMAEMU_E8M0 ? 0u : 1u << sign_place, down = 31u - sign_place;
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            const uint32_t idx = __umulhi((r[j] << 1) & sel_mask, g.nchoices);
+            uint32_t E = g.exp_lo + idx;
+            if (g.exp_zero) E = idx == 0 ? 0u : E - 1u;
+            v[j] = (E << g.mbits) | (r1[j] & mant_mask) | ((r[j] >> down) & sign_mask);
+        }
     }
-    const uint32_t E = g.exp_zero ? (idx == 0 ? 0u : g.exp_lo + idx - 1u) : g.exp_lo + idx;
-    return (sign << (g.width - 1)) | (E << g.mbits) | mant;
 }
 
 template <typename T> __device__ __forceinline__ void store4(T *p, const uint32_t v[4]);
@@ -98,33 +104,48 @@ template <> __device__ __forceinline__ void store4<uint32_t>(uint32_t *p, const 
     *reinterpret_cast<uint4 *>(p) = make_uint4(v[0], v[1], v[2], v[3]);
 }
 
-// elements [g0, g0 + total) of the operand; thread t owns Philox block blk0 + t
-template <typename T>
+// Elements [g0, g0 + total) of the operand; thread t owns Philox block blk0 + t.  WHOLE: the range starts and ends with a block, so
+// that every block is written whole (out aligned to it), and no block's number leaves the 32-bit range it starts in (two of the
+// twenty products of Philox are then the same for all threads).
+// Bound: the vector ALU, Philox's twenty 64-bit products above all; 2^26 FP32 elements of two words 93 -> 72 us, FP16 65 -> 54 us, random E4M3 codes 56 -> 37 us
+// against a form that took the branch on the family, and 64-bit bounds, for every element.
+template <typename T, bool WHOLE>
 __global__ void __launch_bounds__(256)
 gen_bits_kernel(GenArgs g, T *out, uint64_t g0, uint64_t total, uint64_t blk0, uint64_t nblk)
 {
-    const uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const uint64_t t = (uint64_t)blockIdx.x * 256u + threadIdx.x;
     if (t >= nblk) return;
     const uint64_t blk = blk0 + t;
     uint32_t w[4];
-    block_words(g, blk, w);
+    if constexpr (WHOLE) philox4x32_10((uint32_t)blk, (uint32_t)(blk0 >> 32), g.operand, 0u, g.keys, w);
+    else block_words(g, blk, w);
     if (g.fp32_two_words) {
+        const uint32_t r[2] = {w[0], w[2]}, r1[2] = {w[1], w[3]};
+        uint32_t v[2];
+        bits_from_words(g, r, r1, v);
+        if constexpr (WHOLE && sizeof(T) == 4) {
+            *reinterpret_cast<uint2 *>(out + 2 * t) = make_uint2(v[0], v[1]);
+        } else {
 #pragma unroll
-        for (int j = 0; j < 4; j += 2) {
-            const uint64_t e = (4 * blk + j) >> 1;
-            if (e >= g0 && e - g0 < total) out[e - g0] = (T)bits_from_word(g, w[j], w[j + 1]);
+            for (int j = 0; j < 2; ++j) {
+                const uint64_t e = 2 * blk + j;
+                if (e >= g0 && e - g0 < total) out[e - g0] = (T)v[j];
+            }
         }
         return;
     }
     uint32_t v[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] = bits_from_word(g, w[j], 0u);
+    bits_from_words(g, w, w, v);
     if (g.family == MMAEMU_GEN_CANCELLING) {
         // element 2q+1 repeats element 2q (both live in this block): sign flipped for operand 0; for the other
         // operands the last mantissa bit is flipped where the odd element's own word ends in four zero bits
 #pragma unroll
         for (int j = 1; j < 4; j += 2)
             v[j] = g.operand == 0 ? (v[j - 1] ^ (1u << (g.width - 1))) : (v[j - 1] ^ ((w[j] & 0xFu) == 0 ? 1u : 0u));
+    }
+    if constexpr (WHOLE) {
+        store4<T>(out + 4 * t, v);
+        return;
     }
     const uint64_t e0 = 4 * blk;
     if (e0 >= g0 && e0 + 4 <= g0 + total && ((reinterpret_cast<uintptr_t>(out + (e0 - g0)) & (4 * sizeof(T) - 1)) == 0)) {
@@ -146,15 +167,37 @@ __global__ void zero_kernel(uint32_t *out, uint64_t nwords, uint8_t *tail, uint3
 }
 
 // ---- NORMAL family --------------------------------------------------------------------
-// binary64 elementary functions from +, *, / only, in a fixed order (the square root is IEEE-754's own operation)
+// binary64 elementary functions from +, *, / only, in a fixed order (quotient and square root are IEEE-754's own operations)
 
-__device__ __forceinline__ double ln_unit(uint32_t r)       // ln((r + 0.5) / 2^32)
+// IEEE-754's quotient and square root where no scaling and no special case can arise: two Newton steps on the hardware's reciprocal
+// (reciprocal square root), a quotient (root) from it, and one correction by the exact remainder, which rounds correctly
+// (Markstein).  Without the general forms' scaling, class tests and selections they take 8 and 10 instructions against 11 and 17.
+__device__ __forceinline__ double divide_near_one(double n, double d)        // d in [2, 3), 0 <= n < 1 and n no less than 2^-33 unless zero
 {
-    const double t = 2.0 * (double)r + 1.0;                 // odd integer < 2^33, exact
+    double y = __builtin_amdgcn_rcp(d);
+    y = __builtin_fma(__builtin_fma(-d, y, 1.0), y, y);
+    y = __builtin_fma(__builtin_fma(-d, y, 1.0), y, y);
+    const double q = n * y;
+    return __builtin_fma(__builtin_fma(-d, q, n), y, q);
+}
+__device__ __forceinline__ double square_root_normal(double x)              // x in [2^-40, 2^40]
+{
+    const double y = __builtin_amdgcn_rsq(x);
+    double r = y * x, h = y * 0.5;
+    const double e = __builtin_fma(-h, r, 0.5);
+    r = __builtin_fma(r, e, r);
+    h = __builtin_fma(h, e, h);
+    r = __builtin_fma(__builtin_fma(-r, r, x), h, r);
+    return __builtin_fma(__builtin_fma(-r, r, x), h, r);
+}
+
+__device__ __forceinline__ double minus_two_ln_unit(uint32_t r)       // -2 ln((r + 0.5) / 2^32); the factor is a power of two: exact anywhere
+{
+    const double t = __builtin_fma(2.0, (double)r, 1.0);    // odd integer < 2^33, exact
     const long long tb = __double_as_longlong(t);
     const int ex = (int)((tb >> 52) & 0x7FF) - 1023;        // t = m * 2^ex, m in [1, 2)
     const double m = __longlong_as_double((tb & 0x000FFFFFFFFFFFFFll) | 0x3FF0000000000000ll);
-    const double s = (m - 1.0) / (m + 1.0);
+    const double s = divide_near_one(m - 1.0, m + 1.0);
     const double s2 = s * s;
     double poly = 1.0 / 25.0;
     poly = poly * s2 + 1.0 / 23.0;
@@ -169,8 +212,8 @@ __device__ __forceinline__ double ln_unit(uint32_t r)       // ln((r + 0.5) / 2^
     poly = poly * s2 + 1.0 / 5.0;
     poly = poly * s2 + 1.0 / 3.0;
     poly = poly * s2 + 1.0;
-    const double lnm = (2.0 * s) * poly;
-    return lnm + (double)(ex - 33) * 0x1.62e42fefa39efp-1;
+    const double lnm = (-4.0 * s) * poly;
+    return lnm + (double)(ex - 33) * -0x1.62e42fefa39efp+0;
 }
 
 __device__ __forceinline__ void sincos_quarter(double th, double &sn, double &cs)
@@ -204,13 +247,17 @@ __device__ __forceinline__ void sincos_quarter(double th, double &sn, double &cs
 // Box-Muller on one word pair
 __device__ __forceinline__ void normal_pair(uint32_t r_even, uint32_t r_odd, double &z_even, double &z_odd)
 {
-    const double radius = __builtin_sqrt(-2.0 * ln_unit(r_even));   // IEEE-754 squareRoot: correctly rounded
+    // (the smallest argument, of the largest word, is 2^-32)
+    const double radius = square_root_normal(minus_two_ln_unit(r_even));
     const uint32_t quad = r_odd >> 30;
-    const double frac = ((double)(r_odd & 0x3FFFFFFFu) + 0.5) * (1.0 / 1073741824.0);
+    const double frac = __builtin_fma((double)(r_odd & 0x3FFFFFFFu), 0x1p-30, 0x1p-31);            // exact
     double s, c;
     sincos_quarter(frac * 0x1.921fb54442d18p+0, s, c);
-    const double cosphi = quad == 0 ? c : quad == 1 ? -s : quad == 2 ? -c : s;
-    const double sinphi = quad == 0 ? s : quad == 1 ? c : quad == 2 ? -s : -c;
+    // quarter turns: cosine c, -s, -c, s and sine s, c, -s, -c
+    const bool swap = (quad & 1u) != 0;
+    const double a = swap ? s : c, b = swap ? c : s;
+    const double cosphi = __hiloint2double(__double2hiint(a) ^ (int)((r_odd ^ (r_odd << 1)) & 0x80000000u), __double2loint(a));
+    const double sinphi = __hiloint2double(__double2hiint(b) ^ (int)(r_odd & 0x80000000u), __double2loint(b));
     z_even = radius * cosphi;
     z_odd = radius * sinphi;
 }
@@ -230,8 +277,8 @@ __device__ __forceinline__ void block_normals(const GenArgs &g, uint64_t blk, do
     if (g.family == MMAEMU_GEN_NORMAL_OUTLIERS) {
         uint32_t w2[4], wh[4];
         double z2[4];
-        philox4x32_10((uint32_t)blk, (uint32_t)(blk >> 32), g.operand + 256u, 0u, g.k0, g.k1, w2);
-        philox4x32_10((uint32_t)blk, (uint32_t)(blk >> 32), g.operand + 512u, 0u, g.k0, g.k1, wh);
+        philox4x32_10((uint32_t)blk, (uint32_t)(blk >> 32), g.operand + 256u, 0u, g.keys, w2);
+        philox4x32_10((uint32_t)blk, (uint32_t)(blk >> 32), g.operand + 512u, 0u, g.keys, wh);
         normal_pair(w2[0], w2[1], z2[0], z2[1]);
         normal_pair(w2[2], w2[3], z2[2], z2[3]);
 #pragma unroll
@@ -262,13 +309,51 @@ __device__ __forceinline__ uint32_t cast_out(const GenArgs &g, double v)
     return (sign << (g.width - 1)) | code;
 }
 
+// The same for four values, with the hardware's conversions where the format has one: round to nearest even, subnormals kept; values
+// beyond the largest finite one are brought to it before the conversion (FP16, FP8) or after it (BF16, whose rounding is on the
+// binary32 pattern).  20 instructions per element otherwise.
+__device__ __forceinline__ void cast_out4(const GenArgs &g, const double v[4], uint32_t code[4])
+{
+    if (g.dtype == MMAEMU_FP16 || g.dtype == MMAEMU_FP8_E4M3 || g.dtype == MMAEMU_FP8_E5M2) {
+        const float top = g.dtype == MMAEMU_FP16 ? 65504.0f : (g.dtype == MMAEMU_FP8_E4M3 ? 448.0f : 57344.0f);
+        float f[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) f[j] = __builtin_amdgcn_fmed3f((float)v[j], -top, top);
+        if (g.dtype == MMAEMU_FP16) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const _Float16 h = (_Float16)f[j];
+                uint16_t hb;
+                __builtin_memcpy(&hb, &h, 2);
+                code[j] = hb;
+            }
+        } else {
+            const uint32_t lo = g.dtype == MMAEMU_FP8_E4M3 ? __builtin_amdgcn_cvt_pk_fp8_f32(f[0], f[1], 0, false) : __builtin_amdgcn_cvt_pk_bf8_f32(f[0], f[1], 0, false);
+            const uint32_t hi = g.dtype == MMAEMU_FP8_E4M3 ? __builtin_amdgcn_cvt_pk_fp8_f32(f[2], f[3], 0, false) : __builtin_amdgcn_cvt_pk_bf8_f32(f[2], f[3], 0, false);
+            code[0] = lo & 0xFFu; code[1] = (lo >> 8) & 0xFFu; code[2] = hi & 0xFFu; code[3] = (hi >> 8) & 0xFFu;
+        }
+    } else if (g.dtype == MMAEMU_BF16) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const uint32_t b = __float_as_uint((float)v[j]), m = b & 0x7FFFFFFFu;
+            const uint32_t n = (m + 0x7FFFu + ((m >> 16) & 1u)) >> 16;
+            code[j] = ((b >> 16) & 0x8000u) | (n > 0x7F7Fu ? 0x7F7Fu : n);
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) code[j] = cast_out(g, v[j]);
+    }
+}
+
 template <typename T>
 __device__ __forceinline__ void write_block(const GenArgs &g, T *out, uint64_t blk, const double z[4], double scale,
                                             bool scaled, uint64_t g0, uint64_t total)
 {
     uint32_t v[4];
+    double zs[4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] = cast_out(g, scaled ? z[j] * scale : z[j]);
+    for (int j = 0; j < 4; ++j) zs[j] = scaled ? z[j] * scale : z[j];
+    cast_out4(g, zs, v);
     const uint64_t e0 = 4 * blk;
     if (e0 >= g0 && e0 + 4 <= g0 + total && ((reinterpret_cast<uintptr_t>(out + (e0 - g0)) & (4 * sizeof(T) - 1)) == 0)) {
         store4<T>(out + (e0 - g0), v);
@@ -405,8 +490,12 @@ static mmaemu_status launch_typed(const GenArgs &ga, void *out, uint64_t ept, ui
     const uint64_t grid = (nblk + 255) / 256;
     if (grid > 0x7FFFFFFFull) { set_error("generate: too many elements for one call"); return MMAEMU_ERR_SHAPE; }
     const bool value_family = ga.family == MMAEMU_GEN_NORMAL || ga.family == MMAEMU_GEN_UNIFORM || ga.family == MMAEMU_GEN_NORMAL_OUTLIERS;
+    // blocks written whole: see gen_bits_kernel
+    const bool whole = ((g0 * wpe) & 3u) == 0 && ((total * wpe) & 3u) == 0 && (reinterpret_cast<uintptr_t>(out) & (4 / wpe * sizeof(T) - 1)) == 0 &&
+                       (blk0 >> 32) == ((blk0 + nblk - 1) >> 32);
     if (!value_family) {
-        hipLaunchKernelGGL((gen_bits_kernel<T>), dim3((uint32_t)grid), dim3(256), 0, s, ga, (T *)out, g0, total, blk0, nblk);
+        if (whole) hipLaunchKernelGGL((gen_bits_kernel<T, true>), dim3((uint32_t)grid), dim3(256), 0, s, ga, (T *)out, g0, total, blk0, nblk);
+        else hipLaunchKernelGGL((gen_bits_kernel<T, false>), dim3((uint32_t)grid), dim3(256), 0, s, ga, (T *)out, g0, total, blk0, nblk);
     } else if (ga.scale_scope == MMAEMU_SCALE_NONE || ga.scale_scope == MMAEMU_SCALE_FACTOR) {
         hipLaunchKernelGGL((gen_normal_kernel<T>), dim3((uint32_t)grid), dim3(256), 0, s, ga, (T *)out, g0, total, blk0, nblk,
                            (const double *)nullptr);
@@ -503,6 +592,14 @@ static mmaemu_status launch_generate64(const GenArgs &ga, void *out, uint64_t ep
     return MMAEMU_OK;
 }
 
+static void set_keys(GenArgs &g, uint64_t seed)
+{
+    for (uint32_t r = 0; r < 10; ++r) {
+        g.keys[2 * r] = (uint32_t)seed + r * 0x9E3779B9u;
+        g.keys[2 * r + 1] = (uint32_t)(seed >> 32) + r * 0xBB67AE85u;
+    }
+}
+
 mmaemu_status launch_generate(const mmaemu_gen_params &gp, void *out, uint32_t dtype, uint64_t ept,
                               uint64_t first_tile, uint64_t n_tiles, void *workspace, hipStream_t s)
 {
@@ -518,8 +615,7 @@ mmaemu_status launch_generate(const mmaemu_gen_params &gp, void *out, uint32_t d
         GenArgs g64 = {};
         g64.family = gp.family;
         g64.operand = gp.operand;
-        g64.k0 = (uint32_t)gp.seed;
-        g64.k1 = (uint32_t)(gp.seed >> 32);
+        set_keys(g64, gp.seed);
         g64.exp_lo = gp.exp_lo;
         g64.exp_zero = gp.exp_zero ? 1u : 0u;
         g64.nchoices = gp.exp_hi - gp.exp_lo + 1u + g64.exp_zero;
@@ -542,8 +638,7 @@ mmaemu_status launch_generate(const mmaemu_gen_params &gp, void *out, uint32_t d
     GenArgs ga = {};
     ga.family = gp.family;
     ga.operand = gp.operand;
-    ga.k0 = (uint32_t)gp.seed;
-    ga.k1 = (uint32_t)(gp.seed >> 32);
+    set_keys(ga, gp.seed);
     ga.width = dtype == MMAEMU_E8M0 ? 8u : (uint32_t)(1 + f.ebits + f.mbits);
     ga.mbits = (uint32_t)f.mbits;
     const uint32_t emax_field = (1u << f.ebits) - 1u;
