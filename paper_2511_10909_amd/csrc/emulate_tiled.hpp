@@ -520,13 +520,12 @@ __device__ __noinline__ BlockVals<R * C> special_block(const void *A, const void
 // order by magnitude above every positive pattern (unsigned maximum).  For binary64 the high words do: a NaN the
 // multiplier makes is the quiet one, and an infinity has a zero low word.  The caller lets the accumulator join and
 // applies the rules.  Out of line, like special_block.
-template <int R, int C, int SA, int SB, int LEN, bool DBL>
-__device__ __forceinline__ uint2 special_products_of(const void *a_, const void *b_, bool overflow_rule)
+template <int R, int C, int SA, int SB, int LEN, bool DBL, typename THR>
+__device__ __forceinline__ uint2 special_products_of(const void *a_, const void *b_, THR threshold)
 {
     typedef typename std::conditional<DBL, double, float>::type V;
     const V *a = static_cast<const V *>(a_), *b = static_cast<const V *>(b_);
     constexpr uint32_t INF_PAT = DBL ? 0x7FF00000u : 0x7F800000u;
-    const uint32_t thr = (DBL && overflow_rule) ? 0x47F00000u : INF_PAT;       // high word of 2^128
     int32_t pmax[R][C];
     uint32_t nmax[R][C];
 #pragma unroll
@@ -557,7 +556,7 @@ __device__ __forceinline__ uint2 special_products_of(const void *a_, const void 
     for (int r = 0; r < R; ++r)
 #pragma unroll
         for (int c = 0; c < C; ++c) {
-            const uint32_t bit = 1u << (r * C + c);
+            const uint32_t bit = 1u << (r * C + c), thr = threshold(r * C + c);
             if (pmax[r][c] > (int32_t)INF_PAT || nmax[r][c] > (0x80000000u | INF_PAT)) nan |= bit;
             if (pmax[r][c] >= (int32_t)thr) pos |= bit;
             if (nmax[r][c] >= (0x80000000u | thr)) neg |= bit;
@@ -573,8 +572,19 @@ template <int R, int C, int SA_F, int SB_F, int SA_D, int SB_D, int LEN>
 __device__ __noinline__ uint2 special_products(const void *a, const void *b, uint32_t how)
 {
     static_assert(R * C <= 16, "one bit per output in each half of a word");
-    if (how & 1u) return special_products_of<R, C, SA_D, SB_D, LEN, true>(a, b, (how & 2u) != 0);
-    return special_products_of<R, C, SA_F, SB_F, LEN, false>(a, b, (how & 2u) != 0);
+    if (how & 1u) return special_products_of<R, C, SA_D, SB_D, LEN, true>(a, b, [&](int) { return (how & 2u) ? 0x47F00000u : 0x7FF00000u; });      // (high word of 2^128)
+    return special_products_of<R, C, SA_F, SB_F, LEN, false>(a, b, [](int) { return 0x7F800000u; });
+}
+
+// The same for groups under block scales, whose staged values are unscaled (before, these groups went to the integer routine from the
+// raw operands: gfx950's FP8 set on 2^11 tiles of 16x16x128, all bit patterns, 198 -> 54 us; without that routine the kernels of the
+// T-FDPA modes keep five waves per SIMD instead of three or four): thr, per output the pattern from which a product counts
+// as an infinity -- infinity itself, or where the overflow rule applies 2^(128 - s), s the exponent of the group's two scales.
+template <int R, int C, int SA_F, int SB_F, int LEN>
+__device__ __noinline__ uint2 special_products_scaled(const void *a, const void *b, BlockVals<R * C> thr)
+{
+    static_assert(R * C <= 16, "one bit per output in each half of a word");
+    return special_products_of<R, C, SA_F, SB_F, LEN, false>(a, b, [&](int i) { return thr.v[i]; });
 }
 
 // ---- the kernel -------------------------------------------------------------------------
@@ -894,7 +904,7 @@ tiled_body(const TiledArgs &ta_, const void *__restrict__ A, const void *__restr
             const int s = (int)sca[r] + (int)scb[c] - 254;
             sadj[r][c] = s;
             em += s;
-            // a NaN scale; or a product that may reach 2^128 where that counts as an infinity
+            // a NaN scale; or a product that may reach 2^128 where that counts as an infinity: settled with the special values
             to_slow = sca[r] == 0xFFu || scb[c] == 0xFFu || (IS_RD && !(fl & FL_WIDE_PRODUCTS) && em >= 126);
         }
         if (to_slow && !(e & SENTINEL_MASK)) {
@@ -922,13 +932,7 @@ tiled_body(const TiledArgs &ta_, const void *__restrict__ A, const void *__restr
         // bytes), through a pointer the optimiser cannot see through: otherwise every parameter this rare path
         // needs stays in scalar registers for the whole kernel and crowds out the hot loops' values.
         const TiledArgs q = fetch_args();
-        ScaleRef sr = no_scales();
-        if constexpr (SC) {
-            const uint32_t nblk = k / q.block;
-            sr = ScaleRef{q.sa + arow * nblk, q.sb + brow * nblk, q.block, kg};
-        }
-        if constexpr (!SC) return fdpa_group_raw_unscaled(q.p, q.ta, q.tb, a, b, q.p.L, cin);   // (fewer arguments: none on the stack)
-        else return fdpa_group_raw(q.p, q.ta, q.tb, a, b, q.p.L, cin, sr);
+        return fdpa_group_raw_unscaled(q.p, q.ta, q.tb, a, b, q.p.L, cin);       // (scaled groups lie inside a chunk and never come here)
     };
 
     // Steps 3 and 4 of TR-FDPA (4 and 5 of GTR-FDPA) and the variations, for every output of the thread: one(r, c, end) finishes
@@ -1009,7 +1013,7 @@ tiled_body(const TiledArgs &ta_, const void *__restrict__ A, const void *__restr
             // NaN and infinity results first, for the whole block at once; then the integer routine for what is left
             // (the model parameters are fetched from the kernel-argument segment here, as in slow_group)
             const TiledArgs q = fetch_args();
-            if constexpr (!SC && LT != 0) {
+            if constexpr (LT != 0) {
                 // the group lies inside the staged chunk: classes and signs from the staged values.  Under the
                 // product-overflow rule (the RD modes without `wide_products`) BF16 / TF32 groups are also tagged for a
                 // large maximum exponent alone; of those, what the routine leaves unsettled has no special operand and
@@ -1019,14 +1023,32 @@ tiled_body(const TiledArgs &ta_, const void *__restrict__ A, const void *__restr
                 const bool dbl = VM == 2 || (VM == 1 && chunk_is_double);
                 const void *pa = dbl ? static_cast<const void *>(avd + off) : static_cast<const void *>(av + off);
                 const void *pb = dbl ? static_cast<const void *>(bvd + off) : static_cast<const void *>(bv + off);
-                const uint2 sp = special_products<R, C, TI * VS, TJ * VS, TI * VSD, TJ * VSD, LT>(pa, pb, (dbl ? 1u : 0u) | (rule ? 2u : 0u));
+                uint2 sp;
+                uint32_t nan_scale = 0;                           // outputs one of whose group's scales is a NaN
+                if constexpr (SC) {
+                    BlockVals<R * C> thr;
+                    thr.settled = 0;
+                    const uint32_t nblk = k / q.block, qb = kg / q.block;
+#pragma unroll
+                    for (int r = 0; r < R; ++r)
+#pragma unroll
+                        for (int c = 0; c < C; ++c) {
+                            const uint32_t x = q.sa[(my_tile * m + i_base + TI * r) * (uint64_t)nblk + qb], y = q.sb[(my_tile * n + j_base + TJ * c) * (uint64_t)nblk + qb];
+                            const int s = (int)(x + y) - 254;
+                            thr.v[r * C + c] = (uint32_t)(255 - (rule && s > 0 ? s : 0)) << 23;
+                            if (x == 0xFFu || y == 0xFFu) nan_scale |= 1u << (r * C + c);
+                        }
+                    sp = special_products_scaled<R, C, TI * VS, TJ * VS, LT>(pa, pb, thr);
+                } else {
+                    sp = special_products<R, C, TI * VS, TJ * VS, TI * VSD, TJ * VSD, LT>(pa, pb, (dbl ? 1u : 0u) | (rule ? 2u : 0u));
+                }
 #pragma unroll
                 for (int r = 0; r < R; ++r)
 #pragma unroll
                     for (int c = 0; c < C; ++c)
                         if (tg[r][c] & SENTINEL_MASK) {
                             const uint32_t i = r * C + c, cb = d[r][c];
-                            bool nn = (sp.x >> i) & 1u, pp = (sp.y >> i) & 1u, mm = (sp.y >> (16 + i)) & 1u;
+                            bool nn = ((sp.x | nan_scale) >> i) & 1u, pp = (sp.y >> i) & 1u, mm = (sp.y >> (16 + i)) & 1u;
                             if ((cb & 0x7FFFFFFFu) > 0x7F800000u) nn = true;                       // the accumulator joins
                             else if ((cb & 0x7FFFFFFFu) == 0x7F800000u) { if (cb >> 31) mm = true; else pp = true; }
                             if (nn || (pp && mm)) dn[r][c] = q.p.nan_bits;
@@ -1047,7 +1069,7 @@ tiled_body(const TiledArgs &ta_, const void *__restrict__ A, const void *__restr
                             cin.v[r * C + c] = d[r][c];
                             tm |= 1u << (r * C + c);
                         }
-                const bool inf_final = !SC && (q.p.c_mode != MMAEMU_C_AFTER_RD || q.p.wide_products);
+                const bool inf_final = q.p.c_mode != MMAEMU_C_AFTER_RD || q.p.wide_products;
                 const BlockVals<R * C> sp = special_block<R, C, TI, TJ>(A, B, my_tile * m + i_base, my_tile * n + j_base, k, kg, cin, tm, q.ta, q.tb,
                                                                         q.p.L, q.p.ftz_in, q.p.nan_bits, inf_final);
 #pragma unroll

@@ -102,6 +102,30 @@ def test_scaled_tiled_kernels_match_oracle(mm, ta, tb):
         assert len(np.unique(want)) > want.size // 64
 
 
+@pytest.mark.parametrize("split", [0, 1, 2, 3])
+def test_scaled_special_values_and_products_around_2_128(mm, split):
+    # scales that bring products to 2^128 and past it (with and without the rule that makes them infinities), NaN scales, NaN and
+    # infinities among the operands and accumulators: settled from the staged values in the tiled kernels
+    rng = np.random.default_rng(5200 + split)
+    for trial, (ta, tb) in enumerate([(fm.E4M3, fm.E5M2), (fm.E5M2, fm.E5M2), (fm.FP16, fm.E4M3), (fm.E5M2, fm.FP16)]):
+        nb, m, n, k, L = (3, 16, 16, 128, 16) if split < 3 else (2, 32, 32, 64, 32)
+        p = ModelParams(group_len=L, frac_bits=13, frac_bits2=31, c_mode=C_AFTER_RD, split=split, frac_bits_merge=24 if split else 0, frac_bits_acc=24,
+                        wide_products=trial % 2 == 1, skip_zero_terms=trial < 2, nan_bits=0xFFC00000, ftz_in=trial == 2)
+        A, B = synth.random_bits(rng, (nb, m, k), ta), synth.random_bits(rng, (nb, n, k), tb)
+        clean = rng.random((nb, m, 1)) < 0.6                     # rows without NaN and infinities
+        A = np.where(clean, synth.narrow_exponent_bits(rng, A.shape, ta, 1, 12), A).astype(A.dtype)
+        B = np.where(rng.random((nb, n, 1)) < 0.6, synth.narrow_exponent_bits(rng, B.shape, tb, 1, 12), B).astype(B.dtype)
+        C = synth.sprinkle(rng, synth.narrow_exponent_bits(rng, (nb, m, n), fm.FP32, 100, 254), synth.SPECIAL_CODES[fm.FP32], 0.05)
+        SA = rng.integers(178, 200, size=(nb, m, k // 32)).astype(np.uint8)
+        SB = rng.integers(178, 200, size=(nb, n, k // 32)).astype(np.uint8)
+        SA[rng.random(SA.shape) < 0.02] = 255
+        want, _ = o2lib.emulate_mma_scaled(p, A, B, C, SA, SB, 32, ta, tb)
+        print("scaled special", split, ta, tb, p, flush=True)
+        got = gpu_emulate_scaled(mm, p, A, B, C, SA, SB, 32, ta, tb)
+        assert mm.last_kernel().startswith("tiled") and "vm=3" in mm.last_kernel(), mm.last_kernel()
+        assert_same(got, want, "scaled special %s" % p)
+
+
 def test_scaled_groups_across_blocks_use_the_general_kernel(mm):
     rng = np.random.default_rng(8)
     p = ModelParams(group_len=32, frac_bits=24)
