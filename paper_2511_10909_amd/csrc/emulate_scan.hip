@@ -1480,23 +1480,29 @@ static mmaemu_status launch_scan_cfg(const ScanArgs &sa, const void *A, const vo
     const uint64_t blocks = (batch + SLOTS - 1) / SLOTS;
     if (blocks > 0x7FFFFFFFull) { set_error("emulate_compare_many: too many blocks"); return MMAEMU_ERR_SHAPE; }
     if (blocks == 0) return MMAEMU_OK;
-    // Persistent workgroups: every workgroup ends with a few dozen global atomics on the same few cache lines.  Long
-    // launches take 2048 workgroups (the dispatcher balances a grid beyond the resident set); short ones as many as the
-    // device holds at once, and of those just enough that all make the same number of passes.
-    uint32_t grid = 2048u;
-    if (blocks < 8u * 2048u) {
-        static uint32_t resident[16] = {};
-        int dev = 0;
-        MMAEMU_HIP(hipGetDevice(&dev));
-        uint32_t &res = resident[dev & 15];
-        if (!res) {
-            int per_cu = 0, cus = 0;
-            MMAEMU_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, emulate_scan_kernel<TM, KC, ADAPT, FAM, TWIN>, 256, 0));
-            MMAEMU_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-            res = (uint32_t)(per_cu > 0 ? per_cu : 1) * (uint32_t)(cus > 0 ? cus : 1);
-        }
-        const uint64_t passes = (blocks + res - 1) / res;
-        grid = (uint32_t)((blocks + passes - 1) / passes);
+    // Persistent workgroups: each ends with a few dozen global atomics on the same few cache lines, so it should make many passes; but
+    // the fewer it makes, the better the dispatcher balances a grid of several times the resident set (the two waves that a SIMD
+    // issues from at once are fixed by their places, so workgroups beside a lone one run slower).  Up to eight rounds of the resident
+    // set, as long as a workgroup still evaluates 64 models over its passes (32 of the families with binary64 group ends on binary32 values):
+    // three flush variants on 2^18 tiles 1640 us with 2048 workgroups, 1586 with four rounds, 1552 with eight; sixteen T-FDPA sets on
+    // 2^16 tiles BF16 1217 -> 1200 (three workgroups to a CU: four rounds are 3072), FP8 864, 860, 907 with two, four, eight rounds;
+    // sixteen TR-FDPA sets on 2^15 tiles 843, 803, 786 with one, two, four.
+    static uint32_t resident[16] = {};
+    int dev = 0;
+    MMAEMU_HIP(hipGetDevice(&dev));
+    uint32_t &res = resident[dev & 15];
+    if (!res) {
+        int per_cu = 0, cus = 0;
+        MMAEMU_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, emulate_scan_kernel<TM, KC, ADAPT, FAM, TWIN>, 256, 0));
+        MMAEMU_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+        res = (uint32_t)(per_cu > 0 ? per_cu : 1) * (uint32_t)(cus > 0 ? cus : 1);
+    }
+    uint32_t grid = 0;
+    for (uint32_t rounds = 8; rounds >= 1; rounds /= 2) {
+        const uint64_t workgroups = (uint64_t)rounds * res, passes = (blocks + workgroups - 1) / workgroups;
+        // (whole rounds; a single one takes just as many workgroups as make the same number of passes)
+        grid = (uint32_t)(rounds > 1 ? workgroups : (blocks + passes - 1) / passes);
+        if (passes * sa.count >= (FAM == 0 || ADAPT ? 64u : 32u) && workgroups < blocks) break;
     }
     hipLaunchKernelGGL((emulate_scan_kernel<TM, KC, ADAPT, FAM, TWIN>), dim3(grid), dim3(256), 0, s, sa, A, B, C, batch, (uint32_t)blocks);
     MMAEMU_HIP(hipGetLastError());
