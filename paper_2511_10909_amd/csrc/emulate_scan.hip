@@ -891,6 +891,23 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
 #pragma unroll
                 for (int c = 0; c < C; ++c) d[r][c] = c0[r][c];
             bool slow_seen = false;                           // some group left the short route (a NaN may have come out of it)
+            // (families with round-downs) the output conversions other than round to nearest, from the exact values
+            auto convert_rare = [&](const double (&v)[R][C], uint32_t (&dn)[R][C]) {
+#pragma unroll
+                for (int r = 0; r < R; ++r)
+#pragma unroll
+                    for (int c = 0; c < C; ++c) {
+                        uint32_t o = dn[r][c];
+                        if ((fl & FL_RZ)) {
+                            const double back = (double)__uint_as_float(o);
+                            if (__builtin_fabs(back) > __builtin_fabs(v[r][c])) o -= 1u;       // rounded away from zero: step back
+                            o &= out_mask;                                                     // RZ-E8M13 cuts further, still toward zero
+                        }
+                        if ((fl & FL_FTZ_OUT) && (o & 0x7F800000u) == 0) o &= 0x80000000u;
+                        if ((fl & FL_ZERO_POSITIVE) && (o & 0x7FFFFFFFu) == 0) o = 0u;
+                        dn[r][c] = o;
+                    }
+            };
             // The groups of one model, specialised on the group length GL and the arithmetic kind so that the loops
             // unroll and the LDS addresses of a group are immediate offsets.
             auto run_groups = [&](auto gl_c, auto kind_c) {
@@ -1098,19 +1115,29 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
                         slow_seen = true;
                         uint32_t dn[R][C];
                         double vrd[R][C];                         // (FAM 1) the value to convert; one branch on the way for all four outputs
+                        bool low = true;                          // (FAM 1) some result may be a zero of negative sign
                         if constexpr (FAM == 1) {
-                            auto all = [&](auto exact_c) {
+                            if (fl & FL_FTZ_IN) {
 #pragma unroll
                                 for (int r = 0; r < R; ++r)
 #pragma unroll
-                                    for (int c = 0; c < C; ++c) {
-                                        if ((fl & FL_FTZ_IN) && (d[r][c] & 0x7F800000u) == 0) d[r][c] = 0;         // FlushSubnormal on the accumulator
-                                        const double T = Sd[r][c] + (double)S32[r][c];
-                                        if constexpr (decltype(exact_c)::value) vrd[r][c] = rd_exact(T, have[r][c], emax[r][c], F, d[r][c], hot.F2, hot.Fc, hot.drop, fl);
-                                        else vrd[r][c] = rd_general(T, have[r][c], emax[r][c], F, d[r][c], hot.F2, hot.Fc, hot.drop, fl);
-                                    }
-                            };
-                            if (__builtin_expect((fl & FL_SUM_EXACT) != 0u, 0)) all(std::true_type{}); else all(std::false_type{});
+                                    for (int c = 0; c < C; ++c) if ((d[r][c] & 0x7F800000u) == 0) d[r][c] = 0;             // FlushSubnormal on the accumulator
+                            }
+                            auto sum = [&](int r, int c) -> double { return KIND == 0 ? (double)S32[r][c] : Sd[r][c] + (double)S32[r][c]; };
+                            if (__builtin_expect((fl & FL_SUM_EXACT) != 0u, 0)) {
+                                const double T[4] = {sum(0, 0), sum(0, 1), sum(1, 0), sum(1, 1)};
+                                const bool hv[4] = {true, true, true, true};
+                                const int em[4] = {emax[0][0], emax[0][1], emax[1][0], emax[1][1]};
+                                const uint32_t cb[4] = {d[0][0], d[0][1], d[1][0], d[1][1]};
+                                double v[4];
+                                low = rd_exact_all<false>(T, hv, em, F, cb, hot.F2, hot.Fc, hot.drop, fl, v);
+                                vrd[0][0] = v[0]; vrd[0][1] = v[1]; vrd[1][0] = v[2]; vrd[1][1] = v[3];
+                            } else {
+#pragma unroll
+                                for (int r = 0; r < R; ++r)
+#pragma unroll
+                                    for (int c = 0; c < C; ++c) vrd[r][c] = rd_general(sum(r, c), have[r][c], emax[r][c], F, d[r][c], hot.F2, hot.Fc, hot.drop, fl);
+                            }
                         }
 #pragma unroll
                         for (int r = 0; r < R; ++r)
@@ -1127,15 +1154,18 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
                                     v = vrd[r][c];
                                 }
                                 uint32_t o = __float_as_uint((float)v);
-                                if ((fe & FL_RZ)) {
+                                if (FAM == 0 && (fe & FL_RZ)) {
                                     const double back = (double)__uint_as_float(o);
                                     if (__builtin_fabs(back) > __builtin_fabs(v)) o -= 1u;     // rounded away from zero: step back
                                     o &= out_mask;                                             // RZ-E8M13 cuts further, still toward zero
                                 }
-                                if ((fe & FL_FTZ_OUT) && (o & 0x7F800000u) == 0) o &= 0x80000000u;
-                                if (FAM == 1 && (fl & FL_ZERO_POSITIVE) && (o & 0x7FFFFFFFu) == 0) o = 0u;
+                                if (FAM == 0 && (fe & FL_FTZ_OUT) && (o & 0x7F800000u) == 0) o &= 0x80000000u;
                                 dn[r][c] = o;
                             }
+                        if constexpr (FAM == 1) {
+                            // (one test on the common way)
+                            if ((fl & (FL_RZ | FL_FTZ_OUT)) != 0u || (low && (fl & FL_ZERO_POSITIVE) != 0u)) convert_rare(vrd, dn);
+                        }
                         if (tagged) {
                             // NaN and infinite operands (Sec. 4.2): classes and signs from the staged values
                             const bool dbl = ADAPT && chunk_is_double;
@@ -1181,32 +1211,32 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
                 slow_seen = true;
                 uint32_t dn[R][C];
                 double vrd[R][C];
-                auto all = [&](auto exact_c) {
+                bool low = true;
+                if (fl & FL_FTZ_IN) {
 #pragma unroll
                     for (int r = 0; r < R; ++r)
 #pragma unroll
-                        for (int c = 0; c < C; ++c) {
-                            if ((fl & FL_FTZ_IN) && (d[r][c] & 0x7F800000u) == 0) d[r][c] = 0;             // FlushSubnormal on the accumulator
-                            if constexpr (decltype(exact_c)::value) vrd[r][c] = rd_exact(T[r][c], hv[r][c], em[r][c], hot.Fm, d[r][c], hot.F2, hot.Fc, hot.drop, fl);
-                            else vrd[r][c] = rd_general(T[r][c], hv[r][c], em[r][c], hot.Fm, d[r][c], hot.F2, hot.Fc, hot.drop, fl);
-                        }
-                };
-                if (__builtin_expect((fl & FL_SUM_EXACT) != 0u, 0)) all(std::true_type{}); else all(std::false_type{});
+                        for (int c = 0; c < C; ++c) if ((d[r][c] & 0x7F800000u) == 0) d[r][c] = 0;             // FlushSubnormal on the accumulator
+                }
+                if (__builtin_expect((fl & FL_SUM_EXACT) != 0u, 0)) {
+                    const double T4[4] = {T[0][0], T[0][1], T[1][0], T[1][1]};
+                    const bool h4[4] = {true, true, true, true};
+                    const int e4[4] = {em[0][0], em[0][1], em[1][0], em[1][1]};
+                    const uint32_t c4[4] = {d[0][0], d[0][1], d[1][0], d[1][1]};
+                    double v[4];
+                    low = rd_exact_all<false>(T4, h4, e4, hot.Fm, c4, hot.F2, hot.Fc, hot.drop, fl, v);
+                    vrd[0][0] = v[0]; vrd[0][1] = v[1]; vrd[1][0] = v[2]; vrd[1][1] = v[3];
+                } else {
+#pragma unroll
+                    for (int r = 0; r < R; ++r)
+#pragma unroll
+                        for (int c = 0; c < C; ++c) vrd[r][c] = rd_general(T[r][c], hv[r][c], em[r][c], hot.Fm, d[r][c], hot.F2, hot.Fc, hot.drop, fl);
+                }
 #pragma unroll
                 for (int r = 0; r < R; ++r)
 #pragma unroll
-                    for (int c = 0; c < C; ++c) {
-                        const double v = vrd[r][c];
-                        uint32_t o = __float_as_uint((float)v);
-                        if ((fl & FL_RZ)) {
-                            const double back = (double)__uint_as_float(o);
-                            if (__builtin_fabs(back) > __builtin_fabs(v)) o -= 1u;             // rounded away from zero: step back
-                            o &= out_mask;
-                        }
-                        if ((fl & FL_FTZ_OUT) && (o & 0x7F800000u) == 0) o &= 0x80000000u;
-                        if ((fl & FL_ZERO_POSITIVE) && (o & 0x7FFFFFFFu) == 0) o = 0u;
-                        dn[r][c] = o;
-                    }
+                    for (int c = 0; c < C; ++c) dn[r][c] = __float_as_uint((float)vrd[r][c]);
+                if ((fl & (FL_RZ | FL_FTZ_OUT)) != 0u || (low && (fl & FL_ZERO_POSITIVE) != 0u)) convert_rare(vrd, dn);
                 if (tagged) {
                     const uint2 sp = special_products<R, C, TI * VS, TJ * VS, TI * VSD, TJ * VSD, GLT>(av + kg, bv + kg, 2u);
 #pragma unroll

@@ -101,7 +101,19 @@ emulate_small_kernel(SmallArgs sm, const uint8_t *__restrict__ A, const uint8_t 
                         s += pr;
                     }
                 double v;
-                if constexpr (RD) v = rd_value(T, !(fl & FL_SKIP_ZERO) || e >= 2 * ZBIAS, em, F, cb, p.F2, p.Fc, p.sum_drop_distance, fl);
+                if constexpr (RD) {
+                    if (fl & FL_SUM_EXACT) {
+                        const double T1[1] = {T};
+                        const bool h1[1] = {true};
+                        const int e1[1] = {em};
+                        const uint32_t c1[1] = {cb};
+                        double v1[1];
+                        rd_exact_all<false>(T1, h1, e1, F, c1, p.F2, p.Fc, p.sum_drop_distance, fl, v1);
+                        v = v1[0];
+                    } else {
+                        v = rd_general(T, !(fl & FL_SKIP_ZERO) || e >= 2 * ZBIAS, em, F, cb, p.F2, p.Fc, p.sum_drop_distance, fl);
+                    }
+                }
                 else {
                     const int unit = emax - F;
                     v = ldexp(T + __builtin_trunc(ldexp((double)__uint_as_float(cb), -unit)), unit);
