@@ -64,7 +64,7 @@ emulate_small_kernel(SmallArgs sm, const uint8_t *__restrict__ A, const uint8_t 
             uint2 ea[QL];
             small_row<QL>(sm.ta, sm.esa, a + (uint64_t)k0 * sm.esa, fl & FL_FTZ_IN, sm.zbias, fa, ea);
             // Short groups: the four outputs' sums first, then the ends of their groups side by side (gfx950's set on 2^18 tiles of
-            // 4x4x4 FP16 24.6 -> 23.0 us).  Longer ones, and binary64 values, need the registers: one output after the other, its row's
+            // 4x4x4 FP16 24.8 -> 23.1 us).  Longer ones, and binary64 values, need the registers: one output after the other, its row's
             // place made to depend on the output before, or the rows would all be fetched first (groups of 16 on BF16 31.8 -> 36.5 us).
             constexpr int G = QL == 1 && !DBL ? W : 1;
 #pragma unroll
