@@ -24,11 +24,12 @@ INT32_VALU_PEAK = 256 * 4 * 16 * 2.4e9      # lane-instructions / s: 256 CUs x 4
 ALGO_OPS_PER_TERM = 8                       # accounting floor of INT32 VALU instructions per MAC term
 # Counter figures of the emulation kernels, from rocprofv3 --pmc runs of this program (see the named files under profiles/):
 # vector-ALU lane-instructions per MAC term (SQ_INSTS_VALU x 64 / terms) and HBM bytes per launch (FETCH_SIZE + WRITE_SIZE,
-# scaled by a copy kernel of known size).  Keyed by the kernel's name: a kernel that has changed since reports null.
+# scaled by a copy kernel of known size).  Keyed by the kernel's name, so one of another name reports null;
+# taken again whenever a kernel changes under its name.
 COUNTERS = {
-    "multi x16 tiled 16x16 r2x2 kc=16 any L vm=0": {"valu_instr_per_term": 6.10, "traffic": 178563000, "chunk": 1 << 16},
-    "multi x16 tiled 16x16 r2x2 kc=16 any L vm=1": {"valu_instr_per_term": 8.64, "traffic": 211506000, "chunk": 1 << 16},
-    "multi x3 tiled 32x32 r2x2 kc=8 any L vm=0, twins share sums": {"valu_instr_per_term": 7.27, "traffic": 1342572000, "chunk": 1 << 18},
+    "multi x16 tiled 16x16 r2x2 kc=16 any L vm=0": {"valu_instr_per_term": 6.22, "traffic": 188224000, "chunk": 1 << 16},
+    "multi x16 tiled 16x16 r2x2 kc=16 any L vm=1": {"valu_instr_per_term": 8.70, "traffic": 215934000, "chunk": 1 << 16},
+    "multi x3 tiled 32x32 r2x2 kc=8 any L vm=0, twins share sums": {"valu_instr_per_term": 7.31, "traffic": 1345087000, "chunk": 1 << 18},
 }
 COUNTERS_SOURCE = ("profiles/closed_loop_scan_trace_and_counters.md, profiles/subnormal_stress_trace_and_counters.md (rocprofv3 --pmc SQ_INSTS_VALU; "
                    "FETCH_SIZE, WRITE_SIZE scaled by a 64 MiB copy); traffic per launch")

@@ -9,7 +9,8 @@
 //   * v_mfma_f32_16x16x32_f16 against a matrix of zeros and ones adds up eight such terms of each of 64 outputs, exactly (all are
 //     multiples of the unit, and (L + 1) 2^(F+2) <= 2^24); the ones choose the result column, so that the four outputs of a lane
 //     fill one accumulator and come out transposed: four neighbours of a row of D in each lane.  (v_dot2_f32_f16 with ones does the
-//     same without the transposition at two instructions per eight terms: 4960 us against 4270 below.)
+//     same without the transposition at two instructions per eight terms: a 4096^3 pass with its exact dots took 4960 us, against 4270
+//     for the first kernel with the matrix sum.)
 //   * the maximum exponent comes from the matrix cores too.  An element is represented by 2^(8 (Exp - Exp_row)), Exp_row the largest
 //     exponent of its row in the staged chunk; the dot product of two such rows lies in [2^(8 x), 32 * 2^(8 x)) with x the
 //     group's maximum relative to the two rows', so x is the result's exponent field divided by 8: one shift.

@@ -39,9 +39,9 @@
 //   * the reference's ordered keys are formed once per pass, a histogram entry is counted by leading zeros, and the two
 //     reductions over the wavefront run only where they can change something.
 // Measured, one launch of the sixteen sets of the closed-loop scan on 2^16 tiles of 16x16x16, before and after: FP8 1108 ->
-// 675 us (6.10 instructions per term), BF16 bit patterns 1433 -> 1152 us (8.64), all FP16 bit patterns (a quarter of the
-// tiles) 571 -> 253 us; three sets on 2^18 tiles of 32x32x8 1953 -> 1441 us (7.27).  What is left is still issue: 0.82 to
-// 0.99 of the nominal rate.
+// 670 us (6.22 instructions per term), BF16 bit patterns 1433 -> 1137 us (8.70), all FP16 bit patterns (a quarter of the
+// tiles) 571 -> 253 us; three sets on 2^18 tiles of 32x32x8 1953 -> 1354 us (7.31).  What is left is still issue: 0.84 to
+// 1.01 of the nominal rate.
 #include "emulate_tiled.hpp"
 
 namespace mmaemu {
