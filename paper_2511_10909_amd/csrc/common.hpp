@@ -119,7 +119,7 @@ bool small_takes(const ModelArgs &p, uint32_t ta, uint32_t tb, uint32_t m, uint3
 mmaemu_status launch_emulate_small(const ModelArgs &p, const void *A, const void *B, const void *C, void *D, uint32_t m, uint32_t n,
                                    uint32_t k, uint64_t batch, uint32_t ta, uint32_t tb, hipStream_t s);
 // T-FDPA on FP8 operands with a narrow sum, in packed binary16 (emulate_packed.hip)
-bool packed_takes(const ModelArgs &p, uint32_t ta, uint32_t tb, uint32_t m, uint32_t n, uint32_t k);
+bool packed_takes(const ModelArgs &p, uint32_t ta, uint32_t tb, uint32_t m, uint32_t n, uint32_t k, uint64_t batch);
 mmaemu_status launch_emulate_packed(const ModelArgs &p, const void *A, const void *B, const void *C, void *D, uint32_t m, uint32_t n,
                                     uint32_t k, uint64_t batch, uint32_t ta, uint32_t tb, hipStream_t s);
 mmaemu_status launch_emulate_generic(const ModelArgs &p, const void *A, const void *B, const void *C, void *D,

@@ -532,20 +532,32 @@ static mmaemu_status launch_packed_cfg(const PackedArgs &pa, const void *A, cons
     return MMAEMU_OK;
 }
 
+// The side of the blocks that a problem is cut into, 64 or 32; 0 where neither grid has fewer than the 2^32 threads of one launch.
+// A 64 x 64 block costs 0.5 to 0.6 (groups of 32) or 0.7 to 0.8 (groups of 16) of what the tiled kernels take for as many outputs, a
+// 32 x 32 block 0.6 to 0.7 -- but both for the padding of edge blocks too, and 64 x 64 blocks need 2^21 outputs to keep all CUs
+// busy.  So they are taken from there on where they pad at most a seventh more than 32 x 32 blocks do.  Groups of 32 on N(0,1)
+// data, tiled kernel, 64 x 64, 32 x 32: 2^14 tiles of 32x32x64 157, 297, 101 us; 2^13 of 17x17x32 53, 98, 34; 512 of 65x65x64 51,
+// 45, 31; 2^12 of 64x64x64 171, 89, 98; 2^12 of 33x33x32 98, 49, 60.
+static uint32_t packed_side(uint32_t m, uint32_t n, uint64_t batch)
+{
+    auto blocks = [&](uint64_t side) { return batch * ((m + side - 1) / side) * ((n + side - 1) / side); };
+    const uint64_t large = blocks(64), small = blocks(32);
+    if (batch * m * n >= (1ull << 21) && 7 * large <= 2 * small && large < (1ull << 32) / 512) return 64;
+    return small < (1ull << 32) / 256 ? 32 : 0;
+}
+
 template <int TA, int TB>
 static mmaemu_status launch_packed_types(const PackedArgs &pa, uint32_t L, const void *A, const void *B, const void *Cm, void *D, uint32_t m,
                                          uint32_t n, uint32_t k, uint64_t batch, hipStream_t s)
 {
-    // 64 x 64 blocks from 512 of them on (two per CU), 32 x 32 blocks below: 1024^3 takes 128 us with these, 4096 x 512 x 4096 is
-    // 1.96 times as fast as before with those
-    const bool large = batch * m * n >= (1ull << 21);
+    const bool large = packed_side(m, n, batch) == 64;
     if constexpr (TA == TB) {
         if (L == 16) return large ? launch_packed_cfg<TA, TB, 4, 2, 2, 16>(pa, A, B, Cm, D, m, n, k, batch, s) : launch_packed_cfg<TA, TB, 2, 2, 1, 16>(pa, A, B, Cm, D, m, n, k, batch, s);
     }
     return large ? launch_packed_cfg<TA, TB, 4, 2, 2, 32>(pa, A, B, Cm, D, m, n, k, batch, s) : launch_packed_cfg<TA, TB, 2, 2, 1, 32>(pa, A, B, Cm, D, m, n, k, batch, s);
 }
 
-bool packed_takes(const ModelArgs &p, uint32_t ta, uint32_t tb, uint32_t m, uint32_t n, uint32_t k)
+bool packed_takes(const ModelArgs &p, uint32_t ta, uint32_t tb, uint32_t m, uint32_t n, uint32_t k, uint64_t batch)
 {
     if (p.c_mode != MMAEMU_C_IN_GROUP || p.skip_zero_terms || p.zero_result_positive || (p.flags & (FL_ACC16 | FL_NAN_PROPAGATE))) return false;
     // (two E5M2 rows span 64 places together, more than binary16 can scale: the tiled kernels)
@@ -553,6 +565,12 @@ bool packed_takes(const ModelArgs &p, uint32_t ta, uint32_t tb, uint32_t m, uint
     // (groups of 16 with an E5M2 operand: bit patterns of the whole format leave the window in most wavefronts, 2.5 -> 3.5 ms on 2048^3;
     // groups of 32 do not)
     if (!(p.L == 32 || (p.L == 16 && ta == tb)) || k % 32 != 0 || m <= 16 || n <= 16) return false;
+    const uint32_t side = packed_side(m, n, batch);
+    if (side == 0) return false;
+    // (groups of 16, m and n multiples of 16: 16 x 16 blocks of the tiled kernels pad nothing, and 64 x 64 ones that pad more than two
+    // thirds are no faster: 2^10 tiles of 48x48x64 35 us there, 38 here; of 48x112x64, 512 of them, 40 and 38)
+    const uint64_t padded = ((m + 63ull) & ~63ull) * ((n + 63ull) & ~63ull);
+    if (p.L == 16 && side == 64 && m % 16 == 0 && n % 16 == 0 && 3 * padded > 5ull * m * n) return false;
     // every sum an integer below 2^24; below F = 10 a row of E4M3 beside one of E5M2 (T = F - 17) would lose its smallest bits
     return p.F >= 10 && ((uint64_t)(p.L + 1) << (p.F + 2)) <= (1ull << 24);
 }

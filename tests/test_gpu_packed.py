@@ -70,3 +70,33 @@ def test_packed_kernel_keeps_to_its_range(mm):
         got = gpu_emulate(mm, p, A, B, C, fm.E4M3, fm.E5M2)
         assert "packed" not in gpu_emulate.last_kernel, gpu_emulate.last_kernel
         assert_same(got, want, "%s" % ((m, n, k, L, F),))
+
+
+# (m, n, k, tiles, side of the blocks): batches of at least 2^21 outputs, tiles below, at and above the sizes where 64 x 64 blocks pad too much
+BATCHES = [(32, 32, 64, 2048, 32), (17, 33, 32, 3800, 32), (65, 40, 32, 808, 32), (64, 160, 32, 206, 32), (64, 224, 32, 147, 64), (33, 47, 32, 1408, 64)]
+
+
+@pytest.mark.parametrize("m,n,k,nb,side", BATCHES)
+def test_packed_kernel_on_batches_of_small_tiles(mm, m, n, k, nb, side):
+    rng = np.random.default_rng(9300 + m)
+    for (ta, tb), L in (((fm.E4M3, fm.E5M2), 32), ((fm.E4M3, fm.E4M3), 16)):
+        p = ModelParams(group_len=L, frac_bits=14, c_mode=C_IN_GROUP)
+        A, B, C = operands(rng, ta, tb, nb, m, n, k, "special")
+        print("packed batch", ta, tb, (m, n, k, nb), p, flush=True)
+        want, _ = o2lib.emulate_mma(p, A, B, C, ta, tb)
+        got = gpu_emulate(mm, p, A, B, C, ta, tb)
+        assert_same(got, want, "packed batch %s %s" % ((m, n, k, nb), p))
+        assert gpu_emulate.last_kernel == "tiled %dx%d packed fp16 L=%d" % (side, side, L), gpu_emulate.last_kernel
+
+
+def test_padded_batches_of_short_groups_keep_unpadded_blocks(mm):
+    # 64 x 64 blocks would compute 16 / 9 of the outputs; tiles of 48 x 112, padded to 1.5 times their size, take them; fewer tiles of 48 x 48 take 32 x 32 blocks
+    rng = np.random.default_rng(9400)
+    for (m, n, nb, name) in ((48, 48, 911, "tiled 16x16 r2x2"), (48, 112, 391, "tiled 64x64 packed"), (48, 48, 910, "tiled 32x32 packed")):
+        A, B, C = operands(rng, fm.E4M3, fm.E4M3, nb, m, n, 32, "special")
+        p = ModelParams(group_len=16, frac_bits=14, c_mode=C_IN_GROUP)
+        print("packed or not", (m, n, nb), flush=True)
+        want, _ = o2lib.emulate_mma(p, A, B, C, fm.E4M3, fm.E4M3)
+        got = gpu_emulate(mm, p, A, B, C, fm.E4M3, fm.E4M3)
+        assert_same(got, want, "%s" % ((m, n, nb),))
+        assert gpu_emulate.last_kernel.startswith(name), gpu_emulate.last_kernel
