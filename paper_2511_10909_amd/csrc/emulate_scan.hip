@@ -1510,13 +1510,16 @@ static mmaemu_status launch_scan_cfg(const ScanArgs &sa, const void *A, const vo
     const uint64_t blocks = (batch + SLOTS - 1) / SLOTS;
     if (blocks > 0x7FFFFFFFull) { set_error("emulate_compare_many: too many blocks"); return MMAEMU_ERR_SHAPE; }
     if (blocks == 0) return MMAEMU_OK;
-    // Persistent workgroups: each ends with a few dozen global atomics on the same few cache lines, so it should make many passes; but
-    // the fewer it makes, the better the dispatcher balances a grid of several times the resident set (the two waves that a SIMD
-    // issues from at once are fixed by their places, so workgroups beside a lone one run slower).  Up to eight rounds of the resident
-    // set, as long as a workgroup still evaluates 64 models over its passes (32 of the families with binary64 group ends on binary32 values):
-    // three flush variants on 2^18 tiles 1640 us with 2048 workgroups, 1586 with four rounds, 1552 with eight; sixteen T-FDPA sets on
-    // 2^16 tiles BF16 1217 -> 1200 (three workgroups to a CU: four rounds are 3072), FP8 864, 860, 907 with two, four, eight rounds;
-    // sixteen TR-FDPA sets on 2^15 tiles 843, 803, 786 with one, two, four.
+    // Persistent workgroups: one resident set makes equal passes, a grid of several rounds of it lets the dispatcher balance what the
+    // passes' data make unequal.  Against more of them stand the ends: where outputs differ, a workgroup's counters go to the same few
+    // cache lines as every other's, one workgroup after the other at about 0.06 us (FP8 16x16x16, two sets that differ on most outputs,
+    // 2^15 tiles: 105, 149, 261, 504 us with 1024, 2048, 4096, 8192 workgroups; where nothing differs 8192 cost no more than 1024).
+    // What stands beside that is the launch's arithmetic, k x passes x (sets + 1) per workgroup, the last for staging and decoding; the
+    // lines below are where a round more is the faster one with outputs that differ: launches of 1 to 16 sets on 2^12 to 2^18 tiles
+    // take 0.976 of the time that a fixed 2048 workgroups from 2^14 blocks on, one round below, take, and no more than 1.06 of it
+    // (few sets on agreeing outputs: FP8 16x16x32, one set on 2^16 tiles 163 -> 175 us).  Sixteen T-FDPA sets on 2^16 tiles FP8 702,
+    // 673, 667, 700 us with one, two, four, eight rounds; BF16 1057, 992, 978, 992; sixteen TR-FDPA sets on 2^15 tiles FP16 514,
+    // 481, 462, 461; four sets on 2^16 tiles FP8 249, 239, 321, 532.
     static uint32_t resident[16] = {};
     int dev = 0;
     MMAEMU_HIP(hipGetDevice(&dev));
@@ -1532,7 +1535,8 @@ static mmaemu_status launch_scan_cfg(const ScanArgs &sa, const void *A, const vo
         const uint64_t workgroups = (uint64_t)rounds * res, passes = (blocks + workgroups - 1) / workgroups;
         // (whole rounds; a single one takes just as many workgroups as make the same number of passes)
         grid = (uint32_t)(rounds > 1 ? workgroups : (blocks + passes - 1) / passes);
-        if (passes * sa.count >= (FAM == 0 || ADAPT ? 64u : 32u) && workgroups < blocks) break;
+        const uint64_t work = (KC + (FAM == 0 ? 0u : 8u)) * (sa.count + 1ull);          // (binary64 group ends: like eight products more)
+        if (work * passes >= (rounds == 8 ? 1000u : 600u) && workgroups < blocks) break;
     }
     hipLaunchKernelGGL((emulate_scan_kernel<TM, KC, ADAPT, FAM, TWIN>), dim3(grid), dim3(256), 0, s, sa, A, B, C, batch, (uint32_t)blocks);
     MMAEMU_HIP(hipGetLastError());

@@ -570,3 +570,30 @@ def test_argument_checks(mm):
         assert ei.value.status == status, (kw, mm.last_error())
     mm.emulate_compare_many([h], None, None, None, None, None, 16, 16, 16, 0, dt, ok, stream=0)       # no tiles: nothing to do
     mm.model_destroy(h)
+
+
+@pytest.mark.parametrize("nb", [4099, 16399, 40001, 100003])
+@pytest.mark.parametrize("rd", [False, True])
+def test_grids_of_several_rounds_against_the_oracle(mm, nb, rd):
+    """Launches of one resident set of workgroups and of two, four and eight rounds of it, with ragged ends: 64 tiles over and over,
+    so that every counter is a multiple of the oracle's."""
+    rng = np.random.default_rng(7700 + rd)
+    t, m, distinct = fm.FP16, 16, 64
+    A, B, C = make_case(rng, t, t, distinct, m, m, m, special_frac=0.002)
+    plist = rd_sets(rng, m, 16) if rd else [ModelParams(group_len=min(L, m), frac_bits=F, out_round=rho, ftz_in=bool(z), ftz_out=bool(z))
+                                            for (F, L, rho, z) in SETS16]
+    if rd:
+        plist = [p.with_(skip_zero_terms=False) for p in plist]                # (all in one launch)
+    want = oracle_outputs(plist, A, B, C, t, t)
+    ref = want[5].copy()
+    ref.reshape(-1)[::37] ^= 3
+    pick = np.arange(nb) % distinct
+    got, _, kern, _ = run_many(mm, plist, A[pick], B[pick], C[pick], t, t, ref=ref[pick], dump=False, index_base=9)
+    assert kern.startswith("multi x16"), kern
+    whole, rest = divmod(nb, distinct)
+    for i, w in enumerate(want):
+        one, part = ostats.compare(w, ref, index_base=9), ostats.compare(w[:rest], ref[:rest], index_base=9)
+        for key in ("n_compared", "n_mismatch_bits", "n_mismatch_nan_equiv"):
+            assert got[i][key] == whole * one[key] + part[key], (i, key, plist[i])
+        assert got[i]["ulp_hist"] == [whole * a + b for a, b in zip(one["ulp_hist"], part["ulp_hist"])], (i, plist[i])
+        assert got[i]["first_mismatch_index"] == one["first_mismatch_index"] and got[i]["max_ulp_dist"] == one["max_ulp_dist"], (i, plist[i])
