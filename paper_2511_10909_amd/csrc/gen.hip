@@ -46,6 +46,21 @@ struct GenArgs {
     double scale_target;
 };
 
+// The kernel's first argument once more, from the kernel-argument segment through a pointer that the optimiser cannot see through: a loop
+// over blocks then loads the round keys where it uses them.  Kept outside, they put twenty more scalar registers than there are into
+// lanes of vector registers (per-tile scaled N(0,1), 2^24 elements in tiles of 1024: FP32 114 -> 105 us, E2M3 125 -> 115, E4M3 115 -> 106).
+#if defined(__HIP_DEVICE_COMPILE__)
+typedef const GenArgs __attribute__((address_space(4))) *GenArgsPtr;
+__device__ __forceinline__ GenArgs fetch_gen_args()
+{
+    GenArgsPtr kp = (GenArgsPtr)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(kp));
+    return *kp;
+}
+#else
+__device__ __forceinline__ GenArgs fetch_gen_args() { return GenArgs{}; }
+#endif
+
 __device__ __forceinline__ void block_words(const GenArgs &g, uint64_t blk, uint32_t w[4])
 {
     philox4x32_10((uint32_t)blk, (uint32_t)(blk >> 32), g.operand, 0u, g.keys, w);
@@ -405,7 +420,7 @@ gen_absmax_kernel(GenArgs g, uint64_t g0, uint64_t total, uint64_t blk0, uint64_
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
     for (uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; t < nblk; t += stride) {
         double z[4];
-        block_normals(g, blk0 + t, z);
+        block_normals(fetch_gen_args(), blk0 + t, z);
         const double a = block_absmax(z, blk0 + t, g0, g0 + total);
         mx = a > mx ? a : mx;
     }
@@ -432,7 +447,7 @@ gen_normal_tile_kernel(GenArgs g, T *out, uint64_t ept, uint64_t first_tile, uin
         double mx = 0.0, zc[4] = {0.0, 0.0, 0.0, 0.0};
         uint64_t cached = ~0ull;
         for (uint64_t t = threadIdx.x; t < nblk; t += blockDim.x) {
-            block_normals(g, blk_lo + t, zc);
+            block_normals(fetch_gen_args(), blk_lo + t, zc);
             cached = blk_lo + t;
             const double a = block_absmax(zc, cached, lo, hi);
             mx = a > mx ? a : mx;
@@ -443,7 +458,7 @@ gen_normal_tile_kernel(GenArgs g, T *out, uint64_t ept, uint64_t first_tile, uin
         for (uint64_t t = threadIdx.x; t < nblk; t += blockDim.x) {
             double z[4];
             if (blk_lo + t == cached) { z[0] = zc[0]; z[1] = zc[1]; z[2] = zc[2]; z[3] = zc[3]; }
-            else block_normals(g, blk_lo + t, z);
+            else block_normals(fetch_gen_args(), blk_lo + t, z);
             // only this tile's elements: clip the writable range to [lo, hi)
             write_block<T>(g, out + (lo - g_call0), blk_lo + t, z, scale, true, lo, ept);
         }
@@ -465,7 +480,7 @@ gen_normal_tile_wave_kernel(GenArgs g, T *out, uint64_t ept, uint64_t first_tile
         const uint64_t lo = (first_tile + tile) * ept, hi = lo + ept, blk_lo = lo >> 2;
         double z[4] = {0.0, 0.0, 0.0, 0.0}, mx = 0.0;
         if (lane < nblk) {
-            block_normals(g, blk_lo + lane, z);
+            block_normals(fetch_gen_args(), blk_lo + lane, z);
             mx = block_absmax(z, blk_lo + lane, lo, hi);
         }
 #pragma unroll

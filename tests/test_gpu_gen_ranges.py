@@ -32,3 +32,19 @@ def test_generator_ranges(mm, dtype):
             what = (dtype, kw, ept, first, tiles, off)
             assert np.array_equal(got[off:off + ept * tiles].astype(np.uint64), want.astype(np.uint64)), what
             assert not got[:off].any() and not got[off + ept * tiles:].any(), what
+
+
+@pytest.mark.parametrize("dtype", FORMATS + [fm.E2M3])
+def test_scaled_normals(mm, dtype):
+    # per-tile scaling on tiles of one wavefront, of a workgroup (one block per thread and several) and unaligned ones; per tensor
+    import torch
+    torch_type = {1: torch.uint8, 2: torch.int16, 4: torch.int32}[mm.ELEM_BYTES[dtype]]
+    for scope in (mm.SCALE_TILE, mm.SCALE_TENSOR):
+        for (ept, first, tiles) in ((256, 3, 9), (252, 1, 5), (1024, 2, 3), (500, 1, 3), (4100, 1, 2), (7, 5, 11)):
+            for family in (mm.GEN_NORMAL, mm.GEN_NORMAL_OUTLIERS):
+                out = torch.zeros(ept * tiles, dtype=torch_type, device="cuda")
+                kw = dict(family=family, scale_scope=scope, scale_target=100.0)
+                mm.generate(out, dtype, ept, first, tiles, seed=78, operand=1, workspace=torch.zeros(1, dtype=torch.int64, device="cuda"), **kw)
+                got = to_host(out, NP[dtype])
+                want = ogen.generate(ogen.GenParams(seed=78, operand=1, **kw), dtype, ept, first, tiles).reshape(-1)
+                assert np.array_equal(got.astype(np.uint64), want.astype(np.uint64)), (dtype, kw, ept, first, tiles)
