@@ -43,6 +43,7 @@
 // tiles) 571 -> 253 us; three sets on 2^18 tiles of 32x32x8 1953 -> 1354 us (7.31).  What is left is still issue: 0.84 to
 // 1.01 of the nominal rate.
 #include "emulate_tiled.hpp"
+#include <atomic>
 
 namespace mmaemu {
 
@@ -1516,19 +1517,21 @@ static mmaemu_status launch_scan_cfg(const ScanArgs &sa, const void *A, const vo
     // 2^15 tiles: 105, 149, 261, 504 us with 1024, 2048, 4096, 8192 workgroups; where nothing differs 8192 cost no more than 1024).
     // What stands beside that is the launch's arithmetic, k x passes x (sets + 1) per workgroup, the last for staging and decoding; the
     // lines below are where a round more is the faster one with outputs that differ: launches of 1 to 16 sets on 2^12 to 2^18 tiles
-    // take 0.976 of the time that a fixed 2048 workgroups from 2^14 blocks on, one round below, take, and no more than 1.06 of it
-    // (few sets on agreeing outputs: FP8 16x16x32, one set on 2^16 tiles 163 -> 175 us).  Sixteen T-FDPA sets on 2^16 tiles FP8 702,
+    // take 0.977 of the time that a fixed 2048 workgroups from 2^14 blocks on, one round below, take, and no more than 1.06 of it
+    // (few sets on agreeing outputs: FP16 16x16x16, two GTR-FDPA sets on 2^16 tiles 209 -> 222 us).  Sixteen T-FDPA sets on 2^16 tiles FP8 702,
     // 673, 667, 700 us with one, two, four, eight rounds; BF16 1057, 992, 978, 992; sixteen TR-FDPA sets on 2^15 tiles FP16 514,
     // 481, 462, 461; four sets on 2^16 tiles FP8 249, 239, 321, 532.
-    static uint32_t resident[16] = {};
+    // (workgroups that a device holds at once, by device; threads that ask at the same time work out the same number)
+    static std::atomic<uint32_t> resident[16];
     int dev = 0;
     MMAEMU_HIP(hipGetDevice(&dev));
-    uint32_t &res = resident[dev & 15];
+    uint32_t res = dev < 16 ? resident[dev].load(std::memory_order_relaxed) : 0u;
     if (!res) {
         int per_cu = 0, cus = 0;
         MMAEMU_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, emulate_scan_kernel<TM, KC, ADAPT, FAM, TWIN>, 256, 0));
         MMAEMU_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
         res = (uint32_t)(per_cu > 0 ? per_cu : 1) * (uint32_t)(cus > 0 ? cus : 1);
+        if (dev < 16) resident[dev].store(res, std::memory_order_relaxed);
     }
     uint32_t grid = 0;
     for (uint32_t rounds = 8; rounds >= 1; rounds /= 2) {

@@ -597,3 +597,36 @@ def test_grids_of_several_rounds_against_the_oracle(mm, nb, rd):
             assert got[i][key] == whole * one[key] + part[key], (i, key, plist[i])
         assert got[i]["ulp_hist"] == [whole * a + b for a, b in zip(one["ulp_hist"], part["ulp_hist"])], (i, plist[i])
         assert got[i]["first_mismatch_index"] == one["first_mismatch_index"] and got[i]["max_ulp_dist"] == one["max_ulp_dist"], (i, plist[i])
+
+
+def test_launches_from_several_threads_at_once(mm):
+    """The first launches of a kernel from four threads, each on a stream of its own: the same statistics as one after the other."""
+    import threading
+    import torch
+    rng = np.random.default_rng(7800)
+    A, B, C = make_case(rng, fm.E4M3, fm.E5M2, 400, 16, 16, 16, special_frac=0.001)
+    plist = [ModelParams(group_len=min(L, 16), frac_bits=F, out_round=rho) for (F, L, rho, z) in SETS16[::4]]
+    hs = _handles(mm, plist)
+    dA, dB, dC = to_dev(A.astype(NP[fm.E4M3])), to_dev(B.astype(NP[fm.E5M2])), to_dev(C.astype(np.uint32))
+    st = [torch.empty(len(hs) * mm.STATS_BYTES, dtype=torch.uint8, device="cuda") for _ in range(5)]
+    for s in st:
+        for i in range(len(hs)):
+            mm.stats_reset(s[i * mm.STATS_BYTES:])
+    torch.cuda.synchronize()
+
+    def work(i):
+        stream = torch.cuda.Stream()
+        mm.emulate_compare_many(hs, dA, dB, dC, None, None, 16, 16, 16, 400, (fm.E4M3, fm.E5M2, fm.FP32, fm.FP32), st[i], stream=stream)
+        stream.synchronize()
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    work(4)
+    got = [mm.read_stats_array(s, len(hs)) for s in st]
+    for h in hs:
+        mm.model_destroy(h)
+    assert all(g == got[4] for g in got) and got[4] == [ostats.compare(w, oracle_outputs(plist[:1], A, B, C, fm.E4M3, fm.E5M2)[0])
+                                                         for w in oracle_outputs(plist, A, B, C, fm.E4M3, fm.E5M2)]
