@@ -277,14 +277,19 @@ __device__ __forceinline__ void normal_pair(uint32_t r_even, uint32_t r_odd, dou
     z_odd = radius * sinphi;
 }
 
+__device__ __forceinline__ void uniform_values(const uint32_t w[4], double z[4])
+{
+#pragma unroll
+    for (int j = 0; j < 4; ++j) z[j] = ((double)w[j] + 0.5) * (1.0 / 2147483648.0) - 1.0;      // exact
+}
+
 // the four binary64 values of one Philox block, by family
 __device__ __forceinline__ void block_normals(const GenArgs &g, uint64_t blk, double z[4])
 {
     uint32_t w[4];
     block_words(g, blk, w);
     if (g.family == MMAEMU_GEN_UNIFORM) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) z[j] = ((double)w[j] + 0.5) * (1.0 / 2147483648.0) - 1.0;      // exact
+        uniform_values(w, z);
         return;
     }
     normal_pair(w[0], w[1], z[0], z[1]);
@@ -393,6 +398,18 @@ __device__ __forceinline__ double block_absmax(const double z[4], uint64_t blk, 
     return mx;
 }
 
+// Inside a loop over blocks.  UNIFORM's arithmetic is too short to hide the round keys' loads behind, and leaves them their registers:
+// they stay outside (per-tile scaled, 2^10 tiles of 4096: FP32 16.7 us with the loads inside, 15.1 so; E2M3 18.6, 16.3; one tile of 2^24
+// elements, which a single workgroup makes: FP32 13.2 ms, 9.8).
+template <bool UNIFORM> __device__ __forceinline__ void block_values(const GenArgs &g, uint64_t blk, double z[4])
+{
+    if constexpr (UNIFORM) {
+        uint32_t w[4];
+        block_words(g, blk, w);
+        uniform_values(w, z);
+    } else block_normals(fetch_gen_args(), blk, z);
+}
+
 // no scaling, or scaling by a maximum already sitting in *absmax (SCALE_TENSOR, second step)
 template <typename T>
 __global__ void __launch_bounds__(256)
@@ -410,6 +427,7 @@ gen_normal_kernel(GenArgs g, T *out, uint64_t g0, uint64_t total, uint64_t blk0,
 
 // SCALE_TENSOR, first step: max |z| over the call's elements into *absmax (zeroed before).
 // Non-negative doubles order like their bit patterns, so an integer atomic max serves.
+template <bool UNIFORM>
 __global__ void __launch_bounds__(256)
 gen_absmax_kernel(GenArgs g, uint64_t g0, uint64_t total, uint64_t blk0, uint64_t nblk, unsigned long long *absmax)
 {
@@ -420,7 +438,7 @@ gen_absmax_kernel(GenArgs g, uint64_t g0, uint64_t total, uint64_t blk0, uint64_
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
     for (uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; t < nblk; t += stride) {
         double z[4];
-        block_normals(fetch_gen_args(), blk0 + t, z);
+        block_values<UNIFORM>(g, blk0 + t, z);
         const double a = block_absmax(z, blk0 + t, g0, g0 + total);
         mx = a > mx ? a : mx;
     }
@@ -432,7 +450,7 @@ gen_absmax_kernel(GenArgs g, uint64_t g0, uint64_t total, uint64_t blk0, uint64_
 __global__ void zero_u64_kernel(unsigned long long *p) { *p = 0ull; }
 
 // SCALE_TILE: one workgroup per tile; max |z| over the tile, then scale and write.
-template <typename T>
+template <typename T, bool UNIFORM>
 __global__ void __launch_bounds__(256)
 gen_normal_tile_kernel(GenArgs g, T *out, uint64_t ept, uint64_t first_tile, uint64_t n_tiles)
 {
@@ -447,7 +465,7 @@ gen_normal_tile_kernel(GenArgs g, T *out, uint64_t ept, uint64_t first_tile, uin
         double mx = 0.0, zc[4] = {0.0, 0.0, 0.0, 0.0};
         uint64_t cached = ~0ull;
         for (uint64_t t = threadIdx.x; t < nblk; t += blockDim.x) {
-            block_normals(fetch_gen_args(), blk_lo + t, zc);
+            block_values<UNIFORM>(g, blk_lo + t, zc);
             cached = blk_lo + t;
             const double a = block_absmax(zc, cached, lo, hi);
             mx = a > mx ? a : mx;
@@ -458,7 +476,7 @@ gen_normal_tile_kernel(GenArgs g, T *out, uint64_t ept, uint64_t first_tile, uin
         for (uint64_t t = threadIdx.x; t < nblk; t += blockDim.x) {
             double z[4];
             if (blk_lo + t == cached) { z[0] = zc[0]; z[1] = zc[1]; z[2] = zc[2]; z[3] = zc[3]; }
-            else block_normals(fetch_gen_args(), blk_lo + t, z);
+            else block_values<UNIFORM>(g, blk_lo + t, z);
             // only this tile's elements: clip the writable range to [lo, hi)
             write_block<T>(g, out + (lo - g_call0), blk_lo + t, z, scale, true, lo, ept);
         }
@@ -467,7 +485,7 @@ gen_normal_tile_kernel(GenArgs g, T *out, uint64_t ept, uint64_t first_tile, uin
 
 // SCALE_TILE for tiles of at most 256 elements that start on a Philox block (elements per tile a multiple of 4): one
 // wavefront per tile, the maximum by lane shuffles, no LDS and no barrier.  Same values, same scale, same casts.
-template <typename T>
+template <typename T, bool UNIFORM>
 __global__ void __launch_bounds__(256)
 gen_normal_tile_wave_kernel(GenArgs g, T *out, uint64_t ept, uint64_t first_tile, uint64_t n_tiles)
 {
@@ -480,7 +498,7 @@ gen_normal_tile_wave_kernel(GenArgs g, T *out, uint64_t ept, uint64_t first_tile
         const uint64_t lo = (first_tile + tile) * ept, hi = lo + ept, blk_lo = lo >> 2;
         double z[4] = {0.0, 0.0, 0.0, 0.0}, mx = 0.0;
         if (lane < nblk) {
-            block_normals(fetch_gen_args(), blk_lo + lane, z);
+            block_values<UNIFORM>(g, blk_lo + lane, z);
             mx = block_absmax(z, blk_lo + lane, lo, hi);
         }
 #pragma unroll
@@ -517,20 +535,20 @@ static mmaemu_status launch_typed(const GenArgs &ga, void *out, uint64_t ept, ui
     } else if (ga.scale_scope == MMAEMU_SCALE_TENSOR) {
         hipLaunchKernelGGL(zero_u64_kernel, dim3(1), dim3(1), 0, s, (unsigned long long *)workspace);
         const uint64_t rgrid = grid > 2048 ? 2048 : grid;
-        hipLaunchKernelGGL(gen_absmax_kernel, dim3((uint32_t)rgrid), dim3(256), 0, s, ga, g0, total, blk0, nblk,
-                           (unsigned long long *)workspace);
+        if (ga.family == MMAEMU_GEN_UNIFORM) hipLaunchKernelGGL(gen_absmax_kernel<true>, dim3((uint32_t)rgrid), dim3(256), 0, s, ga, g0, total, blk0, nblk, (unsigned long long *)workspace);
+        else hipLaunchKernelGGL(gen_absmax_kernel<false>, dim3((uint32_t)rgrid), dim3(256), 0, s, ga, g0, total, blk0, nblk, (unsigned long long *)workspace);
         hipLaunchKernelGGL((gen_normal_kernel<T>), dim3((uint32_t)grid), dim3(256), 0, s, ga, (T *)out, g0, total, blk0, nblk,
                            (const double *)workspace);
     } else if (ept % 4 == 0 && ept <= 256) {
         const uint64_t wgrid = (n_tiles + 3) / 4 > (1ull << 20) ? (1ull << 20) : (n_tiles + 3) / 4;
-        hipLaunchKernelGGL((gen_normal_tile_wave_kernel<T>), dim3((uint32_t)wgrid), dim3(256), 0, s, ga, (T *)out, ept, first_tile,
-                           n_tiles);
+        if (ga.family == MMAEMU_GEN_UNIFORM) hipLaunchKernelGGL((gen_normal_tile_wave_kernel<T, true>), dim3((uint32_t)wgrid), dim3(256), 0, s, ga, (T *)out, ept, first_tile, n_tiles);
+        else hipLaunchKernelGGL((gen_normal_tile_wave_kernel<T, false>), dim3((uint32_t)wgrid), dim3(256), 0, s, ga, (T *)out, ept, first_tile, n_tiles);
     } else {
         const uint64_t per_tile_blocks = (ept + 3) / 4 + 1;
         uint32_t threads = per_tile_blocks <= 64 ? 64 : per_tile_blocks <= 128 ? 128 : 256;
         const uint64_t tgrid = n_tiles > (1ull << 20) ? (1ull << 20) : n_tiles;
-        hipLaunchKernelGGL((gen_normal_tile_kernel<T>), dim3((uint32_t)tgrid), dim3(threads), 0, s, ga, (T *)out, ept,
-                           first_tile, n_tiles);
+        if (ga.family == MMAEMU_GEN_UNIFORM) hipLaunchKernelGGL((gen_normal_tile_kernel<T, true>), dim3((uint32_t)tgrid), dim3(threads), 0, s, ga, (T *)out, ept, first_tile, n_tiles);
+        else hipLaunchKernelGGL((gen_normal_tile_kernel<T, false>), dim3((uint32_t)tgrid), dim3(threads), 0, s, ga, (T *)out, ept, first_tile, n_tiles);
     }
     MMAEMU_HIP(hipGetLastError());
     return MMAEMU_OK;

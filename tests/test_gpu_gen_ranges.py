@@ -35,13 +35,13 @@ def test_generator_ranges(mm, dtype):
 
 
 @pytest.mark.parametrize("dtype", FORMATS + [fm.E2M3])
-def test_scaled_normals(mm, dtype):
+def test_scaled_values(mm, dtype):
     # per-tile scaling on tiles of one wavefront, of a workgroup (one block per thread and several) and unaligned ones; per tensor
     import torch
     torch_type = {1: torch.uint8, 2: torch.int16, 4: torch.int32}[mm.ELEM_BYTES[dtype]]
     for scope in (mm.SCALE_TILE, mm.SCALE_TENSOR):
         for (ept, first, tiles) in ((256, 3, 9), (252, 1, 5), (1024, 2, 3), (500, 1, 3), (4100, 1, 2), (7, 5, 11)):
-            for family in (mm.GEN_NORMAL, mm.GEN_NORMAL_OUTLIERS):
+            for family in (mm.GEN_NORMAL, mm.GEN_NORMAL_OUTLIERS, mm.GEN_UNIFORM):
                 out = torch.zeros(ept * tiles, dtype=torch_type, device="cuda")
                 kw = dict(family=family, scale_scope=scope, scale_target=100.0)
                 mm.generate(out, dtype, ept, first, tiles, seed=78, operand=1, workspace=torch.zeros(1, dtype=torch.int64, device="cuda"), **kw)
