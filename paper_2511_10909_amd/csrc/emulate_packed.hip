@@ -12,17 +12,21 @@
 //     same without the transposition at two instructions per eight terms: a 4096^3 pass with its exact dots took 4960 us, against 4270
 //     for the first kernel with the matrix sum.)
 //   * the maximum exponent comes from the matrix cores too.  An element is represented by 2^(8 (Exp - Exp_row)), Exp_row the largest
-//     exponent of its row in the staged chunk; the dot product of two such rows lies in [2^(8 x), 32 * 2^(8 x)) with x the
+//     exponent of its row in the group; the dot product of two such rows lies in [2^(8 x), 32 * 2^(8 x)) with x the
 //     group's maximum relative to the two rows', so x is the result's exponent field divided by 8: one shift.
-// Rows are scaled by 2^(T - Exp_row) when they are converted, so that data of any size uses binary16's range: the products'
-// maximum may lie up to 15 places (the matrix result's range) below the rows' and the accumulator up to 9 places above them.
-// A wavefront whose accumulators lie further up, or that holds a NaN or an infinity, scales in two steps; one whose products lie
-// further down takes `packed_slow`.
+// Rows are scaled by 2^(T - Exp_row), group by group, when they are converted, so that data of any size uses binary16's range.  The
+// matrix result and the scale hold maxima down to x = -15, and none lies lower: one of the operands is E4M3, whose exponents
+// (zeros and subnormals included) span 14 places, so the product at the other row's largest element has x >= -14.  The accumulator may
+// lie up to 9 places above the rows' product; a wavefront whose accumulators lie further up, or that holds a NaN or an infinity,
+// scales in two steps.
 //
-// Measured (MI355X), E4M3 x E5M2, L = 32, F = 14, N(0,1) data, the tiled kernel before and this one: 4096^3 9.25 -> 4.18 ms
-// (16.4 T terms/s; 2.1 vector instructions per term at 0.87 of the nominal rate, most of them of the packed kind that issues at that
-// rate and no faster), 2048^3 1.22 -> 0.57 ms, 1024^3 208 -> 128 us, 100 x 77 x 320 35 -> 25 us.  All bit patterns (a NaN or an
-// infinity in every wavefront) 2048^3 2.21 -> 1.08 ms, accumulators of 10^6 1.22 -> 1.04 ms.
+// Measured (MI355X), F = 14, N(0,1) data, the tiled kernel and this one: groups of 32, E4M3 x E5M2, 4096^3 9.13 -> 4.03 ms (17.0 T
+// terms/s; 2.1 vector instructions per term at 0.9 of the nominal rate, most of them of the packed kind that issues at 0.95 of it),
+// 2048^3 1.21 -> 0.53 ms, 1024^3 172 -> 91 us, 100 x 77 x 320 27 -> 15.5 us; all bit patterns (a NaN or an infinity in every
+// wavefront) 2048^3 2.21 -> 1.06 ms, accumulators of 10^6 1.21 -> 1.03 ms.  Groups of 16, E4M3 x E4M3, 4096^3 9.96 -> 5.25 ms;
+// 2048^3 with one large element per row and 32 k 1.32 -> 1.29 ms (4.52 while a row had one scale for both its groups and groups far
+// below it went to a routine of their own; without that routine the kernels need no scratch memory: groups of 32 4.17 -> 4.03 ms,
+// groups of 16 6.43 -> 5.25).
 // 64 x 64 blocks of eight wavefronts hold two blocks of 16 columns each: with four (and half the wavefronts) the loop was 8 % faster,
 // but its second form, which the last two of these take, sent 160 registers to scratch memory and ran at half the tiled kernel's speed.
 #include "emulate_tiled.hpp"
@@ -56,21 +60,6 @@ template <int T> struct Fp8 {
         if constexpr (T == MMAEMU_FP8_E4M3) return high ? __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(raw, scale, true) : __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(raw, scale, false);
         else return high ? __builtin_amdgcn_cvt_scalef32_pk_f16_bf8(raw, scale, true) : __builtin_amdgcn_cvt_scalef32_pk_f16_bf8(raw, scale, false);
     }
-    static __device__ __forceinline__ void values(uint32_t raw, float (&f)[4])
-    {
-        if constexpr (T == MMAEMU_FP8_E4M3) {
-            f[0] = __builtin_amdgcn_cvt_f32_fp8((int)raw, 0); f[1] = __builtin_amdgcn_cvt_f32_fp8((int)raw, 1);
-            f[2] = __builtin_amdgcn_cvt_f32_fp8((int)raw, 2); f[3] = __builtin_amdgcn_cvt_f32_fp8((int)raw, 3);
-        } else {
-            f[0] = __builtin_amdgcn_cvt_f32_bf8((int)raw, 0); f[1] = __builtin_amdgcn_cvt_f32_bf8((int)raw, 1);
-            f[2] = __builtin_amdgcn_cvt_f32_bf8((int)raw, 2); f[3] = __builtin_amdgcn_cvt_f32_bf8((int)raw, 3);
-        }
-    }
-    static __device__ __forceinline__ uint32_t exponents(uint32_t raw)                // max(E, 1) of four elements, a byte each
-    {
-        const uint32_t E = (raw >> MB) & (T == MMAEMU_FP8_E4M3 ? 0x0F0F0F0Fu : 0x1F1F1F1Fu);
-        return E + 0x01010101u - (((E + 0x7F7F7F7Fu) >> 7) & 0x01010101u);
-    }
 };
 
 __device__ __forceinline__ uint32_t as_u32(half2v x) { uint32_t r; __builtin_memcpy(&r, &x, 4); return r; }
@@ -101,83 +90,6 @@ __device__ __forceinline__ uint32_t packed_finish(const PackedArgs &pa, float V,
     return o;
 }
 
-// One group of a wavefront's block some of whose products' maxima lie below the window: exponents and values from the raw operands,
-// terms in binary32.  Out of line, so that its registers do not count against the loops.  A, B: the operands at the tile's first row
-// and the group's first k; i, j: the lane's row and first column of block 0 in them (i below m).
-struct PackedOperands { const uint8_t *A, *B; uint32_t i, j, n, k; };
-
-template <int TA, int TB, int NC, int L>
-__device__ __noinline__ BlockVals<NC * 4> packed_slow(PackedArgs pa, PackedOperands op, BlockVals<NC * 4> din)
-{
-    const uint32_t C1 = (uint32_t)(pa.F + 254) << 23;
-    uint32_t em[NC][4];
-    uint32_t o[NC][4];
-    const uint32_t ftz_in = pa.flags & FL_FTZ_IN;
-    const float min_a = ftz_in ? min_normal_of(TA) : 0.0f, min_b = ftz_in ? min_normal_of(TB) : 0.0f;
-    const uint8_t *pra = op.A + (uint64_t)op.i * op.k;
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-        const uint8_t *prb[4];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) { const uint32_t j = op.j + 16 * c + v; prb[v] = op.B + (uint64_t)(j < op.n ? j : op.n - 1) * op.k; }
-        uint32_t e[4] = {0, 0, 0, 0};
-#pragma unroll 1
-        for (int q = 0; q < L; q += 4) {
-            const uint32_t wa = Fp8<TA>::exponents(*reinterpret_cast<const uint32_t *>(pra + q));
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const uint32_t x = wa + Fp8<TB>::exponents(*reinterpret_cast<const uint32_t *>(prb[v] + q));
-                e[v] = pk_max_u16(e[v], pk_max_u16(x & 0x00FF00FFu, (x >> 8) & 0x00FF00FFu));
-            }
-        }
-#pragma unroll
-        for (int v = 0; v < 4; ++v)
-            em[c][v] = max((max(e[v] & 0xFFFFu, e[v] >> 16) + 127 - Fp8<TA>::BIAS - Fp8<TB>::BIAS) << 23, min(din.v[4 * c + v] & 0x7F800000u, 254u << 23));
-        float S[4] = {0.0f, 0.0f, 0.0f, 0.0f}, I[4] = {0.0f, 0.0f, 0.0f, 0.0f}, sc[4];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) sc[v] = __uint_as_float(C1 - em[c][v]);
-        auto sums = [&](auto flush_c) {
-            constexpr bool FLUSH = decltype(flush_c)::value;
-#pragma unroll 1
-            for (int q = 0; q < L; q += 4) {
-                float fa[4];
-                Fp8<TA>::values(*reinterpret_cast<const uint32_t *>(pra + q), fa);
-#pragma unroll
-                for (int w = 0; w < 4; ++w) if (FLUSH) fa[w] = __builtin_fabsf(fa[w]) < min_a ? 0.0f : fa[w];
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    float fb[4];
-                    Fp8<TB>::values(*reinterpret_cast<const uint32_t *>(prb[v] + q), fb);
-#pragma unroll
-                    for (int w = 0; w < 4; ++w) {
-                        if (FLUSH) fb[w] = __builtin_fabsf(fb[w]) < min_b ? 0.0f : fb[w];
-                        const float p = fa[w] * fb[w];
-                        I[v] += p;
-                        S[v] += __builtin_truncf(p * sc[v]);
-                    }
-                }
-            }
-        };
-        if (ftz_in) sums(std::true_type{}); else sums(std::false_type{});
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            // Sec. 4.2 through the IEEE sum of the group's products and its accumulator, which is a NaN or an infinity exactly
-            // where the group's result is (finite products are below 2^34)
-            const float dc = __uint_as_float(din.v[4 * c + v]);
-            const uint32_t x = __float_as_uint(I[v] + dc);
-            o[c][v] = packed_finish(pa, S[v] + __builtin_truncf(dc * sc[v]), em[c][v]);
-            if ((x & 0x7F800000u) == 0x7F800000u) o[c][v] = (x & 0x007FFFFFu) ? pa.nan_bits : x;
-        }
-    }
-    BlockVals<NC * 4> out;
-    out.settled = 0;
-#pragma unroll
-    for (int c = 0; c < NC; ++c)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) out.v[4 * c + v] = o[c][v];
-    return out;
-}
-
 // A workgroup of WR * WC wavefronts owns WR * 16 rows and WC * NC * 16 columns of one tile's D; a wavefront 16 rows and NC blocks of
 // 16 columns.  A lane multiplies four rows with one column of each block, and owns four neighbouring outputs of one row of each.
 // KC = 32 k are staged at a time.
@@ -191,8 +103,8 @@ emulate_packed_kernel(PackedArgs pa, const uint8_t *__restrict__ A, const uint8_
     constexpr int R = 4;
     __shared__ __attribute__((aligned(16))) uint16_t va[ROWS_A * STRIDE], vb[ROWS_B * STRIDE];      // scaled values, binary16
     __shared__ __attribute__((aligned(16))) uint16_t xa[ROWS_A * STRIDE], xb[ROWS_B * STRIDE];      // 2^(8 (Exp - Exp_row)), bfloat16
-    __shared__ __attribute__((aligned(16))) int32_t ea[ROWS_A];          // Exp_row 2^23
-    __shared__ __attribute__((aligned(16))) int32_t eb[ROWS_B];
+    __shared__ __attribute__((aligned(16))) int32_t ea[KC / L][ROWS_A];          // Exp_row 2^23 of every group
+    __shared__ __attribute__((aligned(16))) int32_t eb[KC / L][ROWS_B];
 
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
     const uint32_t wr = wave % WR, wc = wave / WR;
@@ -221,14 +133,14 @@ emulate_packed_kernel(PackedArgs pa, const uint8_t *__restrict__ A, const uint8_
         for (int i = 0; i < SB_; ++i) raw_b[i] = *reinterpret_cast<const uint2 *>(src_b[i] + k0);
     };
     const uint32_t ftz_in = pa.flags & FL_FTZ_IN;
-    auto stage = [&](auto type_c, const uint2 raw, uint32_t row, uint32_t part, uint16_t *lv, uint16_t *lx, int32_t *le, int t_shift, uint32_t one) {
+    auto stage = [&](auto type_c, const uint2 raw, uint32_t row, uint32_t part, uint16_t *lv, uint16_t *lx, auto &le, int t_shift, uint32_t one) {
         constexpr int T = decltype(type_c)::value;
         using P = Fp8<T>;
-        // the row's largest magnitude code (codes order like exponents)
+        // the largest magnitude code of the row in the group, L / 8 threads (codes order like exponents)
         const uint32_t mx0 = raw.x & 0x007F007Fu, mx1 = (raw.x >> 8) & 0x007F007Fu, mx2 = raw.y & 0x007F007Fu, mx3 = (raw.y >> 8) & 0x007F007Fu;
         uint32_t mx = pk_max_u16(pk_max_u16(mx0, mx1), pk_max_u16(mx2, mx3));
         mx = pk_max_u16(mx, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)mx, 0xB1, 0xF, 0xF, true));      // lanes 1, 0, 3, 2 of the quad
-        mx = pk_max_u16(mx, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)mx, 0x4E, 0xF, 0xF, true));      // lanes 2, 3, 0, 1
+        if constexpr (L == 32) mx = pk_max_u16(mx, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)mx, 0x4E, 0xF, 0xF, true));      // lanes 2, 3, 0, 1
         const uint32_t lo = mx & 0xFFFFu, hi = mx >> 16, top = lo > hi ? lo : hi;
         const uint32_t E = top >> P::MB ? top >> P::MB : 1u;                                                // Exp_row + bias
         // exponent codes: max(E, 1) at bit 10 of every half, relative to the row's
@@ -280,7 +192,7 @@ emulate_packed_kernel(PackedArgs pa, const uint8_t *__restrict__ A, const uint8_
         v.z = as_u32(P::pair(r.y, sc, false)); v.w = as_u32(P::pair(r.y, sc, true));
         *reinterpret_cast<uint4 *>(lv + row * STRIDE + 8 * part) = v;
         *reinterpret_cast<uint4 *>(lx + row * STRIDE + 8 * part) = make_uint4(x[0], x[1], x[2], x[3]);
-        if (part == 0) le[row] = ((int)E - P::BIAS) * (1 << 23);
+        if (part % (L / 8) == 0) le[part / (L / 8)][row] = ((int)E - P::BIAS) * (1 << 23);
     };
 
     // outputs: row c16 of the wavefront's sixteen, columns 4 g4 .. 4 g4 + 3 of each block
@@ -338,11 +250,11 @@ emulate_packed_kernel(PackedArgs pa, const uint8_t *__restrict__ A, const uint8_
             const uint16_t *const xa_w = xa + 16 * wr * STRIDE + g * L, *const xb_w = xb + wc * NC * 16 * STRIDE + g * L;
             packed_maxima<NC, L>(xa_w, xb_w, g4, c16, mx);
             // (result layout: this lane's outputs)
-            const int ka_o = ea[16 * wr + c16] + (111 << 23);
-            uint32_t em[NC][4], least = ~0u, most = 0, reach = 0;
+            const int ka_o = ea[g][16 * wr + c16] + (111 << 23);
+            uint32_t em[NC][4], most = 0, reach = 0;
 #pragma unroll
             for (int c = 0; c < NC; ++c) {
-                const int4 kb = *reinterpret_cast<const int4 *>(eb + (wc * NC + c) * 16 + 4 * g4);
+                const int4 kb = *reinterpret_cast<const int4 *>(eb[g] + (wc * NC + c) * 16 + 4 * g4);
                 const int kv[4] = {kb.x, kb.y, kb.z, kb.w};
 #pragma unroll
                 for (int v = 0; v < 4; v += 2) {
@@ -354,21 +266,9 @@ emulate_packed_kernel(PackedArgs pa, const uint8_t *__restrict__ A, const uint8_
                         em[c][v + h] = ep > ec ? ep : ec;
                         x[h] = em[c][v + h] - kab;
                     }
-                    least = min(min(w[0], w[1]), least);             // (three operands in one instruction)
-                    most = max(max(w[0], w[1]), most);
+                    most = max(max(w[0], w[1]), most);               // (three operands in one instruction)
                     reach = max(max(x[0], x[1]), reach);
                 }
-            }
-            if (__builtin_expect(__any(least < (1u << 26)), 0)) {
-                BlockVals<NC * 4> in;
-                in.settled = 0;
-#pragma unroll
-                for (int x = 0; x < NC * 4; ++x) in.v[x] = d[x / 4][x % 4];
-                const PackedOperands op = {A + tile * m * (uint64_t)k + k0 + g * L, B + tile * n * (uint64_t)k + k0 + g * L, oi < m ? oi : m - 1, out_col(0), n, k};
-                const BlockVals<NC * 4> out = packed_slow<TA, TB, NC, L>(pa, op, in);
-#pragma unroll
-                for (int x = 0; x < NC * 4; ++x) d[x / 4][x % 4] = out.v[x];
-                continue;
             }
             // slow: some accumulator lies more places above its rows' product than one power of two of binary16 can scale by (the
             // scale is then applied in two factors), or the group is a special one (a NaN or an infinity; of an accumulator, whose
@@ -384,7 +284,7 @@ emulate_packed_kernel(PackedArgs pa, const uint8_t *__restrict__ A, const uint8_
             // the accumulator aligned and cut like a term, in units of 2^24: the sums start from it
             float4v S[NC];
             uint32_t sc[R][NC];
-            const int4 ka = *reinterpret_cast<const int4 *>(ea + 16 * wr + 4 * g4);
+            const int4 ka = *reinterpret_cast<const int4 *>(ea[g] + 16 * wr + 4 * g4);
             const int kr[R] = {ka.x, ka.y, ka.z, ka.w};
 #pragma unroll
             for (int c = 0; c < NC; ++c) {
@@ -393,7 +293,7 @@ emulate_packed_kernel(PackedArgs pa, const uint8_t *__restrict__ A, const uint8_
                 // the maxima once more in the layout of the products (rows 4 g4 + r, column c16): the matrix 2^(e_max) times the identity
                 const uint2 packed = make_uint2(__builtin_amdgcn_perm(em[c][1], em[c][0], 0x07060302u), __builtin_amdgcn_perm(em[c][3], em[c][2], 0x07060302u));
                 const float4v t = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(short4v, packed), unit, zero, 0, 0, 0);
-                const uint32_t kb = (uint32_t)eb[(wc * NC + c) * 16 + c16] + (uint32_t)pa.c2;
+                const uint32_t kb = (uint32_t)eb[g][(wc * NC + c) * 16 + c16] + (uint32_t)pa.c2;
                 if (__builtin_expect(slow, 0)) {
 #pragma unroll
                     for (int r = 0; r < R; ++r) {
@@ -533,11 +433,11 @@ static mmaemu_status launch_packed_cfg(const PackedArgs &pa, const void *A, cons
 }
 
 // The side of the blocks that a problem is cut into, 64 or 32; 0 where neither grid has fewer than the 2^32 threads of one launch.
-// A 64 x 64 block costs 0.5 to 0.6 (groups of 32) or 0.7 to 0.8 (groups of 16) of what the tiled kernels take for as many outputs, a
-// 32 x 32 block 0.6 to 0.7 -- but both for the padding of edge blocks too, and 64 x 64 blocks need 2^21 outputs to keep all CUs
-// busy.  So they are taken from there on where they pad at most a seventh more than 32 x 32 blocks do.  Groups of 32 on N(0,1)
-// data, tiled kernel, 64 x 64, 32 x 32: 2^14 tiles of 32x32x64 157, 297, 101 us; 2^13 of 17x17x32 53, 98, 34; 512 of 65x65x64 51,
-// 45, 31; 2^12 of 64x64x64 171, 89, 98; 2^12 of 33x33x32 98, 49, 60.
+// A 64 x 64 block costs 0.47 (groups of 32) or 0.55 (groups of 16) of what the tiled kernels take for as many outputs, a 32 x 32 block
+// 0.55 to 0.65 -- but both for the padding of edge blocks too, and 64 x 64 blocks need 2^21 outputs to keep all CUs busy.  So they
+// are taken from there on where they pad at most a seventh more than 32 x 32 blocks do.  Groups of 32 on N(0,1) data, tiled
+// kernel, 64 x 64, 32 x 32: 2^14 tiles of 32x32x64 162, 296, 100 us; 2^13 of 17x17x32 47, 85, 29; 512 of 65x65x64 50, 41, 29; 2^12 of
+// 64x64x64 170, 80, 94; 2^12 of 33x33x32 98, 45, 58.  Groups of 16: 2^10 of 48x48x64 33 (in 16 x 16 blocks, which pad nothing), 27, 31.
 static uint32_t packed_side(uint32_t m, uint32_t n, uint64_t batch)
 {
     auto blocks = [&](uint64_t side) { return batch * ((m + side - 1) / side) * ((n + side - 1) / side); };
@@ -562,15 +462,9 @@ bool packed_takes(const ModelArgs &p, uint32_t ta, uint32_t tb, uint32_t m, uint
     if (p.c_mode != MMAEMU_C_IN_GROUP || p.skip_zero_terms || p.zero_result_positive || (p.flags & (FL_ACC16 | FL_NAN_PROPAGATE))) return false;
     // (two E5M2 rows span 64 places together, more than binary16 can scale: the tiled kernels)
     if (ta > MMAEMU_FP8_E5M2 || tb > MMAEMU_FP8_E5M2 || (ta == MMAEMU_FP8_E5M2 && tb == MMAEMU_FP8_E5M2)) return false;
-    // (groups of 16 with an E5M2 operand: bit patterns of the whole format leave the window in most wavefronts, 2.5 -> 3.5 ms on 2048^3;
-    // groups of 32 do not)
+    // (groups of 16: built for two E4M3 operands)
     if (!(p.L == 32 || (p.L == 16 && ta == tb)) || k % 32 != 0 || m <= 16 || n <= 16) return false;
-    const uint32_t side = packed_side(m, n, batch);
-    if (side == 0) return false;
-    // (groups of 16, m and n multiples of 16: 16 x 16 blocks of the tiled kernels pad nothing, and 64 x 64 ones that pad more than two
-    // thirds are no faster: 2^10 tiles of 48x48x64 35 us there, 38 here; of 48x112x64, 512 of them, 40 and 38)
-    const uint64_t padded = ((m + 63ull) & ~63ull) * ((n + 63ull) & ~63ull);
-    if (p.L == 16 && side == 64 && m % 16 == 0 && n % 16 == 0 && 3 * padded > 5ull * m * n) return false;
+    if (packed_side(m, n, batch) == 0) return false;
     // every sum an integer below 2^24; below F = 10 a row of E4M3 beside one of E5M2 (T = F - 17) would lose its smallest bits
     return p.F >= 10 && ((uint64_t)(p.L + 1) << (p.F + 2)) <= (1ull << 24);
 }

@@ -1,6 +1,6 @@
 """GPU parity of the packed-binary16 kernel (T-FDPA on FP8 operands, F up to 17) against the CPU oracle, bit for bit: widths at both
-ends of its range, both group lengths, block edges, and the data that leave its window (accumulators far above the products, rows
-whose large elements never meet, NaN and infinities), which take its second route."""
+ends of its range, both group lengths, block edges, the data that reach the ends of its window (rows whose large elements never
+meet) and those that leave it (accumulators far above the products, NaN and infinities), which take its second route."""
 import numpy as np
 import pytest
 
@@ -72,8 +72,40 @@ def test_packed_kernel_keeps_to_its_range(mm):
         assert_same(got, want, "%s" % ((m, n, k, L, F),))
 
 
+def one_large(rng, nb, m, n, k, ta, tb):
+    """One element near the format's top per row and 32 k, the others (zeros and subnormals among them) as far below it as the format
+    goes: groups of 16 without it, and groups whose two large elements do not meet, 14 places and more below the rows' products."""
+    def rows(count, t):
+        x = synth.narrow_exponent_bits(rng, (nb, count, k), t, 0, 1)
+        place = rng.integers(0, 32, (nb, count, k // 32)) + 32 * np.arange(k // 32)
+        np.put_along_axis(x, place, np.uint32({fm.E4M3: 0x76, fm.E5M2: 0x7B}[t]) | (rng.integers(0, 2, place.shape) << 7).astype(np.uint32), axis=2)
+        return x
+    return rows(m, ta), rows(n, tb), synth.narrow_exponent_bits(rng, (nb, m, n), fm.FP32, 90, 130)
+
+
+@pytest.mark.parametrize("ta,tb", PAIRS)
+def test_packed_kernel_where_large_elements_do_not_meet(mm, ta, tb):
+    """With NaN and infinities in a few rows, columns and accumulators of the same wavefronts, and without."""
+    rng = np.random.default_rng(9600 + 8 * ta + tb)
+    for (rows, nb, m, n, k) in ((spread_rows, 4, 64, 48, 64), (one_large, 4, 64, 48, 64), (one_large, 1, 1500, 1412, 32)):
+        for frac in (0.0, 0.0005, 0.05):
+            for L in ((16, 32) if ta == tb else (32,)):
+                A, B, C = rows(rng, nb, m, n, k, ta, tb)
+                A = synth.sprinkle(rng, A, synth.SPECIAL_CODES[ta], frac)
+                B = synth.sprinkle(rng, B, synth.SPECIAL_CODES[tb], frac)
+                C = synth.sprinkle(rng, C, synth.SPECIAL_CODES[fm.FP32], frac)
+                for F in (10, 16):
+                    p = ModelParams(group_len=L, frac_bits=F, c_mode=C_IN_GROUP, out_round=RZ, out_mant_bits=13, ftz_in=frac == 0.0005, nan_bits=0x7FFFFFFF)
+                    print("packed apart", rows.__name__, ta, tb, L, frac, p, flush=True)
+                    want, _ = o2lib.emulate_mma(p, A, B, C, ta, tb)
+                    got = gpu_emulate(mm, p, A, B, C, ta, tb)
+                    assert "packed fp16 L=%d" % L in gpu_emulate.last_kernel, gpu_emulate.last_kernel
+                    assert_same(got, want, "packed apart %s %s %s" % (rows.__name__, frac, p))
+
+
 # (m, n, k, tiles, side of the blocks): batches of at least 2^21 outputs, tiles below, at and above the sizes where 64 x 64 blocks pad too much
-BATCHES = [(32, 32, 64, 2048, 32), (17, 33, 32, 3800, 32), (65, 40, 32, 808, 32), (64, 160, 32, 206, 32), (64, 224, 32, 147, 64), (33, 47, 32, 1408, 64)]
+BATCHES = [(32, 32, 64, 2048, 32), (17, 33, 32, 3800, 32), (65, 40, 32, 808, 32), (64, 160, 32, 206, 32), (64, 224, 32, 147, 64), (33, 47, 32, 1408, 64),
+           (48, 48, 32, 911, 64), (48, 48, 32, 910, 32)]
 
 
 @pytest.mark.parametrize("m,n,k,nb,side", BATCHES)
@@ -87,16 +119,3 @@ def test_packed_kernel_on_batches_of_small_tiles(mm, m, n, k, nb, side):
         got = gpu_emulate(mm, p, A, B, C, ta, tb)
         assert_same(got, want, "packed batch %s %s" % ((m, n, k, nb), p))
         assert gpu_emulate.last_kernel == "tiled %dx%d packed fp16 L=%d" % (side, side, L), gpu_emulate.last_kernel
-
-
-def test_padded_batches_of_short_groups_keep_unpadded_blocks(mm):
-    # 64 x 64 blocks would compute 16 / 9 of the outputs; tiles of 48 x 112, padded to 1.5 times their size, take them; fewer tiles of 48 x 48 take 32 x 32 blocks
-    rng = np.random.default_rng(9400)
-    for (m, n, nb, name) in ((48, 48, 911, "tiled 16x16 r2x2"), (48, 112, 391, "tiled 64x64 packed"), (48, 48, 910, "tiled 32x32 packed")):
-        A, B, C = operands(rng, fm.E4M3, fm.E4M3, nb, m, n, 32, "special")
-        p = ModelParams(group_len=16, frac_bits=14, c_mode=C_IN_GROUP)
-        print("packed or not", (m, n, nb), flush=True)
-        want, _ = o2lib.emulate_mma(p, A, B, C, fm.E4M3, fm.E4M3)
-        got = gpu_emulate(mm, p, A, B, C, fm.E4M3, fm.E4M3)
-        assert_same(got, want, "%s" % ((m, n, nb),))
-        assert gpu_emulate.last_kernel.startswith(name), gpu_emulate.last_kernel

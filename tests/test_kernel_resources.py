@@ -45,3 +45,20 @@ def test_scan_kernels_keep_their_products_in_registers():
     assert len(blocks) == 10, "kernels not found in the resource remarks"
     for b in blocks:
         assert int(re.search(r"VGPRs Spill:\s*(\d+)", b).group(1)) == 0, b
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs hipcc")
+def test_packed_kernels_need_no_scratch_memory():
+    """The packed FP8 kernels run at four waves per SIMD with all their values in registers (with a routine of its own for groups far
+    below their rows' products they once kept up to 36 registers, and that routine's results, in scratch memory)."""
+    cmd = ["hipcc", "-c", os.path.join(CSRC, "emulate_packed.hip"), "-o", os.devnull, "--offload-arch=gfx950", "--cuda-device-only", "-O3", "-fPIC",
+           "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+           "-Rpass-analysis=kernel-resource-usage"]
+    out = subprocess.run(cmd, capture_output=True, text=True, timeout=900)
+    assert out.returncode == 0, out.stderr[-2000:]
+    blocks = [b for b in out.stderr.split("Function Name:")[1:] if "emulate_packed_kernel" in b.split("\n")[0]]
+    # three pairs of types and, of equal types, two group lengths; two block sizes
+    assert len(blocks) == 8, "kernels not found in the resource remarks"
+    for b in blocks:
+        get = lambda key: int(re.search(key + r":\s*(\d+)", b).group(1))
+        assert get("VGPRs Spill") == 0 and get(r"ScratchSize \[bytes/lane\]") == 0 and get(r"Occupancy \[waves/SIMD\]") >= 4, b
