@@ -472,6 +472,7 @@ bool packed_takes(const ModelArgs &p, uint32_t ta, uint32_t tb, uint32_t m, uint
 mmaemu_status launch_emulate_packed(const ModelArgs &p, const void *A, const void *B, const void *Cm, void *D, uint32_t m, uint32_t n,
                                     uint32_t k, uint64_t batch, uint32_t ta, uint32_t tb, hipStream_t s)
 {
+    if (ta == MMAEMU_FP8_E5M2 && tb == MMAEMU_FP8_E5M2) { set_error("emulate_mma: the packed kernel takes no two E5M2 operands"); return MMAEMU_ERR_UNSUPPORTED; }
     PackedArgs pa = {};
     pa.F = p.F;
     pa.flags = p.flags;
