@@ -1127,11 +1127,10 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
                             auto sum = [&](int r, int c) -> double { return KIND == 0 ? (double)S32[r][c] : Sd[r][c] + (double)S32[r][c]; };
                             if (__builtin_expect((fl & FL_SUM_EXACT) != 0u, 0)) {
                                 const double T[4] = {sum(0, 0), sum(0, 1), sum(1, 0), sum(1, 1)};
-                                const bool hv[4] = {true, true, true, true};
                                 const int em[4] = {emax[0][0], emax[0][1], emax[1][0], emax[1][1]};
                                 const uint32_t cb[4] = {d[0][0], d[0][1], d[1][0], d[1][1]};
                                 double v[4];
-                                low = rd_exact_all<false>(T, hv, em, F, cb, hot.F2, hot.Fc, hot.drop, fl, v);
+                                low = rd_exact_all<false>(T, em, F, cb, hot.F2, hot.Fc, hot.drop, fl, v);
                                 vrd[0][0] = v[0]; vrd[0][1] = v[1]; vrd[1][0] = v[2]; vrd[1][1] = v[3];
                             } else {
 #pragma unroll
@@ -1221,11 +1220,10 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
                 }
                 if (__builtin_expect((fl & FL_SUM_EXACT) != 0u, 0)) {
                     const double T4[4] = {T[0][0], T[0][1], T[1][0], T[1][1]};
-                    const bool h4[4] = {true, true, true, true};
                     const int e4[4] = {em[0][0], em[0][1], em[1][0], em[1][1]};
                     const uint32_t c4[4] = {d[0][0], d[0][1], d[1][0], d[1][1]};
                     double v[4];
-                    low = rd_exact_all<false>(T4, h4, e4, hot.Fm, c4, hot.F2, hot.Fc, hot.drop, fl, v);
+                    low = rd_exact_all<false>(T4, e4, hot.Fm, c4, hot.F2, hot.Fc, hot.drop, fl, v);
                     vrd[0][0] = v[0]; vrd[0][1] = v[1]; vrd[1][0] = v[2]; vrd[1][1] = v[3];
                 } else {
 #pragma unroll

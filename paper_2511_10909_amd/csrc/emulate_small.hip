@@ -121,7 +121,7 @@ emulate_small_kernel(SmallArgs sm, const uint8_t *__restrict__ A, const uint8_t 
                 double vw[G];
                 bool low = RD;                                        // some result may be a zero of negative sign
                 if constexpr (RD) {
-                    if (fl & FL_SUM_EXACT) low = rd_exact_all<false>(Tw, hw, ew, F, cw, p.F2, p.Fc, p.sum_drop_distance, fl, vw);
+                    if (fl & FL_SUM_EXACT) low = rd_exact_all<false>(Tw, ew, F, cw, p.F2, p.Fc, p.sum_drop_distance, fl, vw);
                     else {
 #pragma unroll
                         for (int w = 0; w < G; ++w) vw[w] = rd_general(Tw[w], hw[w], ew[w], F, cw[w], p.F2, p.Fc, p.sum_drop_distance, fl);

@@ -347,13 +347,13 @@ __device__ __forceinline__ uint32_t wave_reduce_to_lane63(uint32_t v)
 // 2^(E - Fc), scaled back, and rounded down on its bit pattern: with the sign-magnitude pattern that is clearing the places below F2
 // (all of them in its low word: F2 is 23 at least), after adding them all where the number is negative.
 // The outputs run side by side and what is rare is asked once for all of them: results below 2^-126, where the places are counted
-// from 2^-126.  (One output after the other, each with its branch, sixteen sets of this kind on 2^15 tiles of 16x16x16 FP16 took
-// 786 us; 638 so.)  Returns whether some result of the wavefront may be below 2^-126 (none other makes a zero of negative sign).
+// from 2^-126.  (One output after the other, each with its branch, a pass of candidate sets -- generators, native instruction and a
+// scan launch of sixteen sets of this kind, on 2^15 tiles of 16x16x16 FP16 -- took 786 us; 638 so, of which the launch is 552.)  Returns whether some result of the wavefront may be below 2^-126 (none other makes a zero of negative sign).
 // A group no product of which took part (zero terms kept out) has an exponent maximum more than 100 places below any
-// accumulator's and drops out by it; block scales may lift that maximum: HAVE passes have[] for them.
+// accumulator's and drops out by it; block scales may lift that maximum: HAVE reads have[] for them.
 template <bool HAVE, int N>
-__device__ __forceinline__ bool rd_exact_all(const double (&T)[N], const bool (&have)[N], const int (&em)[N], int F, const uint32_t (&cb)[N], int F2, int Fc,
-                                             int drop, uint32_t fl, double (&r)[N])
+__device__ __forceinline__ bool rd_exact_all(const double (&T)[N], const int (&em)[N], int F, const uint32_t (&cb)[N], int F2, int Fc,
+                                             int drop, uint32_t fl, double (&r)[N], const bool *have = nullptr)
 {
     const uint32_t below = (uint32_t)((1ull << (52 - F2)) - 1ull);
     uint32_t least = 0xFFFFFFFFu;
@@ -925,8 +925,8 @@ tiled_body(const TiledArgs &ta_, const void *__restrict__ A, const void *__restr
             to_slow = sca[r] == 0xFFu || scb[c] == 0xFFu || (IS_RD && !(fl & FL_WIDE_PRODUCTS) && em >= 126);
         }
         if (to_slow && !(e & SENTINEL_MASK)) {
-            // (without scales: a product may reach 2^128, which this mode counts as an infinity) leave the group
-            // to the integer routine
+            // (without scales: a product may reach 2^128, which this mode counts as an infinity) settled at the group's end like one
+            // with special values
             e |= 0x8000u;
             m2[r][c] = e;
         }
@@ -973,7 +973,7 @@ tiled_body(const TiledArgs &ta_, const void *__restrict__ A, const void *__restr
                 for (int r = 0; r < R; ++r)
 #pragma unroll
                     for (int c = 0; c < C; ++c) one(r, c, take);
-                rd_exact_all<SC>(T, have, em, FT, cb, p.F2, p.Fc, p.sum_drop_distance, fe, v);
+                rd_exact_all<SC>(T, em, FT, cb, p.F2, p.Fc, p.sum_drop_distance, fe, v, have);
                 i = 0;
                 auto give = [&](double, bool, int, int, uint32_t) -> double { return v[i++]; };
 #pragma unroll

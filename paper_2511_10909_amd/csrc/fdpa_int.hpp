@@ -431,15 +431,9 @@ __device__ uint32_t fdpa_group(const ModelArgs &p, const FTA &fa, const FTB &fb,
 }
 
 
-// run-time operand types: the tiled kernels' fall-back (a template per type pair there multiplied the code size)
+// run-time operand types: the tiled kernels' fall-back (a template per type pair there multiplied the code size), which block-scaled
+// groups never need
 // (parameters by value: a reference would force the caller to keep a copy of them in scratch memory)
-__device__ __noinline__ uint32_t fdpa_group_raw(ModelArgs p, uint32_t ta, uint32_t tb, const void *a, const void *b,
-                                                uint32_t L, uint32_t c, ScaleRef sr)
-{
-    return fdpa_group(p, dyn_fmt(ta), dyn_fmt(tb), a, b, L, c, sr);
-}
-
-// the same without block scales
 __device__ __noinline__ uint32_t fdpa_group_raw_unscaled(ModelArgs p, uint32_t ta, uint32_t tb, const void *a, const void *b,
                                                          uint32_t L, uint32_t c)
 {
