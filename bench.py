@@ -12,8 +12,10 @@ mmaemu_emulate_mma and one mmaemu_compare per set instead.
 Prints ONE JSON line.  `--gpus N` with N > 1 is refused: the library runs on one GPU.
 """
 import argparse
+import hashlib
 import json
 import os
+import re
 import sys
 import time
 
@@ -24,15 +26,31 @@ INT32_VALU_PEAK = 256 * 4 * 16 * 2.4e9      # lane-instructions / s: 256 CUs x 4
 ALGO_OPS_PER_TERM = 8                       # accounting floor of INT32 VALU instructions per MAC term
 # Counter figures of the emulation kernels, from rocprofv3 --pmc runs of this program (see the named files under profiles/):
 # vector-ALU lane-instructions per MAC term (SQ_INSTS_VALU x 64 / terms) and HBM bytes per launch (FETCH_SIZE + WRITE_SIZE,
-# scaled by a copy kernel of known size).  Keyed by the kernel's name, so one of another name reports null;
-# taken again whenever a kernel changes under its name.
+# scaled by a copy kernel of known size).  They hold for the sources of COUNTERS_SOURCES alone (comments and blanks aside): a kernel of
+# another name, or changed since, reports null.
 COUNTERS = {
     "multi x16 tiled 16x16 r2x2 kc=16 any L vm=0": {"valu_instr_per_term": 6.22, "traffic": 188224000, "chunk": 1 << 16},
     "multi x16 tiled 16x16 r2x2 kc=16 any L vm=1": {"valu_instr_per_term": 8.70, "traffic": 215934000, "chunk": 1 << 16},
     "multi x3 tiled 32x32 r2x2 kc=8 any L vm=0, twins share sums": {"valu_instr_per_term": 7.31, "traffic": 1345087000, "chunk": 1 << 18},
 }
+COUNTERS_SOURCES = "9a253e1f90d68828"
 COUNTERS_SOURCE = ("profiles/closed_loop_scan_trace_and_counters.md, profiles/subnormal_stress_trace_and_counters.md (rocprofv3 --pmc SQ_INSTS_VALU; "
                    "FETCH_SIZE, WRITE_SIZE scaled by a 64 MiB copy); traffic per launch")
+
+
+def scan_sources_digest(csrc=os.path.join(ROOT, "paper_2511_10909_amd", "csrc")):
+    """Of what the scan kernel is compiled from, without comments and blanks."""
+    digest = hashlib.sha256()
+    for name in ("emulate_scan.hip", "emulate_tiled.hpp", "fdpa_int.hpp", "common.hpp"):
+        with open(os.path.join(csrc, name)) as f:
+            digest.update(re.sub(r"//[^\n]*|\s+", "", f.read()).encode())
+    return digest.hexdigest()[:16]
+
+
+def counters_of(kernel, chunk):
+    """The counter figures of a kernel on launches of `chunk` tiles; {} where none were taken of it as it is now."""
+    ctr = COUNTERS.get(kernel, {})
+    return ctr if chunk == ctr.get("chunk") and scan_sources_digest() == COUNTERS_SOURCES else {}
 
 
 def parse():
@@ -105,8 +123,7 @@ def subnormal_stress(args, torch, mm, configs, fused):
         secs += r["seconds"]
     ms = sum(e0.elapsed_time(e1) for _, _, e0, e1 in timed)
     terms = sum(t for _, t, _, _ in timed)
-    ctr = COUNTERS.get(r["kernel"], {})
-    ctr = ctr if chunk == ctr.get("chunk") else {}                           # (the counters were taken on launches of that many tiles)
+    ctr = counters_of(r["kernel"], chunk)
     frac = ALGO_OPS_PER_TERM * terms / (ms * 1e-3) / INT32_VALU_PEAK
     return {
         "metric": "bit-exact emulated MAC terms/sec on 1 MI355X", "value": r["terms"] * args.steps / secs, "unit": "terms/s", "n_gpus": 1,
@@ -226,8 +243,7 @@ def main():
     tot_ms = sum(v["avg_ms"] * v["launches_timed"] for v in kernels.values())
     tot_terms = sum(v["terms_per_launch"] * v["launches_timed"] for v in kernels.values())
     achieved = ALGO_OPS_PER_TERM * dom["terms_per_launch"] / (dom["avg_ms"] * 1e-3)
-    ctr = COUNTERS.get(dom["kernel"], {})
-    ctr = ctr if chunk == ctr.get("chunk") else {}                           # (the counters were taken on launches of that many tiles)
+    ctr = counters_of(dom["kernel"], chunk)
     stats = {scan.kind: scan.read() for scan in scans}
     agreement = {kind: [1.0 - s["n_mismatch_bits"] / max(s["n_compared"], 1) for s in st] for kind, st in stats.items()}
     out = {
