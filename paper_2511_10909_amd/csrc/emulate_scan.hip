@@ -38,10 +38,11 @@
 //     ran at half the speed of ordinary data through the routes of the general loop);
 //   * the reference's ordered keys are formed once per pass, a histogram entry is counted by leading zeros, and the two
 //     reductions over the wavefront run only where they can change something.
-// Measured, one launch of the sixteen sets of the closed-loop scan on 2^16 tiles of 16x16x16, before and after: FP8 1108 ->
+// Measured (kernel times), one launch of the sixteen sets of the closed-loop scan on 2^16 tiles of 16x16x16, before and after: FP8 1108 ->
 // 670 us (6.22 instructions per term), BF16 bit patterns 1433 -> 1137 us (8.70), all FP16 bit patterns (a quarter of the
 // tiles) 571 -> 253 us; three sets on 2^18 tiles of 32x32x8 1953 -> 1354 us (7.31).  What is left is still issue: 0.84 to
-// 1.01 of the nominal rate.
+// 1.02 of the nominal rate, one instruction per SIMD in four cycles, which is no ceiling: independent v_mul_f32 and v_add_u32, half of a
+// term's instructions, issue at 1.4 to 1.6 of it, the others at 0.82 to 0.93.
 #include "emulate_tiled.hpp"
 #include <atomic>
 
@@ -1515,8 +1516,9 @@ static mmaemu_status launch_scan_cfg(const ScanArgs &sa, const void *A, const vo
     // 2^15 tiles: 105, 149, 261, 504 us with 1024, 2048, 4096, 8192 workgroups; where nothing differs 8192 cost no more than 1024).
     // What stands beside that is the launch's arithmetic, k x passes x (sets + 1) per workgroup, the last for staging and decoding; the
     // lines below are where a round more is the faster one with outputs that differ: launches of 1 to 16 sets on 2^12 to 2^18 tiles
-    // take 0.977 of the time that a fixed 2048 workgroups from 2^14 blocks on, one round below, take, and no more than 1.06 of it
-    // (few sets on agreeing outputs: FP16 16x16x16, two GTR-FDPA sets on 2^16 tiles 209 -> 222 us).  Sixteen T-FDPA sets on 2^16 tiles FP8 702,
+    // take 0.977 of the time that a fixed 2048 workgroups from 2^14 blocks on, one round below, take, and no more than 1.08 of it
+    // (few sets on outputs that mostly agree: two T-FDPA sets of equal sums on 2^16 tiles 16x16x16 E4M3 x E5M2 130 -> 141 us; two of
+    // different widths 180 -> 144).  Sixteen T-FDPA sets on 2^16 tiles FP8 702,
     // 673, 667, 700 us with one, two, four, eight rounds; BF16 1057, 992, 978, 992; sixteen TR-FDPA sets on 2^15 tiles FP16 514,
     // 481, 462, 461; four sets on 2^16 tiles FP8 249, 239, 321, 532.
     // (workgroups that a device holds at once, by device; threads that ask at the same time work out the same number)

@@ -10,7 +10,7 @@
 //
 // Bound: vector-ALU issue, about 130 instructions per output of one group of four (the general kernel's 64-bit integers,
 // 128-bit ones in the two round-downs, and its walk over the operands for every question took about 1000: gfx950's fitted
-// set on 2^18 tiles of 4x4x4 FP16 106 us there, 26 us here, 1.9 TB/s).  W = 4 (n a multiple of four) decodes the row of A once for four
+// set on 2^18 tiles of 4x4x4 FP16 106 us there, 23 us here, 2.2 TB/s).  W = 4 (n a multiple of four) decodes the row of A once for four
 // outputs and moves C and D as 128-bit words.
 #include "emulate_tiled.hpp"
 

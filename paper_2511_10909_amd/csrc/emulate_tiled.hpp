@@ -42,9 +42,8 @@
 // where each half of a group runs through passes 1 and 2 as a group of its own before the halves are merged, and
 // CM_RD_QUARTERS, where pass 1 runs over the four quarters first (their maxima and the largest of them), then pass 2
 // quarter by quarter, each sum rounded down into the merged sum as soon as it is complete.
-// NaN and infinities are tagged with an exponent sentinel; a group that meets one is
-// recomputed by the integer routine of the general kernel from the raw operands in
-// global memory.
+// NaN and infinities are tagged with an exponent sentinel; a group that meets one is settled from the staged values, or, where
+// groups span chunks, from the raw operands in global memory (what that leaves open by the integer routine of the general kernel).
 #pragma once
 #include "fdpa_int.hpp"
 

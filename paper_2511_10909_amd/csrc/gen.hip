@@ -122,8 +122,8 @@ template <> __device__ __forceinline__ void store4<uint32_t>(uint32_t *p, const 
 // Elements [g0, g0 + total) of the operand; thread t owns Philox block blk0 + t.  WHOLE: the range starts and ends with a block, so
 // that every block is written whole (out aligned to it), and no block's number leaves the 32-bit range it starts in (two of the
 // twenty products of Philox are then the same for all threads).
-// Bound: the vector ALU, Philox's twenty 64-bit products above all; 2^26 FP32 elements of two words 93 -> 72 us, FP16 65 -> 54 us, random E4M3 codes 56 -> 37 us
-// against a form that took the branch on the family, and 64-bit bounds, for every element.
+// Bound: the vector ALU, Philox's twenty 64-bit products above all; 2^26 elements of UNIFORM_EXP FP32 (two words each) 87 -> 71 us, FP16 56 -> 49, random
+// E4M3 codes 51 -> 28 against a form that took the branch on the family, and 64-bit bounds, for every element.
 template <typename T, bool WHOLE>
 __global__ void __launch_bounds__(256)
 gen_bits_kernel(GenArgs g, T *out, uint64_t g0, uint64_t total, uint64_t blk0, uint64_t nblk)
@@ -184,9 +184,9 @@ __global__ void zero_kernel(uint32_t *out, uint64_t nwords, uint8_t *tail, uint3
 // ---- NORMAL family --------------------------------------------------------------------
 // binary64 elementary functions from +, *, / only, in a fixed order (quotient and square root are IEEE-754's own operations)
 
-// IEEE-754's quotient and square root where no scaling and no special case can arise: two Newton steps on the hardware's reciprocal
-// (reciprocal square root), a quotient (root) from it, and one correction by the exact remainder, which rounds correctly
-// (Markstein).  Without the general forms' scaling, class tests and selections they take 8 and 10 instructions against 11 and 17.
+// IEEE-754's quotient and square root where no scaling and no special case can arise: for the quotient two Newton steps on the
+// hardware's reciprocal, for the root a step of Goldschmidt's iteration on its reciprocal square root, and corrections by the exact
+// remainder, the last of which rounds correctly (Markstein).  Without the general forms' scaling, class tests and selections they take 8 and 10 instructions against 11 and 17.
 __device__ __forceinline__ double divide_near_one(double n, double d)        // d in [2, 3), 0 <= n < 1 and n no less than 2^-33 unless zero
 {
     double y = __builtin_amdgcn_rcp(d);
