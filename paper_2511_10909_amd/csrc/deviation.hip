@@ -103,6 +103,27 @@ __device__ __noinline__ void delta_wide(DynFmt fa, DynFmt fb, const uint8_t *a, 
     ad = ldexp((double)mag, lsb);
 }
 
+// sign, whether delta is zero, floor(delta / 2^bin_exp) clamped to +-NB and |delta|'s binary64 image, from a pair that holds delta
+__device__ __forceinline__ void place_pair(const ExactPair &pr, int bin_exp, uint32_t &neg, bool &zero, int &fi, double &ad)
+{
+    constexpr int NB = MMAEMU_DEVIATION_BINS;
+    double h, l;
+    two_sum(pr.hi, pr.lo, h, l);                                     // h = RN(delta), l = delta - h
+    neg = h < 0.0;
+    zero = h == 0.0;
+    ad = __builtin_fabs(h);
+    // floor(delta / 2^bin_exp): of h, and one less where h is a whole number of bins and l lies below it (a
+    // fractional h / w keeps at least one of its own last places to either side, more than |l / w|)
+    const double qh = ldexp(h, -bin_exp);
+    if (qh >= (double)NB) fi = NB;
+    else if (qh <= -(double)NB) fi = -NB;
+    else if (qh == 0.0) fi = neg ? -1 : 0;                           // (h / w below the binary64 range)
+    else {
+        const double fl = __builtin_floor(qh);
+        fi = (int)fl - ((fl == qh && l < 0.0) ? 1 : 0);
+    }
+}
+
 // Eight elements of one row as binary32 values (NaN and infinities as themselves), one branch on the type for all
 __device__ __forceinline__ void elem_floats8(uint32_t t, const uint32_t (&bits)[8], float (&v)[8])
 {
@@ -150,7 +171,7 @@ __host__ __device__ constexpr bool splits(uint32_t t)
 // SPLIT: products summed as SplitSum does (7 vector instructions per term), only D, the accumulator and the two sums go
 // through the pair of binary64 numbers; else (BF16: hundreds of binary places, or k beyond SPLIT_MAX_K) every product does
 // (15 per term).  With one output per thread, all through the pair, checks per element, 64-bit divisions per sample and three
-// LDS atomics per sample on few addresses, 2^24 outputs of 32x32x8 FP16 tiles took 229 us; now 119 us (5.6e11 -> 1.1e12 terms/s; bound by binary64 issue).
+// LDS atomics per sample on few addresses, 2^24 outputs of 32x32x8 FP16 tiles took 229 us, so 119 (bound by binary64 issue; whole tiles have a kernel of their own below).
 template <int W, bool SPLIT>
 __global__ void __launch_bounds__(256)
 deviation_kernel(const void *__restrict__ A, const void *__restrict__ B, const uint32_t *__restrict__ C,
@@ -276,21 +297,7 @@ deviation_kernel(const void *__restrict__ A, const void *__restrict__ B, const u
             int fi;
             double ad;
             if (pr[w].lost == 0.0) {
-                double h, l;
-                two_sum(pr[w].hi, pr[w].lo, h, l);                       // h = RN(delta), l = delta - h
-                neg = h < 0.0;
-                zero = h == 0.0;
-                ad = __builtin_fabs(h);
-                // floor(delta / 2^bin_exp): of h, and one less where h is a whole number of bins and l lies below it (a
-                // fractional h / w keeps at least one of its own last places to either side, more than |l / w|)
-                const double qh = ldexp(h, -bin_exp);
-                if (qh >= (double)NB) fi = NB;
-                else if (qh <= -(double)NB) fi = -NB;
-                else if (qh == 0.0) fi = neg ? -1 : 0;                   // (h / w below the binary64 range)
-                else {
-                    const double fl = __builtin_floor(qh);
-                    fi = (int)fl - ((fl == qh && l < 0.0) ? 1 : 0);
-                }
+                place_pair(pr[w], bin_exp, neg, zero, fi, ad);
             } else {
                 delta_wide(fa, fb, a, b + (uint64_t)w * k * esb, k, cb[w], db[w], unit_bit, neg, zero, fi, ad);
             }
@@ -344,9 +351,381 @@ deviation_kernel(const void *__restrict__ A, const void *__restrict__ B, const u
     }
 }
 
+// ---- whole tiles of FP16 and FP8 operands: the products' sums on the matrix cores -------------
+//
+// A wavefront owns 16 RB x 16 CB outputs of a tile and forms their sums of products with v_mfma_f64_16x16x4_f64, a chain of fused
+// multiply-adds that is exact while every product is a multiple of one unit and the sums stay below 2^53 of them.  The types alone may
+// guarantee that (E4M3 x E4M3); else the wavefront takes the largest and the smallest exponent of its rows' elements.  An output's end
+// is four binary64 operations, with four comparisons that say whether they were exact: D - S first, which cancels, then the
+// accumulator.  Outputs for which they were not (or not finite) go on one by one, as a pair of binary64 numbers.
+// Where the exponents lie too far apart the wavefront splits every element at 2^-4 into two parts, whose sums of products are exact up
+// to SPLIT_MAX_K, and every output's sum goes on as a pair.
+// Bound: HBM (C and D are read once, 8 bytes per output): 2^24 outputs of 32x32x8 FP16 tiles 114 -> 47 us (3.2 TB/s).  Blocks of 32 rows
+// took 54: fewer wavefronts to hide the loads behind; 256, 1024 and 2048 workgroups for 512 took 55, 48 and 62 (each ends in
+// atomics on the same lines).
+constexpr int TILE_COPIES = 32, TILE_BINS = MMAEMU_DEVIATION_BINS + 1;     // (the last row takes what is not counted)
+
+struct DevTileArgs {
+    const uint8_t *A, *B;
+    const uint32_t *C, *D;
+    uint32_t m, n, k, ta, tb, stride;
+    int32_t bin_exp, slack;             // slack: how far apart the exponents may lie (see the launch)
+    uint32_t exact_types, bm, bn;
+    uint64_t nitems;
+};
+
+// two consecutive elements of a row as they lie in memory, and as binary32 values (FP8: whether E5M2)
+template <bool FP8> __device__ __forceinline__ uint32_t pair_load(const uint8_t *p)
+{
+    if constexpr (FP8) return *reinterpret_cast<const uint16_t *>(p);
+    else return *reinterpret_cast<const uint32_t *>(p);
+}
+template <bool FP8> __device__ __forceinline__ void pair_values(bool e5m2, uint32_t w, float (&v)[2])
+{
+    if constexpr (FP8) {
+        typedef float f32x2 __attribute__((ext_vector_type(2)));
+        const f32x2 x = __builtin_amdgcn_cvt_pk_f32_fp8((int)w, false), y = __builtin_amdgcn_cvt_pk_f32_bf8((int)w, false);
+        v[0] = e5m2 ? y.x : x.x; v[1] = e5m2 ? y.y : x.y;
+    } else {
+        typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+        const f16x2 h = __builtin_bit_cast(f16x2, w);
+        v[0] = (float)h[0]; v[1] = (float)h[1];
+    }
+}
+
+// largest magnitude pattern and (less one, zeros left out) smallest of a lane's elements
+struct Span {
+    uint32_t most = 0u, least = 0xFFFFFFFFu;
+    __device__ __forceinline__ void take(const float (&v)[2])
+    {
+        const uint32_t u0 = __float_as_uint(v[0]) & 0x7FFFFFFFu, u1 = __float_as_uint(v[1]) & 0x7FFFFFFFu;
+        most = max(max(u0, u1), most);
+        least = min(min(u0 - 1u, u1 - 1u), least);
+    }
+    // exponent fields over the wavefront: the largest in the low half, 511 less the smallest in the high half (256 where all are zero)
+    __device__ __forceinline__ uint32_t wave() const
+    {
+        const uint32_t lo = least == 0xFFFFFFFFu ? 255u : (least + 1u) >> 23;
+        uint32_t x = (most >> 23) | ((511u - lo) << 16);
+#if defined(__HIP_DEVICE_COMPILE__)
+        x = pk_max_u16(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, false));
+        x = pk_max_u16(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, false));
+        x = pk_max_u16(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, false));
+        x = pk_max_u16(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, false));
+        x = pk_max_u16(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xA, 0xF, false));
+        x = pk_max_u16(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xC, 0xF, false));
+        x = (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
+#endif
+        return x;
+    }
+};
+
+// One output the long way: its binary64 image and bin, or the row that is not counted.  sum_hi and sum_lo are the
+// products' sum as SplitSum forms it.
+struct Settled { double h; uint32_t bin; };
+__device__ __noinline__ Settled settle_output(const uint8_t *a, const uint8_t *b, uint32_t k, uint32_t ta, uint32_t tb, int bin_exp, double sum_hi, double sum_lo,
+                                              uint32_t cb, uint32_t db)
+{
+    constexpr int NB = MMAEMU_DEVIATION_BINS;
+    const double finite_max = 0x1.fffffffffffffp+1023;
+    Settled out = {0.0, (uint32_t)NB};
+    if ((cb & 0x7F800000u) == 0x7F800000u || (db & 0x7F800000u) == 0x7F800000u || !(__builtin_fabs(sum_hi) <= finite_max) || !(__builtin_fabs(sum_lo) <= finite_max)) return out;
+    ExactPair pr;
+    pr.start(db);
+    double residue;
+    two_sum(pr.hi, -sum_hi, pr.hi, pr.lo);
+    two_sum(pr.lo, -sum_lo, pr.lo, residue);
+    pr.lost = __builtin_fabs(residue);
+    pr.add(-(double)__uint_as_float(cb), 1.0);
+    uint32_t neg;
+    bool zero;
+    int fi;
+    double ad;
+    if (pr.lost == 0.0) place_pair(pr, bin_exp, neg, zero, fi, ad);
+    else delta_wide(dyn_fmt(ta), dyn_fmt(tb), a, b, k, cb, db, bin_exp - XBASE, neg, zero, fi, ad);
+    int bin = zero ? NB / 2 : fi + NB / 2;
+    out.bin = (uint32_t)(bin < 0 ? 0 : (bin > NB - 1 ? NB - 1 : bin));
+    out.h = zero ? 0.0 : (neg ? -ad : ad);
+    return out;
+}
+
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+// What a lane sums up and what its wavefront counts.  `bin` NB: not counted (h is zero then).
+struct DevTally {
+    double sum = 0.0, sum_abs = 0.0, sum_sq = 0.0;
+    uint32_t neg = 0, zero = 0, out = 0, bad = 0;                       // out: not sampled, or left to be settled; bad: skipped (both come with h = 0)
+    __device__ __forceinline__ void take(double h, uint32_t bin, uint32_t lane, uint32_t *bins)
+    {
+        neg += (uint32_t)__popcll(__ballot(h < 0.0));
+        zero += (uint32_t)__popcll(__ballot(h == 0.0));
+        atomicAdd(&bins[bin * TILE_COPIES + (lane & (TILE_COPIES - 1))], 1u);
+        sum += h;
+        sum_abs += __builtin_fabs(h);
+        sum_sq = __builtin_fma(h, h, sum_sq);
+    }
+};
+
+template <bool FP8, int RB, int CB, bool STRIDED>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4)))
+deviation_tile_kernel(DevTileArgs g, mmaemu_deviation_hist *hist)
+{
+    constexpr int NB = MMAEMU_DEVIATION_BINS;
+    __shared__ uint32_t bins[TILE_BINS * TILE_COPIES];
+    for (uint32_t i = threadIdx.x; i < TILE_BINS * TILE_COPIES; i += 512) bins[i] = 0u;
+    __syncthreads();
+    const uint32_t lane = threadIdx.x & 63u, wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const uint32_t c16 = lane & 15u, g4 = lane >> 4;
+    constexpr uint32_t ES = FP8 ? 1u : 2u;
+    const bool a5 = g.ta == MMAEMU_FP8_E5M2, b5 = g.tb == MMAEMU_FP8_E5M2;
+    const uint32_t *const acc = g.C ? g.C : g.D;                       // (without an accumulator D is read again, and masked)
+    const uint32_t acc_mask = g.C ? 0xFFFFFFFFu : 0u;
+    const f64x4 zero4 = {0.0, 0.0, 0.0, 0.0};
+    const uint32_t lane_mod = STRIDED ? (g4 * g.n + CB * c16) % g.stride : 0u;
+    DevTally tally;
+    unsigned long long seen = 0, skipped = 0, negative = 0, none = 0;          // (of the wavefront; none: zero)
+    for (uint64_t item = (uint64_t)blockIdx.x * 8u + wave; item < g.nitems; item += (uint64_t)gridDim.x * 8u) {
+        uint64_t tile; uint32_t rem;
+        split_item(item, g.bm * g.bn, tile, rem);
+        const uint32_t i0 = (rem / g.bn) * (16 * RB), j0 = (rem % g.bn) * (16 * CB);
+        const uint64_t row_a = tile * g.m + i0 + c16, row_b = tile * g.n + j0 + CB * c16;
+        const uint8_t *pa = g.A + (row_a * g.k + 2u * g4) * ES, *pb = g.B + (row_b * g.k + 2u * g4) * ES;
+        const uint64_t out_row = tile * g.m + i0 + g4;                         // rows out_row + 16 r + 4 v, columns j0 + CB c16 + c
+        const uint64_t o0 = out_row * g.n + j0 + CB * c16;
+        uint32_t o0_mod = 0;
+        if constexpr (STRIDED) {
+            o0_mod = (uint32_t)(((tile * g.m + i0) * g.n + j0) % g.stride) + lane_mod;
+            o0_mod -= o0_mod >= g.stride ? g.stride : 0u;
+        }
+        auto sampled = [&](int r, int v, int c) -> bool {
+            if constexpr (!STRIDED) return true;
+            const uint32_t x = o0_mod + ((uint32_t)(16 * r + 4 * v) * g.n + c) % g.stride;      // (the output's index modulo stride, or that and stride)
+            return x == 0u || x == g.stride;
+        };
+        uint32_t db[RB][4][CB], cb[RB][4][CB];
+#pragma unroll
+        for (int r = 0; r < RB; ++r)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const uint64_t o = o0 + (uint64_t)(16 * r + 4 * v) * g.n;
+                if constexpr (CB == 2) {
+                    const uint2 d2 = *reinterpret_cast<const uint2 *>(g.D + o), c2 = *reinterpret_cast<const uint2 *>(acc + o);
+                    db[r][v][0] = d2.x; db[r][v][CB - 1] = d2.y; cb[r][v][0] = c2.x & acc_mask; cb[r][v][CB - 1] = c2.y & acc_mask;
+                } else {
+                    db[r][v][0] = g.D[o];
+                    cb[r][v][0] = acc[o] & acc_mask;
+                }
+            }
+        f64x4 S[RB][CB];
+#pragma unroll
+        for (int r = 0; r < RB; ++r)
+#pragma unroll
+            for (int c = 0; c < CB; ++c) S[r][c] = zero4;
+        Span span_a, span_b;
+        uint32_t wa[RB], wb[CB];
+        auto fetch = [&](uint32_t k0) {
+#pragma unroll
+            for (int r = 0; r < RB; ++r) wa[r] = pair_load<FP8>(pa + ((uint64_t)(16 * r) * g.k + k0) * ES);
+#pragma unroll
+            for (int c = 0; c < CB; ++c) wb[c] = pair_load<FP8>(pb + ((uint64_t)c * g.k + k0) * ES);
+        };
+        fetch(0);
+#pragma unroll 1
+        for (uint32_t k0 = 0; k0 < g.k; k0 += 8) {
+            float a[RB][2], b[CB][2];
+#pragma unroll
+            for (int r = 0; r < RB; ++r) { pair_values<FP8>(a5, wa[r], a[r]); span_a.take(a[r]); }
+#pragma unroll
+            for (int c = 0; c < CB; ++c) { pair_values<FP8>(b5, wb[c], b[c]); span_b.take(b[c]); }
+            if (k0 + 8 < g.k) fetch(k0 + 8);
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int r = 0; r < RB; ++r)
+#pragma unroll
+                    for (int c = 0; c < CB; ++c) S[r][c] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a[r][h], (double)b[c][h], S[r][c], 0, 0, 0);
+        }
+        bool split = false;
+        if (!g.exact_types) {
+            const uint32_t xa = span_a.wave(), xb = span_b.wave();
+            // (an infinite or NaN element, whose field is 255, goes on split)
+            split = (int)((xa & 0xFFFFu) + (xa >> 16) + (xb & 0xFFFFu) + (xb >> 16)) - 2 * 511 > g.slack || (xa & 0xFFFFu) == 255u || (xb & 0xFFFFu) == 255u;
+        }
+        tally.neg = tally.zero = tally.out = tally.bad = 0;
+        uint32_t open = 0;                                            // outputs left to be settled: bit (4 r + v) CB + c
+        // one output's end; LOW: the products' sum is s + low where `held`
+        auto end = [&](auto low_c, int rv, int c, uint32_t dbits, uint32_t cbits, double s, double low, bool held, bool in) {
+            constexpr bool LOW = decltype(low_c)::value;
+            const double dd = (double)__uint_as_float(dbits), cc = (double)__uint_as_float(cbits);
+            // (a difference is exact where adding it to the one, and taking it from the other, operand gives the operands back;
+            // false for NaN)
+            double r1 = dd - s;
+            bool exact = (r1 + s == dd) & (dd - r1 == s);
+            if constexpr (LOW) {
+                const double r0 = r1;
+                r1 = r0 - low;
+                exact = exact & (r1 + low == r0) & (r0 - r1 == low);
+            }
+            const double r2 = r1 - cc;
+            exact = exact & (r2 + cc == r1) & (r1 - r2 == cc) & held;
+            double q = __builtin_floor(ldexp(r2, -g.bin_exp));
+            q = __builtin_fmax(__builtin_fmin(q, (double)(NB / 2 - 1)), (double)(-NB / 2));
+            const uint32_t bin = (uint32_t)((int)q + NB / 2);
+            if (__any(in && !exact)) {
+                // (none of the finite ones overflows, so that r2 is finite exactly where everything is)
+                const bool finite = __builtin_fabs(r2) <= 0x1.fffffffffffffp+1023;
+                if (in && !exact && finite) open |= 1u << (rv * CB + c);
+                const uint32_t skip = (uint32_t)__popcll(__ballot(in && !finite));
+                tally.bad += skip;
+                tally.out -= skip;
+            }
+            tally.out += (uint32_t)__popcll(__ballot(!(in && exact)));
+            tally.take((in && exact) ? r2 : 0.0, (in && exact) ? bin : (uint32_t)NB, lane, bins);
+        };
+        seen += 64u * RB * 4 * CB;
+        if (__builtin_expect(!split, 1)) {
+#pragma unroll
+            for (int r = 0; r < RB; ++r)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+#pragma unroll
+                    for (int c = 0; c < CB; ++c) end(std::false_type{}, 4 * r + v, c, db[r][v][c], cb[r][v][c], S[r][c][v], 0.0, true, sampled(r, v, c));
+        } else {
+#pragma unroll 1
+            for (int rc = 0; rc < RB * CB; ++rc) {
+                const int r = rc / CB, c = rc % CB;
+                f64x4 H = zero4, M = zero4, L = zero4;
+                const uint8_t *const qa = pa + (uint64_t)(16 * r) * g.k * ES, *const qb = pb + (uint64_t)c * g.k * ES;
+                uint32_t xa = pair_load<FP8>(qa), xb = pair_load<FP8>(qb);
+#pragma unroll 1
+                for (uint32_t k0 = 0; k0 < g.k; k0 += 8) {
+                    float a[2], b[2];
+                    pair_values<FP8>(a5, xa, a);
+                    pair_values<FP8>(b5, xb, b);
+                    if (k0 + 8 < g.k) { xa = pair_load<FP8>(qa + (k0 + 8) * ES); xb = pair_load<FP8>(qb + (k0 + 8) * ES); }
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        constexpr float CUT = 0x1.8p+19f;              // (its last place is 2^-4)
+                        const float ah = (a[h] + CUT) - CUT, bh = (b[h] + CUT) - CUT;
+                        const double al = (double)(a[h] - ah), bl = (double)(b[h] - bh);
+                        H = __builtin_amdgcn_mfma_f64_16x16x4f64((double)ah, (double)bh, H, 0, 0, 0);
+                        M = __builtin_amdgcn_mfma_f64_16x16x4f64((double)ah, bl, M, 0, 0, 0);
+                        M = __builtin_amdgcn_mfma_f64_16x16x4f64(al, (double)bh, M, 0, 0, 0);
+                        L = __builtin_amdgcn_mfma_f64_16x16x4f64(al, bl, L, 0, 0, 0);
+                    }
+                }
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    double hi, lo, rest;
+                    two_sum(H[v], M[v], hi, lo);
+                    two_sum(lo, L[v], lo, rest);
+                    const uint64_t o = o0 + (uint64_t)(16 * r + 4 * v) * g.n + c;
+                    end(std::true_type{}, 4 * r + v, c, g.D[o], acc[o] & acc_mask, hi, lo, rest == 0.0, sampled(r, v, c));
+                }
+            }
+        }
+        while (__builtin_expect(__any(open != 0u), 0)) {
+            const bool mine = open != 0u;
+            const uint32_t bit = mine ? (uint32_t)__builtin_ctz(open) : 0u, c = bit % CB, rv = bit / CB;      // (row 4 rv of the lane's)
+            open &= open - 1u;
+            const uint64_t o = o0 + (uint64_t)(4 * rv) * g.n + c;
+            Settled t = {0.0, (uint32_t)NB};
+            if (mine) {
+                SplitSum sp;
+                const uint8_t *qa = g.A + (out_row + 4 * rv) * g.k * ES, *qb = g.B + (row_b + c) * (uint64_t)g.k * ES;
+#pragma unroll 1
+                for (uint32_t kk = 0; kk < g.k; kk += 2) {
+                    float a[2], b[2];
+                    pair_values<FP8>(a5, pair_load<FP8>(qa + kk * ES), a);
+                    pair_values<FP8>(b5, pair_load<FP8>(qb + kk * ES), b);
+                    sp.add(a[0], b[0]);
+                    sp.add(a[1], b[1]);
+                }
+                t = settle_output(qa, qb, g.k, g.ta, g.tb, g.bin_exp, sp.upper, sp.lower, acc[o] & acc_mask, g.D[o]);
+            }
+            seen += 64u;
+            tally.out += (uint32_t)__popcll(__ballot(!mine));
+            tally.bad += (uint32_t)__popcll(__ballot(mine && t.bin == (uint32_t)NB));
+            tally.take(t.h, t.bin, lane, bins);
+        }
+        seen -= tally.out + tally.bad;
+        skipped += tally.bad;
+        negative += tally.neg;
+        none += (unsigned long long)tally.zero - tally.out - tally.bad;
+    }
+    // one atomic per workgroup and word
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        tally.sum += __shfl_xor(tally.sum, off, 64);
+        tally.sum_abs += __shfl_xor(tally.sum_abs, off, 64);
+        tally.sum_sq += __shfl_xor(tally.sum_sq, off, 64);
+    }
+    __shared__ double wave_sums[8][3];
+    __shared__ unsigned long long wave_counts[8][5];
+    if (lane == 0) {
+        wave_sums[wave][0] = tally.sum; wave_sums[wave][1] = tally.sum_abs; wave_sums[wave][2] = tally.sum_sq;
+        wave_counts[wave][0] = seen; wave_counts[wave][1] = skipped; wave_counts[wave][2] = negative; wave_counts[wave][3] = none;
+        wave_counts[wave][4] = seen - negative - none;
+    }
+    __syncthreads();
+    unsigned long long *gc = reinterpret_cast<unsigned long long *>(hist);
+    if (threadIdx.x < 3) {
+        double t = 0.0;
+#pragma unroll
+        for (int w = 0; w < 8; ++w) t += wave_sums[w][threadIdx.x];
+        if (t != 0.0) atomicAdd(reinterpret_cast<double *>(gc + 5 + NB) + threadIdx.x, t);
+    } else if (threadIdx.x >= 64u && threadIdx.x < 64u + 5u) {
+        unsigned long long t = 0;
+#pragma unroll
+        for (int w = 0; w < 8; ++w) t += wave_counts[w][threadIdx.x - 64u];
+        if (t) atomicAdd(gc + (threadIdx.x - 64u), t);
+    } else if (threadIdx.x >= 128u && threadIdx.x < 128u + NB) {
+        const uint32_t bin = threadIdx.x - 128u;
+        uint32_t t = 0;
+#pragma unroll
+        for (uint32_t q = 0; q < TILE_COPIES; ++q) t += bins[bin * TILE_COPIES + ((q + bin) & (TILE_COPIES - 1))];
+        if (t) atomicAdd(gc + 5 + bin, (unsigned long long)t);
+    }
+}
+
 mmaemu_status launch_deviation_reset(mmaemu_deviation_hist *h, hipStream_t s)
 {
     hipLaunchKernelGGL(deviation_reset_kernel, dim3(1), dim3(128), 0, s, h);
+    MMAEMU_HIP(hipGetLastError());
+    return MMAEMU_OK;
+}
+
+constexpr uint64_t TILE_MAX_WORK = 32;
+constexpr uint64_t TILE_MIN_OUTPUTS = 1ull << 17;
+
+static mmaemu_status launch_deviation_tiles(const void *A, const void *B, const uint32_t *C, const uint32_t *D, uint32_t m, uint32_t n, uint32_t k,
+                                            uint64_t batch, uint32_t ta, uint32_t tb, uint32_t stride, int bin_exp, mmaemu_deviation_hist *h, hipStream_t s)
+{
+    const bool wide = n % 32 == 0;                             // two blocks of 16 columns per wavefront
+    DevTileArgs g = {};
+    g.A = (const uint8_t *)A; g.B = (const uint8_t *)B; g.C = C; g.D = D;
+    g.m = m; g.n = n; g.k = k; g.ta = ta; g.tb = tb; g.stride = stride; g.bin_exp = bin_exp;
+    g.bm = m / 16u; g.bn = n / (wide ? 32u : 16u);
+    g.nitems = batch * g.bm * g.bn;
+    // An element lies below 2^(E + 1), E its exponent, and is a multiple of 2^(E' - mbits), E' the smallest exponent; k products then
+    // reach 2^(E_a + E_b + 2 + ceil(log2 k)) in units of 2^(E'_a + E'_b - mbits_a - mbits_b).
+    const FmtInfo fa = fmt_info(ta), fb = fmt_info(tb);
+    int lk = 0;
+    while ((1u << lk) < k) ++lk;
+    g.slack = 53 - 2 - lk - fa.mbits - fb.mbits;
+    auto span = [](const FmtInfo &f) { return (1 << f.ebits) - (f.ieee ? 3 : 2); };     // (subnormals are multiples of the smallest normal numbers' unit)
+    g.exact_types = span(fa) + span(fb) <= g.slack ? 1u : 0u;
+    uint64_t blocks = (g.nitems + 7) / 8;
+    if (blocks > 512) blocks = 512;
+    auto go = [&](auto fp8_c) {
+        constexpr bool FP8 = decltype(fp8_c)::value;
+        if (wide && stride == 1) hipLaunchKernelGGL((deviation_tile_kernel<FP8, 1, 2, false>), dim3((uint32_t)blocks), dim3(512), 0, s, g, h);
+        else if (wide) hipLaunchKernelGGL((deviation_tile_kernel<FP8, 1, 2, true>), dim3((uint32_t)blocks), dim3(512), 0, s, g, h);
+        else if (stride == 1) hipLaunchKernelGGL((deviation_tile_kernel<FP8, 1, 1, false>), dim3((uint32_t)blocks), dim3(512), 0, s, g, h);
+        else hipLaunchKernelGGL((deviation_tile_kernel<FP8, 1, 1, true>), dim3((uint32_t)blocks), dim3(512), 0, s, g, h);
+    };
+    if (ta == MMAEMU_FP16) go(std::false_type{});
+    else go(std::true_type{});
     MMAEMU_HIP(hipGetLastError());
     return MMAEMU_OK;
 }
@@ -367,6 +746,16 @@ mmaemu_status launch_deviation_sample(const void *A, const void *B, const uint32
     const bool split = splits(ta) && splits(tb) && k <= SPLIT_MAX_K;
     const bool fours = split && stride == 1 && n % 4 == 0 && ((reinterpret_cast<uintptr_t>(C) | reinterpret_cast<uintptr_t>(D)) & 15u) == 0;
     const bool wide = fours && (nsamples >= (1ull << 19) || (k <= 32 && nsamples >= (1ull << 18)));
+    // Whole tiles on the matrix cores, which form every output's sum whether it is sampled or not and wait for a chunk of k at a time.
+    // The other kernels and this one, us, 2^24 outputs of 32x32 FP16 tiles, N(0, 1000): k = 8, strides 1, 2, 3, 5, 8 114, 94, 75, 62, 57 and
+    // 47 to 49; k = 16, 32, 64 163, 256, 442 and 54, 89, 236.  Where the exponents lie too far apart (all finite bit patterns, 16x16 tiles):
+    // k = 8, 16, 32 at stride 3 87, 109, 142 and 83, 117, 211; at stride 1, 32x32 tiles, k = 8, 32, 64 114, 255, 443 and 82, 202, 498.  2^17
+    // outputs of k = 32 17 and 13, 2^14 10 and 11.
+    if (((ta == MMAEMU_FP16 && tb == MMAEMU_FP16) || (ta <= MMAEMU_FP8_E5M2 && tb <= MMAEMU_FP8_E5M2)) && m % 16 == 0 && n % 16 == 0 && k % 8 == 0 && k * stride <= TILE_MAX_WORK && total >= TILE_MIN_OUTPUTS &&
+        n <= (1u << 24) && (uint64_t)m * n <= (1ull << 38) && ((reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(B)) & 3u) == 0 &&
+        (n % 32 != 0 || ((reinterpret_cast<uintptr_t>(C) | reinterpret_cast<uintptr_t>(D)) & 7u) == 0)) {
+        return launch_deviation_tiles(A, B, C, D, m, n, k, batch, ta, tb, (uint32_t)stride, bin_exp, h, s);
+    }
     const uint64_t nitems = wide ? nsamples / 4 : nsamples;
     uint64_t blocks = (nitems + 255) / 256;
     // Grid-stride beyond 2048 workgroups (two rounds of what the chip holds); beyond 2^42 samples 4096, so that no workgroup

@@ -206,6 +206,36 @@ def test_deviation_sample_four_outputs_per_thread(mm, ta, tb, n, k):
         same_hist(mm.read_deviation_hist(h), want, (offset, k))
 
 
+@pytest.mark.parametrize("ta,tb,m,n,k,stride,with_c,exps", [
+    (fm.FP16, fm.FP16, 16, 16, 8, 1, True, (0, 30)), (fm.FP16, fm.FP16, 32, 32, 8, 3, True, (12, 22)), (fm.FP16, fm.FP16, 16, 32, 8, 4, True, (0, 30)),
+    (fm.FP16, fm.FP16, 48, 16, 32, 1, False, (9, 24)), (fm.FP16, fm.FP16, 16, 64, 16, 2, True, (14, 20)), (fm.FP16, fm.FP16, 16, 32, 24, 1, True, (0, 30)),
+    (fm.E4M3, fm.E4M3, 16, 16, 32, 1, True, (0, 14)), (fm.E4M3, fm.E5M2, 16, 96, 24, 1, True, (0, 14)), (fm.E5M2, fm.E4M3, 32, 32, 8, 4, False, (0, 14)),
+    (fm.E5M2, fm.E5M2, 16, 32, 16, 1, True, (0, 30))])
+@pytest.mark.parametrize("special", [False, True])
+def test_deviation_sample_whole_tiles(mm, ta, tb, m, n, k, stride, with_c, exps, special):
+    """The sums on the matrix cores: exponents that an exact chain holds and that it does not, outputs that leave its short end (a D far
+    from the sum, accumulators far below it), infinities and NaN, strides; the oracle's histogram of a few tiles, many times over."""
+    import torch
+    rng = np.random.default_rng(90 + k + m + n + stride)
+    nb = 3 if stride == 3 else 2
+    A, B = synth.narrow_exponent_bits(rng, (nb, m, k), ta, *exps), synth.narrow_exponent_bits(rng, (nb, n, k), tb, *exps)
+    A[0, 1], B[1, 2] = 0, 0
+    C = synth.narrow_exponent_bits(rng, (nb, m, n), fm.FP32, 118, 132)
+    C[rng.random(C.shape) < 0.02] = 0x00000003
+    D = o2lib.emulate_mma(ModelParams(group_len=k, frac_bits=14), A, B, C if with_c else np.zeros_like(C), ta, tb)[0]
+    D[0, 3, :6] = [0x00000001, 0x80000000, 0x00000000, 0x80800000, 0x3F800001, 0xBF800001]
+    if special:
+        D[0, 4, :2] = [0x7F7FFFFF, 0x5F000000]                       # (of one sign: their sum is the histogram's)
+        A, B = synth.sprinkle(rng, A, synth.SPECIAL_CODES[ta], 0.01), synth.sprinkle(rng, B, synth.SPECIAL_CODES[tb], 0.01)
+        C, D = (synth.sprinkle(rng, x, [0x7F800000, 0xFF800000, 0x7FC00000, 0xFFFFFFFF], 0.02) for x in (C, D))
+    assert nb * m * n % stride == 0
+    want = deviation_hist(A, B, C if with_c else None, D, ta, tb, stride, -5)
+    copies = (1 << 17) // (nb * m * n) + 1
+    want = {key: [v * copies for v in x] if key == "bins" else x * copies for key, x in want.items()}
+    A, B, C, D = (np.tile(x, (copies, 1, 1)) for x in (A, B, C, D))
+    same_hist(dev_hist(mm, A, B, C if with_c else None, D, ta, tb, stride, -5), want, (ta, tb, m, n, k, stride, special))
+
+
 def test_few_outputs_with_long_rows_keep_one_per_thread(mm):
     """4096 outputs of 4096 terms: as fast as the call whose accumulator is not 16-byte aligned, which always runs one output
     per thread (four per thread took 2.6 times as long)."""
