@@ -56,6 +56,7 @@ mmaemu_status launch_emulate(const ModelArgs &p, const void *A, const void *B, c
                   ((p.c_mode == MMAEMU_C_AFTER_RD && p.skip_zero_terms) ? 2 * (int)ZBIAS : 0);
         if (!scaled && small_takes(p, ta, tb, m, n, k)) return launch_emulate_small(p, A, B, Cm, D, m, n, k, batch, ta, tb, s);
         if (!scaled && packed_takes(p, ta, tb, m, n, k, batch)) return launch_emulate_packed(p, A, B, Cm, D, m, n, k, batch, ta, tb, s);
+        if (packed_rd_takes(p, ta, tb, m, n, k, batch, scaled, block)) return launch_emulate_packed_rd(p, A, B, Cm, D, m, n, k, batch, ta, tb, s, SA, SB);
         bool handled = false;
         mmaemu_status st;
         if (scaled) st = launch_vm<3>(t, A, B, Cm, D, m, n, k, batch, s, handled);
