@@ -347,7 +347,8 @@ __device__ __forceinline__ uint32_t wave_reduce_to_lane63(uint32_t v)
 // (all of them in its low word: F2 is 23 at least), after adding them all where the number is negative.
 // The outputs run side by side and what is rare is asked once for all of them: results below 2^-126, where the places are counted
 // from 2^-126.  (One output after the other, each with its branch, a pass of candidate sets -- generators, native instruction and a
-// scan launch of sixteen sets of this kind, on 2^15 tiles of 16x16x16 FP16 -- took 786 us; 638 so, of which the launch is 552.)  Returns whether some result of the wavefront may be below 2^-126 (none other makes a zero of negative sign).
+// scan launch of sixteen sets of this kind, on 2^15 tiles of 16x16x16 FP16 -- took 786 us; 638 so; 613 since the
+// places are added to the 64-bit pattern at once and the results are looked at only where the exponents allow small ones.)  Returns whether some result of the wavefront may be below 2^-126 (none other makes a zero of negative sign).
 // A group no product of which took part (zero terms kept out) has an exponent maximum more than 100 places below any
 // accumulator's and drops out by it; block scales may lift that maximum: HAVE reads have[] for them.
 template <bool HAVE, int N>
@@ -355,13 +356,12 @@ __device__ __forceinline__ bool rd_exact_all(const double (&T)[N], const int (&e
                                              int drop, uint32_t fl, double (&r)[N], const bool *have = nullptr)
 {
     const uint32_t below = (uint32_t)((1ull << (52 - F2)) - 1ull);
-    uint32_t least = 0xFFFFFFFFu;
+    int least_E = 0x7FFFFFFF;
 #pragma unroll
     for (int i = 0; i < N; ++i) {
-        const int Ec = (int)((cb[i] >> 23) & 0xFFu), emb = em[i] + 127;                       // biased exponents
-        int E = Ec > emb ? Ec : emb;
-        E = E > 1 ? E : 1;
-        if (HAVE && !have[i]) E = Ec > 1 ? Ec : 1;
+        const int Ec = (int)((cb[i] >> 23) & 0xFFu), emb = HAVE && !have[i] ? 0 : em[i] + 127;   // biased exponents
+        const int E = max(max(Ec, emb), 1);
+        least_E = min(E, least_E);
         const double Tk = E - emb >= drop ? 0.0 : T[i];                                        // a product sum too far below drops out
         const int down = Fc + 127 - E;
         double sc = __builtin_floor(ldexp((double)__uint_as_float(cb[i]), down));
@@ -371,13 +371,19 @@ __device__ __forceinline__ bool rd_exact_all(const double (&T)[N], const int (&e
             sc = __hiloint2double(far_below ? 0 : __double2hiint(sc), __double2loint(sc));
         }
         const double v = ldexp(sc + ldexp(Tk, em[i] - F + down), -down);
-        const uint32_t hi = (uint32_t)__double2hiint(v), lo = (uint32_t)__double2loint(v);
-        const uint32_t add = (uint32_t)((int32_t)hi >> 31) & below, sum = lo + add;
-        r[i] = __hiloint2double((int)(hi + (sum < add ? 1u : 0u)), (int)(sum & ~below));
-        const uint32_t mag = (hi & 0x7FFFFFFFu) - 1u;                                           // (zero: all ones)
-        least = mag < least ? mag : least;
+        const uint32_t hi = (uint32_t)__double2hiint(v);
+        const uint64_t sum = (uint64_t)__double_as_longlong(v) + ((uint32_t)((int32_t)hi >> 31) & below);
+        r[i] = __hiloint2double((int)(uint32_t)(sum >> 32), (int)((uint32_t)sum & ~below));
     }
-    const bool low = __any(least < 0x38100000u - 1u) != 0;
+    // A result that is not zero is no less than the finer of the two units: 2^(e_max - F), e_max above E less the drop distance, and
+    // 2^(E - Fc).  The results themselves are looked at only where that lies below 2^-126 (four comparisons on the way less).
+    bool low = false;
+    if (__builtin_expect(__any(least_E < 1 + max(drop - 1 + F, Fc)) != 0, 0)) {
+        uint32_t least = 0xFFFFFFFFu;
+#pragma unroll
+        for (int i = 0; i < N; ++i) least = min(((uint32_t)__double2hiint(r[i]) & 0x7FFFFFFFu) - 1u, least);        // (zero: all ones)
+        low = __any(least < 0x38100000u - 1u) != 0;
+    }
     if (__builtin_expect(low, 0)) {
 #pragma unroll
         for (int i = 0; i < N; ++i) {
