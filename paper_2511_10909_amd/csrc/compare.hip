@@ -2,7 +2,8 @@
 // Sec. 3.1 Step 4: the model must reproduce the interface bit by bit).
 //
 // HBM-bound: 8 (4) bytes read per compared pair.  Each lane handles four (eight) consecutive
-// elements (one 128-bit load per input).  The histogram is kept in LDS in 32 copies per
+// elements (one 128-bit load per input), four such loads in flight at once; a wavefront whose vectors are equal leaves them alone
+// (2^19 equal pairs 6.7 -> 2.3 us, 2^22 7.5 -> 3.4).  The histogram is kept in LDS in 32 copies per
 // bucket (copy = lane mod 32), so that lanes counting the same bucket do not serialise
 // on one address; counters are flushed with one global atomic per non-zero counter per
 // workgroup.
@@ -17,55 +18,53 @@ __global__ void stats_reset_kernel(mmaemu_stats *st)
     if (i < sizeof(mmaemu_stats) / 8) w[i] = (i == 3) ? ~0ull : 0ull;   // word 3: first_mismatch_index
 }
 
-// W = 32: binary32 patterns; W = 16: binary16 patterns (widened to 32 bits by the caller of one_pair)
-template <int W> __device__ __forceinline__ int64_t ordered_key(uint32_t b)
-{
-    constexpr uint32_t SIGN = 1u << (W - 1);
-    return (b & SIGN) ? -(int64_t)(b & (SIGN - 1u)) : (int64_t)b;
-}
-
 struct Local {
     uint32_t mism, nan_equiv;
     uint64_t first, maxd;
 };
 
+// W = 32: binary32 patterns; W = 16: binary16 patterns (widened to 32 bits by the caller).  The ordered distance of two numbers, the
+// difference of their magnitudes' patterns or, across zero, their sum, takes 32 bits (up to twice infinity's pattern, 0xFF000000).
 template <int W>
-__device__ __forceinline__ void one_pair(uint32_t x, uint32_t y, uint64_t idx, Local &lc, uint32_t *hist)
+__device__ __forceinline__ void one_pair(uint32_t x, uint32_t y, uint64_t idx, Local &lc, uint32_t &maxd, uint32_t *hist)
 {
-    constexpr uint32_t MAG = (1u << (W - 1)) - 1u, INF = W == 32 ? 0x7F800000u : 0x7C00u;
-    const bool nx = (x & MAG) > INF, ny = (y & MAG) > INF;
+    constexpr uint32_t SIGN = 1u << (W - 1), MAG = SIGN - 1u, INF = W == 32 ? 0x7F800000u : 0x7C00u;
+    const uint32_t ax = x & MAG, ay = y & MAG;
+    const bool nx = ax > INF, ny = ay > INF;
     uint32_t bucket;
     if (x != y) {
+        lc.first = lc.mism ? lc.first : idx;                         // (a thread's indices ascend)
         lc.mism += 1;
-        lc.first = idx < lc.first ? idx : lc.first;
     }
     if (nx || ny) {
         bucket = (nx && ny) ? 0u : 33u;
         if (nx && ny && x != y) lc.nan_equiv += 1;
     } else {
-        const int64_t kx = ordered_key<W>(x), ky = ordered_key<W>(y);
-        const uint64_t dist = (uint64_t)(kx > ky ? kx - ky : ky - kx);
-        lc.maxd = dist > lc.maxd ? dist : lc.maxd;
-        bucket = dist ? 64u - (uint32_t)__builtin_clzll(dist) : 0u;
+        const uint32_t dist = ((x ^ y) & SIGN) ? ax + ay : max(ax, ay) - min(ax, ay);
+        maxd = max(dist, maxd);
+        bucket = dist ? 32u - (uint32_t)__builtin_clz(dist) : 0u;
     }
     if (bucket) atomicAdd(&hist[bucket * 32u + (threadIdx.x & 31u)], 1u);   // bucket 0 is derived from the total
 }
 
 // the 128 / W elements of one 128-bit load from each input, first element index i0
 template <int W>
-__device__ __forceinline__ void one_vector(const uint4 &x, const uint4 &y, uint64_t i0, Local &lc, uint32_t *hist)
+__device__ __forceinline__ void one_vector(const uint4 &x, const uint4 &y, uint64_t i0, Local &lc, uint32_t &maxd, uint32_t *hist)
 {
     const uint32_t xs[4] = {x.x, x.y, x.z, x.w}, ys[4] = {y.x, y.y, y.z, y.w};
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
         if (W == 32) {
-            one_pair<W>(xs[w], ys[w], i0 + w, lc, hist);
+            one_pair<W>(xs[w], ys[w], i0 + w, lc, maxd, hist);
         } else {
-            one_pair<W>(xs[w] & 0xFFFFu, ys[w] & 0xFFFFu, i0 + 2 * w, lc, hist);
-            one_pair<W>(xs[w] >> 16, ys[w] >> 16, i0 + 2 * w + 1, lc, hist);
+            one_pair<W>(xs[w] & 0xFFFFu, ys[w] & 0xFFFFu, i0 + 2 * w, lc, maxd, hist);
+            one_pair<W>(xs[w] >> 16, ys[w] >> 16, i0 + 2 * w + 1, lc, maxd, hist);
         }
     }
 }
+
+// (equal vectors count nowhere: a wavefront that meets no other leaves the pairs alone)
+__device__ __forceinline__ bool differ(const uint4 &x, const uint4 &y) { return ((x.x ^ y.x) | (x.y ^ y.y) | (x.z ^ y.z) | (x.w ^ y.w)) != 0u; }
 
 // per-workgroup state in LDS
 struct WgStats {
@@ -150,24 +149,32 @@ compare_kernel(const T *__restrict__ d0, const T *__restrict__ d1, uint64_t coun
     uint32_t *hist = ws.hist;
 
     Local lc = {0, 0, ~0ull, 0};
+    uint32_t maxd = 0;
     const uint64_t nvec = count / EPV;
     const bool aligned = ((reinterpret_cast<uintptr_t>(d0) | reinterpret_cast<uintptr_t>(d1)) & 15) == 0;
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
     if (aligned) {
         const uint4 *v0 = reinterpret_cast<const uint4 *>(d0), *v1 = reinterpret_cast<const uint4 *>(d1);
         uint64_t v = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-        for (; v + stride < nvec; v += 2 * stride) {               // two independent 128-bit loads per input in flight
-            const uint4 x0 = v0[v], y0 = v1[v], x1 = v0[v + stride], y1 = v1[v + stride];
-            one_vector<W>(x0, y0, base + EPV * v, lc, hist);
-            one_vector<W>(x1, y1, base + EPV * (v + stride), lc, hist);
+        for (; v + 3 * stride < nvec; v += 4 * stride) {           // four independent 128-bit loads per input in flight
+            uint4 x[4], y[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) { x[i] = v0[v + i * stride]; y[i] = v1[v + i * stride]; }
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (__any(differ(x[i], y[i]))) one_vector<W>(x[i], y[i], base + EPV * (v + i * stride), lc, maxd, hist);
         }
-        for (; v < nvec; v += stride) one_vector<W>(v0[v], v1[v], base + EPV * v, lc, hist);
+        for (; v < nvec; v += stride) {
+            const uint4 x = v0[v], y = v1[v];
+            if (__any(differ(x, y))) one_vector<W>(x, y, base + EPV * v, lc, maxd, hist);
+        }
         for (uint64_t i = EPV * nvec + (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += stride)
-            one_pair<W>(d0[i], d1[i], base + i, lc, hist);
+            one_pair<W>(d0[i], d1[i], base + i, lc, maxd, hist);
     } else {
         for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += stride)
-            one_pair<W>(d0[i], d1[i], base + i, lc, hist);
+            one_pair<W>(d0[i], d1[i], base + i, lc, maxd, hist);
     }
+    lc.maxd = maxd;
     wg_flush(ws, lc, count, st);
 }
 
@@ -238,12 +245,14 @@ mmaemu_status launch_compare(const void *d0, const void *d1, uint64_t count, uin
                              mmaemu_stats *st, hipStream_t s)
 {
     // Few, fat workgroups: a workgroup with differing pairs ends with atomics on up to 38 words of the same few lines, and
-    // those serialise across the chip (about 30 ns per workgroup: 2^24 pairs, 256 workgroups, 24.6 us equal and 33.2 differing),
-    // so a workgroup covers at least 16K pairs before it pays for them; 1024 threads each, so that a workgroup has 16 waves' worth
-    // of loads in flight (a small comparison is latency-bound).  One workgroup per CU at most: with two, equal inputs streamed
+    // those serialise across the chip (about 30 ns per workgroup: 2^24 pairs, 256 workgroups, 20.5 us equal and 33 differing),
+    // so beyond 64 workgroups one covers at least 16K pairs before it pays for them; up to there 4K, one vector of each input per thread (2^14
+    // pairs, 80 % differing, workgroups of 4K, 8K, 16K pairs 5.4, 6.3, 8.8 us; 2^18 7.3, 7.1, 9.2; 2^20 14.3, 10.5, 10.9).  1024 threads each, so that a
+    // workgroup has 16 waves' worth of loads in flight (a small comparison is latency-bound).  One workgroup per CU at most: with two, equal inputs streamed
     // 4 % faster, but inputs that differ paid twice the atomics (15 % more at 2^24 pairs, measured when each counter was an
     // atomic of its own), and the closed-loop workloads compare mostly differing outputs.
-    uint64_t blocks = (count + 16383) / 16384;
+    const uint64_t fine = (count + 4095) / 4096, fat = (count + 16383) / 16384;
+    uint64_t blocks = fine < 64 ? fine : (fat > 64 ? fat : 64);
     if (blocks < 1) blocks = 1;
     if (blocks > 256) blocks = 256;
     if (half)

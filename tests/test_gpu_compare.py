@@ -33,3 +33,24 @@ def test_single_differing_pairs(mm, width, count, misalign):
             want = ostats.compare(x1[misalign:], y1[misalign:], stats=want, index_base=base, width=width)
             assert mm.read_stats(st) == want, (at, hex(int(a)), hex(int(b)))
             base += count
+
+
+@pytest.mark.parametrize("width", [16, 32])
+@pytest.mark.parametrize("count", [4095, 4097, 16384, 64 * 4096 - 3, 64 * 4096 + 5, 65 * 16384 + 1])
+def test_many_differing_pairs(mm, width, count):
+    """Both sides of the workgroups' sizes, with patches that differ beside patches that do not (each wavefront's vectors equal, one pair
+    of them different, all different): first index, largest distance (of numbers on either side of zero too) and every bucket."""
+    dtype, word, nan, nan2, minus_zero = WIDTHS[width]
+    rng = np.random.default_rng(width + count)
+    x = rng.integers(0, 1 << width, size=count, dtype=word)
+    y = x.copy()
+    st = dev_empty(mm.STATS_BYTES)
+    mm.stats_reset(st)
+    want = ostats.empty_stats()
+    for base, (lo, hi, frac) in enumerate(((count // 3, count, 0.0), (count - 1, count, 1.0), (count // 2, count, 0.01), (0, count, 1.0))):
+        y = x.copy()
+        pick = np.arange(lo, hi)[rng.random(hi - lo) < frac]
+        y[pick] = rng.integers(0, 1 << width, size=len(pick), dtype=word)
+        mm.compare(to_dev(x), to_dev(y), count, st, index_base=base * count, d=dtype)
+        want = ostats.compare(x, y, stats=want, index_base=base * count, width=width)
+        assert mm.read_stats(st) == want, (lo, hi, frac)
