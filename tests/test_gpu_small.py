@@ -37,6 +37,27 @@ def test_small_tiles(mm, ta, tb, m, n, k):
         assert_same(got, want, "set %d, %s" % (i, (ta, tb, m, n, k)))
 
 
+@pytest.mark.parametrize("ta,tb", [(fm.FP16, fm.FP16), (fm.E5M2, fm.E4M3), (fm.E2M3, fm.E3M2), (fm.E4M3, fm.E2M1)])
+@pytest.mark.parametrize("L,F,k,quads", [(4, 27, 4, True), (4, 28, 4, False), (8, 26, 24, True), (8, 27, 8, False), (16, 25, 48, True), (16, 26, 16, False), (16, 3, 32, True)])
+def test_tiles_of_four_lanes(mm, ta, tb, L, F, k, quads):
+    """4 x 4 tiles: sums that fill 32 bits and that do not (the largest products of one sign), special values in some tiles of a
+    wavefront, flushes, truncation, and a batch that ends inside a wavefront."""
+    rng = np.random.default_rng(100 * L + F + 10 * ta + tb)
+    nb = 531
+    for i, p in enumerate((ModelParams(group_len=L, frac_bits=F), ModelParams(group_len=L, frac_bits=F, out_round=RZ, ftz_in=True, ftz_out=True), RD.with_(group_len=L, frac_bits=F),
+                           FITTED.with_(group_len=L, frac_bits=F, frac_bits_acc=min(F, 24)), RD.with_(group_len=L, frac_bits=F, rd_toward_zero=True))):
+        A, B, C = make_case(rng, ta, tb, nb, 4, 4, k, special_frac=0.003 if i % 2 else 0.0)
+        C[nb // 2:] = synth.narrow_exponent_bits(rng, C[nb // 2:].shape, fm.FP32, 110, 140)
+        top = {fm.FP16: 0x7BFF, fm.E5M2: 0x7B, fm.E4M3: 0x7E, fm.E2M3: 0x1F, fm.E3M2: 0x1F, fm.E2M1: 7}
+        A[:3], B[:3] = top[ta], top[tb]
+        C.ravel()[:4] = [0x80000000, 0, 0x00000001, 0x7F7FFFFF]
+        C[5, 1] = [0x7F800000, 0xFF800000, 0x7FC00000, 0xFF7FFFFF]
+        want, _ = o2lib.emulate_mma(p, A, B, C, ta, tb)
+        got = gpu_emulate(mm, p, A, B, C, ta, tb)
+        assert ("four threads per tile" in gpu_emulate.last_kernel) == quads, gpu_emulate.last_kernel
+        assert_same(got, want, "set %d, %s" % (i, (ta, tb, L, F, k)))
+
+
 @pytest.mark.parametrize("ta,tb", [(fm.FP16, fm.FP16), (fm.BF16, fm.BF16), (fm.E4M3, fm.E5M2)])
 @pytest.mark.parametrize("m,n,k,nb,outputs", [(8, 8, 64, 20, 1), (4, 4, 56, 3, 1), (8, 4, 64, (1 << 19) // 32, 4), (8, 4, 64, (1 << 19) // 32 - 1, 1), (4, 8, 48, 7, 4)])
 def test_outputs_per_thread(mm, ta, tb, m, n, k, nb, outputs):
