@@ -5,9 +5,11 @@
 // One wavefront per sampled output: lanes stride over k, each accumulating exact products
 // in units of 2^LSB0 (LSB0 = the smallest last-place exponent a product can have); an FP8
 // product is below 2^33 in value and a multiple of 2^-32, so it needs at most 66 bits;
-// per-lane sums are kept in two binary64 numbers that split every product at 2^(LSB0 + 32),
+// sums are kept in two binary64 numbers that split at 2^(LSB0 + 32),
 // both exact, and combined into a two-limb (128-bit) signed value that is exact for any
-// k <= 2^20.
+// k <= 2^20.  Everything after the sum is one lane's work: it waits until every lane has a sample
+// (an end per sample took longer than the sum: every 100th output of 4096^3 E4M3 x E5M2 423 -> 141 us, 2048x2048x512, every tenth
+// 412 -> 163; bound now by vector issue, 4.5 instructions per term).
 #include "common.hpp"
 
 namespace mmaemu {
@@ -77,6 +79,14 @@ template <int T> __device__ __forceinline__ void fp8x4_values(uint32_t w, float 
     v[0] = lo.x; v[1] = lo.y; v[2] = hi.x; v[3] = hi.y;
 }
 
+// sum over the wavefront, in every lane
+__device__ __forceinline__ double wave_sum(double x)
+{
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) x += __shfl_xor(x, off, 64);
+    return x;
+}
+
 template <int TA, int TB>
 __global__ void __launch_bounds__(256)
 exact_dot_kernel(const uint8_t *__restrict__ A, const uint8_t *__restrict__ B, const uint32_t *__restrict__ D,
@@ -94,54 +104,84 @@ exact_dot_kernel(const uint8_t *__restrict__ A, const uint8_t *__restrict__ B, c
     __syncthreads();
     unsigned long long *g = ls;
     double *gd = reinterpret_cast<double *>(ls + 5 + 34);
-    for (uint64_t sidx = wave; sidx < nsamples; sidx += nwaves) {
-        const uint64_t o = sidx * stride;
-        const uint32_t i = (uint32_t)(o / n), j = (uint32_t)(o % n);
-        const uint8_t *a = A + (uint64_t)i * k, *b = B + (uint64_t)j * k;
-        // Per lane: four consecutive k per 32-bit load, decoded by the hardware's own FP8 -> binary32 conversions (two
-        // elements per instruction); a product is exact in binary32 (at most 8 significant bits, 2^-32 <= |p| < 2^33).
-        // Its binary64 image is split at 2^(LSB0 + 32) by adding and subtracting a constant whose last place that is:
-        // the upper part is a multiple of 2^(LSB0 + 32), the lower part a multiple of 2^LSB0 of at most 2^(LSB0 + 31),
-        // and with at most 2^14 terms per lane (k <= 2^20) both sums stay below 2^53 of their units, i.e. exact.
-        // A NaN or an infinity among the operands makes one of the sums a NaN or an infinity.
-        constexpr double SPLIT = 0x1.8p+52 * (LSB0 + 32 >= 0 ? (double)(1ull << (LSB0 + 32 >= 0 ? LSB0 + 32 : 0)) : 1.0 / (double)(1ull << (LSB0 + 32 >= 0 ? 0 : -(LSB0 + 32))));
+    // (up to) 64 samples' sums, one in each lane, then the ends of all of them side by side
+    const bool vec = k % 16u == 0 && ((reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(B)) & 15u) == 0;
+    for (uint64_t first = wave; first < nsamples; first += 64 * nwaves) {
         double sum_hi = 0.0, sum_lo = 0.0;
-        for (uint32_t q = 4 * lane; q < k; q += 256) {
-            uint32_t wa, wb;
-            if (q + 4 <= k && (((uintptr_t)(a + q) | (uintptr_t)(b + q)) & 3) == 0) {
-                wa = *reinterpret_cast<const uint32_t *>(a + q);
-                wb = *reinterpret_cast<const uint32_t *>(b + q);
-            } else {
-                wa = wb = 0;                                                     // (padding bytes are zero: +0.0)
-                for (uint32_t u = 0; u < 4 && q + u < k; ++u) { wa |= (uint32_t)a[q + u] << (8 * u); wb |= (uint32_t)b[q + u] << (8 * u); }
-            }
-            float va[4], vb[4];
-            fp8x4_values<TA>(wa, va);
-            fp8x4_values<TB>(wb, vb);
+#pragma unroll 1
+        for (uint32_t s = 0; s < 64; ++s) {
+            const uint64_t sidx = first + s * nwaves;
+            if (sidx >= nsamples) break;
+            const uint64_t o = sidx * stride;
+            uint32_t i, j;
+            if ((o >> 32) == 0) { i = (uint32_t)o / n; j = (uint32_t)o - i * n; }                // (a 64-bit division takes far longer)
+            else { i = (uint32_t)(o / n); j = (uint32_t)(o % n); }
+            const uint8_t *a = A + (uint64_t)i * k, *b = B + (uint64_t)j * k;
+            // Per lane, elements decoded by the hardware's own FP8 -> binary32 conversions (two per instruction); a product is exact in
+            // binary32 (at most 8 significant bits, 2^-32 <= |p| < 2^33).  Its binary64 image, or the sum of RUN of them where that is
+            // exact too, is split at 2^(LSB0 + 32) by adding and subtracting a constant whose last place that is: the upper part is a
+            // multiple of 2^(LSB0 + 32), the lower part a multiple of 2^LSB0 of at most 2^(LSB0 + 31), and for k <= 2^20 all sums of
+            // either, over the lanes too, stay below 2^53 of their units, i.e. exact.  A NaN or an infinity among the operands
+            // makes one of the sums a NaN or an infinity.
+            constexpr double SPLIT = 0x1.8p+52 * (LSB0 + 32 >= 0 ? (double)(1ull << (LSB0 + 32 >= 0 ? LSB0 + 32 : 0)) : 1.0 / (double)(1ull << (LSB0 + 32 >= 0 ? 0 : -(LSB0 + 32))));
+            // (E4M3 x E4M3 products span 36 bits, E4M3 x E5M2 50, E5M2 x E5M2 64)
+            constexpr int RUN = TA == MMAEMU_FP8_E5M2 && TB == MMAEMU_FP8_E5M2 ? 1 : (TA == TB ? 16 : 8);
+            double hi = 0.0, lo = 0.0;
+            auto take = [&](double x) {
+                const double upper = (x + SPLIT) - SPLIT;
+                hi += upper;
+                lo += x - upper;
+            };
+            if (vec) {
+                uint4 na = make_uint4(0u, 0u, 0u, 0u), nb = na;
+                if (16 * lane < k) { na = *reinterpret_cast<const uint4 *>(a + 16 * lane); nb = *reinterpret_cast<const uint4 *>(b + 16 * lane); }
+                for (uint32_t q = 16 * lane; q < k; q += 1024) {
+                    const uint32_t wa[4] = {na.x, na.y, na.z, na.w}, wb[4] = {nb.x, nb.y, nb.z, nb.w};
+                    if (q + 1024 < k) { na = *reinterpret_cast<const uint4 *>(a + q + 1024); nb = *reinterpret_cast<const uint4 *>(b + q + 1024); }
+                    double run = 0.0;
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const double pd = (double)(va[u] * vb[u]);
-                const double upper = (pd + SPLIT) - SPLIT;
-                sum_hi += upper;
-                sum_lo += pd - upper;
+                    for (int w = 0; w < 4; ++w) {
+                        float va[4], vb[4];
+                        fp8x4_values<TA>(wa[w], va);
+                        fp8x4_values<TB>(wb[w], vb);
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            const double pd = (double)(va[u] * vb[u]);
+                            run = (4 * w + u) % RUN == 0 ? pd : run + pd;
+                            if ((4 * w + u) % RUN == RUN - 1) take(run);
+                        }
+                    }
+                }
+            } else {
+                for (uint32_t q = 4 * lane; q < k; q += 256) {
+                    uint32_t wa, wb;
+                    if (q + 4 <= k && (((uintptr_t)(a + q) | (uintptr_t)(b + q)) & 3) == 0) {
+                        wa = *reinterpret_cast<const uint32_t *>(a + q);
+                        wb = *reinterpret_cast<const uint32_t *>(b + q);
+                    } else {
+                        wa = wb = 0;                                                     // (padding bytes are zero: +0.0)
+                        for (uint32_t u = 0; u < 4 && q + u < k; ++u) { wa |= (uint32_t)a[q + u] << (8 * u); wb |= (uint32_t)b[q + u] << (8 * u); }
+                    }
+                    float va[4], vb[4];
+                    fp8x4_values<TA>(wa, va);
+                    fp8x4_values<TB>(wb, vb);
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) take((double)(va[u] * vb[u]));
+                }
             }
+            hi = wave_sum(hi);
+            lo = wave_sum(lo);
+            if (lane == s) { sum_hi = hi; sum_lo = lo; }
         }
+        const uint64_t sidx = first + lane * nwaves;
+        if (sidx >= nsamples) continue;                       // (nothing below exchanges lanes)
+        const uint64_t o = sidx * stride;
         const double finite_max = 0x1.fffffffffffffp+1023;
-        bool bad = !(__builtin_fabs(sum_hi) <= finite_max) || !(__builtin_fabs(sum_lo) <= finite_max);
+        const bool bad = !(__builtin_fabs(sum_hi) <= finite_max) || !(__builtin_fabs(sum_lo) <= finite_max);
         const int64_t acc_hi = bad ? 0 : (int64_t)__builtin_ldexp(sum_hi, -(LSB0 + 32));
         const int64_t acc_lo = bad ? 0 : (int64_t)__builtin_ldexp(sum_lo, -LSB0);
         I128 acc = {(uint64_t)acc_lo, acc_lo < 0 ? -1ll : 0ll};
         acc = add128(acc, shl128(I128{(uint64_t)acc_hi, acc_hi < 0 ? -1ll : 0ll}, 32));
-        // wavefront reduction of the two-limb sums
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) {
-            I128 o2;
-            o2.lo = __shfl_xor((unsigned long long)acc.lo, off, 64);
-            o2.hi = (int64_t)__shfl_xor((unsigned long long)acc.hi, off, 64);
-            acc = add128(acc, o2);
-            bad |= (bool)__shfl_xor((int)bad, off, 64);
-        }
-        if (lane == 0) {
         const uint32_t d = D[o];
         if (bad || (d & 0x7F800000u) == 0x7F800000u) {
             atomicAdd(&g[4], 1ull);
@@ -198,7 +238,6 @@ exact_dot_kernel(const uint8_t *__restrict__ A, const uint8_t *__restrict__ B, c
             atomicMax(reinterpret_cast<unsigned long long *>(&gd[3]), (unsigned long long)__double_as_longlong(rel));
         }
         }   // finite sample
-        }   // lane 0
     }
     __syncthreads();
     if (threadIdx.x < NW && ls[threadIdx.x] != 0ull) {
@@ -224,7 +263,10 @@ static mmaemu_status launch_t(const void *A, const void *B, const uint32_t *D, u
     const uint64_t total = (uint64_t)m * n;
     const uint64_t nsamples = (total + stride - 1) / stride;
     uint64_t blocks = (nsamples + 3) / 4;
-    if (blocks > 1024) blocks = 1024;                      // wave-stride beyond that
+    // Wave-stride beyond 1024 workgroups, which end in atomics on the same lines; 2048 (all that the chip holds) where every wavefront
+    // still has sixteen samples.
+    const uint64_t most = nsamples >= (1ull << 17) ? 2048 : 1024;
+    if (blocks > most) blocks = most;
     hipLaunchKernelGGL((exact_dot_kernel<TA, TB>), dim3((uint32_t)blocks), dim3(256), 0, s, (const uint8_t *)A,
                        (const uint8_t *)B, D, m, n, k, stride, nsamples, st);
     MMAEMU_HIP(hipGetLastError());

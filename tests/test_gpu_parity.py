@@ -326,6 +326,34 @@ def test_exact_dot_sample_matches_oracle(mm):
             assert got[key] == pytest.approx(want[key], rel=1e-9, abs=1e-300), key
 
 
+@pytest.mark.parametrize("ta,tb", [(fm.E4M3, fm.E5M2), (fm.E5M2, fm.E5M2), (fm.E4M3, fm.E4M3), (fm.E5M2, fm.E4M3)])
+@pytest.mark.parametrize("m,n,k,stride", [(1024, 1030, 16, 1), (512, 700, 20, 1), (40, 48, 2064, 1), (3, 5, 3000, 2)])
+def test_exact_dot_sample_many_per_wavefront(mm, ta, tb, m, n, k, stride):
+    """More samples than the wavefronts' lanes, and fewer; rows of whole 16-byte vectors beyond 1024 and rows that are not; the largest
+    products of one sign, where the runs of products that are summed unsplit are full."""
+    rng = np.random.default_rng(m + k + 10 * ta + tb)
+    A, B = synth.random_bits(rng, (m, k), ta), synth.random_bits(rng, (n, k), tb)
+    big = {fm.E4M3: 0x7E, fm.E5M2: 0x7B}
+    A, B = (np.where((x & 0x7F) > big[t], big[t], x).astype(x.dtype) for x, t in ((A, ta), (B, tb)))       # (finite: the oracle sums no others)
+    A[0], B[0], B[1] = big[ta], big[tb], big[tb] | 0x80
+    A[1, : k // 2], B[2, k // 2 :] = 1, 0x81
+    import torch
+    as64 = lambda x, t: torch.from_numpy(x.astype(np.uint8)).view(torch.float8_e4m3fn if t == fm.E4M3 else torch.float8_e5m2).double().numpy()
+    D = (as64(A, ta) @ as64(B, tb).T * (1 + 1e-6 * rng.standard_normal((m, n)))).astype(np.float32)
+    D[np.abs(D) < 2.0 ** -10] = 1.0                        # (the oracle takes a D near the exact value, and no zeros)
+    D = D.view(np.uint32)
+    want = o2lib.exact_dot_stats(A, B, D, ta, tb, stride)
+    st = dev_empty(mm.ERR_STATS_BYTES)
+    mm.err_stats_reset(st)
+    mm.exact_dot_sample(to_dev(A), to_dev(B), to_dev(D), m, n, k, (ta, tb, fm.FP32, fm.FP32), stride, st)
+    got = mm.read_err_stats(st)
+    for key in ("n_samples", "n_equal_rne", "n_above", "n_below", "ulp_hist"):
+        assert got[key] == want[key], key
+    for key in ("sum_abs_err", "max_abs_err", "sum_rel_err", "max_rel_err"):
+        assert got[key] == pytest.approx(want[key], rel=1e-9, abs=1e-300), key
+    assert got["sum_signed_err"] == pytest.approx(want["sum_signed_err"], rel=1e-9, abs=1e-9 * want["sum_abs_err"])
+
+
 def test_exact_dot_every_pair_of_codes(mm):
     # every pair of FP8 codes as the one non-zero product of a dot product of four: D holds the exact product (every one is
     # a binary32 number), so each finite pair must be counted as equal, and each pair with a NaN or an infinity as skipped
