@@ -108,7 +108,7 @@ if not os.path.exists(LIB_PATH):
                       "__graft_entry__.build() first -- there is no fallback path" % LIB_PATH)
 # PyTorch first: it ships its own HIP runtime, and the library must bind to that same copy (tensors and streams
 # come from it).  Loaded the other way round, the library's runtime is a second one that sees no device.
-import torch  # noqa: E402,F401
+import torch  # noqa: E402
 
 _lib = ctypes.CDLL(LIB_PATH)
 
@@ -162,8 +162,9 @@ def _ptr(x):
 
 def _stream(stream):
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        # the current stream's handle without a torch.cuda.Stream object around it, which took 2.6 of the 6 to 8 us that a call
+        # takes on the host (nine small calls 59 -> 36 us)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
