@@ -978,22 +978,9 @@ tiled_body(const TiledArgs &ta_, const void *__restrict__ A, const void *__restr
                 for (int r = 0; r < R; ++r)
 #pragma unroll
                     for (int c = 0; c < C; ++c) one(r, c, take);
-                // (BF16 operands on 32 x 32 blocks: one after the other.  Beside that kernel's binary64 sums four at once take longer where few
-                // waves run: gfx950's set on 512x512x256 52.3 -> 51.3 us, with truncation 53.5 -> 50.9, with flushes 53.8 -> 51.6; on
-                // 1024x1024x256 97.6 -> 98.8, 100.9 -> 98.9, 99.7 -> 100.7.  FP16 and TF32, and 16 x 16 blocks, take 0.92 to 1.00 with four)
-                if constexpr (VM_ == 1 && TM == 32) {
-#pragma unroll
-                    for (int x = 0; x < R * C; ++x) {
-                        const double T1[1] = {T[x]};
-                        const int em1[1] = {em[x]};
-                        const uint32_t cb1[1] = {cb[x]};
-                        double v1[1];
-                        rd_exact_all<SC>(T1, em1, FT, cb1, p.F2, p.Fc, p.sum_drop_distance, fe, v1, have + x);
-                        v[x] = v1[0];
-                    }
-                } else {
-                    rd_exact_all<SC>(T, em, FT, cb, p.F2, p.Fc, p.sum_drop_distance, fe, v, have);
-                }
+                // (all four at once, BF16 operands beside their binary64 sums too: gfx950's set on 1024x1024x256 104 -> 95 us against one after
+                // the other, on 512x512x256 54.0 -> 52.2, all finite patterns 98.0 -> 98.2)
+                rd_exact_all<SC>(T, em, FT, cb, p.F2, p.Fc, p.sum_drop_distance, fe, v, have);
                 i = 0;
                 auto give = [&](double, bool, int, int, uint32_t) -> double { return v[i++]; };
 #pragma unroll
