@@ -38,6 +38,8 @@
 //     ran at half the speed of ordinary data through the routes of the general loop);
 //   * the reference's ordered keys are formed once per pass, a histogram entry is counted by leading zeros, and the two
 //     reductions over the wavefront run only where they can change something.
+// Launches of six and more TR-FDPA sets on FP8 and FP16 operands go the same way (FAM 4): the sixteen sets of the closed-loop scan
+// on 2^15 tiles of 16x16x16 FP16, N(0,1) operands, 566 -> 523 us.
 // Measured (kernel times), one launch of the sixteen sets of the closed-loop scan on 2^16 tiles of 16x16x16, before and after: FP8 1108 ->
 // 670 us (6.22 instructions per term), BF16 bit patterns 1433 -> 1137 us (8.70), all FP16 bit patterns (a quarter of the
 // tiles) 571 -> 253 us; three sets on 2^18 tiles of 32x32x8 1953 -> 1354 us (7.31).  What is left is still issue: 0.84 to
@@ -124,6 +126,9 @@ __device__ __forceinline__ uint32_t key_distance(uint32_t kx, uint32_t ky)
 // A value that every lane of the wavefront holds alike, in a scalar register.
 __device__ __forceinline__ uint32_t scalar(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
 
+// The products of a thread's outputs fit its registers: T-FDPA, and TR-FDPA on binary32 values, on tiles of up to 16 k.
+template <int KC, bool ADAPT, int FAM> constexpr bool scan_fast() { return FAM == 4 || (FAM == 0 && KC <= 16); }
+
 // LDS of one workgroup: staged values and exponents, the kept quarter maxima, the statistics
 template <int TM, int KC, bool ADAPT, int FAM>
 constexpr int scan_lds_bytes()
@@ -131,7 +136,7 @@ constexpr int scan_lds_bytes()
     constexpr int SLOTS = 256 / ((TM / 2) * (TM / 2));
     constexpr int VS = KC + 4, VSD = KC + 2, ES = KC / 2 + (KC == 8 ? 4 : 2);
     constexpr int KEPT = FAM == 3 ? KC / 4 : (KC / 4 + 1) / 2;            // dwords of kept maxima per output
-    return 2 * SLOTS * TM * (ADAPT ? VSD * 8 : VS * 4) + 2 * SLOTS * TM * ES * 4 + KEPT * 4 * 256 * 4 + (FAM == 0 && KC <= 16 ? 3 : 0) * 4 * 256 * 4 +
+    return 2 * SLOTS * TM * (ADAPT ? VSD * 8 : VS * 4) + 2 * SLOTS * TM * ES * 4 + KEPT * 4 * 256 * 4 + (scan_fast<KC, ADAPT, FAM>() ? 3 : 0) * 4 * 256 * 4 +
            (int)sizeof(MultiLds) + 16;
 }
 // workgroups (of four waves, one per SIMD) that a CU's 160 KB of LDS hold, four at most: the waves per SIMD to compile for
@@ -146,7 +151,8 @@ constexpr int scan_waves()
 // FAM 0: T-FDPA, the accumulator a term of the sum; FAM 1: TR-FDPA (unsplit groups), the accumulator added after the
 // products' sum with the two round-downs; FAM 2: GTR-FDPA's merge of sub-group sums with the sub-groups being the two
 // halves or the four quarters of a group (binary32 values only: FP8 / FP16 operands, a sub-group's sum in 32 bits); FAM 3:
-// GTR-FDPA as printed, the sub-groups being the even and the odd products.
+// GTR-FDPA as printed, the sub-groups being the even and the odd products; FAM 4: FAM 1 on binary32 values and up to 16 k, with the
+// products in registers.
 // TWIN (FAM 0, tiles of one group): a model marked `twin` is followed by one that differs from it only in the output
 // conversion (rounding, E8M13, output flush, NaN pattern); the two share the group's maximum and sum, and only the end of
 // the group and the statistics run twice.
@@ -157,7 +163,7 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
     constexpr int R = 2, C = 2, TN = TM;
     constexpr int TI = TM / R, TJ = TN / C, TPS = TI * TJ, SLOTS = 256 / TPS;
     static_assert(TPS * SLOTS == 256, "thread layout");
-    constexpr bool FAST = FAM == 0 && KC <= 16;                   // the products of a thread's outputs fit its registers
+    constexpr bool FAST = scan_fast<KC, ADAPT, FAM>();
     constexpr int VS = KC + 4, VSD = KC + 2, ES = KC / 2 + (KC == 8 ? 4 : 2);
     constexpr int NQ4 = KC / 4;                                   // quarter groups per row
     constexpr int NK2 = (NQ4 + 1) / 2;                            // dwords of kept maxima per output
@@ -371,8 +377,8 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
                         // under it cannot be the group's maximum); a tagged one stays far above every other
                         const int mb = (int)mx + ebase + 127;
                         mx = mb < 1 ? 1u : (uint32_t)mb;
-                        if constexpr (FAST) top = mx > top ? mx : top;
                     }
+                    if constexpr (FAST) top = mx > top ? mx : top;
                     // (each thread its own words: no barrier needed)
                     if constexpr (FAM == 3) m2k[q][tid][r * C + c] = x;           // low half: the even k, high half: the odd k
                     else if (q % 2 == 0) m2k[q / 2][tid][r * C + c] = mx;
@@ -500,7 +506,7 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
             // special: an operand of the wavefront's is a NaN or an infinity, or an accumulator is one or may become one.  The
             // groups' results then follow Sec. 4.2 through an IEEE sum of the group's products and its accumulator (special_sum).
             // (An infinity that a BF16 chain reaches by overflow is no such case: it stays by itself, see rho32.)
-            bool odd = top >= TAGGED;
+            bool odd = top >= (FAM == 0 ? TAGGED : SENTINEL);
 #pragma unroll
             for (int r = 0; r < R; ++r)
 #pragma unroll
@@ -612,7 +618,7 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
                     const uint32_t fl = hot.flags;
                     const bool twin = TWIN && hot.twin != 0;
                     if ((fl & FL_FTZ_IN) && !flushed) { form_products(true); flushed = true; }
-                    set_f32_round_toward_zero((fl & FL_RZ) != 0);
+                    if constexpr (FAM == 0) set_f32_round_toward_zero((fl & FL_RZ) != 0);
                     // (the kept maxima are read again for every model: hoisted out of this loop they would take up to 28 registers)
                     const uint32_t tid = opaque_thread_index();
                     auto kept = [&](int q, int r, int c) -> uint32_t { return (m2k[q / 2][tid][r * C + c] >> (16 * (q & 1))) & 0xFFFFu; };
@@ -832,8 +838,102 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
                         }
                         }
                     };
+                    // TR-FDPA: the products' sum alone at their own maximum exponent, then the last steps of all four outputs side by side.
+                    // WIDTH 0: the group's aligned terms in 32 bits; 1: two terms to a 32-bit sum, the sums in binary64; 2: one by one.
+                    auto run_rd = [&](auto gl_c, auto width_c) {
+                        constexpr int GL = decltype(gl_c)::value, WIDTH = decltype(width_c)::value;
+                        if constexpr (GL <= KC && FAM == 4) {
+#pragma unroll
+                        for (int g = 0; g < KC / GL; ++g) {
+                            double T[R * C], v[R * C];
+                            int em[R * C];
+                            uint32_t cb[R * C], o[R * C];
+                            bool have[R * C];
+#pragma unroll
+                            for (int r = 0; r < R; ++r)
+#pragma unroll
+                                for (int c = 0; c < C; ++c) {
+                                    const int i = r * C + c;
+                                    uint32_t e;
+                                    if constexpr (GL == 4) e = kept(g, r, c);
+                                    else {
+                                        uint32_t x = m2k[g * (GL / 8)][tid][i];
+#pragma unroll
+                                        for (int j = 1; j < GL / 8; ++j) x = pk_max_u16(x, m2k[g * (GL / 8) + j][tid][i]);
+                                        const uint32_t lo = x & 0xFFFFu, hi = x >> 16;
+                                        e = lo > hi ? lo : hi;
+                                    }
+                                    em[i] = (int)e + ebase;
+                                    have[i] = !(fl & FL_SKIP_ZERO) || e >= 2 * ZBIAS;
+                                    cb[i] = d[r][c];
+                                    int se = F + 127 - em[i];
+                                    se = se < 1 ? 1 : (se > 254 ? 254 : se);                       // (the clamps never change a truncated term)
+                                    const float scale = __uint_as_float((uint32_t)se << 23);
+                                    if constexpr (WIDTH == 0) {
+                                        int32_t S = 0;
+#pragma unroll
+                                        for (int w = 0; w < GL; ++w) S += (int32_t)(p[r][c][g * GL + w] * scale);
+                                        T[i] = (double)S;
+                                    } else {
+                                        T[i] = 0.0;
+#pragma unroll
+                                        for (int w = 0; w < GL; w += 2) {
+                                            const float t0 = p[r][c][g * GL + w] * scale, t1 = p[r][c][g * GL + w + 1] * scale;
+                                            if constexpr (WIDTH == 1) T[i] += (double)((int32_t)t0 + (int32_t)t1);
+                                            else {
+                                                T[i] += (double)__builtin_truncf(t0);
+                                                T[i] += (double)__builtin_truncf(t1);
+                                            }
+                                        }
+                                    }
+                                    one_at_a_time();
+                                }
+                            if (fl & FL_FTZ_IN) {
+#pragma unroll
+                                for (int i = 0; i < R * C; ++i) if ((cb[i] & 0x7F800000u) == 0) cb[i] = 0;             // FlushSubnormal on the accumulator
+                            }
+                            bool low = true;                          // some result may be a zero of negative sign
+                            if (__builtin_expect((fl & FL_SUM_EXACT) != 0u, 1)) low = rd_exact_all<false>(T, em, F, cb, hot.F2, hot.Fc, hot.drop, fl, v);
+                            else {
+#pragma unroll
+                                for (int i = 0; i < R * C; ++i) v[i] = rd_general(T[i], have[i], em[i], F, cb[i], hot.F2, hot.Fc, hot.drop, fl);
+                            }
+#pragma unroll
+                            for (int i = 0; i < R * C; ++i) o[i] = __float_as_uint((float)v[i]);
+                            if ((fl & (FL_RZ | FL_FTZ_OUT)) != 0u || (low && (fl & FL_ZERO_POSITIVE) != 0u)) {         // (one test on the common way)
+#pragma unroll
+                                for (int i = 0; i < R * C; ++i) {
+                                    if (fl & FL_RZ) {
+                                        const double back = (double)__uint_as_float(o[i]);
+                                        if (__builtin_fabs(back) > __builtin_fabs(v[i])) o[i] -= 1u;               // rounded away from zero: step back
+                                        o[i] &= hot.out_mask;                                                      // RZ-E8M13 cuts further, still toward zero
+                                    }
+                                    if ((fl & FL_FTZ_OUT) && (o[i] & 0x7F800000u) == 0) o[i] &= 0x80000000u;
+                                    if ((fl & FL_ZERO_POSITIVE) && (o[i] & 0x7FFFFFFFu) == 0) o[i] = 0u;
+                                }
+                            }
+#pragma unroll
+                            for (int r = 0; r < R; ++r)
+#pragma unroll
+                                for (int c = 0; c < C; ++c) {
+                                    if (__builtin_expect(special, 0)) {
+                                        const uint32_t t = special_sum(gl_c, g, r, c, d[r][c]);
+                                        if ((t & 0x7F800000u) == 0x7F800000u) o[r * C + c] = t;
+                                        one_at_a_time();
+                                    }
+                                    d[r][c] = o[r * C + c];
+                                }
+                        }
+                        }
+                    };
                     auto by_width = [&](auto gl_c) {
                         constexpr int GL = decltype(gl_c)::value;
+                        if constexpr (FAM == 4) {
+                            if (hot.kind == 0) run_rd(gl_c, std::integral_constant<int, 0>{});
+                            else if (F <= 28) run_rd(gl_c, std::integral_constant<int, 1>{});
+                            else run_rd(gl_c, std::integral_constant<int, 2>{});
+                            return;
+                        }
                         const bool fits = F >= 1 && F <= 28 && ((uint64_t)(GL + 1) << (F + 2)) <= (1ull << 31);
                         if (fits) { run_fast(gl_c, std::integral_constant<int, 0>{}); return; }
                         // (an aligned term is below 2^(F+2): two of them stay inside 32 bits up to F = 28)
@@ -1543,7 +1643,7 @@ static mmaemu_status launch_scan_cfg(const ScanArgs &sa, const void *A, const vo
     }
     hipLaunchKernelGGL((emulate_scan_kernel<TM, KC, ADAPT, FAM, TWIN>), dim3(grid), dim3(256), 0, s, sa, A, B, C, batch, (uint32_t)blocks);
     MMAEMU_HIP(hipGetLastError());
-    set_last_kernel("multi x%u tiled %dx%d r2x2 kc=%d any L vm=%d%s", sa.count, TM, TM, KC, ADAPT ? 1 : 0, FAM == 1 ? " rd" : (FAM == 2 ? " rd split" : (FAM == 3 ? " rd even/odd" : (TWIN ? ", twins share sums" : ""))));
+    set_last_kernel("multi x%u tiled %dx%d r2x2 kc=%d any L vm=%d%s", sa.count, TM, TM, KC, ADAPT ? 1 : 0, FAM == 1 ? " rd" : FAM == 4 ? " kept rd" : (FAM == 2 ? " rd split" : (FAM == 3 ? " rd even/odd" : (TWIN ? ", twins share sums" : ""))));
     return MMAEMU_OK;
 }
 
@@ -1607,7 +1707,9 @@ static mmaemu_status launch_scan_shape(const ScanArgs &sa, const void *A, const 
     if constexpr (FAM >= 2) {                    // (binary32 values only)
         if (m == 16 && n == 16 && k == 16) return launch_scan_cfg<16, 16, false, FAM>(sa, A, B, Cm, batch, s);
         if (m == 32 && n == 32 && k == 8) return launch_scan_cfg<32, 8, false, FAM>(sa, A, B, Cm, batch, s);
-        if (m == 16 && n == 16 && k == 32) return launch_scan_cfg<16, 32, false, FAM>(sa, A, B, Cm, batch, s);
+        if constexpr (FAM != 4) {
+            if (m == 16 && n == 16 && k == 32) return launch_scan_cfg<16, 32, false, FAM>(sa, A, B, Cm, batch, s);
+        }
         if (m == 32 && n == 32 && k == 16) return launch_scan_cfg<32, 16, false, FAM>(sa, A, B, Cm, batch, s);
     } else {
     if (m == 16 && n == 16 && k == 16) return adapt ? launch_scan_cfg<16, 16, true, FAM>(sa, A, B, Cm, batch, s) : launch_scan_cfg<16, 16, false, FAM>(sa, A, B, Cm, batch, s);
@@ -1669,6 +1771,11 @@ mmaemu_status launch_scan(const MultiLaunch &ml, const void *A, const void *B, c
     const uint32_t *Cm = static_cast<const uint32_t *>(C);
     if (ml.cls == 0 && any_twin) return launch_scan_twins(sa, A, B, Cm, m, n, k, batch, adapt, s);
     if (ml.cls == 0) return launch_scan_shape<0>(sa, A, B, Cm, m, n, k, batch, adapt, s);
+    // TR-FDPA with the products in registers from six sets on: forming them, and the registers they take, cost a launch of few sets more than
+    // the models save.  gfx950's sets of several widths on 2^15 tiles of 16x16x16 FP16, N(0,1), products formed for every model and
+    // kept, 1, 4, 6, 8, 12, 16 sets: 55, 166, 232, 281, 411, 525 us and 66, 172, 231, 270, 385, 487; all bit patterns 82, 283, 407, 505, 717,
+    // 951 and 72, 194, 262, 315, 440, 567.
+    if (ml.cls <= 3 && !adapt && k <= 16 && ml.count >= 6) return launch_scan_shape<4>(sa, A, B, Cm, m, n, k, batch, false, s);
     if (ml.cls <= 3) return launch_scan_shape<1>(sa, A, B, Cm, m, n, k, batch, adapt, s);
     if (ml.cls <= 6) return launch_scan_shape<2>(sa, A, B, Cm, m, n, k, batch, false, s);
     return launch_scan_shape<3>(sa, A, B, Cm, m, n, k, batch, false, s);

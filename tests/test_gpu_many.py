@@ -381,6 +381,41 @@ def test_tr_fdpa_sets_in_the_fused_kernel(mm, ta, tb, m, k):
             assert_same(got_D[i][t:t + 1, :4], o1_emulate(plist[i], A[t:t + 1, :4], B[t:t + 1], C[t:t + 1, :4], ta, tb), "rational oracle, set %d tile %d" % (i, t))
 
 
+def rd_class(p):
+    """The launch that the binding puts a TR-FDPA set into."""
+    return (2 if p.ftz_in else 1) if p.skip_zero_terms else 0
+
+
+@pytest.mark.parametrize("cls", [0, 1, 2])
+@pytest.mark.parametrize("count", [5, 6, 16])
+@pytest.mark.parametrize("ta,tb,m,k", [(fm.FP16, fm.FP16, 16, 16), (fm.FP16, fm.FP16, 32, 8), (fm.E5M2, fm.E4M3, 32, 16), (fm.FP16, fm.E5M2, 16, 16),
+                                       (fm.E4M3, fm.E4M3, 16, 32)])
+def test_tr_fdpa_launches_on_either_side_of_the_kept_products(mm, ta, tb, m, k, count, cls):
+    # five sets to a launch go through the kernel that forms the products for every model, six and more through the one
+    # that keeps them (up to 16 k); ordinary data, whose tiles stay on the common way, beside the whole formats with NaN and
+    # infinities, in the same launch.  `cls` 0 mixes models with and without input flushes.
+    rng = np.random.default_rng(17000 + 1000 * cls + 100 * ta + 10 * tb + m + k + count)
+    nb = 27
+    A, B, C = make_case(rng, ta, tb, nb, m, m, k, special_frac=0.003)
+    third = nb // 3
+    A[:third], B[:third] = top_of_binade(rng, (third, m, k), ta), top_of_binade(rng, (third, m, k), tb)
+    C[:third] = synth.narrow_exponent_bits(rng, (third, m, m), fm.FP32, 120, 136)
+    A[third:2 * third] = synth.narrow_exponent_bits(rng, (third, m, k), ta, 1, 14)
+    B[third:2 * third] = synth.narrow_exponent_bits(rng, (third, m, k), tb, 1, 14)
+    A = synth.sprinkle(rng, A, np.array([0, 1 << (A.dtype.itemsize * 8 - 1)], dtype=A.dtype), 0.05)
+    C = np.where(rng.random(C.shape) < 0.1, np.uint32(0x80000000), C).astype(np.uint32)
+    plist = [p for p in rd_sets(rng, k, 40 * count) if rd_class(p) == cls][:count]
+    for i, F in enumerate((24, 27, 28, 29, 30, 31, 33)[:count - 1]):               # the widths where the arithmetic changes
+        plist[i] = plist[i].with_(frac_bits=F, frac_bits_acc=0, frac_bits2=31)
+    assert len(plist) == count
+    want = oracle_outputs(plist, A, B, C, ta, tb)
+    st, D, kern, _ = run_many(mm, plist, A, B, C, ta, tb, ref=want[0])
+    assert kern.startswith("multi x%d tiled" % count) and kern.endswith(" kept rd") == (count >= 6 and k <= 16), kern
+    for p, d, w, s in zip(plist, D, want, st):
+        assert_same(d, w, str(p))
+        assert s == ostats.compare(w, want[0]), p
+
+
 @pytest.mark.parametrize("ta,tb,m,k", [(fm.FP16, fm.FP16, 16, 16), (fm.E4M3, fm.E5M2, 16, 32), (fm.FP16, fm.FP16, 32, 8), (fm.E5M2, fm.E5M2, 32, 16),
                                        (fm.E4M3, fm.E4M3, 16, 16), (fm.FP16, fm.E5M2, 16, 32)])
 def test_split_group_sets_in_the_fused_kernel(mm, ta, tb, m, k):
