@@ -106,6 +106,31 @@ def test_tf32_tiled_kernels(mm, shape):
         assert_same(got, want, "tf32 tiled %s %s" % (shape, p))
 
 
+@pytest.mark.parametrize("ftz_in,skip_zero,cm", [(False, False, C_IN_GROUP), (True, False, C_AFTER_EXACT), (False, True, C_AFTER_RD), (True, True, C_AFTER_RD),
+                                                 (True, False, C_AFTER_RD)])
+def test_tf32_edge_codes_within_a_quad(mm, ftz_in, skip_zero, cm):
+    # four elements are staged together: one or more of a quad on either side of every line the staging draws (zeros, the
+    # least and largest subnormal and normal, the ends of binary32's safe products, infinities, NaN), the others ordinary; the
+    # 13 surplus bits at random, so that a NaN's payload may lie in them alone
+    rng = np.random.default_rng(9300 + ftz_in + 2 * skip_zero + 4 * cm)
+    nb, m, k = 24, 16, 16
+    edge = np.array([0, 1 << 13, 0x3FF << 13, 1 << 23, 95 << 23, (96 << 23) - 8192, 96 << 23, 158 << 23, (159 << 23) - 8192, 159 << 23,
+                     254 << 23, 0x7F7FE000, 0x7F800000, 0x7FC00000, 0x7F802000], dtype=np.uint32)
+    A, B = (synth.narrow_exponent_bits(rng, (nb, m, k), fm.TF32, 120, 134) for _ in range(2))
+    for t in range(nb):
+        codes = edge[t % len(edge):][:1] if t < len(edge) else edge
+        for X in (A, B):
+            X[t] = np.where(rng.random((m, k)) < (0.03, 0.3)[t % 2], rng.choice(codes, (m, k)) | (rng.integers(0, 2, (m, k)).astype(np.uint32) << 31), X[t])
+    A, B = (X | rng.integers(0, 8192, X.shape).astype(np.uint32) for X in (A, B))
+    C = synth.narrow_exponent_bits(rng, (nb, m, m), fm.FP32, 110, 140)
+    p = ModelParams(group_len=8, frac_bits=24, frac_bits2=31 if cm == C_AFTER_RD else 0, c_mode=cm, out_round=RNE if cm else RZ, ftz_in=ftz_in,
+                    skip_zero_terms=skip_zero, nan_bits=0x7FC00000)
+    want, _ = o2lib.emulate_mma(p, A, B, C, fm.TF32, fm.TF32)
+    got = gpu_emulate(mm, p, A, B, C, fm.TF32, fm.TF32)
+    assert gpu_emulate.last_kernel.startswith("tiled") and gpu_emulate.last_kernel.endswith("vm=4"), gpu_emulate.last_kernel
+    assert_same(got, want, "tf32 edges %s" % (p,))
+
+
 def test_tf32_tiled_equals_general_kernel_on_the_paper_sets(mm):
     # the same problem through both routes: F = 30 sends TF32 to the general kernel, and with products of a few bits
     # F = 29 and F = 30 give the same sums
