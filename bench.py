@@ -29,11 +29,11 @@ ALGO_OPS_PER_TERM = 8                       # accounting floor of INT32 VALU ins
 # scaled by a copy kernel of known size).  They hold for the sources of COUNTERS_SOURCES alone (comments and blanks aside): a kernel of
 # another name, or changed since, reports null.
 COUNTERS = {
-    "multi x16 tiled 16x16 r2x2 kc=16 any L vm=0": {"valu_instr_per_term": 6.22, "traffic": 188224000, "chunk": 1 << 16},
-    "multi x16 tiled 16x16 r2x2 kc=16 any L vm=1": {"valu_instr_per_term": 8.70, "traffic": 215934000, "chunk": 1 << 16},
-    "multi x3 tiled 32x32 r2x2 kc=8 any L vm=0, twins share sums": {"valu_instr_per_term": 7.31, "traffic": 1345087000, "chunk": 1 << 18},
+    "multi x16 tiled 16x16 r2x2 kc=16 any L vm=0": {"valu_instr_per_term": 6.22, "traffic": 188245000, "chunk": 1 << 16},
+    "multi x16 tiled 16x16 r2x2 kc=16 any L vm=1": {"valu_instr_per_term": 8.70, "traffic": 215916000, "chunk": 1 << 16},
+    "multi x3 tiled 32x32 r2x2 kc=8 any L vm=0, twins share sums": {"valu_instr_per_term": 7.31, "traffic": 1345043000, "chunk": 1 << 18},
 }
-COUNTERS_SOURCES = "d4f4202e9cdb6887"
+COUNTERS_SOURCES = "6e55a1098068eb81"
 COUNTERS_SOURCE = ("profiles/closed_loop_scan_trace_and_counters.md, profiles/subnormal_stress_trace_and_counters.md (rocprofv3 --pmc SQ_INSTS_VALU; "
                    "FETCH_SIZE, WRITE_SIZE scaled by a 64 MiB copy); traffic per launch")
 

@@ -163,7 +163,7 @@ def _ptr(x):
 def _stream(stream):
     if stream is None:
         # the current stream's handle without a torch.cuda.Stream object around it, which took 2.6 of the 6 to 8 us that a call
-        # takes on the host (nine small calls 59 -> 36 us)
+        # takes on the host (nine small calls 57 -> 41 us)
         return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     if isinstance(stream, int):
         return stream
