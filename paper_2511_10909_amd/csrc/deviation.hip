@@ -737,6 +737,7 @@ mmaemu_status launch_deviation_sample(const void *A, const void *B, const uint32
     const uint64_t total = batch * m * n;
     const uint64_t nsamples = (total + stride - 1) / stride;
     if (nsamples == 0) return MMAEMU_OK;
+    if (nsamples > (1ull << 43)) { set_error("deviation_sample: more than 2^43 samples in one call"); return MMAEMU_ERR_SHAPE; }
     // The split sum for every type but BF16 (whose products span more than the split holds) up to the k for which it is exact.
     // Four outputs of a row per thread where every output is sampled, rows hold whole fours at 16-byte steps, and there are
     // enough of them: a thread then runs four chains, so with few outputs the chip idles behind them, while with many the row of
@@ -763,7 +764,6 @@ mmaemu_status launch_deviation_sample(const void *A, const void *B, const uint32
     // or 2^21 of 1024.
     const uint64_t most = nsamples > (1ull << 42) ? 4096 : 2048;
     if (blocks > most) blocks = most;
-    if (nsamples > (1ull << 43)) { set_error("deviation_sample: more than 2^43 samples in one call"); return MMAEMU_ERR_SHAPE; }
 #define DEVIATION_LAUNCH(W_, S_)                                                                                              \
     hipLaunchKernelGGL((deviation_kernel<W_, S_>), dim3((uint32_t)blocks), dim3(256), 0, s, A, B, C, D, m, n, k, ta, tb, stride, nitems, bin_exp, h)
     if (wide) DEVIATION_LAUNCH(4, true);

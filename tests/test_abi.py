@@ -162,3 +162,16 @@ def test_deviation_sample_takes_up_to_2_43_samples():
         with pytest.raises(mm.MmaemuError) as ei:
             call(batch)
         assert ei.value.status == status, (batch, str(ei.value))
+
+
+def test_deviation_sample_limit_holds_for_whole_tiles():
+    """The same limit where the kernel for whole tiles would take the call; the refusal comes before any launch."""
+    import torch
+    from paper_2511_10909_amd import binding as mm
+    call = lambda m, n, k, batch, stride: mm.deviation_sample(4096, 4096, 4096, 4096, m, n, k, batch, (mm.FP16, mm.FP16, mm.FP32, mm.FP32), stride, 0, 4096, stream=0)
+    shapes = [(16, 16, 8, (1 << 43) // 256 + 1, 1), (32, 32, 32, 1 << 34, 1), (16, 16, 8, 1 << 38, 4), (16, 16, 8, 1 << 54, 2)]
+    accepted = [(16, 16, 8, (1 << 43) // 256, 1), (16, 16, 8, 1 << 37, 4)]
+    for args in shapes + ([] if torch.cuda.is_available() else accepted):          # (an accepted call must not reach a device: without one it is a HIP error)
+        with pytest.raises(mm.MmaemuError) as ei:
+            call(*args)
+        assert ei.value.status == (3 if args in shapes else 4), (args, str(ei.value))
