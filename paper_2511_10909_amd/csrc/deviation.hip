@@ -363,7 +363,11 @@ deviation_kernel(const void *__restrict__ A, const void *__restrict__ B, const u
 // Bound: HBM (C and D are read once, 8 bytes per output): 2^24 outputs of 32x32x8 FP16 tiles 114 -> 47 us (3.2 TB/s).  Blocks of 32 rows
 // took 54: fewer wavefronts to hide the loads behind; 256, 1024 and 2048 workgroups for 512 took 55, 48 and 62 (each ends in
 // atomics on the same lines).
-constexpr int TILE_COPIES = 32, TILE_BINS = MMAEMU_DEVIATION_BINS + 1;     // (the last row takes what is not counted)
+constexpr int TILE_COPIES = 32, TILE_BINS = MMAEMU_DEVIATION_BINS + 1;     // (the last row takes what is not counted, modulo 2^32)
+constexpr uint64_t MAX_SAMPLES = 1ull << 43, TILE_WORKGROUPS = 512;
+// A workgroup counts at most MAX_SAMPLES / TILE_WORKGROUPS (and one wavefront's more) samples.  Its counters of 32 bits hold them where all
+// fall into one bin: strides of up to four on 16 columns leave a quarter of the copies, so none takes more than an eighth of them.
+static_assert(MAX_SAMPLES / TILE_WORKGROUPS / 8 <= 1ull << 31, "counters of a workgroup");
 
 struct DevTileArgs {
     const uint8_t *A, *B;
@@ -681,10 +685,10 @@ deviation_tile_kernel(DevTileArgs g, mmaemu_deviation_hist *hist)
         if (t) atomicAdd(gc + (threadIdx.x - 64u), t);
     } else if (threadIdx.x >= 128u && threadIdx.x < 128u + NB) {
         const uint32_t bin = threadIdx.x - 128u;
-        uint32_t t = 0;
+        unsigned long long t = 0;                                      // (up to 2^34)
 #pragma unroll
         for (uint32_t q = 0; q < TILE_COPIES; ++q) t += bins[bin * TILE_COPIES + ((q + bin) & (TILE_COPIES - 1))];
-        if (t) atomicAdd(gc + 5 + bin, (unsigned long long)t);
+        if (t) atomicAdd(gc + 5 + bin, t);
     }
 }
 
@@ -716,7 +720,7 @@ static mmaemu_status launch_deviation_tiles(const void *A, const void *B, const 
     auto span = [](const FmtInfo &f) { return (1 << f.ebits) - (f.ieee ? 3 : 2); };     // (subnormals are multiples of the smallest normal numbers' unit)
     g.exact_types = span(fa) + span(fb) <= g.slack ? 1u : 0u;
     uint64_t blocks = (g.nitems + 7) / 8;
-    if (blocks > 512) blocks = 512;
+    if (blocks > TILE_WORKGROUPS) blocks = TILE_WORKGROUPS;
     auto go = [&](auto fp8_c) {
         constexpr bool FP8 = decltype(fp8_c)::value;
         if (wide && stride == 1) hipLaunchKernelGGL((deviation_tile_kernel<FP8, 1, 2, false>), dim3((uint32_t)blocks), dim3(512), 0, s, g, h);
@@ -737,7 +741,7 @@ mmaemu_status launch_deviation_sample(const void *A, const void *B, const uint32
     const uint64_t total = batch * m * n;
     const uint64_t nsamples = (total + stride - 1) / stride;
     if (nsamples == 0) return MMAEMU_OK;
-    if (nsamples > (1ull << 43)) { set_error("deviation_sample: more than 2^43 samples in one call"); return MMAEMU_ERR_SHAPE; }
+    if (nsamples > MAX_SAMPLES) { set_error("deviation_sample: more than 2^43 samples in one call"); return MMAEMU_ERR_SHAPE; }
     // The split sum for every type but BF16 (whose products span more than the split holds) up to the k for which it is exact.
     // Four outputs of a row per thread where every output is sampled, rows hold whole fours at 16-byte steps, and there are
     // enough of them: a thread then runs four chains, so with few outputs the chip idles behind them, while with many the row of
