@@ -519,6 +519,10 @@ mmaemu_status mmaemu_deviation_hist_reset(mmaemu_deviation_hist *dev_hist, void 
 mmaemu_status mmaemu_deviation_sample(const void *A, const void *B, const void *C, const void *D, uint32_t m, uint32_t n,
                                       uint32_t k, uint64_t batch, mmaemu_dtypes dtypes, uint64_t stride, int32_t bin_exp,
                                       mmaemu_deviation_hist *dev_hist, void *hip_stream);
+/* Name of the kernel that mmaemu_deviation_sample takes for these arguments ("whole tiles", "four outputs per thread",
+ * "one output per thread, ..."): decided on the host, no GPU needed, nothing is read or launched; for tests and reports. */
+mmaemu_status mmaemu_deviation_sample_kernel(const void *A, const void *B, const void *C, const void *D, uint32_t m, uint32_t n,
+                                             uint32_t k, uint64_t batch, mmaemu_dtypes dtypes, uint64_t stride, const char **name);
 
 /*
  * Issue-rate probes: the measured counterpart of the vector-ALU peak that the emulation kernels' roofline is quoted

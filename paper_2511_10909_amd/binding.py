@@ -140,6 +140,7 @@ _lib.mmaemu_err_stats_reset.argtypes = [_vp, _vp]
 _lib.mmaemu_exact_dot_sample.argtypes = [_vp, _vp, _vp, _u32, _u32, _u32, Dtypes, _u64, _vp, _vp]
 _lib.mmaemu_deviation_hist_reset.argtypes = [_vp, _vp]
 _lib.mmaemu_deviation_sample.argtypes = [_vp, _vp, _vp, _vp, _u32, _u32, _u32, _u64, Dtypes, _u64, ctypes.c_int32, _vp, _vp]
+_lib.mmaemu_deviation_sample_kernel.argtypes = [_vp, _vp, _vp, _vp, _u32, _u32, _u32, _u64, Dtypes, _u64, ctypes.POINTER(ctypes.c_char_p)]
 
 
 def _status_string(s):
@@ -297,6 +298,15 @@ def deviation_sample(A, B, C, D, m, n, k, batch, dtypes, stride, bin_exp, dev_hi
     dt = dtypes if isinstance(dtypes, Dtypes) else Dtypes(*dtypes)
     _check(_lib.mmaemu_deviation_sample(_ptr(A), _ptr(B), _ptr(C) if C is not None else None, _ptr(D), m, n, k, batch, dt, stride,
                                         bin_exp, _ptr(dev_hist), _stream(stream)))
+
+
+def deviation_sample_kernel(A, B, C, D, m, n, k, batch, dtypes, stride):
+    """Name of the kernel that deviation_sample takes for these arguments; nothing is read or launched."""
+    dt = dtypes if isinstance(dtypes, Dtypes) else Dtypes(*dtypes)
+    name = ctypes.c_char_p()
+    _check(_lib.mmaemu_deviation_sample_kernel(_ptr(A), _ptr(B), _ptr(C) if C is not None else None, _ptr(D), m, n, k, batch, dt, stride,
+                                               ctypes.byref(name)))
+    return name.value.decode()
 
 
 # ---- unpacking of the device-side result structs (host copies; no arithmetic) -----------

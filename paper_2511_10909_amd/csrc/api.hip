@@ -821,9 +821,8 @@ mmaemu_status mmaemu_deviation_hist_reset(mmaemu_deviation_hist *h, void *hip_st
     return launch_deviation_reset(h, (hipStream_t)hip_stream);
 }
 
-mmaemu_status mmaemu_deviation_sample(const void *A, const void *B, const void *C, const void *D, uint32_t m, uint32_t n,
-                                      uint32_t k, uint64_t batch, mmaemu_dtypes dt, uint64_t stride, int32_t bin_exp,
-                                      mmaemu_deviation_hist *h, void *hip_stream)
+static mmaemu_status check_deviation(const void *A, const void *B, const void *C, const void *D, uint32_t m, uint32_t n, uint32_t k, uint64_t batch,
+                                     mmaemu_dtypes dt, uint64_t stride, int32_t bin_exp, const mmaemu_deviation_hist *h)
 {
     if (!A || !B || !D || !h) { set_error("deviation_sample: NULL pointer"); return MMAEMU_ERR_INVALID_ARG; }
     if (((uintptr_t)D & 3) || ((uintptr_t)C & 3) || ((uintptr_t)h & 7)) { set_error("deviation_sample: misaligned pointer"); return MMAEMU_ERR_INVALID_ARG; }
@@ -836,9 +835,29 @@ mmaemu_status mmaemu_deviation_sample(const void *A, const void *B, const void *
     }
     if (((uintptr_t)A & (is_byte_type(dt.a) ? 0 : 1)) || ((uintptr_t)B & (is_byte_type(dt.b) ? 0 : 1))) { set_error("deviation_sample: misaligned operands"); return MMAEMU_ERR_INVALID_ARG; }
     if (bin_exp < -280 || bin_exp > 250) { set_error("deviation_sample: bin_exp outside -280 .. 250"); return MMAEMU_ERR_INVALID_ARG; }
+    return MMAEMU_OK;
+}
+
+mmaemu_status mmaemu_deviation_sample(const void *A, const void *B, const void *C, const void *D, uint32_t m, uint32_t n,
+                                      uint32_t k, uint64_t batch, mmaemu_dtypes dt, uint64_t stride, int32_t bin_exp,
+                                      mmaemu_deviation_hist *h, void *hip_stream)
+{
+    const mmaemu_status st = check_deviation(A, B, C, D, m, n, k, batch, dt, stride, bin_exp, h);
+    if (st != MMAEMU_OK) return st;
     if (batch == 0) return MMAEMU_OK;
     return launch_deviation_sample(A, B, (const uint32_t *)C, (const uint32_t *)D, m, n, k, batch, dt.a, dt.b, stride, bin_exp, h,
                                    (hipStream_t)hip_stream);
+}
+
+mmaemu_status mmaemu_deviation_sample_kernel(const void *A, const void *B, const void *C, const void *D, uint32_t m, uint32_t n,
+                                             uint32_t k, uint64_t batch, mmaemu_dtypes dt, uint64_t stride, const char **name)
+{
+    if (!name) { set_error("deviation_sample_kernel: NULL pointer"); return MMAEMU_ERR_INVALID_ARG; }
+    alignas(8) static const mmaemu_deviation_hist none = {};
+    const mmaemu_status st = check_deviation(A, B, C, D, m, n, k, batch, dt, stride, 0, &none);
+    if (st != MMAEMU_OK) return st;
+    *name = deviation_kernel_name(A, B, C, D, m, n, k, batch, dt.a, dt.b, stride);
+    return MMAEMU_OK;
 }
 
 } // extern "C"

@@ -164,6 +164,8 @@ mmaemu_status launch_deviation_reset(mmaemu_deviation_hist *h, hipStream_t s);
 mmaemu_status launch_deviation_sample(const void *A, const void *B, const uint32_t *C, const uint32_t *D, uint32_t m, uint32_t n,
                                       uint32_t k, uint64_t batch, uint32_t ta, uint32_t tb, uint64_t stride, int bin_exp,
                                       mmaemu_deviation_hist *h, hipStream_t s);
+const char *deviation_kernel_name(const void *A, const void *B, const void *C, const void *D, uint32_t m, uint32_t n, uint32_t k, uint64_t batch,
+                                  uint32_t ta, uint32_t tb, uint64_t stride);
 
 // issue-rate probes (issue_rate.hip)
 uint32_t issue_probe_count();

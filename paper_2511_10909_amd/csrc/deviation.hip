@@ -734,14 +734,13 @@ static mmaemu_status launch_deviation_tiles(const void *A, const void *B, const 
     return MMAEMU_OK;
 }
 
-mmaemu_status launch_deviation_sample(const void *A, const void *B, const uint32_t *C, const uint32_t *D, uint32_t m, uint32_t n,
-                                      uint32_t k, uint64_t batch, uint32_t ta, uint32_t tb, uint64_t stride, int bin_exp,
-                                      mmaemu_deviation_hist *h, hipStream_t s)
+// The kernel for a call
+enum class DevKernel { WholeTiles, FourOutputs, SplitSum, Pairs };
+
+static DevKernel deviation_kernel_for(const void *A, const void *B, const void *C, const void *D, uint32_t m, uint32_t n, uint32_t k, uint64_t batch,
+                                      uint32_t ta, uint32_t tb, uint64_t stride)
 {
-    const uint64_t total = batch * m * n;
-    const uint64_t nsamples = (total + stride - 1) / stride;
-    if (nsamples == 0) return MMAEMU_OK;
-    if (nsamples > MAX_SAMPLES) { set_error("deviation_sample: more than 2^43 samples in one call"); return MMAEMU_ERR_SHAPE; }
+    const uint64_t total = batch * m * n, nsamples = (total + stride - 1) / stride;
     // The split sum for every type but BF16 (whose products span more than the split holds) up to the k for which it is exact.
     // Four outputs of a row per thread where every output is sampled, rows hold whole fours at 16-byte steps, and there are
     // enough of them: a thread then runs four chains, so with few outputs the chip idles behind them, while with many the row of
@@ -756,12 +755,35 @@ mmaemu_status launch_deviation_sample(const void *A, const void *B, const uint32
     // 47 to 49; k = 16, 32, 64 163, 256, 442 and 54, 89, 236.  Where the exponents lie too far apart (all finite bit patterns, 16x16 tiles):
     // k = 8, 16, 32 at stride 3 87, 109, 142 and 83, 117, 211; at stride 1, 32x32 tiles, k = 8, 32, 64 114, 255, 443 and 82, 202, 498.  2^17
     // outputs of k = 32 17 and 13, 2^14 10 and 11.
-    if (((ta == MMAEMU_FP16 && tb == MMAEMU_FP16) || (ta <= MMAEMU_FP8_E5M2 && tb <= MMAEMU_FP8_E5M2)) && m % 16 == 0 && n % 16 == 0 && k % 8 == 0 && k * stride <= TILE_MAX_WORK && total >= TILE_MIN_OUTPUTS &&
+    if (((ta == MMAEMU_FP16 && tb == MMAEMU_FP16) || (ta <= MMAEMU_FP8_E5M2 && tb <= MMAEMU_FP8_E5M2)) && m % 16 == 0 && n % 16 == 0 && k % 8 == 0 && stride <= TILE_MAX_WORK / k && total >= TILE_MIN_OUTPUTS &&
         n <= (1u << 24) && (uint64_t)m * n <= (1ull << 38) && ((reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(B)) & 3u) == 0 &&
         (n % 32 != 0 || ((reinterpret_cast<uintptr_t>(C) | reinterpret_cast<uintptr_t>(D)) & 7u) == 0)) {
-        return launch_deviation_tiles(A, B, C, D, m, n, k, batch, ta, tb, (uint32_t)stride, bin_exp, h, s);
+        return DevKernel::WholeTiles;
     }
-    const uint64_t nitems = wide ? nsamples / 4 : nsamples;
+    return wide ? DevKernel::FourOutputs : split ? DevKernel::SplitSum : DevKernel::Pairs;
+}
+
+const char *deviation_kernel_name(const void *A, const void *B, const void *C, const void *D, uint32_t m, uint32_t n, uint32_t k, uint64_t batch,
+                                  uint32_t ta, uint32_t tb, uint64_t stride)
+{
+    switch (deviation_kernel_for(A, B, C, D, m, n, k, batch, ta, tb, stride)) {
+    case DevKernel::WholeTiles: return "whole tiles";
+    case DevKernel::FourOutputs: return "four outputs per thread";
+    case DevKernel::SplitSum: return "one output per thread, split sum";
+    default: return "one output per thread, pairs";
+    }
+}
+
+mmaemu_status launch_deviation_sample(const void *A, const void *B, const uint32_t *C, const uint32_t *D, uint32_t m, uint32_t n,
+                                      uint32_t k, uint64_t batch, uint32_t ta, uint32_t tb, uint64_t stride, int bin_exp,
+                                      mmaemu_deviation_hist *h, hipStream_t s)
+{
+    const uint64_t nsamples = (batch * m * n + stride - 1) / stride;
+    if (nsamples == 0) return MMAEMU_OK;
+    if (nsamples > MAX_SAMPLES) { set_error("deviation_sample: more than 2^43 samples in one call"); return MMAEMU_ERR_SHAPE; }
+    const DevKernel kernel = deviation_kernel_for(A, B, C, D, m, n, k, batch, ta, tb, stride);
+    if (kernel == DevKernel::WholeTiles) return launch_deviation_tiles(A, B, C, D, m, n, k, batch, ta, tb, (uint32_t)stride, bin_exp, h, s);
+    const uint64_t nitems = kernel == DevKernel::FourOutputs ? nsamples / 4 : nsamples;
     uint64_t blocks = (nitems + 255) / 256;
     // Grid-stride beyond 2048 workgroups (two rounds of what the chip holds); beyond 2^42 samples 4096, so that no workgroup
     // counts more than 2^31: its rounds of 256 items come to nitems / 2^19 (2^20) rounded up, at most 2^23 rounds of 256 samples
@@ -770,8 +792,8 @@ mmaemu_status launch_deviation_sample(const void *A, const void *B, const uint32
     if (blocks > most) blocks = most;
 #define DEVIATION_LAUNCH(W_, S_)                                                                                              \
     hipLaunchKernelGGL((deviation_kernel<W_, S_>), dim3((uint32_t)blocks), dim3(256), 0, s, A, B, C, D, m, n, k, ta, tb, stride, nitems, bin_exp, h)
-    if (wide) DEVIATION_LAUNCH(4, true);
-    else if (split) DEVIATION_LAUNCH(1, true);
+    if (kernel == DevKernel::FourOutputs) DEVIATION_LAUNCH(4, true);
+    else if (kernel == DevKernel::SplitSum) DEVIATION_LAUNCH(1, true);
     else DEVIATION_LAUNCH(1, false);
 #undef DEVIATION_LAUNCH
     MMAEMU_HIP(hipGetLastError());

@@ -175,3 +175,29 @@ def test_deviation_sample_limit_holds_for_whole_tiles():
         with pytest.raises(mm.MmaemuError) as ei:
             call(*args)
         assert ei.value.status == (3 if args in shapes else 4), (args, str(ei.value))
+
+
+def test_deviation_sample_kernel_for_a_call():
+    """Each side of every condition on the kernel for whole tiles, strides whose product with k leaves 64 bits among them."""
+    from paper_2511_10909_amd import binding as mm
+    base = dict(A=4096, B=4096, C=4096, D=4096, m=32, n=32, k=8, batch=128, a=mm.FP16, b=mm.FP16, stride=1)
+    def kernel(**kw):
+        c = dict(base, **kw)
+        return mm.deviation_sample_kernel(c["A"], c["B"], c["C"], c["D"], c["m"], c["n"], c["k"], c["batch"], (c["a"], c["b"], mm.FP32, mm.FP32), c["stride"])
+    for kw in ({}, dict(C=None), dict(stride=4), dict(k=32), dict(k=16, stride=2), dict(k=24), dict(A=4100, B=4108), dict(C=4104, D=4112), dict(n=16, m=64, C=4100, D=4108),
+               dict(a=mm.E4M3, b=mm.E5M2), dict(m=16, n=16, batch=512), dict(m=48, n=48, batch=57)):
+        assert kernel(**kw) == "whole tiles", kw
+    one, four = "one output per thread, split sum", "four outputs per thread"
+    for kw, want in ((dict(stride=5), one), (dict(stride=33), one), (dict(k=16, stride=3), one), (dict(k=32, stride=2), one), (dict(k=40), one), (dict(k=9), one),
+                     (dict(batch=127), one), (dict(A=4098), one), (dict(B=4098), one), (dict(C=4100), one), (dict(D=4100), one), (dict(a=mm.E4M3, B=4097, b=mm.E4M3), one),
+                     (dict(m=31, batch=133), one), (dict(n=36), one), (dict(a=mm.FP16, b=mm.E4M3), one), (dict(a=mm.E2M3, b=mm.E2M3), one),
+                     (dict(a=mm.BF16, b=mm.BF16), "one output per thread, pairs"), (dict(k=40, batch=512), four), (dict(k=64, batch=256), one),
+                     (dict(n=1 << 25, m=16, batch=1), four), (dict(k=1 << 14), "one output per thread, pairs")):
+        assert kernel(**kw) == want, kw
+    for k in (8, 16, 24, 32):
+        for stride in [(1 << 64) // k + d for d in range(4)] + [(1 << e) + d for e in (32, 59, 60, 61, 62, 63) for d in (0, 1, 2, 4)] + [(1 << 64) - (1 << 20)]:
+            assert kernel(k=k, stride=stride) == one, (k, stride)
+    for kw, status in ((dict(stride=0), 3), (dict(D=None), 1), (dict(A=4097), 1), (dict(a=mm.TF32), 2)):
+        with pytest.raises(mm.MmaemuError) as ei:
+            kernel(**kw)
+        assert ei.value.status == status, kw

@@ -236,6 +236,18 @@ def test_deviation_sample_whole_tiles(mm, ta, tb, m, n, k, stride, with_c, exps,
     same_hist(dev_hist(mm, A, B, C if with_c else None, D, ta, tb, stride, -5), want, (ta, tb, m, n, k, stride, special))
 
 
+@pytest.mark.parametrize("stride", [(1 << 61) + 1, 1 << 61, 1 << 63, (1 << 32) + 1])
+def test_deviation_sample_strides_beyond_the_outputs(mm, stride):
+    """One sample, output 0, also where the product of stride and k leaves 64 bits."""
+    rng = np.random.default_rng(17)
+    nb, m, n, k = 513, 16, 16, 8
+    A, B = synth.narrow_exponent_bits(rng, (nb, m, k), fm.FP16, 10, 20), synth.narrow_exponent_bits(rng, (nb, n, k), fm.FP16, 10, 20)
+    C = synth.narrow_exponent_bits(rng, (nb, m, n), fm.FP32, 118, 132)
+    got = dev_hist(mm, A, B, C, C, fm.FP16, fm.FP16, stride, -5)
+    same_hist(got, deviation_hist(A[:1], B[:1], C[:1], C[:1], fm.FP16, fm.FP16, 256, -5), stride)
+    assert got["n_samples"] == 1
+
+
 def test_few_outputs_with_long_rows_keep_one_per_thread(mm):
     """4096 outputs of 4096 terms: as fast as the call whose accumulator is not 16-byte aligned, which always runs one output
     per thread (four per thread took 2.6 times as long)."""
