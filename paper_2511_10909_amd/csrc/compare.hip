@@ -2,7 +2,7 @@
 // Sec. 3.1 Step 4: the model must reproduce the interface bit by bit).
 //
 // HBM-bound: 8 (4) bytes read per compared pair.  Each lane handles four (eight) consecutive
-// elements (one 128-bit load per input), four such loads in flight at once; a wavefront whose vectors are equal leaves them alone
+// elements (one 128-bit load per input), four or two such loads in flight at once; a wavefront whose vectors are equal leaves them alone
 // (2^19 equal pairs 6.7 -> 2.3 us, 2^22 7.5 -> 3.4).  The histogram is kept in LDS in 32 copies per
 // bucket (copy = lane mod 32), so that lanes counting the same bucket do not serialise
 // on one address; counters are flushed with one global atomic per non-zero counter per
@@ -139,7 +139,8 @@ __device__ __forceinline__ void wg_flush(WgStats &ws, Local lc, uint64_t count, 
     }
 }
 
-template <int W, typename T>
+// N: 128-bit loads per input in flight
+template <int W, int N, typename T>
 __global__ void __launch_bounds__(1024)
 compare_kernel(const T *__restrict__ d0, const T *__restrict__ d1, uint64_t count, uint64_t base, mmaemu_stats *st)
 {
@@ -156,12 +157,12 @@ compare_kernel(const T *__restrict__ d0, const T *__restrict__ d1, uint64_t coun
     if (aligned) {
         const uint4 *v0 = reinterpret_cast<const uint4 *>(d0), *v1 = reinterpret_cast<const uint4 *>(d1);
         uint64_t v = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-        for (; v + 3 * stride < nvec; v += 4 * stride) {           // four independent 128-bit loads per input in flight
-            uint4 x[4], y[4];
+        for (; v + (N - 1) * stride < nvec; v += N * stride) {
+            uint4 x[N], y[N];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) { x[i] = v0[v + i * stride]; y[i] = v1[v + i * stride]; }
+            for (int i = 0; i < N; ++i) { x[i] = v0[v + i * stride]; y[i] = v1[v + i * stride]; }
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+            for (int i = 0; i < N; ++i)
                 if (__any(differ(x[i], y[i]))) one_vector<W>(x[i], y[i], base + EPV * (v + i * stride), lc, maxd, hist);
         }
         for (; v < nvec; v += stride) {
@@ -241,11 +242,17 @@ mmaemu_status launch_compare64(const void *d0, const void *d1, uint64_t count, u
     return MMAEMU_OK;
 }
 
+// Pairs of binary32 up to which four loads per input are in flight, two beyond: long streams of differing pairs are slower with four.  Two
+// and four, us, equal / 0.01 % / 1 % / 80 % differing: 2^22 4.5, 11.4, 15.9, 16.2 and 4.4, 10.8, 16.1, 16.4; 2^24 20.3, 26.6, 28.9, 28.3 and 20.5,
+// 26.8, 29.3, 28.5; 2^26 86, 88, 91, 93 and 88, 91, 97, 100; 2^28 345, 346, 357, 357 and 356, 360, 380, 385.  binary16 (twice the arithmetic per
+// byte): 2^29 pairs 345, 348, 481, 511 and 358, 365, 468, 496.
+constexpr uint64_t COMPARE_FOUR_LOADS = 1ull << 23;
+
 mmaemu_status launch_compare(const void *d0, const void *d1, uint64_t count, uint64_t base, bool half,
                              mmaemu_stats *st, hipStream_t s)
 {
     // Few, fat workgroups: a workgroup with differing pairs ends with atomics on up to 38 words of the same few lines, and
-    // those serialise across the chip (about 30 ns per workgroup: 2^24 pairs, 256 workgroups, 20.5 us equal and 33 differing),
+    // those serialise across the chip (about 30 ns per workgroup: 2^24 pairs, 256 workgroups, 20.3 us equal and 28.3 differing),
     // so beyond 64 workgroups one covers at least 16K pairs before it pays for them; up to there 4K, one vector of each input per thread (2^14
     // pairs, 80 % differing, workgroups of 4K, 8K, 16K pairs 5.4, 6.3, 8.8 us; 2^18 7.3, 7.1, 9.2; 2^20 14.3, 10.5, 10.9).  1024 threads each, so that a
     // workgroup has 16 waves' worth of loads in flight (a small comparison is latency-bound).  One workgroup per CU at most: with two, equal inputs streamed
@@ -256,10 +263,13 @@ mmaemu_status launch_compare(const void *d0, const void *d1, uint64_t count, uin
     if (blocks < 1) blocks = 1;
     if (blocks > 256) blocks = 256;
     if (half)
-        hipLaunchKernelGGL((compare_kernel<16, uint16_t>), dim3((uint32_t)blocks), dim3(1024), 0, s, (const uint16_t *)d0,
+        hipLaunchKernelGGL((compare_kernel<16, 4, uint16_t>), dim3((uint32_t)blocks), dim3(1024), 0, s, (const uint16_t *)d0,
                            (const uint16_t *)d1, count, base, st);
+    else if (count <= COMPARE_FOUR_LOADS)
+        hipLaunchKernelGGL((compare_kernel<32, 4, uint32_t>), dim3((uint32_t)blocks), dim3(1024), 0, s, (const uint32_t *)d0,
+                           (const uint32_t *)d1, count, base, st);
     else
-        hipLaunchKernelGGL((compare_kernel<32, uint32_t>), dim3((uint32_t)blocks), dim3(1024), 0, s, (const uint32_t *)d0,
+        hipLaunchKernelGGL((compare_kernel<32, 2, uint32_t>), dim3((uint32_t)blocks), dim3(1024), 0, s, (const uint32_t *)d0,
                            (const uint32_t *)d1, count, base, st);
     MMAEMU_HIP(hipGetLastError());
     return MMAEMU_OK;

@@ -54,3 +54,19 @@ def test_many_differing_pairs(mm, width, count):
         mm.compare(to_dev(x), to_dev(y), count, st, index_base=base * count, d=dtype)
         want = ostats.compare(x, y, stats=want, index_base=base * count, width=width)
         assert mm.read_stats(st) == want, (lo, hi, frac)
+
+
+@pytest.mark.parametrize("count", [(1 << 23) - 2, 1 << 23, (1 << 23) + 1, (1 << 23) + (1 << 22) + 6])
+def test_both_sides_of_the_loads_in_flight(mm, count):
+    """Up to 2^23 pairs a thread has four loads per input in flight, beyond two: a differing patch at either end and in the middle, and
+    pairs that differ in the vectors that are left over."""
+    rng = np.random.default_rng(count & 0xFFFF)
+    x = rng.integers(0, 1 << 32, size=count, dtype=np.uint32)
+    y = x.copy()
+    for lo, hi, frac in ((0, 3000, 0.5), (count // 2, count // 2 + 20000, 0.01), (count - 1100, count, 0.3)):
+        pick = np.arange(lo, hi)[rng.random(hi - lo) < frac]
+        y[pick] = rng.integers(0, 1 << 32, size=len(pick), dtype=np.uint32)
+    st = dev_empty(mm.STATS_BYTES)
+    mm.stats_reset(st)
+    mm.compare(to_dev(x), to_dev(y), count, st, index_base=11)
+    assert mm.read_stats(st) == ostats.compare(x, y, index_base=11)
