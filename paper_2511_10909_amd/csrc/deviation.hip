@@ -357,17 +357,20 @@ deviation_kernel(const void *__restrict__ A, const void *__restrict__ B, const u
 // multiply-adds that is exact while every product is a multiple of one unit and the sums stay below 2^53 of them.  The types alone may
 // guarantee that (E4M3 x E4M3); else the wavefront takes the largest and the smallest exponent of its rows' elements.  An output's end
 // is four binary64 operations, with four comparisons that say whether they were exact: D - S first, which cancels, then the
-// accumulator.  Outputs for which they were not (or not finite) go on one by one, as a pair of binary64 numbers.
+// accumulator.  Outputs for which they were not follow one after the other, an output of all lanes at a time, as expansions of
+// binary64 numbers, exact for all finite ones: accumulators of 2^30 (some 53 places above the products' unit) or of any exponent 95 us where
+// the others take 38 (2^24 outputs of 32x32x8 FP16; the kernel of four outputs per thread 115 and 2150).  With the expansion beside every
+// output's end they took 68, but the others 39.
 // Where the exponents lie too far apart the wavefront splits every element at 2^-4 into two parts, whose sums of products are exact up
-// to SPLIT_MAX_K, and every output's sum goes on as a pair.
+// to SPLIT_MAX_K, and every output's sum is two numbers.
 // Bound: HBM (C and D are read once, 8 bytes per output): 2^24 outputs of 32x32x8 FP16 tiles 114 -> 47 us (3.2 TB/s).  Blocks of 32 rows
 // took 54: fewer wavefronts to hide the loads behind; 256, 1024 and 2048 workgroups for 512 took 55, 48 and 62 (each ends in
 // atomics on the same lines).
 constexpr int TILE_COPIES = 32, TILE_BINS = MMAEMU_DEVIATION_BINS + 1;     // (the last row takes what is not counted, modulo 2^32)
-constexpr uint64_t MAX_SAMPLES = 1ull << 43, TILE_WORKGROUPS = 512;
-// A workgroup counts at most MAX_SAMPLES / TILE_WORKGROUPS (and one wavefront's more) samples.  Its counters of 32 bits hold them where all
-// fall into one bin: strides of up to four on 16 columns leave a quarter of the copies, so none takes more than an eighth of them.
-static_assert(MAX_SAMPLES / TILE_WORKGROUPS / 8 <= 1ull << 31, "counters of a workgroup");
+// Workgroups, and as many more beyond 2^40 samples that none counts more than 2^31 (a sum of 64 bits at its end, over copies of which
+// none could wrap, cost a launch 0.7 us).
+constexpr uint64_t MAX_SAMPLES = 1ull << 43, TILE_WORKGROUPS = 512, TILE_WORKGROUPS_MANY = 4096;
+static_assert((1ull << 40) / TILE_WORKGROUPS <= 1ull << 31 && MAX_SAMPLES / TILE_WORKGROUPS_MANY <= 1ull << 31, "counters of a workgroup");
 
 struct DevTileArgs {
     const uint8_t *A, *B;
@@ -424,33 +427,39 @@ struct Span {
     }
 };
 
-// One output the long way: its binary64 image and bin, or the row that is not counted.  sum_hi and sum_lo are the
-// products' sum as SplitSum forms it.
-struct Settled { double h; uint32_t bin; };
-__device__ __noinline__ Settled settle_output(const uint8_t *a, const uint8_t *b, uint32_t k, uint32_t ta, uint32_t tb, int bin_exp, double sum_hi, double sum_lo,
-                                              uint32_t cb, uint32_t db)
+// delta = d - s - low - c (finite; low only where LOW) exactly, as an expansion: h, delta rounded once, and q, floor(delta / 2^bin_exp).  One
+// summand after the other goes through the parts so far from the smallest upward, which leaves parts that do not overlap (Shewchuk 1997);
+// on the way down again they become h and remainders, of which the first that is not zero has the sign of delta - h.
+template <bool LOW>
+__device__ __forceinline__ void place_expansion(double d, double s, double low, double c, int bin_exp, double &h, double &q)
 {
-    constexpr int NB = MMAEMU_DEVIATION_BINS;
-    const double finite_max = 0x1.fffffffffffffp+1023;
-    Settled out = {0.0, (uint32_t)NB};
-    if ((cb & 0x7F800000u) == 0x7F800000u || (db & 0x7F800000u) == 0x7F800000u || !(__builtin_fabs(sum_hi) <= finite_max) || !(__builtin_fabs(sum_lo) <= finite_max)) return out;
-    ExactPair pr;
-    pr.start(db);
-    double residue;
-    two_sum(pr.hi, -sum_hi, pr.hi, pr.lo);
-    two_sum(pr.lo, -sum_lo, pr.lo, residue);
-    pr.lost = __builtin_fabs(residue);
-    pr.add(-(double)__uint_as_float(cb), 1.0);
-    uint32_t neg;
-    bool zero;
-    int fi;
-    double ad;
-    if (pr.lost == 0.0) place_pair(pr, bin_exp, neg, zero, fi, ad);
-    else delta_wide(dyn_fmt(ta), dyn_fmt(tb), a, b, k, cb, db, bin_exp - XBASE, neg, zero, fi, ad);
-    int bin = zero ? NB / 2 : fi + NB / 2;
-    out.bin = (uint32_t)(bin < 0 ? 0 : (bin > NB - 1 ? NB - 1 : bin));
-    out.h = zero ? 0.0 : (neg ? -ad : ad);
-    return out;
+    double e0 = 0.0, e1, e2, e3, t, u;
+    two_sum(d, -s, u, t);
+    if constexpr (LOW) {
+        double f1, f2;
+        two_sum(t, -low, t, e0);
+        two_sum(u, t, f2, f1);
+        two_sum(e0, -c, t, e0);
+        two_sum(f1, t, t, e1);
+        two_sum(f2, t, e3, e2);
+    } else {
+        two_sum(t, -c, t, e1);
+        two_sum(u, t, e3, e2);
+    }
+    double r1, r2, r3, r4;
+    two_sum(e3, e2, e3, r1);
+    two_sum(r1, e1, r2, r3);
+    two_sum(e3, r2, h, r4);
+    double rest = r4 != 0.0 ? r4 : r3;
+    if constexpr (LOW) {
+        two_sum(r3, e0, t, r3);
+        two_sum(r4, t, t, r4);
+        two_sum(h, t, h, rest);
+        rest = rest != 0.0 ? rest : (r4 != 0.0 ? r4 : r3);
+    }
+    const double qh = ldexp(h, -bin_exp);
+    q = __builtin_floor(qh);
+    if (q == qh && rest < 0.0) q -= 1.0;                                 // (a fractional h / w lies further from the next whole number)
 }
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
@@ -458,7 +467,7 @@ typedef double f64x4 __attribute__((ext_vector_type(4)));
 // What a lane sums up and what its wavefront counts.  `bin` NB: not counted (h is zero then).
 struct DevTally {
     double sum = 0.0, sum_abs = 0.0, sum_sq = 0.0;
-    uint32_t neg = 0, zero = 0, out = 0, bad = 0;                       // out: not sampled, or left to be settled; bad: skipped (both come with h = 0)
+    uint32_t neg = 0, zero = 0, out = 0, bad = 0;                       // out: not sampled; bad: skipped (both come with h = 0)
     __device__ __forceinline__ void take(double h, uint32_t bin, uint32_t lane, uint32_t *bins)
     {
         neg += (uint32_t)__popcll(__ballot(h < 0.0));
@@ -556,9 +565,9 @@ deviation_tile_kernel(DevTileArgs g, mmaemu_deviation_hist *hist)
             split = (int)((xa & 0xFFFFu) + (xa >> 16) + (xb & 0xFFFFu) + (xb >> 16)) - 2 * 511 > g.slack || (xa & 0xFFFFu) == 255u || (xb & 0xFFFFu) == 255u;
         }
         tally.neg = tally.zero = tally.out = tally.bad = 0;
-        uint32_t open = 0;                                            // outputs left to be settled: bit (4 r + v) CB + c
-        // one output's end; LOW: the products' sum is s + low where `held`
-        auto end = [&](auto low_c, int rv, int c, uint32_t dbits, uint32_t cbits, double s, double low, bool held, bool in) {
+        uint32_t open = 0;                                            // outputs whose end was not exact, bit (4 r + v) CB + c; 0 where split
+        // one output's end; LOW: the products' sum is s + low
+        auto end = [&](auto low_c, int i, uint32_t dbits, uint32_t cbits, double s, double low, bool in) {
             constexpr bool LOW = decltype(low_c)::value;
             const double dd = (double)__uint_as_float(dbits), cc = (double)__uint_as_float(cbits);
             // (a difference is exact where adding it to the one, and taking it from the other, operand gives the operands back;
@@ -570,21 +579,33 @@ deviation_tile_kernel(DevTileArgs g, mmaemu_deviation_hist *hist)
                 r1 = r0 - low;
                 exact = exact & (r1 + low == r0) & (r0 - r1 == low);
             }
-            const double r2 = r1 - cc;
-            exact = exact & (r2 + cc == r1) & (r1 - r2 == cc) & held;
-            double q = __builtin_floor(ldexp(r2, -g.bin_exp));
-            q = __builtin_fmax(__builtin_fmin(q, (double)(NB / 2 - 1)), (double)(-NB / 2));
-            const uint32_t bin = (uint32_t)((int)q + NB / 2);
+            double h = r1 - cc;
+            exact = exact & (h + cc == r1) & (r1 - h == cc);
+            double q = __builtin_floor(ldexp(h, -g.bin_exp));
+            const bool counted = in & exact;
             if (__any(in && !exact)) {
-                // (none of the finite ones overflows, so that r2 is finite exactly where everything is)
-                const bool finite = __builtin_fabs(r2) <= 0x1.fffffffffffffp+1023;
-                if (in && !exact && finite) open |= 1u << (rv * CB + c);
+                // (none of the finite ones overflows, so that h is finite exactly where everything is)
+                const bool finite = __builtin_fabs(h) <= 0x1.fffffffffffffp+1023;
+                if (in && !exact && finite) open |= 1u << i;
                 const uint32_t skip = (uint32_t)__popcll(__ballot(in && !finite));
                 tally.bad += skip;
                 tally.out -= skip;
             }
-            tally.out += (uint32_t)__popcll(__ballot(!(in && exact)));
-            tally.take((in && exact) ? r2 : 0.0, (in && exact) ? bin : (uint32_t)NB, lane, bins);
+            q = __builtin_fmax(__builtin_fmin(q, (double)(NB / 2 - 1)), (double)(-NB / 2));
+            const uint32_t bin = (uint32_t)((int)q + NB / 2);
+            tally.out += (uint32_t)__popcll(__ballot(!counted));
+            tally.take(counted ? h : 0.0, counted ? bin : (uint32_t)NB, lane, bins);
+        };
+        // the end of an output of the lanes' as an expansion (row 4 rv of theirs)
+        auto settle = [&](auto low_c, int rv, int c, double s, double low, bool mine) {
+            constexpr bool LOW = decltype(low_c)::value;
+            const uint64_t o = o0 + (uint64_t)(4 * rv) * g.n + c;
+            double h, q;
+            place_expansion<LOW>((double)__uint_as_float(g.D[o]), s, low, (double)__uint_as_float(acc[o] & acc_mask), g.bin_exp, h, q);
+            q = __builtin_fmax(__builtin_fmin(q, (double)(NB / 2 - 1)), (double)(-NB / 2));
+            seen += 64u;
+            tally.out += (uint32_t)__popcll(__ballot(!mine));
+            tally.take(mine ? h : 0.0, mine ? (uint32_t)((int)q + NB / 2) : (uint32_t)NB, lane, bins);
         };
         seen += 64u * RB * 4 * CB;
         if (__builtin_expect(!split, 1)) {
@@ -593,7 +614,21 @@ deviation_tile_kernel(DevTileArgs g, mmaemu_deviation_hist *hist)
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
 #pragma unroll
-                    for (int c = 0; c < CB; ++c) end(std::false_type{}, 4 * r + v, c, db[r][v][c], cb[r][v][c], S[r][c][v], 0.0, true, sampled(r, v, c));
+                    for (int c = 0; c < CB; ++c) end(std::false_type{}, (4 * r + v) * CB + c, db[r][v][c], cb[r][v][c], S[r][c][v], 0.0, sampled(r, v, c));
+            if (__builtin_expect(__any(open != 0u), 0)) {
+#pragma unroll 1
+                for (int i = 0; i < RB * 4 * CB; ++i) {
+                    if (!__any((open >> i) & 1u)) continue;
+                    double sum = 0.0;
+#pragma unroll
+                    for (int r = 0; r < RB; ++r)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v)
+#pragma unroll
+                            for (int c = 0; c < CB; ++c) sum = i == (4 * r + v) * CB + c ? S[r][c][v] : sum;
+                    settle(std::false_type{}, i / CB, i % CB, sum, 0.0, ((open >> i) & 1u) != 0u);
+                }
+            }
         } else {
 #pragma unroll 1
             for (int rc = 0; rc < RB * CB; ++rc) {
@@ -620,37 +655,15 @@ deviation_tile_kernel(DevTileArgs g, mmaemu_deviation_hist *hist)
                 }
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
-                    double hi, lo, rest;
+                    double hi, lo;
                     two_sum(H[v], M[v], hi, lo);
-                    two_sum(lo, L[v], lo, rest);
+                    lo += L[v];                                        // (exact: below 2^4, a multiple of 2^-48)
                     const uint64_t o = o0 + (uint64_t)(16 * r + 4 * v) * g.n + c;
-                    end(std::true_type{}, 4 * r + v, c, g.D[o], acc[o] & acc_mask, hi, lo, rest == 0.0, sampled(r, v, c));
+                    open = 0;
+                    end(std::true_type{}, 0, g.D[o], acc[o] & acc_mask, hi, lo, sampled(r, v, c));
+                    if (__builtin_expect(__any(open != 0u), 0)) settle(std::true_type{}, 4 * r + v, c, hi, lo, open != 0u);
                 }
             }
-        }
-        while (__builtin_expect(__any(open != 0u), 0)) {
-            const bool mine = open != 0u;
-            const uint32_t bit = mine ? (uint32_t)__builtin_ctz(open) : 0u, c = bit % CB, rv = bit / CB;      // (row 4 rv of the lane's)
-            open &= open - 1u;
-            const uint64_t o = o0 + (uint64_t)(4 * rv) * g.n + c;
-            Settled t = {0.0, (uint32_t)NB};
-            if (mine) {
-                SplitSum sp;
-                const uint8_t *qa = g.A + (out_row + 4 * rv) * g.k * ES, *qb = g.B + (row_b + c) * (uint64_t)g.k * ES;
-#pragma unroll 1
-                for (uint32_t kk = 0; kk < g.k; kk += 2) {
-                    float a[2], b[2];
-                    pair_values<FP8>(a5, pair_load<FP8>(qa + kk * ES), a);
-                    pair_values<FP8>(b5, pair_load<FP8>(qb + kk * ES), b);
-                    sp.add(a[0], b[0]);
-                    sp.add(a[1], b[1]);
-                }
-                t = settle_output(qa, qb, g.k, g.ta, g.tb, g.bin_exp, sp.upper, sp.lower, acc[o] & acc_mask, g.D[o]);
-            }
-            seen += 64u;
-            tally.out += (uint32_t)__popcll(__ballot(!mine));
-            tally.bad += (uint32_t)__popcll(__ballot(mine && t.bin == (uint32_t)NB));
-            tally.take(t.h, t.bin, lane, bins);
         }
         seen -= tally.out + tally.bad;
         skipped += tally.bad;
@@ -685,10 +698,10 @@ deviation_tile_kernel(DevTileArgs g, mmaemu_deviation_hist *hist)
         if (t) atomicAdd(gc + (threadIdx.x - 64u), t);
     } else if (threadIdx.x >= 128u && threadIdx.x < 128u + NB) {
         const uint32_t bin = threadIdx.x - 128u;
-        unsigned long long t = 0;                                      // (up to 2^34)
+        uint32_t t = 0;
 #pragma unroll
         for (uint32_t q = 0; q < TILE_COPIES; ++q) t += bins[bin * TILE_COPIES + ((q + bin) & (TILE_COPIES - 1))];
-        if (t) atomicAdd(gc + 5 + bin, t);
+        if (t) atomicAdd(gc + 5 + bin, (unsigned long long)t);
     }
 }
 
@@ -720,7 +733,8 @@ static mmaemu_status launch_deviation_tiles(const void *A, const void *B, const 
     auto span = [](const FmtInfo &f) { return (1 << f.ebits) - (f.ieee ? 3 : 2); };     // (subnormals are multiples of the smallest normal numbers' unit)
     g.exact_types = span(fa) + span(fb) <= g.slack ? 1u : 0u;
     uint64_t blocks = (g.nitems + 7) / 8;
-    if (blocks > TILE_WORKGROUPS) blocks = TILE_WORKGROUPS;
+    const uint64_t most = batch * m * n / stride < 1ull << 40 ? TILE_WORKGROUPS : TILE_WORKGROUPS_MANY;
+    if (blocks > most) blocks = most;
     auto go = [&](auto fp8_c) {
         constexpr bool FP8 = decltype(fp8_c)::value;
         if (wide && stride == 1) hipLaunchKernelGGL((deviation_tile_kernel<FP8, 1, 2, false>), dim3((uint32_t)blocks), dim3(512), 0, s, g, h);
