@@ -292,6 +292,19 @@ bool small_takes(const ModelArgs &p, uint32_t ta, uint32_t tb, uint32_t m, uint3
     return (p.L == 4 || p.L == 8 || p.L == 16) && k % p.L == 0;
 }
 
+// Long rows: a lane walks a row of A and of B four to sixteen elements at a time, and with more of them resident than the second-level caches
+// (4 MB per XCD) hold, every group fetches its lines again.  Then only as many workgroups are launched as hold QUAD_BYTES of rows,
+// but no fewer than QUAD_RESIDENT (beyond 128 bytes a row is not held whole), and each walks several tiles (a quarter more than fit are
+// left at once with longer groups: two rounds take longer).  The kernel above, workgroups for all tiles, and so, us, 2^18 tiles, T-FDPA: FP8, groups
+// of 8, k = 56, 80, 128, 256: 196, 289, 607, 1242; 116, 356, 1209, 2204; 116, 211, 457, 958.  FP8, groups of 4, k = 32, 48, 64, 128: 127, 187, 270,
+// 1184; 71, 167, 309, 1248; 71, 124, 168, 614.  FP16, groups of 4, k = 24, 32, 64: 86, 156, 601; 87, 156, 618; 61, 82, 318.  FP16, groups
+// of 16, k = 48, 80, 256: 123, 218, 660; 89, 224, 704; 89, 201, 625.  TR-FDPA, FP8, groups of 16, k = 80, 128, 256: 278, 478, 951; 152, 326, 1265;
+// 152, 326, 811.
+constexpr uint64_t QUAD_BYTES = 32ull << 20, QUAD_RESIDENT = 640;
+// ... from so many bytes of a row of A and of B together: the shorter a group, the more of them share a line, and the round-downs of
+// TR-FDPA leave the loads more time
+static uint32_t quad_long_rows(uint32_t L, bool rd) { return L == 4 ? (rd ? 112u : 96u) : L == 8 ? (rd ? 160u : 144u) : (rd ? 320u : 224u); }
+
 mmaemu_status launch_emulate_small(const ModelArgs &p, const void *A, const void *B, const void *Cm, void *D, uint32_t m, uint32_t n,
                                    uint32_t k, uint64_t batch, uint32_t ta, uint32_t tb, hipStream_t s)
 {
@@ -320,6 +333,12 @@ mmaemu_status launch_emulate_small(const ModelArgs &p, const void *A, const void
     // (four lanes per tile and sums of 32 bits: see the kernel)
     const bool quad = wide && m == 4 && n == 4 && !dbl && ((uint64_t)p.L << (p.F + 2)) <= (1ull << 31);
     if (quad) {
+        const uint64_t row_bytes = (uint64_t)k * (sm.esa + sm.esb);
+        if (row_bytes >= quad_long_rows(p.L, rd)) {
+            const uint64_t resident = QUAD_BYTES / (256 * row_bytes) > QUAD_RESIDENT ? QUAD_BYTES / (256 * row_bytes) : QUAD_RESIDENT;
+            const uint64_t rounds = (blocks + resident - 1) / resident;
+            if (blocks > resident + (p.L > 4 ? resident / 4 : 0)) blocks = (blocks + rounds - 1) / rounds;
+        }
 #define QUAD(QL_, RD_) hipLaunchKernelGGL((emulate_quad_kernel<QL_, RD_>), dim3((uint32_t)blocks), dim3(256), 0, s, sm, a, b, c, d, k, nitems)
         if (p.L == 4) { if (rd) QUAD(1, true); else QUAD(1, false); }
         else if (p.L == 8) { if (rd) QUAD(2, true); else QUAD(2, false); }

@@ -99,3 +99,46 @@ def test_few_outputs_with_long_rows_run_one_per_thread(mm):
         best.append(min(times))
     mm.model_destroy(h)
     assert best[1] < 1.6 * best[0], best
+
+
+@pytest.mark.parametrize("ta,tb,k,nb", [(fm.E4M3, fm.E5M2, 128, 40961), (fm.E4M3, fm.E5M2, 48, 90001), (fm.FP16, fm.FP16, 64, 70001), (fm.FP16, fm.FP16, 24, 131071), (fm.FP16, fm.E4M3, 112, 51203)])
+@pytest.mark.parametrize("L", [4, 8, 16])
+def test_long_rows_of_4x4_tiles(mm, ta, tb, k, nb, L):
+    """Rows of which not all that are resident fit the caches: workgroups that walk several tiles, with a ragged last round, beside
+    shorter rows of the same list that do not; one small problem many times."""
+    if k % L:
+        k = k // L * L
+    rng = np.random.default_rng(k + nb + L)
+    some = 37
+    A, B, C = make_case(rng, ta, tb, some, 4, 4, k, special_frac=0.0005, c_exp=(100, 150))
+    pick = np.arange(nb) % some
+    for p in (ModelParams(group_len=L, frac_bits=24, out_round=1), FITTED.with_(group_len=L)):
+        want, _ = o2lib.emulate_mma(p, A, B, C, ta, tb)
+        got = gpu_emulate(mm, p, A[pick], B[pick], C[pick], ta, tb)
+        assert gpu_emulate.last_kernel.startswith("small tiles, 4 outputs per thread, four threads per tile"), gpu_emulate.last_kernel
+        assert_same(got, want[pick], str(p))
+
+
+def test_long_rows_of_4x4_tiles_cost_what_they_are(mm):
+    """2^18 tiles of 4x4x128 FP8 (groups of 8) in no more than sixteen times the time of 2^15: with all their workgroups resident they took
+    28 times as long, every group's lines fetched again."""
+    import torch
+    k = 128
+    h = mm.model_create(group_len=8, frac_bits=24, out_round=mm.RZ)
+    A, B = (torch.zeros((1 << 18) * 4 * k, dtype=torch.uint8, device="cuda") for _ in range(2))
+    C = torch.zeros((1 << 18) * 16, dtype=torch.int32, device="cuda")
+    D = torch.empty_like(C)
+    best = []
+    for nb in (1 << 15, 1 << 18):
+        times = []
+        for _ in range(8):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            for _ in range(4):
+                mm.emulate_mma(h, A, B, C, D, 4, 4, k, nb, (mm.E4M3, mm.E5M2, mm.FP32, mm.FP32))
+            end.record()
+            torch.cuda.synchronize()
+            times.append(start.elapsed_time(end))
+        best.append(min(times))
+    mm.model_destroy(h)
+    assert best[1] < 16 * best[0], best
