@@ -161,11 +161,20 @@ def _ptr(x):
     return x.data_ptr()
 
 
+# The current stream's handle without a torch.cuda.Stream object around it, which took 2.6 of the 6 to 8 us that a call takes on the
+# host (nine small calls 57 -> 41 us).  Not part of torch's public interface: where it is missing, the stream object is asked.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def _current_stream():
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
+
+
 def _stream(stream):
     if stream is None:
-        # the current stream's handle without a torch.cuda.Stream object around it, which took 2.6 of the 6 to 8 us that a call
-        # takes on the host (nine small calls 57 -> 41 us)
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+        return _current_stream()
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream

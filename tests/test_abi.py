@@ -201,3 +201,16 @@ def test_deviation_sample_kernel_for_a_call():
         with pytest.raises(mm.MmaemuError) as ei:
             kernel(**kw)
         assert ei.value.status == status, kw
+
+
+def test_current_stream_without_the_private_call(monkeypatch):
+    """Both ways to the current stream's handle: torch's raw one for the current device, and the stream object's where torch lacks it."""
+    import types
+    import torch
+    from paper_2511_10909_amd import binding as mm
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=77))
+    monkeypatch.setattr(mm, "_raw_stream", lambda device: 100 + device)
+    assert mm._stream(None) == 103
+    monkeypatch.setattr(mm, "_raw_stream", None)
+    assert mm._stream(None) == 77 and mm._stream(5) == 5
