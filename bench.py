@@ -33,7 +33,7 @@ COUNTERS = {
     "multi x16 tiled 16x16 r2x2 kc=16 any L vm=1": {"valu_instr_per_term": 8.70, "traffic": 215916000, "chunk": 1 << 16},
     "multi x3 tiled 32x32 r2x2 kc=8 any L vm=0, twins share sums": {"valu_instr_per_term": 7.31, "traffic": 1345043000, "chunk": 1 << 18},
 }
-COUNTERS_SOURCES = "6e55a1098068eb81"
+COUNTERS_SOURCES = "55c1aca1b57f1720"
 COUNTERS_SOURCE = ("profiles/closed_loop_scan_trace_and_counters.md, profiles/subnormal_stress_trace_and_counters.md (rocprofv3 --pmc SQ_INSTS_VALU; "
                    "FETCH_SIZE, WRITE_SIZE scaled by a 64 MiB copy); traffic per launch")
 

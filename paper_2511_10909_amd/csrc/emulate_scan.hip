@@ -38,8 +38,11 @@
 //     ran at half the speed of ordinary data through the routes of the general loop);
 //   * the reference's ordered keys are formed once per pass, a histogram entry is counted by leading zeros, and the two
 //     reductions over the wavefront run only where they can change something.
-// Launches of six and more TR-FDPA sets on FP8 and FP16 operands go the same way (FAM 4): the sixteen sets of the closed-loop scan
-// on 2^15 tiles of 16x16x16 FP16, N(0,1) operands, 566 -> 523 us.
+// Launches of six and more TR-FDPA sets on all operands but BF16 go the same way (FAM 4): the sixteen sets of the closed-loop scan
+// on 2^15 tiles of 16x16x16 FP16, N(0,1) operands, 566 -> 523 us.  At four waves per SIMD 15 registers of a thread lie in scratch memory on
+// 16x16x16, 8 on 32x32x16 and none on 32x32x8.  Three waves and four, us: six and sixteen sets on
+// 2^15 tiles of 16x16x16 252, 542 and 241, 501, 2^13 of 32x32x16 239, 536 and 227, 495, of 32x32x8 186, 376 and 148, 330; but 2^12 tiles of
+// 16x16x16 59, 107 and 75, 119, 2^9 25, 52 and 26, 53.
 // Measured (kernel times), one launch of the sixteen sets of the closed-loop scan on 2^16 tiles of 16x16x16, before and after: FP8 1108 ->
 // 670 us (6.22 instructions per term), BF16 bit patterns 1433 -> 1137 us (8.70), all FP16 bit patterns (a quarter of the
 // tiles) 571 -> 253 us; three sets on 2^18 tiles of 32x32x8 1953 -> 1354 us (7.31).  What is left is still issue: 0.84 to
@@ -127,7 +130,7 @@ __device__ __forceinline__ uint32_t key_distance(uint32_t kx, uint32_t ky)
 __device__ __forceinline__ uint32_t scalar(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
 
 // The products of a thread's outputs fit its registers: T-FDPA, and TR-FDPA on binary32 values, on tiles of up to 16 k.
-template <int KC, bool ADAPT, int FAM> constexpr bool scan_fast() { return FAM == 4 || (FAM == 0 && KC <= 16); }
+template <int KC, int FAM> constexpr bool scan_fast() { return FAM == 4 || (FAM == 0 && KC <= 16); }
 
 // LDS of one workgroup: staged values and exponents, the kept quarter maxima, the statistics
 template <int TM, int KC, bool ADAPT, int FAM>
@@ -136,7 +139,7 @@ constexpr int scan_lds_bytes()
     constexpr int SLOTS = 256 / ((TM / 2) * (TM / 2));
     constexpr int VS = KC + 4, VSD = KC + 2, ES = KC / 2 + (KC == 8 ? 4 : 2);
     constexpr int KEPT = FAM == 3 ? KC / 4 : (KC / 4 + 1) / 2;            // dwords of kept maxima per output
-    return 2 * SLOTS * TM * (ADAPT ? VSD * 8 : VS * 4) + 2 * SLOTS * TM * ES * 4 + KEPT * 4 * 256 * 4 + (scan_fast<KC, ADAPT, FAM>() ? 3 : 0) * 4 * 256 * 4 +
+    return 2 * SLOTS * TM * (ADAPT ? VSD * 8 : VS * 4) + 2 * SLOTS * TM * ES * 4 + KEPT * 4 * 256 * 4 + (scan_fast<KC, FAM>() ? 3 : 0) * 4 * 256 * 4 +
            (int)sizeof(MultiLds) + 16;
 }
 // workgroups (of four waves, one per SIMD) that a CU's 160 KB of LDS hold, four at most: the waves per SIMD to compile for
@@ -151,8 +154,8 @@ constexpr int scan_waves()
 // FAM 0: T-FDPA, the accumulator a term of the sum; FAM 1: TR-FDPA (unsplit groups), the accumulator added after the
 // products' sum with the two round-downs; FAM 2: GTR-FDPA's merge of sub-group sums with the sub-groups being the two
 // halves or the four quarters of a group (binary32 values only: FP8 / FP16 operands, a sub-group's sum in 32 bits); FAM 3:
-// GTR-FDPA as printed, the sub-groups being the even and the odd products; FAM 4: FAM 1 on binary32 values and up to 16 k, with the
-// products in registers.
+// GTR-FDPA as printed, the sub-groups being the even and the odd products; FAM 4: FAM 1 on binary32 values (all operands but BF16) and
+// up to 16 k, with the products in registers.
 // TWIN (FAM 0, tiles of one group): a model marked `twin` is followed by one that differs from it only in the output
 // conversion (rounding, E8M13, output flush, NaN pattern); the two share the group's maximum and sum, and only the end of
 // the group and the statistics run twice.
@@ -163,7 +166,7 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
     constexpr int R = 2, C = 2, TN = TM;
     constexpr int TI = TM / R, TJ = TN / C, TPS = TI * TJ, SLOTS = 256 / TPS;
     static_assert(TPS * SLOTS == 256, "thread layout");
-    constexpr bool FAST = scan_fast<KC, ADAPT, FAM>();
+    constexpr bool FAST = scan_fast<KC, FAM>();
     constexpr int VS = KC + 4, VSD = KC + 2, ES = KC / 2 + (KC == 8 ? 4 : 2);
     constexpr int NQ4 = KC / 4;                                   // quarter groups per row
     constexpr int NK2 = (NQ4 + 1) / 2;                            // dwords of kept maxima per output
@@ -507,6 +510,9 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
             // groups' results then follow Sec. 4.2 through an IEEE sum of the group's products and its accumulator (special_sum).
             // (An infinity that a BF16 chain reaches by overflow is no such case: it stays by itself, see rho32.)
             bool odd = top >= (FAM == 0 ? TAGGED : SENTINEL);
+            // TR-FDPA's last steps keep an infinite or NaN accumulator by themselves, so only operands ask for that sum: six and twelve sets on
+            // 2^15 tiles of 16x16x16, N(0,1) operands and all accumulators, 287, 479 us with it and 273, 446 without
+            const bool special_operand = FAM == 4 && scalar(__any(odd) ? 1u : 0u) != 0u;
 #pragma unroll
             for (int r = 0; r < R; ++r)
 #pragma unroll
@@ -916,7 +922,7 @@ emulate_scan_kernel(ScanArgs sa_, const void *__restrict__ A, const void *__rest
                             for (int r = 0; r < R; ++r)
 #pragma unroll
                                 for (int c = 0; c < C; ++c) {
-                                    if (__builtin_expect(special, 0)) {
+                                    if (__builtin_expect(special_operand, 0)) {
                                         const uint32_t t = special_sum(gl_c, g, r, c, d[r][c]);
                                         if ((t & 0x7F800000u) == 0x7F800000u) o[r * C + c] = t;
                                         one_at_a_time();
@@ -1774,7 +1780,10 @@ mmaemu_status launch_scan(const MultiLaunch &ml, const void *A, const void *B, c
     // TR-FDPA with the products in registers from six sets on: forming them, and the registers they take, cost a launch of few sets more than
     // the models save.  gfx950's sets of several widths on 2^15 tiles of 16x16x16 FP16, N(0,1), products formed for every model and
     // kept, 1, 4, 6, 8, 12, 16 sets: 55, 166, 232, 281, 411, 525 us and 66, 172, 231, 270, 385, 487; all bit patterns 82, 283, 407, 505, 717,
-    // 951 and 72, 194, 262, 315, 440, 567.
+    // 951 and 72, 194, 262, 315, 440, 567.  Other tiles, six and twelve sets, 2^13 of 32x32x8 169, 291 and 150, 268 (all bit patterns 280, 499 and
+    // 190, 329), of 32x32x16 245, 433 and 227, 389 (440, 784 and 283, 479); FP8, FP6 and FP4 within 2 % of that.  Sets whose sums no
+    // flag calls exact save less (cdna3's, 2^15 tiles of 16x16x16: 266, 470 and 269, 451; all bit patterns 458, 808 and 323, 550): six of
+    // them on 3000 to 10000 such tiles take 1.02 to 1.10, sixteen 0.93 to 1.04; below 3000 tiles 1.00 to 1.04.
     if (ml.cls <= 3 && !adapt && k <= 16 && ml.count >= 6) return launch_scan_shape<4>(sa, A, B, Cm, m, n, k, batch, false, s);
     if (ml.cls <= 3) return launch_scan_shape<1>(sa, A, B, Cm, m, n, k, batch, adapt, s);
     if (ml.cls <= 6) return launch_scan_shape<2>(sa, A, B, Cm, m, n, k, batch, false, s);

@@ -416,6 +416,39 @@ def test_tr_fdpa_launches_on_either_side_of_the_kept_products(mm, ta, tb, m, k, 
         assert s == ostats.compare(w, want[0]), p
 
 
+def test_infinite_accumulators_ask_for_no_sum_of_products(mm):
+    """Sixteen TR-FDPA sets on all finite operands and all accumulators take less than on all operands: NaN among the accumulators alone
+    cost an IEEE sum per group too, 0.96 of the other's time (0.90 without)."""
+    import torch
+    nb, m, k, dt = 1 << 14, 16, 16, (fm.FP16, fm.FP16, fm.FP32, fm.FP32)
+    base = dict(c_mode=mm.C_AFTER_RD, skip_zero_terms=True, f2_at_leading_bit=True, zero_result_positive=True, sum_drop_distance=28)
+    hs = [mm.model_create(frac_bits=F, frac_bits2=F2, group_len=L, **base) for F in (20, 24) for F2 in (27, 31) for L in (4, 8, 16, 8)]
+    A, B = ([torch.empty(nb * m * k, dtype=torch.int16, device="cuda") for _ in range(2)] for _ in range(2))
+    C, ref = (torch.empty(nb * m * m, dtype=torch.int32, device="cuda") for _ in range(2))
+    for i, fam in enumerate((mm.GEN_FINITE_BITS, mm.GEN_RANDOM_BITS)):
+        mm.generate(A[i], mm.FP16, m * k, 0, nb, fam, seed=4, operand=0)
+        mm.generate(B[i], mm.FP16, m * k, 0, nb, fam, seed=4, operand=1)
+    mm.generate(C, mm.FP32, m * m, 0, nb, mm.GEN_RANDOM_BITS, seed=4, operand=2)
+    ref.copy_(C)
+    st = torch.empty(len(hs) * mm.STATS_BYTES, dtype=torch.uint8, device="cuda")
+    for i in range(len(hs)):
+        mm.stats_reset(st[i * mm.STATS_BYTES:])
+    best = [1e9, 1e9]
+    for _ in range(12):
+        for i in range(2):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            for _ in range(3):
+                mm.emulate_compare_many(hs, A[i], B[i], C, ref, None, m, m, k, nb, dt, st)
+            end.record()
+            torch.cuda.synchronize()
+            best[i] = min(best[i], start.elapsed_time(end))
+    print("finite operands, all operands (ms)", best, flush=True)
+    for h in hs:
+        mm.model_destroy(h)
+    assert best[0] < 0.93 * best[1], best
+
+
 @pytest.mark.parametrize("ta,tb,m,k", [(fm.FP16, fm.FP16, 16, 16), (fm.E4M3, fm.E5M2, 16, 32), (fm.FP16, fm.FP16, 32, 8), (fm.E5M2, fm.E5M2, 32, 16),
                                        (fm.E4M3, fm.E4M3, 16, 16), (fm.FP16, fm.E5M2, 16, 32)])
 def test_split_group_sets_in_the_fused_kernel(mm, ta, tb, m, k):
