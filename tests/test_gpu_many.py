@@ -416,6 +416,33 @@ def test_tr_fdpa_launches_on_either_side_of_the_kept_products(mm, ta, tb, m, k, 
         assert s == ostats.compare(w, want[0]), p
 
 
+@pytest.mark.parametrize("cls", [0, 1, 2])
+@pytest.mark.parametrize("count", [5, 6, 16])
+@pytest.mark.parametrize("ta,tb,m,k", [(fm.E2M3, fm.E3M2, 16, 16), (fm.E2M1, fm.E4M3, 32, 8), (fm.E3M2, fm.E2M1, 32, 16), (fm.E5M2, fm.E2M3, 16, 16)])
+def test_tr_fdpa_launches_on_fp6_and_fp4(mm, ta, tb, m, k, count, cls):
+    """The same two kernels on FP6 and FP4 operands, and on those beside FP8: all codes, rows of zeros, subnormal elements that some models
+    flush; finite operands against infinite and NaN accumulators."""
+    rng = np.random.default_rng(18000 + 1000 * cls + 100 * ta + 10 * tb + m + k + count)
+    nb = 27
+    A, B, C = make_case(rng, ta, tb, nb, m, m, k)
+    C[: nb // 2] = synth.narrow_exponent_bits(rng, (nb // 2, m, m), fm.FP32, 115, 136)
+    C = synth.sprinkle(rng, C, synth.SPECIAL_CODES[fm.FP32], 0.02)
+    signs = lambda t: np.array([0, 1 << (fm.FORMATS[t].width - 1)], dtype=NP[t])
+    A, B = synth.sprinkle(rng, A, signs(ta), 0.3), synth.sprinkle(rng, B, signs(tb), 0.1)
+    A[2, 1, :] = 0
+    if fm.E4M3 in (ta, tb) or fm.E5M2 in (ta, tb):
+        t, X = (ta, A) if ta in (fm.E4M3, fm.E5M2) else (tb, B)
+        X[nb - 5:] = synth.sprinkle(rng, X[nb - 5:], synth.SPECIAL_CODES[t], 0.01)
+    plist = [p for p in rd_sets(rng, k, 40 * count) if rd_class(p) == cls][:count]
+    assert len(plist) == count
+    want = oracle_outputs(plist, A, B, C, ta, tb)
+    st, D, kern, _ = run_many(mm, plist, A, B, C, ta, tb, ref=want[0])
+    assert kern.startswith("multi x%d tiled" % count) and kern.endswith(" kept rd") == (count >= 6), kern
+    for p, d, w, s in zip(plist, D, want, st):
+        assert_same(d, w, str(p))
+        assert s == ostats.compare(w, want[0]), p
+
+
 def test_infinite_accumulators_ask_for_no_sum_of_products(mm):
     """Sixteen TR-FDPA sets on all finite operands and all accumulators take less than on all operands: NaN among the accumulators alone
     cost an IEEE sum per group too, 0.96 of the other's time (0.90 without)."""
