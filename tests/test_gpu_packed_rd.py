@@ -62,6 +62,27 @@ def test_packed_halves(mm, ta, tb, mode):
             assert_same(got, want, "%s %s %s" % ((nb, m, n, k), mode, p))
 
 
+# tiles, m, n, k, rows per lane: either side of 768 blocks, workgroups of four wavefronts that are not full, blocks of tiles that are not
+# square (819 of them; 1152 and 640, which are dealt to the XCDs in turn)
+GRIDS = [(767, 16, 16, 32, 2), (768, 16, 16, 32, 4), (769, 16, 16, 32, 4), (770, 16, 16, 32, 4), (13, 112, 144, 64, 4), (24, 96, 128, 32, 4), (20, 32, 256, 32, 2)]
+
+
+@pytest.mark.parametrize("nb,m,n,k,rows", GRIDS)
+@pytest.mark.parametrize("scaled", [False, True])
+def test_packed_halves_grids(mm, nb, m, n, k, rows, scaled):
+    rng = np.random.default_rng(7300 + nb + m + n)
+    ta, tb = fm.E4M3, fm.E5M2
+    A, B, C = operands(rng, ta, tb, nb, m, n, k, "bits")
+    print("packed halves", (nb, m, n, k), "scaled" if scaled else "", flush=True)
+    if scaled:
+        SA, SB = (rng.integers(100, 150, size=(nb, x, k // 32)).astype(np.uint8) for x in (m, n))
+        want, got = o2lib.emulate_mma_scaled(BASE, A, B, C, SA, SB, 32, ta, tb)[0], gpu_emulate_scaled(mm, BASE, A, B, C, SA, SB, 32, ta, tb)
+    else:
+        want, got = o2lib.emulate_mma(BASE, A, B, C, ta, tb)[0], gpu_emulate(mm, BASE, A, B, C, ta, tb)
+    assert "packed halves r%d" % rows in mm.last_kernel(), mm.last_kernel()
+    assert_same(got, want, "%s" % ((nb, m, n, k),))
+
+
 @pytest.mark.parametrize("ta,tb", PAIRS)
 @pytest.mark.parametrize("mode", ["mid", "bits", "zeros"])
 def test_packed_halves_with_block_scales(mm, ta, tb, mode):
