@@ -416,4 +416,11 @@ def test_bias_experiment_workload(mm):
     for name, want in zip(("rd", "rz"), run_pool(jobs, workers=2)):
         got = to_host(f[name], np.uint32)[:t]
         assert np.array_equal(got, want), name
-        same_hist(dev_hist(mm, A, B, C, got, fm.FP16, fm.FP16, 1, configs.BIAS_BIN_EXP), deviation_hist(A, B, C, want, fm.FP16, fm.FP16, 1, configs.BIAS_BIN_EXP), name)
+        hist = deviation_hist(A, B, C, want, fm.FP16, fm.FP16, 1, configs.BIAS_BIN_EXP)
+        same_hist(dev_hist(mm, A, B, C, got, fm.FP16, fm.FP16, 1, configs.BIAS_BIN_EXP), hist, name)
+        # ... and that prefix many times over, in the kernel for whole tiles, which fills the workload's histograms
+        copies = 50
+        many = [np.tile(x, (copies, 1, 1)) for x in (A, B, C, got)]
+        assert mm.deviation_sample_kernel(4096, 4096, 4096, 4096, 32, 32, 8, t * copies, (fm.FP16, fm.FP16, fm.FP32, fm.FP32), 1) == "whole tiles"
+        same_hist(dev_hist(mm, *many, fm.FP16, fm.FP16, 1, configs.BIAS_BIN_EXP),
+                  {key: [v * copies for v in x] if key == "bins" else x * copies for key, x in hist.items()}, name)
