@@ -1,9 +1,9 @@
 // Distribution of the deviation delta = D - D_real of a model's (or an instruction's) outputs from the real result
 // (Sec. 6.2.4: the bias of the round-down modes shows as a distribution of delta shifted toward the negative side,
-// against a symmetric one for the variant that truncates toward zero).  D_real = c + sum_k a_k b_k is taken exactly:
-// per sampled output one thread adds D and subtracts every product and the accumulator, in an unevaluated pair of
-// binary64 numbers while that is exact and in a wide fixed-point number otherwise, so delta itself is exact; only its
-// binary64 image (for the three sums) is rounded.  Linear bins of width 2^bin_exp
+// against a symmetric one for the variant that truncates toward zero).  D_real = c + sum_k a_k b_k is taken exactly, and so is
+// delta; only its binary64 image (for the three sums) is rounded.  Two ways: one thread sums an output's products (or four outputs'), adds D and
+// subtracts that sum and the accumulator, in an unevaluated pair of binary64 numbers while that is exact and in a wide fixed-point
+// number otherwise; whole tiles of FP16 and FP8 operands have their sums of products formed on the matrix cores (see there).  Linear bins of width 2^bin_exp
 // around zero: bin i holds delta in [(i - 32) w, (i - 31) w), the outermost bins everything beyond.
 #include "efdpa_pair.hpp"
 
@@ -353,7 +353,7 @@ deviation_kernel(const void *__restrict__ A, const void *__restrict__ B, const u
 
 // ---- whole tiles of FP16 and FP8 operands: the products' sums on the matrix cores -------------
 //
-// A wavefront owns 16 RB x 16 CB outputs of a tile and forms their sums of products with v_mfma_f64_16x16x4_f64, a chain of fused
+// A wavefront owns 16 x 16 CB outputs of a tile and forms their sums of products with v_mfma_f64_16x16x4_f64, a chain of fused
 // multiply-adds that is exact while every product is a multiple of one unit and the sums stay below 2^53 of them.  The types alone may
 // guarantee that (E4M3 x E4M3); else the wavefront takes the largest and the smallest exponent of its rows' elements.  An output's end
 // is four binary64 operations, with four comparisons that say whether they were exact: D - S first, which cancels, then the
@@ -479,7 +479,7 @@ struct DevTally {
     }
 };
 
-template <bool FP8, int RB, int CB, bool STRIDED>
+template <bool FP8, int CB, bool STRIDED>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4)))
 deviation_tile_kernel(DevTileArgs g, mmaemu_deviation_hist *hist)
 {
@@ -500,63 +500,56 @@ deviation_tile_kernel(DevTileArgs g, mmaemu_deviation_hist *hist)
     for (uint64_t item = (uint64_t)blockIdx.x * 8u + wave; item < g.nitems; item += (uint64_t)gridDim.x * 8u) {
         uint64_t tile; uint32_t rem;
         split_item(item, g.bm * g.bn, tile, rem);
-        const uint32_t i0 = (rem / g.bn) * (16 * RB), j0 = (rem % g.bn) * (16 * CB);
+        const uint32_t i0 = (rem / g.bn) * 16, j0 = (rem % g.bn) * (16 * CB);
         const uint64_t row_a = tile * g.m + i0 + c16, row_b = tile * g.n + j0 + CB * c16;
         const uint8_t *pa = g.A + (row_a * g.k + 2u * g4) * ES, *pb = g.B + (row_b * g.k + 2u * g4) * ES;
-        const uint64_t out_row = tile * g.m + i0 + g4;                         // rows out_row + 16 r + 4 v, columns j0 + CB c16 + c
+        const uint64_t out_row = tile * g.m + i0 + g4;                         // rows out_row + 4 v, columns j0 + CB c16 + c
         const uint64_t o0 = out_row * g.n + j0 + CB * c16;
         uint32_t o0_mod = 0;
         if constexpr (STRIDED) {
             o0_mod = (uint32_t)(((tile * g.m + i0) * g.n + j0) % g.stride) + lane_mod;
             o0_mod -= o0_mod >= g.stride ? g.stride : 0u;
         }
-        auto sampled = [&](int r, int v, int c) -> bool {
+        auto sampled = [&](int v, int c) -> bool {
             if constexpr (!STRIDED) return true;
-            const uint32_t x = o0_mod + ((uint32_t)(16 * r + 4 * v) * g.n + c) % g.stride;      // (the output's index modulo stride, or that and stride)
+            const uint32_t x = o0_mod + ((uint32_t)(4 * v) * g.n + c) % g.stride;      // (the output's index modulo stride, or that and stride)
             return x == 0u || x == g.stride;
         };
-        uint32_t db[RB][4][CB], cb[RB][4][CB];
+        uint32_t db[4][CB], cb[4][CB];
 #pragma unroll
-        for (int r = 0; r < RB; ++r)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const uint64_t o = o0 + (uint64_t)(16 * r + 4 * v) * g.n;
-                if constexpr (CB == 2) {
-                    const uint2 d2 = *reinterpret_cast<const uint2 *>(g.D + o), c2 = *reinterpret_cast<const uint2 *>(acc + o);
-                    db[r][v][0] = d2.x; db[r][v][CB - 1] = d2.y; cb[r][v][0] = c2.x & acc_mask; cb[r][v][CB - 1] = c2.y & acc_mask;
-                } else {
-                    db[r][v][0] = g.D[o];
-                    cb[r][v][0] = acc[o] & acc_mask;
-                }
+        for (int v = 0; v < 4; ++v) {
+            const uint64_t o = o0 + (uint64_t)(4 * v) * g.n;
+            if constexpr (CB == 2) {
+                const uint2 d2 = *reinterpret_cast<const uint2 *>(g.D + o), c2 = *reinterpret_cast<const uint2 *>(acc + o);
+                db[v][0] = d2.x; db[v][CB - 1] = d2.y; cb[v][0] = c2.x & acc_mask; cb[v][CB - 1] = c2.y & acc_mask;
+            } else {
+                db[v][0] = g.D[o];
+                cb[v][0] = acc[o] & acc_mask;
             }
-        f64x4 S[RB][CB];
+        }
+        f64x4 S[CB];
 #pragma unroll
-        for (int r = 0; r < RB; ++r)
-#pragma unroll
-            for (int c = 0; c < CB; ++c) S[r][c] = zero4;
+        for (int c = 0; c < CB; ++c) S[c] = zero4;
         Span span_a, span_b;
-        uint32_t wa[RB], wb[CB];
+        uint32_t wa, wb[CB];
         auto fetch = [&](uint32_t k0) {
-#pragma unroll
-            for (int r = 0; r < RB; ++r) wa[r] = pair_load<FP8>(pa + ((uint64_t)(16 * r) * g.k + k0) * ES);
+            wa = pair_load<FP8>(pa + (uint64_t)k0 * ES);
 #pragma unroll
             for (int c = 0; c < CB; ++c) wb[c] = pair_load<FP8>(pb + ((uint64_t)c * g.k + k0) * ES);
         };
         fetch(0);
 #pragma unroll 1
         for (uint32_t k0 = 0; k0 < g.k; k0 += 8) {
-            float a[RB][2], b[CB][2];
-#pragma unroll
-            for (int r = 0; r < RB; ++r) { pair_values<FP8>(a5, wa[r], a[r]); span_a.take(a[r]); }
+            float a[2], b[CB][2];
+            pair_values<FP8>(a5, wa, a);
+            span_a.take(a);
 #pragma unroll
             for (int c = 0; c < CB; ++c) { pair_values<FP8>(b5, wb[c], b[c]); span_b.take(b[c]); }
             if (k0 + 8 < g.k) fetch(k0 + 8);
 #pragma unroll
             for (int h = 0; h < 2; ++h)
 #pragma unroll
-                for (int r = 0; r < RB; ++r)
-#pragma unroll
-                    for (int c = 0; c < CB; ++c) S[r][c] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a[r][h], (double)b[c][h], S[r][c], 0, 0, 0);
+                for (int c = 0; c < CB; ++c) S[c] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a[h], (double)b[c][h], S[c], 0, 0, 0);
         }
         bool split = false;
         if (!g.exact_types) {
@@ -565,7 +558,7 @@ deviation_tile_kernel(DevTileArgs g, mmaemu_deviation_hist *hist)
             split = (int)((xa & 0xFFFFu) + (xa >> 16) + (xb & 0xFFFFu) + (xb >> 16)) - 2 * 511 > g.slack || (xa & 0xFFFFu) == 255u || (xb & 0xFFFFu) == 255u;
         }
         tally.neg = tally.zero = tally.out = tally.bad = 0;
-        uint32_t open = 0;                                            // outputs whose end was not exact, bit (4 r + v) CB + c; 0 where split
+        uint32_t open = 0;                                            // outputs whose end was not exact, bit v CB + c; 0 where split
         // one output's end; LOW: the products' sum is s + low
         auto end = [&](auto low_c, int i, uint32_t dbits, uint32_t cbits, double s, double low, bool in) {
             constexpr bool LOW = decltype(low_c)::value;
@@ -596,10 +589,10 @@ deviation_tile_kernel(DevTileArgs g, mmaemu_deviation_hist *hist)
             tally.out += (uint32_t)__popcll(__ballot(!counted));
             tally.take(counted ? h : 0.0, counted ? bin : (uint32_t)NB, lane, bins);
         };
-        // the end of an output of the lanes' as an expansion (row 4 rv of theirs)
-        auto settle = [&](auto low_c, int rv, int c, double s, double low, bool mine) {
+        // the end of an output of the lanes' as an expansion (row 4 v of theirs)
+        auto settle = [&](auto low_c, int v, int c, double s, double low, bool mine) {
             constexpr bool LOW = decltype(low_c)::value;
-            const uint64_t o = o0 + (uint64_t)(4 * rv) * g.n + c;
+            const uint64_t o = o0 + (uint64_t)(4 * v) * g.n + c;
             double h, q;
             place_expansion<LOW>((double)__uint_as_float(g.D[o]), s, low, (double)__uint_as_float(acc[o] & acc_mask), g.bin_exp, h, q);
             q = __builtin_fmax(__builtin_fmin(q, (double)(NB / 2 - 1)), (double)(-NB / 2));
@@ -607,41 +600,36 @@ deviation_tile_kernel(DevTileArgs g, mmaemu_deviation_hist *hist)
             tally.out += (uint32_t)__popcll(__ballot(!mine));
             tally.take(mine ? h : 0.0, mine ? (uint32_t)((int)q + NB / 2) : (uint32_t)NB, lane, bins);
         };
-        seen += 64u * RB * 4 * CB;
+        seen += 64u * 4 * CB;
         if (__builtin_expect(!split, 1)) {
 #pragma unroll
-            for (int r = 0; r < RB; ++r)
+            for (int v = 0; v < 4; ++v)
 #pragma unroll
-                for (int v = 0; v < 4; ++v)
-#pragma unroll
-                    for (int c = 0; c < CB; ++c) end(std::false_type{}, (4 * r + v) * CB + c, db[r][v][c], cb[r][v][c], S[r][c][v], 0.0, sampled(r, v, c));
+                for (int c = 0; c < CB; ++c) end(std::false_type{}, v * CB + c, db[v][c], cb[v][c], S[c][v], 0.0, sampled(v, c));
             if (__builtin_expect(__any(open != 0u), 0)) {
 #pragma unroll 1
-                for (int i = 0; i < RB * 4 * CB; ++i) {
+                for (int i = 0; i < 4 * CB; ++i) {
                     if (!__any((open >> i) & 1u)) continue;
                     double sum = 0.0;
 #pragma unroll
-                    for (int r = 0; r < RB; ++r)
+                    for (int v = 0; v < 4; ++v)
 #pragma unroll
-                        for (int v = 0; v < 4; ++v)
-#pragma unroll
-                            for (int c = 0; c < CB; ++c) sum = i == (4 * r + v) * CB + c ? S[r][c][v] : sum;
+                        for (int c = 0; c < CB; ++c) sum = i == v * CB + c ? S[c][v] : sum;
                     settle(std::false_type{}, i / CB, i % CB, sum, 0.0, ((open >> i) & 1u) != 0u);
                 }
             }
         } else {
 #pragma unroll 1
-            for (int rc = 0; rc < RB * CB; ++rc) {
-                const int r = rc / CB, c = rc % CB;
+            for (int c = 0; c < CB; ++c) {
                 f64x4 H = zero4, M = zero4, L = zero4;
-                const uint8_t *const qa = pa + (uint64_t)(16 * r) * g.k * ES, *const qb = pb + (uint64_t)c * g.k * ES;
-                uint32_t xa = pair_load<FP8>(qa), xb = pair_load<FP8>(qb);
+                const uint8_t *const qb = pb + (uint64_t)c * g.k * ES;
+                uint32_t xa = pair_load<FP8>(pa), xb = pair_load<FP8>(qb);
 #pragma unroll 1
                 for (uint32_t k0 = 0; k0 < g.k; k0 += 8) {
                     float a[2], b[2];
                     pair_values<FP8>(a5, xa, a);
                     pair_values<FP8>(b5, xb, b);
-                    if (k0 + 8 < g.k) { xa = pair_load<FP8>(qa + (k0 + 8) * ES); xb = pair_load<FP8>(qb + (k0 + 8) * ES); }
+                    if (k0 + 8 < g.k) { xa = pair_load<FP8>(pa + (k0 + 8) * ES); xb = pair_load<FP8>(qb + (k0 + 8) * ES); }
 #pragma unroll
                     for (int h = 0; h < 2; ++h) {
                         constexpr float CUT = 0x1.8p+19f;              // (its last place is 2^-4)
@@ -658,10 +646,10 @@ deviation_tile_kernel(DevTileArgs g, mmaemu_deviation_hist *hist)
                     double hi, lo;
                     two_sum(H[v], M[v], hi, lo);
                     lo += L[v];                                        // (exact: below 2^4, a multiple of 2^-48)
-                    const uint64_t o = o0 + (uint64_t)(16 * r + 4 * v) * g.n + c;
+                    const uint64_t o = o0 + (uint64_t)(4 * v) * g.n + c;
                     open = 0;
-                    end(std::true_type{}, 0, g.D[o], acc[o] & acc_mask, hi, lo, sampled(r, v, c));
-                    if (__builtin_expect(__any(open != 0u), 0)) settle(std::true_type{}, 4 * r + v, c, hi, lo, open != 0u);
+                    end(std::true_type{}, 0, g.D[o], acc[o] & acc_mask, hi, lo, sampled(v, c));
+                    if (__builtin_expect(__any(open != 0u), 0)) settle(std::true_type{}, v, c, hi, lo, open != 0u);
                 }
             }
         }
@@ -737,10 +725,10 @@ static mmaemu_status launch_deviation_tiles(const void *A, const void *B, const 
     if (blocks > most) blocks = most;
     auto go = [&](auto fp8_c) {
         constexpr bool FP8 = decltype(fp8_c)::value;
-        if (wide && stride == 1) hipLaunchKernelGGL((deviation_tile_kernel<FP8, 1, 2, false>), dim3((uint32_t)blocks), dim3(512), 0, s, g, h);
-        else if (wide) hipLaunchKernelGGL((deviation_tile_kernel<FP8, 1, 2, true>), dim3((uint32_t)blocks), dim3(512), 0, s, g, h);
-        else if (stride == 1) hipLaunchKernelGGL((deviation_tile_kernel<FP8, 1, 1, false>), dim3((uint32_t)blocks), dim3(512), 0, s, g, h);
-        else hipLaunchKernelGGL((deviation_tile_kernel<FP8, 1, 1, true>), dim3((uint32_t)blocks), dim3(512), 0, s, g, h);
+        if (wide && stride == 1) hipLaunchKernelGGL((deviation_tile_kernel<FP8, 2, false>), dim3((uint32_t)blocks), dim3(512), 0, s, g, h);
+        else if (wide) hipLaunchKernelGGL((deviation_tile_kernel<FP8, 2, true>), dim3((uint32_t)blocks), dim3(512), 0, s, g, h);
+        else if (stride == 1) hipLaunchKernelGGL((deviation_tile_kernel<FP8, 1, false>), dim3((uint32_t)blocks), dim3(512), 0, s, g, h);
+        else hipLaunchKernelGGL((deviation_tile_kernel<FP8, 1, true>), dim3((uint32_t)blocks), dim3(512), 0, s, g, h);
     };
     if (ta == MMAEMU_FP16) go(std::false_type{});
     else go(std::true_type{});
