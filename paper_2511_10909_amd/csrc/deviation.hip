@@ -700,8 +700,8 @@ mmaemu_status launch_deviation_reset(mmaemu_deviation_hist *h, hipStream_t s)
     return MMAEMU_OK;
 }
 
-constexpr uint64_t TILE_MAX_WORK = 32;
-constexpr uint64_t TILE_MIN_OUTPUTS = 1ull << 17;
+constexpr uint64_t TILE_MAX_WORK = 32, TILE_MAX_K = 64;                    // k times the stride; k where every one of many outputs is sampled
+constexpr uint64_t TILE_MIN_OUTPUTS = 1ull << 17, TILE_MIN_OUTPUTS_LONG = 1ull << 20;
 
 static mmaemu_status launch_deviation_tiles(const void *A, const void *B, const uint32_t *C, const uint32_t *D, uint32_t m, uint32_t n, uint32_t k,
                                             uint64_t batch, uint32_t ta, uint32_t tb, uint32_t stride, int bin_exp, mmaemu_deviation_hist *h, hipStream_t s)
@@ -754,10 +754,12 @@ static DevKernel deviation_kernel_for(const void *A, const void *B, const void *
     const bool wide = fours && (nsamples >= (1ull << 19) || (k <= 32 && nsamples >= (1ull << 18)));
     // Whole tiles on the matrix cores, which form every output's sum whether it is sampled or not and wait for a chunk of k at a time.
     // The other kernels and this one, us, 2^24 outputs of 32x32 FP16 tiles, N(0, 1000): k = 8, strides 1, 2, 3, 5, 8 114, 94, 75, 62, 57 and
-    // 47 to 49; k = 16, 32, 64 163, 256, 442 and 54, 89, 236.  Where the exponents lie too far apart (all finite bit patterns, 16x16 tiles):
-    // k = 8, 16, 32 at stride 3 87, 109, 142 and 83, 117, 211; at stride 1, 32x32 tiles, k = 8, 32, 64 114, 255, 443 and 82, 202, 498.  2^17
-    // outputs of k = 32 17 and 13, 2^14 10 and 11.
-    if (((ta == MMAEMU_FP16 && tb == MMAEMU_FP16) || (ta <= MMAEMU_FP8_E5M2 && tb <= MMAEMU_FP8_E5M2)) && m % 16 == 0 && n % 16 == 0 && k % 8 == 0 && stride <= TILE_MAX_WORK / k && total >= TILE_MIN_OUTPUTS &&
+    // 47 to 49; k = 16, 32 163, 256 and 54, 89.  Where the exponents lie too far apart (all finite bit patterns, 16x16 tiles):
+    // k = 8, 16, 32 at stride 3 87, 109, 142 and 83, 117, 211; at stride 1, 32x32 tiles, k = 8, 32 114, 255 and 82, 202.  2^17
+    // outputs of k = 32 17 and 13, 2^14 10 and 11.  Longer rows, stride 1, N(0,1) and finite patterns: 2^24 outputs, k = 40, 64 298, 435 and
+    // 111, 188; 298, 438 and 193, 284; 2^20, k = 64 37 and 22, 54 and 31; but 2^17 16 and 20, 25 and 24.
+    const bool taken = stride <= TILE_MAX_WORK / k ? total >= TILE_MIN_OUTPUTS : stride == 1 && k <= TILE_MAX_K && total >= TILE_MIN_OUTPUTS_LONG;
+    if (((ta == MMAEMU_FP16 && tb == MMAEMU_FP16) || (ta <= MMAEMU_FP8_E5M2 && tb <= MMAEMU_FP8_E5M2)) && m % 16 == 0 && n % 16 == 0 && k % 8 == 0 && taken &&
         n <= (1u << 24) && (uint64_t)m * n <= (1ull << 38) && ((reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(B)) & 3u) == 0 &&
         (n % 32 != 0 || ((reinterpret_cast<uintptr_t>(C) | reinterpret_cast<uintptr_t>(D)) & 7u) == 0)) {
         return DevKernel::WholeTiles;

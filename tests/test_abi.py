@@ -185,16 +185,17 @@ def test_deviation_sample_kernel_for_a_call():
         c = dict(base, **kw)
         return mm.deviation_sample_kernel(c["A"], c["B"], c["C"], c["D"], c["m"], c["n"], c["k"], c["batch"], (c["a"], c["b"], mm.FP32, mm.FP32), c["stride"])
     for kw in ({}, dict(C=None), dict(stride=4), dict(k=32), dict(k=16, stride=2), dict(k=24), dict(A=4100, B=4108), dict(C=4104, D=4112), dict(n=16, m=64, C=4100, D=4108),
-               dict(a=mm.E4M3, b=mm.E5M2), dict(m=16, n=16, batch=512), dict(m=48, n=48, batch=57)):
+               dict(k=40, batch=1024), dict(k=64, batch=1024), dict(a=mm.E4M3, b=mm.E5M2), dict(m=16, n=16, batch=512), dict(m=48, n=48, batch=57)):
         assert kernel(**kw) == "whole tiles", kw
     one, four = "one output per thread, split sum", "four outputs per thread"
     for kw, want in ((dict(stride=5), one), (dict(stride=33), one), (dict(k=16, stride=3), one), (dict(k=32, stride=2), one), (dict(k=40), one), (dict(k=9), one),
                      (dict(batch=127), one), (dict(A=4098), one), (dict(B=4098), one), (dict(C=4100), one), (dict(D=4100), one), (dict(a=mm.E4M3, B=4097, b=mm.E4M3), one),
                      (dict(m=31, batch=133), one), (dict(n=36), one), (dict(a=mm.FP16, b=mm.E4M3), one), (dict(a=mm.E2M3, b=mm.E2M3), one),
-                     (dict(a=mm.BF16, b=mm.BF16), "one output per thread, pairs"), (dict(k=40, batch=512), four), (dict(k=64, batch=256), one),
+                     (dict(a=mm.BF16, b=mm.BF16), "one output per thread, pairs"), (dict(k=40, batch=512), four), (dict(k=64, batch=1023), four), (dict(k=72, batch=1024), four), (dict(k=64, batch=2048, stride=2), one),
+                     (dict(k=40, batch=2048, stride=2), one), (dict(k=64, batch=256), one),
                      (dict(n=1 << 25, m=16, batch=1), four), (dict(k=1 << 14), "one output per thread, pairs")):
         assert kernel(**kw) == want, kw
-    for k in (8, 16, 24, 32):
+    for k in (8, 16, 24, 32, 40, 64):
         for stride in [(1 << 64) // k + d for d in range(4)] + [(1 << e) + d for e in (32, 59, 60, 61, 62, 63) for d in (0, 1, 2, 4)] + [(1 << 64) - (1 << 20)]:
             assert kernel(k=k, stride=stride) == one, (k, stride)
     for kw, status in ((dict(stride=0), 3), (dict(D=None), 1), (dict(A=4097), 1), (dict(a=mm.TF32), 2)):

@@ -238,7 +238,8 @@ def test_deviation_sample_whole_tiles(mm, ta, tb, m, n, k, stride, with_c, exps,
 
 WHOLE_TILES = [(fm.FP16, fm.FP16, 32, 32, 8, 1, 2100), (fm.FP16, fm.FP16, 32, 32, 8, 3, 2100), (fm.FP16, fm.FP16, 16, 16, 8, 4, 4500),
                (fm.FP16, fm.FP16, 48, 16, 16, 1, 1400), (fm.E4M3, fm.E5M2, 16, 32, 24, 1, 4300), (fm.E5M2, fm.E5M2, 16, 16, 32, 1, 4200),
-               (fm.E4M3, fm.E4M3, 32, 64, 8, 2, 1100)]
+               (fm.E4M3, fm.E4M3, 32, 64, 8, 2, 1100), (fm.FP16, fm.FP16, 32, 32, 40, 1, 1100), (fm.FP16, fm.FP16, 16, 16, 64, 1, 4200),
+               (fm.E4M3, fm.E5M2, 32, 32, 64, 1, 1100), (fm.E5M2, fm.E5M2, 48, 16, 56, 1, 1400)]
 
 
 @pytest.mark.parametrize("ta,tb,m,n,k,stride,nb", WHOLE_TILES)
