@@ -263,9 +263,12 @@ static mmaemu_status launch_t(const void *A, const void *B, const uint32_t *D, u
     const uint64_t total = (uint64_t)m * n;
     const uint64_t nsamples = (total + stride - 1) / stride;
     uint64_t blocks = (nsamples + 3) / 4;
-    // Wave-stride beyond 1024 workgroups, which end in atomics on the same lines; 2048 (all that the chip holds) where every wavefront
-    // still has sixteen samples.
-    const uint64_t most = nsamples >= (1ull << 17) ? 2048 : 1024;
+    // Wave-stride beyond 1024 workgroups, which end in atomics on the same lines; 2048 (all that the chip holds) from as many samples on as
+    // pay for twice the ends, fewer where a sum is longer.  1024 and 2048 workgroups, us: E4M3 x E4M3, k = 1024, 2^17, 9 2^14, 10 2^14, 11 2^14,
+    // 2^18 samples 68, 74, 80, 86, 117 and 78, 78, 78, 81, 105 (k = 64 the same); k = 2048, 4096, 2^17 samples 82, 117 and 78, 108; E5M2 x E5M2,
+    // every product split, k = 64, 2^17, 2^18 76, 142 and 75, 125.
+    const bool longer = k > 1024 || (TA == MMAEMU_FP8_E5M2 && TB == MMAEMU_FP8_E5M2);
+    const uint64_t most = nsamples >= (longer ? 8ull << 14 : 10ull << 14) ? 2048 : 1024;
     if (blocks > most) blocks = most;
     hipLaunchKernelGGL((exact_dot_kernel<TA, TB>), dim3((uint32_t)blocks), dim3(256), 0, s, (const uint8_t *)A,
                        (const uint8_t *)B, D, m, n, k, stride, nsamples, st);
