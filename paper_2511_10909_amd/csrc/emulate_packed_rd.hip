@@ -295,7 +295,8 @@ emulate_packed_rd_kernel(PackedRdArgs pa, const uint8_t *__restrict__ A, const u
 
 // Blocks below which two wavefronts share one: each stages all of it, which costs 15 %, but with fewer than a wavefront for every SIMD the
 // chain of groups counts.  One wavefront and two, us: 256, 512, 1024, 2048 blocks of k = 128 12.0, 11.3, 11.5, 16.8 and 10.1, 10.0, 12.6,
-// 19.1; 2^11 and 2^13 of k = 32 9.3, 17.1 and 8.5, 20.5.
+// 19.1; 2^11 and 2^13 of k = 32 9.3, 17.1 and 8.5, 20.5.  The line is that of k = 128, for every k: with one group or two to a chain it
+// lies higher (somewhere between 2^11 and 2^13 blocks of k = 32), for a tenth of launches of 9 us, and was not looked for.
 constexpr uint64_t PRD_SPLIT_BELOW = 768;
 
 template <int TA, int TB, int R, bool SC>
