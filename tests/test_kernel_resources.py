@@ -45,6 +45,11 @@ def test_scan_kernels_keep_their_products_in_registers():
     assert len(blocks) == 10, "kernels not found in the resource remarks"
     for b in blocks:
         assert int(re.search(r"VGPRs Spill:\s*(\d+)", b).group(1)) == 0, b
+    # TR-FDPA with its products kept, at four waves per SIMD: 15, 8 and no registers of a thread (three waves take longer from 2^14 tiles of 16x16x16 on)
+    for tile, most in (("Li16ELi16E", 16), ("Li32ELi16E", 10), ("Li32ELi8E", 0)):
+        blocks = [b for b in out.stderr.split("Function Name:")[1:] if "emulate_scan_kernelI" + tile + "Lb0ELi4E" in b.split("\n")[0]]
+        assert len(blocks) == 1, "kernel not found in the resource remarks"
+        assert int(re.search(r"VGPRs Spill:\s*(\d+)", blocks[0]).group(1)) <= most and int(re.search(r"Occupancy \[waves/SIMD\]:\s*(\d+)", blocks[0]).group(1)) >= 4, blocks[0]
 
 
 @pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs hipcc")
@@ -62,3 +67,24 @@ def test_packed_kernels_need_no_scratch_memory():
     for b in blocks:
         get = lambda key: int(re.search(key + r":\s*(\d+)", b).group(1))
         assert get("VGPRs Spill") == 0 and get(r"ScratchSize \[bytes/lane\]") == 0 and get(r"Occupancy \[waves/SIMD\]") >= 4, b
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs hipcc")
+@pytest.mark.parametrize("source,kernel,count,waves,spill", [
+    ("emulate_packed_rd", "emulate_packed_rd_kernelILi\\dELi\\dELi2E", 6, 5, 0), ("emulate_packed_rd", "emulate_packed_rd_kernelILi\\dELi\\dELi4ELb0E", 3, 4, 0),
+    ("emulate_packed_rd", "emulate_packed_rd_kernelILi\\dELi\\dELi4ELb1E", 3, 3, 0), ("emulate_small", "emulate_quad_kernel", 6, 4, 0),
+    ("deviation", "deviation_tile_kernelILb[01]ELi1E", 4, 4, 0), ("deviation", "deviation_tile_kernelILb0ELi2E", 2, 4, 0),
+    ("deviation", "deviation_tile_kernelILb1ELi2E", 2, 4, 4)])
+def test_kernels_and_the_waves_they_are_measured_at(source, kernel, count, waves, spill):
+    """Packed halves (two rows per lane, four, four with block scales), 4 x 4 tiles, and whole tiles of the deviation histogram: waves per
+    SIMD, and registers in scratch memory, which only the 32-column kernel of FP8 operands has (2 of them)."""
+    cmd = ["hipcc", "-c", os.path.join(CSRC, source + ".hip"), "-o", os.devnull, "--offload-arch=gfx950", "--cuda-device-only", "-O3", "-fPIC",
+           "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+           "-Rpass-analysis=kernel-resource-usage"]
+    out = subprocess.run(cmd, capture_output=True, text=True, timeout=900)
+    assert out.returncode == 0, out.stderr[-2000:]
+    blocks = [b for b in out.stderr.split("Function Name:")[1:] if re.search(kernel, b.split("\n")[0])]
+    assert len(blocks) == count, "kernels not found in the resource remarks"
+    for b in blocks:
+        get = lambda key: int(re.search(key + r":\s*(\d+)", b).group(1))
+        assert get("VGPRs Spill") <= spill and get(r"Occupancy \[waves/SIMD\]") >= waves, b
