@@ -171,8 +171,9 @@ __device__ __forceinline__ void decode4(uint2 raw, uint32_t ftz_in, uint32_t zbi
     e = make_uint2(x[0] | (x[1] << 16), x[2] | (x[3] << 16));
 }
 
-// The same for elements held in 32-bit words (TF32), the exponents two at a time and one range test for the quad (element by element,
-// hopper's set on 1000x744x512, N(0,1): 108.7 us; so 106.0; on 512x512x512 71 and 64; of random bit patterns 231 and 231, 149 and 147).
+// The same for elements held in 32-bit words (TF32), the exponents two at a time and one range test for the quad (element by element, all
+// else the same, hopper's set on 1000x744x512, N(0,1): 113.9 us; so 111.0; on 512x512x512 68.7 and 62.9; of random bit patterns 227 and 226,
+// 150 and 148).
 template <int T>
 __device__ __forceinline__ void decode4(uint4 raw, uint32_t ftz_in, uint32_t zbias, float (&f)[4], uint2 &e, bool &wild)
 {
