@@ -736,13 +736,16 @@ static mmaemu_status launch_deviation_tiles(const void *A, const void *B, const 
     return MMAEMU_OK;
 }
 
+// Every stride-th of `total` outputs, output 0 among them (no sum that a large stride could take beyond 64 bits)
+static uint64_t samples_of(uint64_t total, uint64_t stride) { return total ? (total - 1) / stride + 1 : 0; }
+
 // The kernel for a call
 enum class DevKernel { WholeTiles, FourOutputs, SplitSum, Pairs };
 
 static DevKernel deviation_kernel_for(const void *A, const void *B, const void *C, const void *D, uint32_t m, uint32_t n, uint32_t k, uint64_t batch,
                                       uint32_t ta, uint32_t tb, uint64_t stride)
 {
-    const uint64_t total = batch * m * n, nsamples = (total + stride - 1) / stride;
+    const uint64_t total = batch * m * n, nsamples = samples_of(total, stride);
     // The split sum for every type but BF16 (whose products span more than the split holds) up to the k for which it is exact.
     // Four outputs of a row per thread where every output is sampled, rows hold whole fours at 16-byte steps, and there are
     // enough of them: a thread then runs four chains, so with few outputs the chip idles behind them, while with many the row of
@@ -782,7 +785,7 @@ mmaemu_status launch_deviation_sample(const void *A, const void *B, const uint32
                                       uint32_t k, uint64_t batch, uint32_t ta, uint32_t tb, uint64_t stride, int bin_exp,
                                       mmaemu_deviation_hist *h, hipStream_t s)
 {
-    const uint64_t nsamples = (batch * m * n + stride - 1) / stride;
+    const uint64_t nsamples = samples_of(batch * m * n, stride);
     if (nsamples == 0) return MMAEMU_OK;
     if (nsamples > MAX_SAMPLES) { set_error("deviation_sample: more than 2^43 samples in one call"); return MMAEMU_ERR_SHAPE; }
     const DevKernel kernel = deviation_kernel_for(A, B, C, D, m, n, k, batch, ta, tb, stride);

@@ -261,7 +261,7 @@ static mmaemu_status launch_t(const void *A, const void *B, const uint32_t *D, u
                               uint64_t stride, mmaemu_err_stats *st, hipStream_t s)
 {
     const uint64_t total = (uint64_t)m * n;
-    const uint64_t nsamples = (total + stride - 1) / stride;
+    const uint64_t nsamples = (total - 1) / stride + 1;                  // (no sum that a large stride could take beyond 64 bits)
     uint64_t blocks = (nsamples + 3) / 4;
     // Wave-stride beyond 1024 workgroups, which end in atomics on the same lines; 2048 (all that the chip holds) from as many samples on as
     // pay for twice the ends, fewer where a sum is longer.  1024 and 2048 workgroups, us: E4M3 x E4M3, k = 1024, 2^17, 9 2^14, 10 2^14, 11 2^14,

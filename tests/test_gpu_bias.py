@@ -313,9 +313,9 @@ def test_whole_tiles_are_no_slower_for_any_accumulator(mm, lo, hi, tiles):
     assert best[1] < 1.1 * best[0], best
 
 
-@pytest.mark.parametrize("stride", [(1 << 61) + 1, 1 << 61, 1 << 63, (1 << 32) + 1])
+@pytest.mark.parametrize("stride", [(1 << 61) + 1, 1 << 61, 1 << 63, (1 << 32) + 1, (1 << 64) - 1, (1 << 64) - (513 << 8)])
 def test_deviation_sample_strides_beyond_the_outputs(mm, stride):
-    """One sample, output 0, also where the product of stride and k leaves 64 bits."""
+    """One sample, output 0, also where the product of stride and k, or the sum of stride and outputs, leaves 64 bits."""
     rng = np.random.default_rng(17)
     nb, m, n, k = 513, 16, 16, 8
     A, B = synth.narrow_exponent_bits(rng, (nb, m, k), fm.FP16, 10, 20), synth.narrow_exponent_bits(rng, (nb, n, k), fm.FP16, 10, 20)

@@ -327,7 +327,8 @@ def test_exact_dot_sample_matches_oracle(mm):
 
 
 @pytest.mark.parametrize("ta,tb", [(fm.E4M3, fm.E5M2), (fm.E5M2, fm.E5M2), (fm.E4M3, fm.E4M3), (fm.E5M2, fm.E4M3)])
-@pytest.mark.parametrize("m,n,k,stride", [(1024, 1030, 16, 1), (512, 700, 20, 1), (40, 48, 2064, 1), (3, 5, 3000, 2)])
+@pytest.mark.parametrize("m,n,k,stride", [(1024, 1030, 16, 1), (512, 700, 20, 1), (40, 48, 2064, 1), (3, 5, 3000, 2), (400, 409, 24, 1), (512, 320, 24, 1),
+                                        (256, 512, 1040, 1), (7, 9, 64, (1 << 64) - 1)])
 def test_exact_dot_sample_many_per_wavefront(mm, ta, tb, m, n, k, stride):
     """More samples than the wavefronts' lanes, and fewer; rows of whole 16-byte vectors beyond 1024 and rows that are not; the largest
     products of one sign, where the runs of products that are summed unsplit are full."""
