@@ -2,6 +2,7 @@
 issue, and their 2 x 2 variants lose about a fifth of their throughput when they drop from four waves per SIMD to three.
 Called routines count against a kernel's registers, so a change far from the hot loops can cost that wave; this test
 recompiles the translation unit of the chained bench kernel with the compiler's resource remarks and checks them."""
+import functools
 import os
 import re
 import shutil
@@ -69,6 +70,16 @@ def test_packed_kernels_need_no_scratch_memory():
         assert get("VGPRs Spill") == 0 and get(r"ScratchSize \[bytes/lane\]") == 0 and get(r"Occupancy \[waves/SIMD\]") >= 4, b
 
 
+@functools.lru_cache(maxsize=None)
+def resource_remarks(source):
+    cmd = ["hipcc", "-c", os.path.join(CSRC, source + ".hip"), "-o", os.devnull, "--offload-arch=gfx950", "--cuda-device-only", "-O3", "-fPIC",
+           "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+           "-Rpass-analysis=kernel-resource-usage"]
+    out = subprocess.run(cmd, capture_output=True, text=True, timeout=900)
+    assert out.returncode == 0, out.stderr[-2000:]
+    return out.stderr.split("Function Name:")[1:]
+
+
 @pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs hipcc")
 @pytest.mark.parametrize("source,kernel,count,waves,spill", [
     ("emulate_packed_rd", "emulate_packed_rd_kernelILi\\dELi\\dELi2E", 6, 5, 0), ("emulate_packed_rd", "emulate_packed_rd_kernelILi\\dELi\\dELi4ELb0E", 3, 4, 0),
@@ -78,12 +89,7 @@ def test_packed_kernels_need_no_scratch_memory():
 def test_kernels_and_the_waves_they_are_measured_at(source, kernel, count, waves, spill):
     """Packed halves (two rows per lane, four, four with block scales), 4 x 4 tiles, and whole tiles of the deviation histogram: waves per
     SIMD, and registers in scratch memory, which only the 32-column kernel of FP8 operands has (2 of them)."""
-    cmd = ["hipcc", "-c", os.path.join(CSRC, source + ".hip"), "-o", os.devnull, "--offload-arch=gfx950", "--cuda-device-only", "-O3", "-fPIC",
-           "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-           "-Rpass-analysis=kernel-resource-usage"]
-    out = subprocess.run(cmd, capture_output=True, text=True, timeout=900)
-    assert out.returncode == 0, out.stderr[-2000:]
-    blocks = [b for b in out.stderr.split("Function Name:")[1:] if re.search(kernel, b.split("\n")[0])]
+    blocks = [b for b in resource_remarks(source) if re.search(kernel, b.split("\n")[0])]
     assert len(blocks) == count, "kernels not found in the resource remarks"
     for b in blocks:
         get = lambda key: int(re.search(key + r":\s*(\d+)", b).group(1))
